@@ -145,10 +145,10 @@ int64_t bifeat_codes_per_row(const bifeat_params *p);
  *   `vq_length` rows (it must have at least that many); every update then runs
  *   Lloyd rounds over its chunk (10, option "vq_iters"): nearest entry by the
  *   encoder's rule for the scheme's metric, entry = mean of its members, an
- *   entry without members keeps its value.  Sums are accumulated with fp32
- *   atomics, so the codebooks are reproducible in distortion, not bit for bit.
- *   Training a large or cosine codebook uses library scratch (two bytes per
- *   part and sample row).  finalize synchronises `stream` for the cosine metric
+ *   entry without members keeps its value.  Sums are accumulated with atomics,
+ *   so the codebooks are reproducible in distortion, not bit for bit.
+ *   Training uses library scratch: two bytes per part and sample row for a large or
+ *   cosine codebook, otherwise partial sums (a few times the codebooks).  finalize synchronises `stream` for the cosine metric
  *   (the entry norms are evaluated on the host in fp64).
  * finalize without any update returns BIFEAT_ENOTFIT. */
 int bifeat_fit_reset(bifeat_params *p, void *stream);

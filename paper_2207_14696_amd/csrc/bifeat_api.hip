@@ -65,7 +65,7 @@ int ensure_device(bifeat_params *p) {
         nfloat = 128 + 256 + (p->scheme.bits == 1 ? 2 * D : p->scheme.bits == 2 ? 4 * D : 0);
         nfit = 4 + 2 * 2 * bf::kLogHistBins;
     }
-    else nfloat = (size_t)p->P * p->scheme.vq_length * (2 * p->scheme.vq_width + 2) + 64;
+    else nfloat = (size_t)p->P * p->scheme.vq_length * (2 * p->scheme.vq_width + 2) + 128;
     nfloat = (nfloat + 3) / 4 * 4;
     nfit = (nfit + 3) / 4 * 4;
     void *blk = nullptr;
@@ -94,7 +94,7 @@ int ensure_device(bifeat_params *p) {
         p->d_cb = p->d_block;
         p->d_rnorm = p->d_block + ncb;
         p->d_train = p->d_rnorm + nent;
-        p->d_dist = p->d_train + ncb + nent;
+        p->d_dist = reinterpret_cast<double *>(p->d_train + ncb + nent);  // an even number of floats in
     }
     p->d_fit = reinterpret_cast<int32_t *>(p->d_block + nfloat);
     if (p->scheme.kind == BIFEAT_SQ_LOG) p->d_hist = reinterpret_cast<unsigned long long *>(p->d_fit + 4);
@@ -551,11 +551,11 @@ int bifeat_params_get_codebooks(bifeat_params *p, float *codebooks) {
 int bifeat_vq_distortion(bifeat_params *p, float *out, int32_t n) {
     if (!p || p->scheme.kind != BIFEAT_VQ || !out || n < 0) return BIFEAT_EINVAL;
     if (!p->vq_seeded || p->vq_last_rows == 0) return BIFEAT_ENOTFIT;
-    float tmp[64];
+    double tmp[64];
     BF_HIP(hipDeviceSynchronize());
     BF_HIP(hipMemcpy(tmp, p->d_dist, sizeof(tmp), hipMemcpyDeviceToHost));
     for (int k = 0; k < n; k++)
-        out[k] = k < p->vq_last_rounds ? tmp[k] / (float)p->vq_last_rows : 0.0f;
+        out[k] = k < p->vq_last_rounds ? (float)(tmp[k] / (double)p->vq_last_rows) : 0.0f;
     return BIFEAT_OK;
 }
 

@@ -35,7 +35,7 @@ struct bifeat_params {
     float *d_T = nullptr, *d_V = nullptr, *d_cb = nullptr;
     float *d_rnorm = nullptr;   // vq, cosine metric: [P][len]
     float *d_train = nullptr;   // vq training scratch: sums [P][len][w], counts [P][len]
-    float *d_dist = nullptr;    // vq training: summed squared distance per Lloyd round (64 slots)
+    double *d_dist = nullptr;   // vq training: summed squared distance per Lloyd round (64 slots)
     uint8_t *d_scratch = nullptr;  // grow-only workspace (vector codes: slice-major code strips)
     size_t scratch_bytes = 0;
     std::vector<void *> retired;   // outgrown workspaces, kept allocated until the handle dies

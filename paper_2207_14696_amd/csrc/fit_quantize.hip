@@ -7,6 +7,7 @@
 // registers while consecutive lanes still read consecutive addresses.
 #include "common.hpp"
 #include "stream_kernels.hpp"
+#include "vq_nearest.hpp"
 
 namespace bf {
 
@@ -225,6 +226,9 @@ template <typename T>
 void launch_vq_assign(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
                       hipStream_t s) {
     const int w = p->scheme.vq_width;
+    // the matrix-core search gives the same codes; what it leaves (wide parts, tiny codebooks)
+    // takes the plain search
+    if (launch_vq_nearest_codes<T>(p, x, rows, codes, rb, s)) return;
     switch (w) {
         case 1: launch_vq_w<T, 1, 1>(p, x, rows, codes, rb, s); break;
         case 2: launch_vq_w<T, 2, 2>(p, x, rows, codes, rb, s); break;

@@ -1,0 +1,605 @@
+// Nearest codebook entry on the matrix cores (Sec. 3.2's search; the encoder and the assignment
+// step of the codebook training use it).
+//
+// The result is defined bit by bit: the entry with the smallest fp32 distance, columns in order,
+// every operation rounded by itself, ties to the lowest index (cosine: the largest fp32 dot
+// product times the entry's reciprocal norm).  Evaluating that rule for every entry costs 3
+// vector instructions per column and entry and leaves the matrix cores idle.  Here they do the
+// search: s = |c|^2/2 - x.c (cosine: -x.c/|c|) for 32 rows x 32 entries at a time, both factors
+// split into two half-precision pieces (hi + lo, 22 bits) so that all four piece products are
+// two MFMAs of K = 16 per 8 columns.  A lane keeps, per row, the best and the second best *cell*
+// (4 consecutive entries: the accumulator registers 4q..4q+3), which costs 5 vector instructions
+// per 4 scores; the rule itself then decides inside the winning cell.  That the winning cell
+// holds the rule's entry is certain when the second best cell is further away than the errors of
+// both evaluations together (`margin`, derived at vq_margin below); a row for which it is not -
+// near ties, values outside the range the split holds - is searched by the rule over the whole
+// codebook, by the wave together, or lane by lane when many rows of a wave need it.
+// The codes are therefore the same as the plain search gives, for any input.
+//
+// What bounds it: vector instructions - 368 of ~720 per 64 rows and part are the running minima
+// over 256 entries, ~190 the rule inside the cell, ~70 the split of x - next to 16 cycles of MFMA
+// per row and part (164 of the 706 us below).  64 rows per wave reuse each 1 KB of entry pieces
+// read from LDS four times; cells of 8 entries would save 96 instructions of the minima and cost
+// as many in the cell.  262 144 rows of 96 parts x 256 entries x 8 columns: 706 us, the plain
+// search 3111 us.
+//
+// Training adds each part to its entry's sum in LDS.  The sums are kept in 64 bits: an LDS
+// float add takes 196 cycles per wave here whatever the addresses, a double add 22 (integer: 8).
+// A workgroup writes its sums to the workspace and a second kernel adds them up in a fixed order
+// (global float adds onto the same few addresses ran at 22.6 G/s, a quarter of the round).  One
+// round over 65 536 rows of that shape: 210 us, before (plain search, fp32 adds) 1030 us.
+#include "vq_nearest.hpp"
+
+#include <algorithm>
+
+namespace bf {
+
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+
+template <typename T>
+struct VqNearestArgs {
+    const T *x;             // [rows x D]
+    int64_t rows;
+    int D, w, len, P, cbytes;
+    int vec;                // 4 columns of a part can be loaded at once
+    int NT;                 // tiles of 32 entries in LDS at a time
+    int ny;                 // workgroups per part
+    const float *cb;        // [P][len][w]
+    const float *rnorm;     // [P][len], cosine metric
+    float margin;           // see vq_margin
+    uint32_t cell_mask;     // low bits of a score that hold a cell's number
+    uint8_t *codes;         // (the encoder)
+    int64_t rb;
+    float *sums;            // (training) [ny][P][w][len]
+    uint32_t *counts;       // [ny][P][len]
+    double *distortion;
+};
+
+// codebooks of up to this many entries and wider parts stay with the plain search
+constexpr int kNearestMinLength = 16;
+constexpr int kNearestMaxWidth = 32;
+constexpr int kCuLds = 160 * 1024;
+// rows of a wave that need the whole codebook searched by the rule: from this many on every lane
+// searches for its own row (one pass over the codebook for all), below it the wave works on one
+// row at a time with its lanes sharing the codebook
+constexpr int kLaneSearch = 24;
+
+constexpr float kPadScore = 1e30f;   // score of the entries that fill up the last tile
+constexpr int kScaleExp = 11;        // largest magnitude of a part's codebook: [2^10, 2^11)
+constexpr float kMaxNorm2 = 1073741824.0f;  // rows with a scaled |x|^2 of 2^30 or more go by the rule
+
+// One instruction for up to three operands, and none to quiet NaNs first (fminf needs one each); a
+// NaN wins, which the caller's comparison with the margin then sees.
+__device__ inline float minimum(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+
+// One row's distance to one entry by the rule (smaller = better; cosine: the negated score).
+template <int WP, int METRIC>
+__device__ inline float rule_value(const float (&x)[WP], const float (&c)[WP], float rn) {
+    float acc = 0.0f;
+#pragma unroll
+    for (int d = 0; d < WP; d++) {
+        if constexpr (METRIC == BIFEAT_VQ_COSINE) {
+            acc = __fadd_rn(acc, __fmul_rn(x[d], c[d]));
+        } else {
+            const float diff = __fsub_rn(x[d], c[d]);
+            acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+        }
+    }
+    if constexpr (METRIC == BIFEAT_VQ_COSINE) return -__fmul_rn(acc, rn);
+    else return acc;
+}
+
+template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
+__global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_kernel(VqNearestArgs<T> a) {
+    constexpr int WP = 8 * G;          // columns of a part, padded with zeros
+    constexpr int TH = ENT ? 256 : 512;
+    constexpr int WAVES = TH / 64;
+    constexpr int CELL = 4 * WP + 4;   // floats of a cell in LDS: 16 bytes of padding spread the banks
+    constexpr bool COS = METRIC == BIFEAT_VQ_COSINE;
+    extern __shared__ uint4 s_raw[];
+    // [entry pieces: NT x G x 64 lanes x 16 bytes | scores' constant: NT x 32 | entries | rnorm |
+    // sums by column, counts]
+    half8 *s_frag = reinterpret_cast<half8 *>(s_raw);
+    float *s_half = reinterpret_cast<float *>(s_frag + (size_t)a.NT * G * 64);
+    float *s_ent = s_half + a.NT * 32;
+    float *s_rn = s_ent + (ENT ? a.NT * 8 * CELL : 0);
+    // (every piece above is a multiple of 32 floats)
+    double *s_sum = reinterpret_cast<double *>(s_rn + (ENT && COS ? a.NT * 32 : 0));
+    uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s_sum + (TRAIN ? a.len * a.w : 0));
+    __shared__ unsigned s_cmax, s_c2max;
+    __shared__ int s_bad;
+    __shared__ double s_dist;
+
+    // workgroups are dealt to the XCDs in turn: consecutive logical ids (the parts of one strip
+    // of rows, which share memory lines of x and of the codes) belong on one XCD
+    const unsigned per_xcd = gridDim.x >> 3;
+    const unsigned id = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (id >= (unsigned)(a.P * a.ny)) return;
+    const int part = (int)(id % (unsigned)a.P), by = (int)(id / (unsigned)a.P);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int half = lane >> 5, col = lane & 31;
+    const int w = a.w, len = a.len;
+    const float *part_cb = a.cb + (int64_t)part * len * w;
+    const float *part_rn = COS ? a.rnorm + (int64_t)part * len : nullptr;
+
+    // ---- the part's scale: a power of two that brings its largest magnitude to [2^10, 2^11)
+    if (threadIdx.x == 0) { s_cmax = 0u; s_c2max = 0u; s_bad = 0; s_dist = 0.0; }
+    __syncthreads();
+    float scale;
+    {
+        float m = 0.0f;
+        bool bad = false;
+        for (int i = threadIdx.x; i < len * w; i += TH) {
+            const float c = fabsf(part_cb[i]);
+            bad |= !(c <= 0x1p40f);
+            m = fmaxf(m, c);
+        }
+        if constexpr (COS)
+            for (int i = threadIdx.x; i < len; i += TH) bad |= !(part_rn[i] <= 0x1p40f);
+        atomicMax(&s_cmax, __float_as_uint(m));
+        if (bad) s_bad = 1;
+        __syncthreads();
+        const float cmax = __uint_as_float(s_cmax);
+        int e = 0;
+        frexpf(cmax, &e);
+        scale = COS ? 1.0f : ldexpf(1.0f, kScaleExp - e);
+        // outside this range distances by the rule could overflow or lose bits to underflow
+        if (threadIdx.x == 0 && !(cmax >= 0x1p-40f)) s_bad = 1;
+    }
+    if constexpr (TRAIN) {
+        for (int i = threadIdx.x; i < len * w; i += TH) s_sum[i] = 0.0;
+        for (int i = threadIdx.x; i < len; i += TH) s_cnt[i] = 0u;
+    }
+
+    // tiles [t0, t0 + nt) of 32 entries into LDS; a thread prepares one entry
+    auto stage = [&](int t0, int nt) {
+        for (int i = threadIdx.x; i < nt * 32; i += TH) {
+            const int e = t0 * 32 + i;
+            const bool real = e < len;
+            const float rn = COS ? (real ? part_rn[e] : 0.0f) : 0.0f;
+            float s2 = 0.0f;
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                half8 hi, lo;
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    const int d = 8 * g + j;
+                    const float c = real && d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
+                    // (an entry past the last one is NaN to the rule: never less than another)
+                    if constexpr (ENT) s_ent[(i >> 2) * CELL + (i & 3) * WP + d] = real ? c : __builtin_nanf("");
+                    float cs = COS ? c * (rn * 1024.0f) : c * scale;
+                    // one fp32 value for both pieces: the compiler may otherwise fold the product
+                    // into one of the conversions and round the pieces from different values
+                    asm volatile("" : "+v"(cs));
+                    s2 += cs * cs;
+                    hi[j] = (_Float16)(-cs);
+                    lo[j] = (_Float16)(-cs - (float)hi[j]);
+                }
+                half8 *f = s_frag + ((i >> 5) * G + g) * 64 + (i & 31);
+                f[0] = hi;
+                f[32] = lo;
+            }
+            s_half[i] = real ? (COS ? 0.0f : 0.5f * s2) : kPadScore;
+            if constexpr (ENT && COS) s_rn[i] = rn;
+            if (!COS) atomicMax(&s_c2max, __float_as_uint(s2));
+        }
+    };
+    const int tiles = (len + 31) >> 5;
+    const bool single = tiles <= a.NT;
+    if (single) stage(0, tiles);
+    if (!single && !COS) {
+        // the largest norm over the whole codebook bounds every chunk's scores
+        for (int e = threadIdx.x; e < len; e += TH) {
+            float s2 = 0.0f;
+            for (int d = 0; d < w; d++) {
+                const float cs = part_cb[(int64_t)e * w + d] * scale;
+                s2 += cs * cs;
+            }
+            atomicMax(&s_c2max, __float_as_uint(s2));
+        }
+    }
+    __syncthreads();
+    const bool part_bad = s_bad != 0;
+    const float c2max = __uint_as_float(s_c2max) * 1.0001f;
+    uint32_t keep = ~a.cell_mask;
+    asm volatile("" : "+v"(keep));  // in a vector register: mask and cell number are then one instruction
+
+    // entry e as the rule sees it (columns past w: zeros)
+    auto entry = [&](int e, float (&c)[WP], float &rn) {
+        if constexpr (ENT) {
+            const float4 *src = reinterpret_cast<const float4 *>(s_ent + (e >> 2) * CELL + (e & 3) * WP);
+#pragma unroll
+            for (int k = 0; k < WP / 4; k++) {
+                const float4 v = src[k];
+                c[4 * k] = v.x; c[4 * k + 1] = v.y; c[4 * k + 2] = v.z; c[4 * k + 3] = v.w;
+            }
+            rn = COS ? s_rn[e] : 0.0f;
+        } else {
+            const float *src = part_cb + (int64_t)e * w;
+#pragma unroll
+            for (int d = 0; d < WP; d++) c[d] = d < w ? src[d] : 0.0f;
+            rn = COS ? part_rn[e] : 0.0f;
+        }
+    };
+
+    float dsum = 0.0f;
+    // every wave of the workgroup walks the same strips (staging a chunk synchronises)
+    constexpr int ROWS = WAVES * 64;
+    for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += (int64_t)a.ny * ROWS) {
+        // ---- 2 x 32 rows per wave: sub-vectors split into pieces.  Both halves of the wave hold
+        // the pieces of both sets; a lane decides row `lane` in the end and keeps that one whole.
+        auto load_row = [&](int64_t r, float (&v)[WP]) {
+            const T *src = a.x + (r < a.rows ? r : a.rows - 1) * a.D + (int64_t)part * w;
+            if (a.vec) {  // w % 4 == 0, D % 4 == 0, 4 columns aligned
+#pragma unroll
+                for (int k = 0; k < WP / 4; k++) {
+                    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (4 * k < w && part * w + 4 * k < a.D) q = load4(src + 4 * k);
+                    v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < WP; d++) v[d] = d < w && part * w + d < a.D ? load1(src + d) : 0.0f;
+            }
+        };
+        const int64_t r = r0 + wave * 64 + lane;
+        const bool valid = r < a.rows;
+        float xr[WP];
+        load_row(r, xr);
+        half8 xh[2][G], xl[2][G];
+        float margin[2];
+        bool zero[2];
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+            float x[WP];
+            load_row(r0 + wave * 64 + s * 32 + col, x);
+            float f = scale;
+            bool bad = part_bad;
+            zero[s] = false;
+            if constexpr (COS) {  // the best entry does not depend on the row's length
+                float m = 0.0f;
+#pragma unroll
+                for (int d = 0; d < WP; d++) m = fmaxf(m, fabsf(x[d]));
+                int e = 0;
+                frexpf(m, &e);
+                zero[s] = m == 0.0f;
+                bad |= !zero[s] && !(m >= 0x1p-50f && m <= 0x1p50f);
+                f = zero[s] || bad ? 1.0f : ldexpf(1.0f, kScaleExp - e);
+            }
+            float s2 = 0.0f;
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {
+                    const float u = x[8 * g + j] * f, v = x[8 * g + j + 1] * f;
+                    s2 = fmaf(u, u, s2);
+                    s2 = fmaf(v, v, s2);
+                    const auto h = __builtin_amdgcn_cvt_pkrtz(u, v);
+                    const auto l = __builtin_amdgcn_cvt_pkrtz(u - (float)h[0], v - (float)h[1]);
+                    xh[s][g][j] = (_Float16)h[0];
+                    xh[s][g][j + 1] = (_Float16)h[1];
+                    xl[s][g][j] = (_Float16)l[0];
+                    xl[s][g][j + 1] = (_Float16)l[1];
+                }
+            }
+            bad |= !(s2 < kMaxNorm2);  // also NaN
+            const float big = COS ? sqrtf(s2) * 1024.5f : s2 + c2max;
+            margin[s] = bad ? INFINITY : big * a.margin;
+            if constexpr (COS) zero[s] = zero[s] && s2 == 0.0f && !part_bad;  // not a NaN that fmaxf passed over
+        }
+        float best[2] = {3e38f, 3e38f}, second[2] = {3e38f, 3e38f};
+        for (int t0 = 0; t0 < tiles; t0 += a.NT) {
+            const int nt = min(a.NT, tiles - t0);
+            if (!single) {
+                __syncthreads();
+                stage(t0, nt);
+                __syncthreads();
+            }
+            for (int t = 0; t < nt; t++) {
+                float16v c;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const float4 n = *reinterpret_cast<const float4 *>(s_half + t * 32 + 8 * q + 4 * half);
+                    c[4 * q] = n.x; c[4 * q + 1] = n.y; c[4 * q + 2] = n.z; c[4 * q + 3] = n.w;
+                }
+                float16v acc[2] = {c, c};
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    const half8 ent = s_frag[(t * G + g) * 64 + lane];
+#pragma unroll
+                    for (int s = 0; s < 2; s++)
+                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent, xh[s][g], acc[s], 0, 0, 0);
+#pragma unroll
+                    for (int s = 0; s < 2; s++)
+                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent, xl[s][g], acc[s], 0, 0, 0);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    uint32_t number = (uint32_t)(4 * (t0 + t) + q);
+                    asm volatile("" : "+s"(number));  // one scalar: the compiler would add it up per lane
+#pragma unroll
+                    for (int s = 0; s < 2; s++) {
+                        const float m = minimum(minimum(minimum(acc[s][4 * q], acc[s][4 * q + 1]), acc[s][4 * q + 2]),
+                                                acc[s][4 * q + 3]);
+                        // the cell's number replaces the low bits of its score
+                        const float key = __uint_as_float((__float_as_uint(m) & keep) | number);
+                        second[s] = __builtin_amdgcn_fmed3f(best[s], second[s], key);
+                        best[s] = minimum(best[s], key);
+                    }
+                }
+            }
+        }
+        // ---- the two halves of the wave hold different cells of the same rows; afterwards lane
+        // half h decides the rows of set h
+        float b = 0.0f, gap = 0.0f;
+        int h_of = 0;
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+            const float ob = __shfl_xor(best[s], 32), os = __shfl_xor(second[s], 32);
+            const float lo = minimum(best[s], ob), hi = fmaxf(best[s], ob);
+            const float g = minimum(hi, minimum(second[s], os)) - lo;
+            if (half == s) {
+                b = lo;
+                gap = g;
+                h_of = best[s] <= ob ? half : 1 - half;
+            }
+        }
+        const uint32_t cell = __float_as_uint(b) & a.cell_mask;
+        bool open = !(gap > (half ? margin[1] : margin[0]));  // the rule has to look at all entries
+        int code = 0;
+        float value = INFINITY;
+        {
+            const int e0 = open ? 0 : (int)(8 * cell + 4 * h_of);
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                float c[WP], rn;
+                entry(ENT ? e0 + k : min(e0 + k, len - 1), c, rn);
+                const float v = rule_value<WP, METRIC>(xr, c, rn);
+                if ((ENT || e0 + k < len) && (k == 0 || v < value)) {
+                    value = v;
+                    code = e0 + k;
+                }
+            }
+        }
+        if (COS && (half ? zero[1] : zero[0])) {  // all scores are zero: the first entry
+            open = false;
+            code = 0;
+            value = 0.0f;
+        }
+        uint64_t todo = __ballot(open && valid);
+        if (todo) {
+            if (__popcll(todo) >= kLaneSearch) {
+                int bc = 0;
+                float bv = INFINITY;
+                for (int e = 0; e < len; e++) {
+                    float c[WP], rn;
+                    entry(e, c, rn);
+                    const float v = rule_value<WP, METRIC>(xr, c, rn);
+                    if (v < bv) { bv = v; bc = e; }
+                }
+                if (open) { code = bc; value = bv; }
+            } else {
+                while (todo) {
+                    const int j = __ffsll((unsigned long long)todo) - 1;
+                    todo &= todo - 1;
+                    float xj[WP];
+#pragma unroll
+                    for (int d = 0; d < WP; d++)
+                        xj[d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xr[d]), j));
+                    int bc = 0x7FFFFFFF;
+                    float bv = INFINITY;
+                    for (int e = lane; e < len; e += 64) {
+                        float c[WP], rn;
+                        entry(e, c, rn);
+                        const float v = rule_value<WP, METRIC>(xj, c, rn);
+                        if (v < bv) { bv = v; bc = e; }
+                    }
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) {
+                        const float ov = __shfl_xor(bv, o);
+                        const int oc = __shfl_xor(bc, o);
+                        if (ov < bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
+                    }
+                    if (lane == j) {
+                        code = bc == 0x7FFFFFFF ? 0 : bc;
+                        value = bv;
+                    }
+                }
+            }
+        }
+        if constexpr (TRAIN) {
+            if (valid) {
+#pragma unroll
+                for (int d = 0; d < WP; d++)
+                    if (d < w) unsafeAtomicAdd(&s_sum[d * len + code], (double)xr[d]);
+                atomicAdd(&s_cnt[code], 1u);
+                dsum += value;
+            }
+        } else if (valid) {
+            uint8_t *row = a.codes + r * a.rb;
+            if (a.cbytes == 1) row[part] = (uint8_t)code;
+            else reinterpret_cast<uint16_t *>(row)[part] = (uint16_t)code;
+            if (part == 0)
+                for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) row[k] = 0;  // padding
+        }
+    }
+    if constexpr (TRAIN) {
+        __syncthreads();
+        float *sums = a.sums + ((int64_t)by * a.P + part) * len * w;
+        uint32_t *counts = a.counts + ((int64_t)by * a.P + part) * len;
+        for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
+        for (int i = threadIdx.x; i < len; i += TH) counts[i] = s_cnt[i];
+        for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
+        if (lane == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
+        __syncthreads();
+        if (threadIdx.x == 0) unsafeAtomicAdd(a.distortion, s_dist);
+    }
+}
+
+// An entry becomes the mean of its members (one without members keeps its value) from the
+// workgroups' sums; a thread per column of an entry, in the sums' order.
+__global__ __launch_bounds__(kThreads) void vq_means_kernel(const float *__restrict__ sums,
+                                                            const uint32_t *__restrict__ counts, int ny, int P, int w,
+                                                            int len, float *__restrict__ cb) {
+    const int64_t n = (int64_t)P * w * len;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+        const int e = (int)(i % len);
+        const int64_t pd = i / len, p = pd / w;
+        const int d = (int)(pd - p * w);
+        double sum = 0.0;
+        uint64_t count = 0;
+        for (int k = 0; k < ny; k++) {
+            sum += (double)sums[k * n + i];
+            count += counts[((int64_t)k * P + p) * len + e];
+        }
+        if (count > 0) cb[(p * len + e) * w + d] = (float)(sum / (double)count);
+    }
+}
+
+// Bound on how far the difference of two scores can be from what the rule decides on, relative to
+// M = |x|^2 + max|c|^2 (scaled; every |score| and half of every squared distance is at most M;
+// cosine: M = |x||c|).  u = 2^-24.
+//   pieces: x rounded towards zero twice (2^-20 of each column), c to nearest twice (2^-22); by
+//     Cauchy at most (2^-20 + 2^-22) M/2 per score, and what is lost below the smallest normal
+//     half (2^-14 of codebooks scaled to 2^10) at most 2^-20 M: 2^-19 M per score
+//   sums: 32 products per 8 columns and the constant added in fp32, each addition to 2u M;
+//     the constant itself (w + 2) u M
+//   the cell number in the low bits: 2^(bits - 23) M
+//   the rule: distances (w + 2) u relative, i.e. (w + 2) u M per score
+// twice that for two scores, and a quarter on top.
+float vq_margin(int w, int groups, int cell_bits) {
+    const double u = ldexp(1.0, -24);
+    const double score = ldexp(1.0, -19) + 2.0 * u * (32.0 * groups + 2.0) + ldexp(1.0, cell_bits - 23) +
+                         2.0 * u * (w + 4.0);
+    return (float)(1.25 * 2.0 * score);
+}
+
+size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) {
+    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    const bool cosine = p->scheme.vq_metric == BIFEAT_VQ_COSINE;
+    size_t n = (size_t)NT * G * 1024 + sizeof(float) * NT * 32;
+    if (ent) n += sizeof(float) * ((size_t)NT * 8 * (32 * G + 4) + (cosine ? NT * 32 : 0));
+    if (train) n += (size_t)len * (sizeof(double) * w + sizeof(uint32_t));
+    return n;
+}
+
+template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
+bool launch_one(bifeat_params *p, VqNearestArgs<T> a, size_t lds, hipStream_t s) {
+    auto kern = vq_nearest_kernel<T, G, METRIC, ENT, TRAIN>;
+    // (the kernel's few static words count too)
+    if (lds > 65536 - 64 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    constexpr int TH = ENT ? 256 : 512;
+    const int64_t strips = (a.rows + TH - 1) / TH;
+    // workgroups: four times what the chip holds at once, a little less rather than a little more
+    // (staging the codebook is about as long as one strip, so a workgroup should have many); in
+    // training, where each also adds its sums to memory, as many as the chip holds
+    const int64_t resident = 256 * std::min<int64_t>(ENT ? (G == 1 ? 4 : 2) : 1, kCuLds / (int64_t)lds);
+    int64_t ny = (TRAIN ? 1 : 4) * resident / a.P;
+    if (ny < 1) ny = 1;
+    if (ny > strips) ny = strips;
+    if constexpr (TRAIN) {
+        // every workgroup's sums; without room for them (a stream that is being captured) one
+        // workgroup per part and the handle's own block of one set
+        const int64_t books = (int64_t)a.P * a.len * a.w, ents = (int64_t)a.P * a.len;
+        if (ensure_scratch(p, sizeof(float) * (size_t)(ny * (books + ents)), s)) {
+            a.sums = (float *)p->d_scratch;
+        } else {
+            ny = 1;
+            a.sums = p->d_train;
+        }
+        a.counts = (uint32_t *)(a.sums + ny * books);
+    }
+    a.ny = (int)ny;
+    const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
+    kern<<<(unsigned)blocks, TH, lds, s>>>(a);
+    if constexpr (TRAIN)
+        vq_means_kernel<<<blocks_for((int64_t)a.P * a.len * a.w), kThreads, 0, s>>>(a.sums, a.counts, a.ny, a.P, a.w,
+                                                                                   a.len, p->d_cb);
+    return true;
+}
+
+template <typename T, int G, int METRIC>
+bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t s) {
+    const int tiles = (a.len + 31) / 32;
+    // entries in LDS next to their pieces when as many workgroups share a CU as their registers
+    // allow (training: when it fits at all); else as many pieces as a CU holds, the rule reading
+    // its few entries from L2
+    const bool ent = nearest_lds(p, G, tiles, true, train) <= (size_t)(train ? kCuLds - 1024 : kCuLds / (G == 1 ? 4 : G == 2 ? 3 : 2));
+    if (train && !ent) return false;
+    const int fit = (int)(152 * 1024 / (G * 1024 + 128));
+    a.NT = ent || tiles < fit ? tiles : fit;
+    const size_t lds = nearest_lds(p, G, a.NT, ent, train);
+    if (train) {
+        if constexpr (METRIC == BIFEAT_VQ_L2) return launch_one<T, G, METRIC, true, true>(p, a, lds, s);
+        else return false;  // the rounds of a cosine codebook go through its codes
+    }
+    return ent ? launch_one<T, G, METRIC, true, false>(p, a, lds, s)
+               : launch_one<T, G, METRIC, false, false>(p, a, lds, s);
+}
+
+template <typename T, int G>
+bool launch_groups(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t s) {
+    const int cell_bits = ilog2(4 * ((a.len + 31) / 32));
+    a.margin = vq_margin(a.w, G, cell_bits);
+    a.cell_mask = (1u << cell_bits) - 1u;
+    return p->scheme.vq_metric == BIFEAT_VQ_COSINE ? launch_metric<T, G, BIFEAT_VQ_COSINE>(p, a, train, s)
+                                                   : launch_metric<T, G, BIFEAT_VQ_L2>(p, a, train, s);
+}
+
+// codes == nullptr: training
+template <typename T>
+bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, double *distortion,
+                    hipStream_t s) {
+    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    if (w > kNearestMaxWidth || len <= kNearestMinLength) return false;
+    VqNearestArgs<T> a{};
+    a.x = x;
+    a.rows = rows;
+    a.D = (int)p->D;
+    a.w = w;
+    a.len = len;
+    a.P = p->P;
+    a.cbytes = p->cbytes;
+    a.vec = w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
+    a.cb = p->d_cb;
+    a.rnorm = p->d_rnorm;
+    a.codes = codes;
+    a.rb = rb;
+    a.distortion = distortion;
+    switch ((w + 7) / 8) {
+        case 1: return launch_groups<T, 1>(p, a, !codes, s);
+        case 2: return launch_groups<T, 2>(p, a, !codes, s);
+        case 3: return launch_groups<T, 3>(p, a, !codes, s);
+        default: return launch_groups<T, 4>(p, a, !codes, s);
+    }
+}
+
+}  // namespace
+
+template <typename T>
+bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
+                             hipStream_t s) {
+    return launch_nearest<T>(p, x, rows, codes, rb, nullptr, s);
+}
+
+template <typename T>
+bool launch_vq_nearest_round(bifeat_params *p, const T *x, int64_t rows, double *distortion, hipStream_t s) {
+    return launch_nearest<T>(p, x, rows, nullptr, 0, distortion, s);
+}
+
+#define BF_VN(T)                                                                                              \
+    template bool launch_vq_nearest_codes<T>(bifeat_params *, const T *, int64_t, uint8_t *, int64_t, hipStream_t); \
+    template bool launch_vq_nearest_round<T>(bifeat_params *, const T *, int64_t, double *, hipStream_t);
+BF_VN(float)
+BF_VN(__half)
+#undef BF_VN
+
+}  // namespace bf

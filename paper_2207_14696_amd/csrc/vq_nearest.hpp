@@ -1,0 +1,23 @@
+// Nearest-entry search of the vector codes on the matrix cores: what its callers see.
+#pragma once
+
+#include "common.hpp"
+
+namespace bf {
+
+// Both return false (nothing launched) for shapes that stay with the plain search: parts of more
+// than 32 columns, codebooks of up to 16 entries, and in training codebooks whose sums do not fit
+// LDS next to the entries.
+
+// the index of every part's nearest entry into the rows at `codes` (row stride rb bytes, indices
+// of p->cbytes bytes, the bytes behind them zeroed)
+template <typename T>
+bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
+                             hipStream_t s);
+
+// one Lloyd round over the rows (Euclidean codebooks): every entry becomes the mean of the parts
+// nearest to it, their squared distances are added to *distortion
+template <typename T>
+bool launch_vq_nearest_round(bifeat_params *p, const T *x, int64_t rows, double *distortion, hipStream_t s);
+
+}  // namespace bf

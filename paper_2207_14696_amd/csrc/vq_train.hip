@@ -10,11 +10,13 @@
 // the result depend on the order of additions in the last bits; it is judged on
 // distortion, not bit for bit.
 // Two forms: Euclidean one-byte codebooks small enough for LDS fuse the search
-// with the accumulation (sums first in LDS per workgroup, then global atomics);
-// everything else (cosine metric, up to 16384 entries, wide parts) runs the
+// with the accumulation (vq_nearest.hip; parts of more than 32 columns and codebooks
+// of up to 16 entries: the plain search here, sums first in LDS per workgroup, then
+// global atomics); everything else (cosine metric, up to 16384 entries) runs the
 // encoder's own kernel into a scratch code array and accumulates from that with
 // global atomics.
 #include "common.hpp"
+#include "vq_nearest.hpp"
 
 namespace bf {
 
@@ -43,7 +45,7 @@ __global__ void vq_zero_kernel(float *__restrict__ a, int64_t n) {
 template <typename T, int W>
 __global__ __launch_bounds__(kThreads) void vq_lloyd_accumulate_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w_rt, int len, const float *__restrict__ cb,
-    float *__restrict__ sums, float *__restrict__ counts, float *__restrict__ distortion) {
+    float *__restrict__ sums, float *__restrict__ counts, double *__restrict__ distortion) {
     extern __shared__ float sm[];
     const int w = W > 0 ? W : w_rt;
     float *s_cb = sm, *s_sum = sm + len * w, *s_cnt = s_sum + len * w;
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void vq_lloyd_accumulate_kernel(
     for (int i = threadIdx.x; i < len; i += kThreads)
         if (s_cnt[i] != 0.0f) atomicAdd(&counts[(int64_t)p * len + i], s_cnt[i]);
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
-    if ((threadIdx.x & 63) == 0) atomicAdd(distortion, dsum);
+    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(distortion, (double)dsum);
 }
 
 __global__ void vq_lloyd_update_kernel(float *__restrict__ cb, const float *__restrict__ sums,
@@ -110,7 +112,9 @@ __global__ void vq_lloyd_update_kernel(float *__restrict__ cb, const float *__re
 }
 
 template <typename T>
-void lloyd_round(bifeat_params *p, const T *x, int64_t rows, float *dist_slot, hipStream_t s) {
+void lloyd_round(bifeat_params *p, const T *x, int64_t rows, double *dist_slot, hipStream_t s) {
+    if (launch_vq_nearest_round<T>(p, x, rows, dist_slot, s)) return;
+    // what the matrix-core search leaves: wide parts and tiny codebooks
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
     const int64_t n = (int64_t)P * len * w;
     float *sums = p->d_train, *counts = p->d_train + n;
@@ -150,7 +154,7 @@ template <typename T, typename CODE>
 __global__ __launch_bounds__(kThreads) void vq_accumulate_codes_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w, int len, int P,
     const CODE *__restrict__ codes, const float *__restrict__ cb, float *__restrict__ sums,
-    float *__restrict__ counts, float *__restrict__ distortion) {
+    float *__restrict__ counts, double *__restrict__ distortion) {
     const int64_t items = rows * P;
     float dsum = 0.0f;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < items;
@@ -168,11 +172,11 @@ __global__ __launch_bounds__(kThreads) void vq_accumulate_codes_kernel(
         atomicAdd(&counts[e], 1.0f);
     }
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
-    if ((threadIdx.x & 63) == 0) atomicAdd(distortion, dsum);
+    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(distortion, (double)dsum);
 }
 
 template <typename T>
-void lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, float *dist_slot, hipStream_t s) {
+void lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, double *dist_slot, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
     const int64_t n = (int64_t)P * len * w;
     float *sums = p->d_train, *counts = p->d_train + n;
@@ -237,7 +241,7 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
         else
             vq_init_kernel<__half><<<256, 256, 0, s>>>((const __half *)chunk, (int)p->D, w, len, P, p->d_cb);
     }
-    vq_zero_kernel<<<1, 64, 0, s>>>(p->d_dist, rounds);
+    vq_zero_kernel<<<1, 128, 0, s>>>(reinterpret_cast<float *>(p->d_dist), 2 * rounds);
     for (int k = 0; k < rounds; k++) {
         if (fused) {
             if (dtype == BIFEAT_F32) lloyd_round(p, (const float *)chunk, rows, p->d_dist + k, s);

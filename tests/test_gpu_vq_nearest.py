@@ -1,0 +1,122 @@
+"""The encoder's nearest-entry search on the matrix cores against the oracle's plain search, code for
+code: the edges of its tiles (32 entries, 64 rows, 8 columns a group), both metrics, codebooks that fit
+LDS and that do not, and inputs for which the score alone cannot decide (ties, values outside the range
+of the split, NaN and infinities)."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from helpers import scheme_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bf():
+    import paper_2207_14696_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    return t
+
+
+def _codes(bf, torch, x, cb, D, w, length, metric):
+    q = bf.Quantizer(scheme_of("vq", 8, w, length, metric), D)
+    q.params_set_codebooks(cb)
+    codes = torch.full((len(x), q.row_bytes), 0xEE, dtype=torch.uint8, device="cuda")
+    q.quantize(torch.from_numpy(x).cuda(), codes, 0)
+    return codes.cpu().numpy()
+
+
+def _check(bf, torch, x, cb, D, w, length, metric):
+    got = _codes(bf, torch, x, cb, D, w, length, metric)
+    with np.errstate(all="ignore"):
+        want = orc.pack(orc.vq_assign(x, w, cb, metric=metric), orc.vq_code_bits(length))
+    bad = (got != want).any(1)
+    assert not bad.any(), f"{bad.sum()} of {len(x)} rows differ, first {np.nonzero(bad)[0][:4]}"
+
+
+def _codebook(rng, D, w, length):
+    P = -(-D // w)
+    return rng.normal(size=(P, length, w)).astype(np.float32)
+
+
+# w: one to four groups of 8 columns, 4-column loads or not, a short last part; length: either side of
+# the plain search's limit, of a tile and of a cell, up to several chunks of LDS (4500 x 32)
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("D,w,length,rows,dtype", [
+    (24, 8, 16, 300, np.float32), (24, 8, 17, 300, np.float32), (24, 8, 32, 64, np.float32),
+    (24, 8, 33, 65, np.float32), (64, 8, 256, 1000, np.float32), (64, 8, 255, 1000, np.float16),
+    (22, 5, 64, 257, np.float32), (23, 4, 100, 257, np.float32), (3, 1, 20, 500, np.float32),
+    (48, 12, 130, 511, np.float16), (50, 16, 256, 513, np.float32), (64, 16, 2048, 600, np.float32),
+    (40, 20, 64, 129, np.float32), (64, 32, 256, 300, np.float32), (33, 32, 70, 300, np.float32),
+    (32, 32, 4500, 200, np.float32), (33, 33, 64, 100, np.float32)])
+def test_codes_equal_the_plain_search(bf, torch, D, w, length, rows, dtype, metric):
+    rng = np.random.default_rng(D * 1000 + w * 7 + length)
+    cb = _codebook(rng, D, w, length)
+    x = (rng.normal(size=(rows, D)) * 1.2 + 0.3).astype(dtype)
+    _check(bf, torch, x, cb, D, w, length, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("scale", [1e-30, 1e-6, 1.0, 1e5, 1e18])
+def test_scale_of_the_data(bf, torch, scale, metric):
+    rng = np.random.default_rng(5)
+    cb = (_codebook(rng, 32, 8, 128) * scale).astype(np.float32)
+    x = (rng.normal(size=(400, 32)) * scale).astype(np.float32)
+    x[::7] *= 1e3               # rows far outside the codebook
+    x[3::50] *= 1e8
+    _check(bf, torch, x, cb, 32, 8, 128, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+def test_ties_and_near_ties_go_by_the_rule(bf, torch, metric):
+    # integer features: many entries at exactly the same distance, entries repeated
+    rng = np.random.default_rng(6)
+    cb = rng.integers(0, 2, size=(4, 256, 8)).astype(np.float32)
+    x = rng.integers(0, 2, size=(2000, 32)).astype(np.float32)
+    _check(bf, torch, x, cb, 32, 8, 256, metric)
+    # entries a few units in the last place apart; a handful of open rows per wave
+    base = rng.normal(size=(4, 64, 8)).astype(np.float32)
+    near = np.nextafter(base, np.float32(9))
+    cb = np.concatenate([base, near, base + np.float32(1e-6), rng.normal(size=base.shape).astype(np.float32) * 3], 1)
+    x = (rng.normal(size=(2000, 32)) * 2).astype(np.float32)
+    _check(bf, torch, x, cb, 32, 8, 256, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+def test_special_values(bf, torch, metric):
+    rng = np.random.default_rng(7)
+    cb = _codebook(rng, 32, 8, 96)
+    cb[1, 40] = 0.0
+    x = rng.normal(size=(300, 32)).astype(np.float32)
+    x[0] = np.nan
+    x[1, 3] = np.inf
+    x[2, 9] = -np.inf
+    x[3, 20] = np.nan
+    x[4] = 0.0
+    x[5] = -0.0
+    x[6] = 1e-42
+    x[7] = 3e38
+    x[8, :8] = 0.0
+    x[70:90] = np.inf            # many rows of one wave
+    _check(bf, torch, x, cb, 32, 8, 96, metric)
+    cb[0, 17, 2] = np.inf        # a part whose codebook is not finite
+    cb[2] = 0.0                  # and one that is all zeros
+    _check(bf, torch, x, cb, 32, 8, 96, metric)
+
+
+def test_rounds_of_training_agree_with_the_oracle(bf, torch):
+    # distances and assignments of every round (the sums' order leaves 1e-6 of the distortion)
+    rng = np.random.default_rng(8)
+    x = rng.normal(size=(3001, 44)).astype(np.float32)
+    q = bf.Quantizer(scheme_of("vq", 8, 8, 200), 44)
+    q.fit_update(torch.from_numpy(x).cuda())
+    q.fit_finalize()
+    _, want = orc.vq_train(x, 8, 200, iters=10)
+    np.testing.assert_allclose(q.vq_distortion(10)[:3], want[:3], rtol=1e-5)
+    assert np.all(np.diff(q.vq_distortion(10)) <= 1e-6 * want[0])
