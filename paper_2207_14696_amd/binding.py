@@ -117,8 +117,12 @@ def _check(status: int) -> None:
 
 
 def _stream() -> int:
+    """Handle of the current stream of the current device.  Asked for at every call: building the
+    Stream object of torch.cuda.current_stream() takes 2.8 us of a call's 10, the handle 0.2."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev_ptr(t, dtypes=None) -> int:
