@@ -44,6 +44,7 @@ constexpr int kStageMinLprLog2 = 3;  // ... when at least 8 lanes share a destin
 #ifndef BF_LEAN_U
 #define BF_LEAN_U 4
 #endif
+constexpr int64_t kSplitWaves = 2048;
 #ifndef BF_LEAN_WPE
 #define BF_LEAN_WPE 6
 #endif
@@ -59,12 +60,12 @@ constexpr int kStageMinLprLog2 = 3;  // ... when at least 8 lanes share a destin
 // longer than thr (the caller promised there are none): such a list gets a row of NaNs and
 // raises the status word.
 // STAGE: the tile's list entries are fetched once by the wave and parked in LDS (see below).
-template <int BITS, int CW, bool WIDE, bool SUM, bool PAIR, bool STAGE, typename IT>
+template <int BITS, int CW, bool WIDE, bool SUM, bool PAIR, bool STAGE, bool SHARE, typename IT>
 __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_kernel(
     const uint8_t *__restrict__ codes, uint32_t rb, const int64_t *__restrict__ indptr,
     const IT *__restrict__ indices, int64_t V, int D, int Dp, const float *__restrict__ mn,
     const float *__restrict__ sc, const uint8_t *__restrict__ zero_row, float *__restrict__ out,
-    int lpr_log2, int chunks, int thr, int lo, int alone, int32_t *__restrict__ status) {
+    int lpr_log2, int s_log2_rt, int chunks, int thr, int lo, int alone, int32_t *__restrict__ status) {
     using W = LeanSwar<BITS, WIDE>;
     constexpr int R = CW * W::kN;   // accumulator registers per lane
     constexpr int CPW = 32 / BITS;  // codes per word
@@ -82,11 +83,17 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
     uint32_t *stage = smem + 2 * Dp + 64 * kLeanWaves + wave * (64 * R);
     uint32_t *sidx = smem + 2 * Dp + 64 * kLeanWaves + kLeanWaves * (64 * R) + wave * kIdxStage;
 
+    // LPR lanes fetch a row, S groups of them share a destination's list (S > 1: small launches,
+    // see the launcher): group `grp` takes the entries grp, grp + S, ...
+    // (compiled apart: the strides cost large launches half a percent)
+    const int s_log2 = SHARE ? s_log2_rt : 0;
     const int LPR = 1 << lpr_log2;
-    const int dpw_log2 = 6 - lpr_log2;
+    const int dl_log2 = lpr_log2 + s_log2;
+    const int dpw_log2 = 6 - dl_log2;
     const int dpw = 1 << dpw_log2;
     const int lane_chunk = lane & (LPR - 1);
-    const int d_local = lane >> lpr_log2;
+    const int grp = (lane >> lpr_log2) & ((1 << s_log2) - 1);
+    const int d_local = lane >> dl_log2;
     const bool chunk_ok = lane_chunk < chunks;
     const uint32_t coff = (uint32_t)lane_chunk * (CW * 4);
     const int nf4 = D >> 2;
@@ -133,13 +140,13 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
         bool staged = false;
         if constexpr (STAGE) {
             tbeg = __shfl(beg, 0);
-            const int64_t tlen = __shfl(end, (ndst - 1) << lpr_log2) - tbeg;
+            const int64_t tlen = __shfl(end, (ndst - 1) << dl_log2) - tbeg;
             staged = tlen <= kIdxStage;
             if (staged)
                 for (int i = lane; i < (int)tlen; i += 64) sidx[i] = (uint32_t)indices[tbeg + i];
         }
         const int n = mine ? (int)n64 : 0;
-        if (lane_chunk == 0) {
+        if (lane_chunk == 0 && grp == 0) {
             // > 0: scale of the sum; 0: empty list; < 0: another kernel's destination; NaN: over
             meta[d_local] = mine ? (n > 0 ? (SUM ? (float)n : 1.0f / (float)n) : 0.0f)
                                  : (over ? __builtin_nanf("") : -1.0f);
@@ -150,7 +157,7 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
         uint32_t acc[R];
 #pragma unroll
         for (int r = 0; r < R; r++) acc[r] = 0u;
-        const int cnt = chunk_ok ? n : 0;
+        const int cnt = chunk_ok ? (n - grp + (1 << s_log2) - 1) >> s_log2 : 0;  // <= 0: none
         // U rows per step: their ids first, all together and unconditional (the compiler would
         // otherwise sink each read into a branch on its slot's validity and serialise the row
         // loads behind them), then the U row loads, then the field-parallel adds; slots past
@@ -159,7 +166,7 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
     for (int k = 0; k < cnt; k += U) {                                                            \
         uint32_t row[U];                                                                          \
         uint32_t w[U][CW];                                                                        \
-        _Pragma("unroll") for (int u = 0; u < U; u++) row[u] = (uint32_t)ROW_OF[min(k + u, cnt - 1)]; \
+        _Pragma("unroll") for (int u = 0; u < U; u++) row[u] = (uint32_t)ROW_OF[min(k + u, cnt - 1) << s_log2]; \
         _Pragma("unroll") for (int u = 0; u < U; u++) asm volatile("" : "+v"(row[u]));            \
         _Pragma("unroll") for (int u = 0; u < U; u++) {                                           \
             const uint8_t *src = (k + u < cnt) ? codes + (uint64_t)row[u] * rb + coff : zero_row; \
@@ -170,10 +177,10 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
                 _Pragma("unroll") for (int i = 0; i < W::kN; i++)                                 \
                     acc[c * W::kN + i] += (w[u][c] >> (BITS * i)) & W::kMask;                     \
     }
-        const IT *ip = indices + beg;
+        const IT *ip = indices + beg + grp;
         if constexpr (STAGE) {
             if (staged) {
-                const uint32_t *lp = sidx + (int)(beg - tbeg);
+                const uint32_t *lp = sidx + (int)(beg - tbeg) + grp;
                 BF_LEAN_STEP(lp)
             } else {
                 BF_LEAN_STEP(ip)
@@ -184,8 +191,14 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
 #undef BF_LEAN_STEP
         // the next tile's list bounds travel while this tile's rows are written
         bounds(tile + n_waves, beg, end);
-        {
-            uint32_t *sp = stage + lane * R;
+        if constexpr (SHARE) {
+            for (int m = LPR; m < 1 << dl_log2; m <<= 1) {  // the groups of a destination add up
+#pragma unroll
+                for (int r = 0; r < R; r++) acc[r] += (uint32_t)__shfl_xor((int)acc[r], m);
+            }
+        }
+        if (grp == 0) {
+            uint32_t *sp = stage + ((d_local << lpr_log2) + lane_chunk) * R;
 #pragma unroll
             for (int r = 0; r < R; r++) sp[r] = acc[r];
         }
@@ -306,7 +319,18 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
     if (!cw) return false;  // packed row longer than 64 lane loads
     const int chunks = (int)(payload / (4 * cw));
     const int lpr = pow2ceil(chunks);
-    const int dpw = 64 / lpr;
+    // A launch of few destinations leaves most of the chip idle and takes as long as its longest
+    // chain of dependent row fetches: there the groups of a wave share the lists, until a group's
+    // share of the longest list that is to be expected (the caller's bound, else twice the
+    // average) is one step of BF_LEAN_U rows (the mean only: the sums keep one form), up to 2048 waves (8 per CU).  4-bit rows of 64 bytes,
+    // lists of up to 25: 1 024 destinations 9.3 -> 4.8 us (512 waves); 6 200 destinations 8.9 us
+    // unshared, 6.1 with 2048 waves, 7.1 with 4096.
+    const int64_t longest = c.max_degree > 0 ? c.max_degree : 2 * c.E / (V > 0 ? V : 1);
+    int s_log2 = 0;
+    while (!c.agg_sum && (lpr << (s_log2 + 1)) <= 64 && ((int64_t)BF_LEAN_U << s_log2) < longest &&
+           (V * (lpr << (s_log2 + 1)) + 63) / 64 <= kSplitWaves)
+        s_log2++;
+    const int dpw = 64 / (lpr << s_log2);
     const int64_t tiles = (V + dpw - 1) / dpw;
     const int64_t cap = p->opt_mean_blocks > 0 ? p->opt_mean_blocks : (1 << 16);
     int64_t want = (tiles + kLeanWaves - 1) / kLeanWaves;
@@ -316,10 +340,15 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
     const size_t shm = sizeof(uint32_t) * ((size_t)2 * Dp + 64 * kLeanWaves + (size_t)kLeanWaves * 64 * R +
                                            (size_t)kLeanWaves * kIdxStage);
     const bool stage = ilog2(lpr) >= kStageMinLprLog2;
-#define BF_LK(CWV, SUMV, STG, IT)                                                                  \
-    gather_mean_lean_kernel<BITS, CWV, WIDE, SUMV, PAIR, STG, IT><<<blocks, kLeanThreads, shm, c.s>>>( \
+#define BF_LK1(CWV, SUMV, STG, SHR, IT)                                                            \
+    gather_mean_lean_kernel<BITS, CWV, WIDE, SUMV, PAIR, STG, SHR, IT><<<blocks, kLeanThreads, shm, c.s>>>( \
         c.codes, (uint32_t)rb, c.indptr, (const IT *)c.indices, V, D, Dp, mn, sc, p->d_zero,       \
-        c.out, ilog2(lpr), chunks, thr, lo, alone ? 1 : 0, c.status)
+        c.out, ilog2(lpr), s_log2, chunks, thr, lo, alone ? 1 : 0, c.status)
+#define BF_LK(CWV, SUMV, STG, IT)                                                                  \
+    do {                                                                                           \
+        if (!SUMV && s_log2 > 0) BF_LK1(CWV, SUMV, STG, !SUMV, IT);                                \
+        else BF_LK1(CWV, SUMV, STG, false, IT);                                                    \
+    } while (0)
 #define BF_LS(CWV, SUMV)                                                                           \
     do {                                                                                           \
         if (stage) {                                                                               \
@@ -344,6 +373,7 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
 #undef BF_LN
 #undef BF_LS
 #undef BF_LK
+#undef BF_LK1
     return true;
 }
 
