@@ -115,25 +115,34 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
     float *s_par = reinterpret_cast<float *>(smem);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint4 *raw = reinterpret_cast<uint4 *>(smem + ((npar + 3) & ~3)) + wave * 64;
+    const int RT = 64 / c16;
+    const int r = lane / c16, c = lane - r * c16;
+    const int64_t tiles = (M + RT - 1) / RT;
+    const int64_t n_waves = (int64_t)gridDim.x * (kThreads / 64);
+    // the packed rows of a tile, one 16-byte piece per lane (lane = r*c16 + c); the first tile's
+    // travel while the parameters are staged
+    auto fetch = [&](int64_t tile) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (tile < tiles && r < RT && tile * RT + r < M) v = codes16[idx[tile * RT + r] * s16 + c];
+        return v;
+    };
+    int64_t tile = (int64_t)blockIdx.x * (kThreads / 64) + wave;
+    uint4 next = fetch(tile);
     for (int i = threadIdx.x; i < npar; i += kThreads) {
         if constexpr (DEC == DEC_UNIFORM) s_par[i] = i < D ? pb[i] : pa[i - D];  // [scale | min]
         else s_par[i] = pa[i];
     }
     __syncthreads();
 
-    const int RT = 64 / c16;
-    const int r = lane / c16, c = lane - r * c16;
     const int nf4 = D >> 2;
     const int step_d = 64 / nf4, step_f = 64 % nf4;
     const int lane_d = lane / nf4, lane_f = lane % nf4;
     const int rb = c16 * 16;
-    const int64_t tiles = (M + RT - 1) / RT;
-    const int64_t n_waves = (int64_t)gridDim.x * (kThreads / 64);
     constexpr uint32_t mask = (1u << BITS) - 1u;
-    for (int64_t tile = (int64_t)blockIdx.x * (kThreads / 64) + wave; tile < tiles; tile += n_waves) {
+    for (; tile < tiles; tile += n_waves) {
         const int64_t row0 = tile * RT;
         const int nrow = (int)min((int64_t)RT, M - row0);
-        if (r < nrow) raw[lane] = codes16[idx[row0 + r] * s16 + c];  // lane = r*c16 + c
+        if (r < nrow) raw[lane] = next;
         wave_sync();
         float4 *span = reinterpret_cast<float4 *>(out + row0 * D);
         const int ngran = nrow * nf4;
@@ -164,6 +173,7 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
                 d++;
             }
         }
+        next = fetch(tile + n_waves);
         wave_sync();  // raw is rewritten by the next tile
     }
 }
