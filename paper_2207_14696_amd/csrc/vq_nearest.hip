@@ -8,26 +8,27 @@
 // search: s = |c|^2/2 - x.c (cosine: -x.c/|c|) for 32 rows x 32 entries at a time, both factors
 // split into two half-precision pieces (hi + lo, 22 bits) so that all four piece products are
 // two MFMAs of K = 16 per 8 columns.  A lane keeps, per row, the best and the second best *cell*
-// (4 consecutive entries: the accumulator registers 4q..4q+3), which costs 5 vector instructions
-// per 4 scores; the rule itself then decides inside the winning cell.  That the winning cell
-// holds the rule's entry is certain when the second best cell is further away than the errors of
-// both evaluations together (`margin`, derived at vq_margin below); a row for which it is not -
-// near ties, values outside the range the split holds - is searched by the rule over the whole
-// codebook, by the wave together, or lane by lane when many rows of a wave need it.
-// The codes are therefore the same as the plain search gives, for any input.
+// (8 entries: the accumulator registers 4q..4q+3 of two neighbouring tiles), which costs 7 vector
+// instructions per 8 scores; the 8 entries of the winning cell are then scored in fp32.  Each of
+// the two decisions is certain to be the rule's own when the second best is further away than
+// the errors of both evaluations together (derived at vq_margin and vq_cell_margin below); a row
+// for which it is not - near ties, values outside the range the split holds - is searched by the
+// rule over the whole codebook, by the wave together, or lane by lane when many rows of a wave
+// need it.  The codes are therefore the same as the plain search gives, for any input.
 //
-// What bounds it: vector instructions - 368 of ~720 per 64 rows and part are the running minima
-// over 256 entries, ~190 the rule inside the cell, ~70 the split of x - next to 16 cycles of MFMA
-// per row and part (164 of the 706 us below).  64 rows per wave reuse each 1 KB of entry pieces
-// read from LDS four times; cells of 8 entries would save 96 instructions of the minima and cost
-// as many in the cell.  262 144 rows of 96 parts x 256 entries x 8 columns: 706 us, the plain
-// search 3111 us.
+// What bounds it: vector instructions - of ~570 per 64 rows and part 272 are the running minima
+// over 256 entries, 133 the scores inside the cell, 59 the split of x - at 75 % of the issue rate,
+// next to LDS (entry pieces, constants and cells: 430 cycles per 64 rows) and 18 cycles of MFMA
+// per row and part.  64 rows per wave reuse each 1 KB of entry pieces read from LDS four times.
+// Cells of 4 entries decided by the rule itself: 660 instructions, 680 us; one tile at a time
+// instead of a set's minima under the other set's product: 706 us.  262 144 rows of 96 parts x 256
+// entries x 8 columns: 661 us, the plain search 3111 us.
 //
 // Training adds each part to its entry's sum in LDS.  The sums are kept in 64 bits: an LDS
 // float add takes 196 cycles per wave here whatever the addresses, a double add 22 (integer: 8).
 // A workgroup writes its sums to the workspace and a second kernel adds them up in a fixed order
 // (global float adds onto the same few addresses ran at 22.6 G/s, a quarter of the round).  One
-// round over 65 536 rows of that shape: 210 us, before (plain search, fp32 adds) 1030 us.
+// round over 65 536 rows of that shape: 200 us, before (plain search, fp32 adds) 1030 us.
 #include "vq_nearest.hpp"
 
 #include <algorithm>
@@ -49,7 +50,7 @@ struct VqNearestArgs {
     int ny;                 // workgroups per part
     const float *cb;        // [P][len][w]
     const float *rnorm;     // [P][len], cosine metric
-    float margin;           // see vq_margin
+    float margin, cell_margin;  // see vq_margin
     uint32_t cell_mask;     // low bits of a score that hold a cell's number
     uint8_t *codes;         // (the encoder)
     int64_t rb;
@@ -97,7 +98,9 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     constexpr int WP = 8 * G;          // columns of a part, padded with zeros
     constexpr int TH = ENT ? 256 : 512;
     constexpr int WAVES = TH / 64;
-    constexpr int CELL = 4 * WP + 4;   // floats of a cell in LDS: 16 bytes of padding spread the banks
+    // floats of 4 entries in LDS and of the 16 such groups of two tiles: the padding spreads the
+    // groups, which different lanes read at the same time, over the banks
+    constexpr int CELL = 4 * WP + 4, PAIR = 16 * CELL + 4;
     constexpr bool COS = METRIC == BIFEAT_VQ_COSINE;
     extern __shared__ uint4 s_raw[];
     // [entry pieces: NT x G x 64 lanes x 16 bytes | scores' constant: NT x 32 | entries | rnorm |
@@ -105,8 +108,8 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     half8 *s_frag = reinterpret_cast<half8 *>(s_raw);
     float *s_half = reinterpret_cast<float *>(s_frag + (size_t)a.NT * G * 64);
     float *s_ent = s_half + a.NT * 32;
-    float *s_rn = s_ent + (ENT ? a.NT * 8 * CELL : 0);
-    // (every piece above is a multiple of 32 floats)
+    float *s_rn = s_ent + (ENT ? a.NT / 2 * PAIR : 0);
+    // (every piece above is a multiple of 4 floats)
     double *s_sum = reinterpret_cast<double *>(s_rn + (ENT && COS ? a.NT * 32 : 0));
     uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s_sum + (TRAIN ? a.len * a.w : 0));
     __shared__ unsigned s_cmax, s_c2max;
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     if (id >= (unsigned)(a.P * a.ny)) return;
     const int part = (int)(id % (unsigned)a.P), by = (int)(id / (unsigned)a.P);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5, col = lane & 31;
+    const int half = lane >> 5;
     const int w = a.w, len = a.len;
     const float *part_cb = a.cb + (int64_t)part * len * w;
     const float *part_rn = COS ? a.rnorm + (int64_t)part * len : nullptr;
@@ -168,8 +171,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
                 for (int j = 0; j < 8; j++) {
                     const int d = 8 * g + j;
                     const float c = real && d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
-                    // (an entry past the last one is NaN to the rule: never less than another)
-                    if constexpr (ENT) s_ent[(i >> 2) * CELL + (i & 3) * WP + d] = real ? c : __builtin_nanf("");
+                    if constexpr (ENT) s_ent[(i >> 6) * PAIR + ((i >> 2) & 15) * CELL + (i & 3) * WP + d] = c;
                     float cs = COS ? c * (rn * 1024.0f) : c * scale;
                     // one fp32 value for both pieces: the compiler may otherwise fold the product
                     // into one of the conversions and round the pieces from different values
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             if (!COS) atomicMax(&s_c2max, __float_as_uint(s2));
         }
     };
-    const int tiles = (len + 31) >> 5;
+    const int tiles = ((len + 63) >> 6) << 1;  // in pairs: a cell spans two tiles
     const bool single = tiles <= a.NT;
     if (single) stage(0, tiles);
     if (!single && !COS) {
@@ -204,13 +206,15 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     __syncthreads();
     const bool part_bad = s_bad != 0;
     const float c2max = __uint_as_float(s_c2max) * 1.0001f;
+    const float unscale = 1.0f / (scale * scale);
     uint32_t keep = ~a.cell_mask;
     asm volatile("" : "+v"(keep));  // in a vector register: mask and cell number are then one instruction
 
     // entry e as the rule sees it (columns past w: zeros)
     auto entry = [&](int e, float (&c)[WP], float &rn) {
         if constexpr (ENT) {
-            const float4 *src = reinterpret_cast<const float4 *>(s_ent + (e >> 2) * CELL + (e & 3) * WP);
+            const float4 *src = reinterpret_cast<const float4 *>(s_ent + (e >> 6) * PAIR +
+                                                                      ((e >> 2) & 15) * CELL + (e & 3) * WP);
 #pragma unroll
             for (int k = 0; k < WP / 4; k++) {
                 const float4 v = src[k];
@@ -228,68 +232,83 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     float dsum = 0.0f;
     // every wave of the workgroup walks the same strips (staging a chunk synchronises)
     constexpr int ROWS = WAVES * 64;
-    for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += (int64_t)a.ny * ROWS) {
-        // ---- 2 x 32 rows per wave: sub-vectors split into pieces.  Both halves of the wave hold
-        // the pieces of both sets; a lane decides row `lane` in the end and keeps that one whole.
-        auto load_row = [&](int64_t r, float (&v)[WP]) {
-            const T *src = a.x + (r < a.rows ? r : a.rows - 1) * a.D + (int64_t)part * w;
-            if (a.vec) {  // w % 4 == 0, D % 4 == 0, 4 columns aligned
+    // a row past the last one reads the last one
+    auto load_row = [&](int64_t row, float (&v)[WP]) {
+        const T *src = a.x + (row < a.rows ? row : a.rows - 1) * a.D + (int64_t)part * w;
+        if (a.vec) {  // w % 4 == 0, D % 4 == 0, 4 columns aligned
 #pragma unroll
-                for (int k = 0; k < WP / 4; k++) {
-                    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (4 * k < w && part * w + 4 * k < a.D) q = load4(src + 4 * k);
-                    v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
-                }
-            } else {
-#pragma unroll
-                for (int d = 0; d < WP; d++) v[d] = d < w && part * w + d < a.D ? load1(src + d) : 0.0f;
+            for (int k = 0; k < WP / 4; k++) {
+                float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (4 * k < w && part * w + 4 * k < a.D) q = load4(src + 4 * k);
+                v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
             }
-        };
+        } else {
+#pragma unroll
+            for (int d = 0; d < WP; d++) v[d] = d < w && part * w + d < a.D ? load1(src + d) : 0.0f;
+        }
+    };
+    float xn[WP];
+    load_row((int64_t)by * ROWS + wave * 64 + lane, xn);
+    for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += (int64_t)a.ny * ROWS) {
+        // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which both halves of
+        // the wave then hold for both sets of 32 rows
         const int64_t r = r0 + wave * 64 + lane;
         const bool valid = r < a.rows;
         float xr[WP];
-        load_row(r, xr);
-        half8 xh[2][G], xl[2][G];
-        float margin[2];
-        bool zero[2];
 #pragma unroll
-        for (int s = 0; s < 2; s++) {
-            float x[WP];
-            load_row(r0 + wave * 64 + s * 32 + col, x);
-            float f = scale;
-            bool bad = part_bad;
-            zero[s] = false;
-            if constexpr (COS) {  // the best entry does not depend on the row's length
-                float m = 0.0f;
+        for (int d = 0; d < WP; d++) xr[d] = xn[d];
+        float f = scale;
+        bool bad = part_bad, zero = false;
+        if constexpr (COS) {  // the best entry does not depend on the row's length
+            float m = 0.0f;
 #pragma unroll
-                for (int d = 0; d < WP; d++) m = fmaxf(m, fabsf(x[d]));
-                int e = 0;
-                frexpf(m, &e);
-                zero[s] = m == 0.0f;
-                bad |= !zero[s] && !(m >= 0x1p-50f && m <= 0x1p50f);
-                f = zero[s] || bad ? 1.0f : ldexpf(1.0f, kScaleExp - e);
-            }
-            float s2 = 0.0f;
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-#pragma unroll
-                for (int j = 0; j < 8; j += 2) {
-                    const float u = x[8 * g + j] * f, v = x[8 * g + j + 1] * f;
-                    s2 = fmaf(u, u, s2);
-                    s2 = fmaf(v, v, s2);
-                    const auto h = __builtin_amdgcn_cvt_pkrtz(u, v);
-                    const auto l = __builtin_amdgcn_cvt_pkrtz(u - (float)h[0], v - (float)h[1]);
-                    xh[s][g][j] = (_Float16)h[0];
-                    xh[s][g][j + 1] = (_Float16)h[1];
-                    xl[s][g][j] = (_Float16)l[0];
-                    xl[s][g][j + 1] = (_Float16)l[1];
-                }
-            }
-            bad |= !(s2 < kMaxNorm2);  // also NaN
-            const float big = COS ? sqrtf(s2) * 1024.5f : s2 + c2max;
-            margin[s] = bad ? INFINITY : big * a.margin;
-            if constexpr (COS) zero[s] = zero[s] && s2 == 0.0f && !part_bad;  // not a NaN that fmaxf passed over
+            for (int d = 0; d < WP; d++) m = fmaxf(m, fabsf(xr[d]));
+            int e = 0;
+            frexpf(m, &e);
+            zero = m == 0.0f;
+            bad |= !zero && !(m >= 0x1p-50f && m <= 0x1p50f);
+            f = zero || bad ? 1.0f : ldexpf(1.0f, kScaleExp - e);
         }
+        float s2 = 0.0f;
+        half8 xh[2][G], xl[2][G];
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const float u = xr[8 * g + 2 * j] * f, v = xr[8 * g + 2 * j + 1] * f;
+                s2 = fmaf(u, u, s2);
+                s2 = fmaf(v, v, s2);
+                const auto h = __builtin_amdgcn_cvt_pkrtz(u, v);
+                const auto l = __builtin_amdgcn_cvt_pkrtz(u - (float)h[0], v - (float)h[1]);
+                hi[j] = __builtin_bit_cast(uint32_t, h);
+                lo[j] = __builtin_bit_cast(uint32_t, l);
+            }
+            uint32_t set[2][2][4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                // one exchange of halves: [rows 0..31 twice], [rows 32..63 twice]
+                const auto h = __builtin_amdgcn_permlane32_swap(hi[j], hi[j], false, false);
+                const auto l = __builtin_amdgcn_permlane32_swap(lo[j], lo[j], false, false);
+                set[0][0][j] = h[0];
+                set[0][1][j] = h[1];
+                set[1][0][j] = l[0];
+                set[1][1][j] = l[1];
+            }
+#pragma unroll
+            for (int s = 0; s < 2; s++) {
+                __builtin_memcpy(&xh[s][g], set[0][s], 16);
+                __builtin_memcpy(&xl[s][g], set[1][s], 16);
+            }
+        }
+        bad |= !(s2 < kMaxNorm2);  // also NaN
+        const float big = COS ? sqrtf(s2) * 1024.5f : s2 + c2max;
+        const float margin = bad ? INFINITY : big * a.margin;
+        // (the cosine cell's scores are in units of |x|, unscaled)
+        const float cell_margin = COS ? sqrtf(s2) * a.cell_margin / f : big * unscale * a.cell_margin;
+        if constexpr (COS) zero = zero && s2 == 0.0f && !part_bad;  // not a NaN that fmaxf passed over
+        // the next strip's rows travel during this strip's search
+        load_row(r + (int64_t)a.ny * ROWS, xn);
         float best[2] = {3e38f, 3e38f}, second[2] = {3e38f, 3e38f};
         for (int t0 = 0; t0 < tiles; t0 += a.NT) {
             const int nt = min(a.NT, tiles - t0);
@@ -298,38 +317,75 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
                 stage(t0, nt);
                 __syncthreads();
             }
-            for (int t = 0; t < nt; t++) {
-                float16v c;
+            // A set's minima are taken while the matrix cores work on the other set: the next tile's
+            // product is started as soon as its accumulators are free, its operands having been
+            // read from LDS one half-step earlier.
+            half8 ent[G];
+            float16v c;
+            auto fetch = [&](int t) {
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
                     const float4 n = *reinterpret_cast<const float4 *>(s_half + t * 32 + 8 * q + 4 * half);
                     c[4 * q] = n.x; c[4 * q + 1] = n.y; c[4 * q + 2] = n.z; c[4 * q + 3] = n.w;
                 }
-                float16v acc[2] = {c, c};
+#pragma unroll
+                for (int g = 0; g < G; g++) ent[g] = s_frag[(t * G + g) * 64 + lane];
+            };
+            float16v acc[2];
+            auto product = [&](int s) {
+                acc[s] = c;
 #pragma unroll
                 for (int g = 0; g < G; g++) {
-                    const half8 ent = s_frag[(t * G + g) * 64 + lane];
-#pragma unroll
-                    for (int s = 0; s < 2; s++)
-                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent, xh[s][g], acc[s], 0, 0, 0);
-#pragma unroll
-                    for (int s = 0; s < 2; s++)
-                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent, xl[s][g], acc[s], 0, 0, 0);
+                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent[g], xh[s][g], acc[s], 0, 0, 0);
+                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent[g], xl[s][g], acc[s], 0, 0, 0);
                 }
+            };
+            float part4[2][4];  // of the pair's first tile
+            auto first = [&](int s) {
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    part4[s][q] = minimum(minimum(minimum(acc[s][4 * q], acc[s][4 * q + 1]), acc[s][4 * q + 2]),
+                                          acc[s][4 * q + 3]);
+            };
+            auto minima = [&](int s, int t) {
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    uint32_t number = (uint32_t)(4 * (t0 + t) + q);
+                    uint32_t number = (uint32_t)(2 * (t0 + t) + q);
                     asm volatile("" : "+s"(number));  // one scalar: the compiler would add it up per lane
-#pragma unroll
-                    for (int s = 0; s < 2; s++) {
-                        const float m = minimum(minimum(minimum(acc[s][4 * q], acc[s][4 * q + 1]), acc[s][4 * q + 2]),
-                                                acc[s][4 * q + 3]);
-                        // the cell's number replaces the low bits of its score
-                        const float key = __uint_as_float((__float_as_uint(m) & keep) | number);
-                        second[s] = __builtin_amdgcn_fmed3f(best[s], second[s], key);
-                        best[s] = minimum(best[s], key);
-                    }
+                    const float m = minimum(minimum(minimum(minimum(part4[s][q], acc[s][4 * q]), acc[s][4 * q + 1]),
+                                                    acc[s][4 * q + 2]), acc[s][4 * q + 3]);
+                    // the cell's number replaces the low bits of its score
+                    const float key = __uint_as_float((__float_as_uint(m) & keep) | number);
+                    second[s] = __builtin_amdgcn_fmed3f(best[s], second[s], key);
+                    best[s] = minimum(best[s], key);
                 }
+            };
+            fetch(0);
+            product(0);
+            product(1);
+            fetch(1);
+            for (int t = 0; t < nt; t += 2) {
+                // (past the last tile its product is computed once more and dropped; c outlives both
+                // products of a step: one of them would otherwise take over its registers, and 32
+                // copies would put things back in place)
+                __builtin_amdgcn_sched_barrier(0);
+                first(0);
+                __builtin_amdgcn_sched_barrier(0);
+                product(0);
+                first(1);
+                __builtin_amdgcn_sched_barrier(0);
+                product(1);
+                asm volatile("" : : "v"(c));
+                fetch(min(t + 2, nt - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                minima(0, t);
+                __builtin_amdgcn_sched_barrier(0);
+                product(0);
+                minima(1, t);
+                __builtin_amdgcn_sched_barrier(0);
+                product(1);
+                asm volatile("" : : "v"(c));
+                fetch(min(t + 3, nt - 1));
             }
         }
         // ---- the two halves of the wave hold different cells of the same rows; afterwards lane
@@ -348,26 +404,63 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             }
         }
         const uint32_t cell = __float_as_uint(b) & a.cell_mask;
-        bool open = !(gap > (half ? margin[1] : margin[0]));  // the rule has to look at all entries
+        bool open = !(gap > margin);  // the rule has to look at all entries
+        // ---- the cell's 8 entries in fp32, again with the second best; rows too close to call join
+        // the open ones
         int code = 0;
-        float value = INFINITY;
+        float value = 0.0f;
         {
-            const int e0 = open ? 0 : (int)(8 * cell + 4 * h_of);
+            // cell number = 2 * (first tile) + q; entries 8q + 4h .. + 3 of both tiles
+            const uint32_t e0 = open ? 0u : (cell >> 2) * 64u + (cell & 3u) * 8u + 4u * (uint32_t)h_of;
+            // (in LDS the two runs of 4 entries are 8 cells of 4 apart)
+            const float *near_ent = s_ent + (e0 >> 6) * (uint32_t)PAIR + ((e0 >> 2) & 15u) * (uint32_t)CELL;
+            const float *near_half = s_half + e0, *near_rn = s_rn + e0;
+            float b1 = 3e38f, b2 = 3e38f;
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                float c[WP], rn;
-                entry(ENT ? e0 + k : min(e0 + k, len - 1), c, rn);
-                const float v = rule_value<WP, METRIC>(xr, c, rn);
-                if ((ENT || e0 + k < len) && (k == 0 || v < value)) {
-                    value = v;
-                    code = e0 + k;
+            for (int k = 0; k < 8; k++) {
+                const int e = (int)e0 + (k & 3) + 32 * (k >> 2);
+                float c[WP], rn, sc = 0.0f;
+                if constexpr (ENT) {
+                    const float4 *src =
+                        reinterpret_cast<const float4 *>(near_ent + (k >> 2) * 8 * CELL + (k & 3) * WP);
+#pragma unroll
+                    for (int i = 0; i < WP / 4; i++) {
+                        const float4 v = src[i];
+                        c[4 * i] = v.x; c[4 * i + 1] = v.y; c[4 * i + 2] = v.z; c[4 * i + 3] = v.w;
+                    }
+                    rn = COS ? near_rn[(k & 3) + 32 * (k >> 2)] : 0.0f;
+                } else {
+                    entry(min(e, len - 1), c, rn);
                 }
+                if constexpr (COS) {
+#pragma unroll
+                    for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
+                    sc *= rn;
+                } else if constexpr (ENT) {
+                    sc = near_half[(k & 3) + 32 * (k >> 2)] * unscale;
+#pragma unroll
+                    for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
+                } else {
+#pragma unroll
+                    for (int d = 0; d < WP; d++) sc = fmaf(c[d], fmaf(0.5f, c[d], -xr[d]), sc);
+                }
+                if ((!ENT || COS) && e >= len) sc = 3e38f;
+                const float key = __uint_as_float((__float_as_uint(sc) & ~7u) | (uint32_t)k);
+                b2 = __builtin_amdgcn_fmed3f(b1, b2, key);
+                b1 = minimum(b1, key);
+            }
+            const int k = (int)(__float_as_uint(b1) & 7u);
+            open |= !(b2 - b1 > cell_margin);
+            code = (int)e0 + (k & 3) + 32 * (k >> 2);
+            if constexpr (TRAIN) {  // the rule's distance; an open row's is found below
+                float c[WP], rn;
+                entry(min(code, len - 1), c, rn);
+                value = rule_value<WP, METRIC>(xr, c, rn);
             }
         }
-        if (COS && (half ? zero[1] : zero[0])) {  // all scores are zero: the first entry
+        if (COS && zero) {  // all scores are zero: the first entry
             open = false;
             code = 0;
-            value = 0.0f;
         }
         uint64_t todo = __ballot(open && valid);
         if (todo) {
@@ -418,12 +511,18 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
                 atomicAdd(&s_cnt[code], 1u);
                 dsum += value;
             }
-        } else if (valid) {
-            uint8_t *row = a.codes + r * a.rb;
-            if (a.cbytes == 1) row[part] = (uint8_t)code;
-            else reinterpret_cast<uint16_t *>(row)[part] = (uint16_t)code;
-            if (part == 0)
-                for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) row[k] = 0;  // padding
+        } else {
+            // the next rows have arrived by now; waiting for them here keeps that wait from covering
+            // the stores below (loads and stores of a wave complete in one order)
+#pragma unroll
+            for (int d = 0; d < WP; d++) asm volatile("" : "+v"(xn[d]));
+            if (valid) {
+                uint8_t *row = a.codes + r * a.rb;
+                if (a.cbytes == 1) row[part] = (uint8_t)code;
+                else reinterpret_cast<uint16_t *>(row)[part] = (uint16_t)code;
+                if (part == 0)
+                    for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) row[k] = 0;  // padding
+            }
         }
     }
     if constexpr (TRAIN) {
@@ -477,11 +576,17 @@ float vq_margin(int w, int groups, int cell_bits) {
     return (float)(1.25 * 2.0 * score);
 }
 
+// The same for the scores inside a cell: fp32 throughout, (w + 4) u M, and three low bits.
+float vq_cell_margin(int w) {
+    const double u = ldexp(1.0, -24);
+    return (float)(1.25 * 2.0 * (2.0 * (w + 4.0) * u + ldexp(1.0, 3 - 23)));
+}
+
 size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const bool cosine = p->scheme.vq_metric == BIFEAT_VQ_COSINE;
     size_t n = (size_t)NT * G * 1024 + sizeof(float) * NT * 32;
-    if (ent) n += sizeof(float) * ((size_t)NT * 8 * (32 * G + 4) + (cosine ? NT * 32 : 0));
+    if (ent) n += sizeof(float) * ((size_t)NT / 2 * (16 * (32 * G + 4) + 4) + (cosine ? NT * 32 : 0));
     if (train) n += (size_t)len * (sizeof(double) * w + sizeof(uint32_t));
     return n;
 }
@@ -528,13 +633,13 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, size_t lds, hipStream_t s)
 
 template <typename T, int G, int METRIC>
 bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t s) {
-    const int tiles = (a.len + 31) / 32;
+    const int tiles = (a.len + 63) / 64 * 2;
     // entries in LDS next to their pieces when as many workgroups share a CU as their registers
     // allow (training: when it fits at all); else as many pieces as a CU holds, the rule reading
     // its few entries from L2
     const bool ent = nearest_lds(p, G, tiles, true, train) <= (size_t)(train ? kCuLds - 1024 : kCuLds / (G == 1 ? 4 : G == 2 ? 3 : 2));
     if (train && !ent) return false;
-    const int fit = (int)(152 * 1024 / (G * 1024 + 128));
+    const int fit = (int)(152 * 1024 / (G * 1024 + 128)) & ~1;
     a.NT = ent || tiles < fit ? tiles : fit;
     const size_t lds = nearest_lds(p, G, a.NT, ent, train);
     if (train) {
@@ -547,8 +652,9 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t
 
 template <typename T, int G>
 bool launch_groups(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t s) {
-    const int cell_bits = ilog2(4 * ((a.len + 31) / 32));
+    const int cell_bits = ilog2(4 * ((a.len + 63) / 64));
     a.margin = vq_margin(a.w, G, cell_bits);
+    a.cell_margin = vq_cell_margin(a.w);
     a.cell_mask = (1u << cell_bits) - 1u;
     return p->scheme.vq_metric == BIFEAT_VQ_COSINE ? launch_metric<T, G, BIFEAT_VQ_COSINE>(p, a, train, s)
                                                    : launch_metric<T, G, BIFEAT_VQ_L2>(p, a, train, s);
