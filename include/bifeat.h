@@ -364,7 +364,8 @@ const char *bifeat_strerror(int status);
  * "mean_generic" = 1 routes uniform tables through the float-accumulate
  * kernel; "mean_lean" = 0 disables the short-list kernel; "max_blocks" caps the
  * gather_dequant grid; "dequant_flat" = 1 / "vq_sliced" = 0 select the
- * unstaged decode kernels.  Two options carry information rather than tuning:
+ * unstaged decode kernels ("vq_sliced" = 2: the staged ones for small gather_mean
+ * calls too).  Two options carry information rather than tuning:
  * "mean_max_degree" = d is the caller's promise that no neighbour list of the
  * following bifeat_gather_mean calls is longer than d (0 = unknown; a sampler
  * knows its fan-out), which lets the library skip the pass that looks for

@@ -68,7 +68,7 @@ struct bifeat_params {
     int opt_mean_lean = 1;        // 0: never use the short-list kernel
     int opt_mean_max_degree = 0;  // caller's promise: no neighbour list is longer (0 = unknown)
     int opt_vq_iters = 10;        // Lloyd rounds per training chunk
-    int opt_vq_sliced = 1;        // 0: vector codes decode from L2 instead of LDS-resident slices
+    int opt_vq_sliced = 1;        // 0: vector codes decode from L2 instead of LDS-resident slices; 2: never
     int opt_dequant_flat = 0;  // 1: gather_dequant without the LDS-staged tile kernel
     int opt_mean_generic = 0;  // 1: route uniform tables through the float-accumulate kernel
     int opt_validate = 0;      // 1: check indices / list bounds on the GPU before every gather (synchronises)
@@ -151,6 +151,9 @@ void launch_zero_doubles(double *p, int n, hipStream_t s);
 bool launch_gather_dequant_vq_sliced(bifeat_params *p, const uint8_t *codes, const int64_t *idx,
                                      int64_t M, float *out, hipStream_t s, uint32_t *planes);
 bool launch_gather_mean_vq_sliced(bifeat_params *p, const MeanCall &c);
+// Whether a launch the sliced mean could take is so small that looking the entries up in L2 is
+// faster; *over_len then is the list length beyond which the caller's promise is broken (0: none).
+bool vq_mean_from_l2(const bifeat_params *p, const MeanCall &c, int *over_len);
 int lean_capacity(int bits, bool wide);
 // logarithmic codes of 4 / 8 bits, lists of at most logf_capacity() neighbours
 int logf_capacity();

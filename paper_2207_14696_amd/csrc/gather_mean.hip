@@ -31,8 +31,8 @@ template <int KIND, int BITS, bool VEC, typename IT>
 __global__ __launch_bounds__(kThreads) void gather_mean_float_kernel(
     const uint8_t *__restrict__ codes, int64_t rb, const int64_t *__restrict__ indptr,
     const IT *__restrict__ indices, int64_t V, int D, const float *__restrict__ pa,
-    const float *__restrict__ pb, int w, int len, int agg_sum, int min_len,
-    float *__restrict__ out) {
+    const float *__restrict__ pb, int w, int len, int agg_sum, int min_len, int over_len,
+    int32_t *__restrict__ status, float *__restrict__ out) {
     __shared__ float s_lut[KIND == MK_LOG ? (1 << (BITS & 15)) : 1];
     if constexpr (KIND == MK_LOG) {
         for (int i = threadIdx.x; i < (1 << BITS); i += kThreads) s_lut[i] = pa[i];
@@ -62,6 +62,9 @@ __global__ __launch_bounds__(kThreads) void gather_mean_float_kernel(
     for (int64_t v = t / G; v < V; v += per_pass) {
         const int64_t beg = indptr[v], end = indptr[v + 1];
         if (end - beg <= min_len) continue;  // a short-list kernel's destination
+        // over_len > 0: the caller promised shorter lists; this one's row is NaN
+        const bool over = over_len > 0 && end - beg > over_len;
+        if (over && g == 0) raise_status(status, kStatusListTooLong);
         // fp32 sums over runs of kRun neighbours, runs combined in fp64: keeps the
         // rounding error of very long lists far below the 1e-5 budget
         constexpr int kRun = 32;
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void gather_mean_float_kernel(
         const double inv_nd = agg_sum ? 1.0 : (end > beg ? 1.0 / (double)(end - beg) : 0.0);
         float acc[4];
 #pragma unroll
-        for (int k = 0; k < 4; k++) acc[k] = (float)(total[k] * inv_nd);
+        for (int k = 0; k < 4; k++) acc[k] = over ? __builtin_nanf("") : (float)(total[k] * inv_nd);
         float *dst = out + v * D + col0;
         if constexpr (VEC) {
             store_stream(reinterpret_cast<float4 *>(dst), make_float4(acc[0], acc[1], acc[2], acc[3]));
@@ -110,7 +113,7 @@ __global__ __launch_bounds__(kThreads) void gather_mean_float_kernel(
 
 template <int KIND>
 static void launch_float(bifeat_params *p, const MeanCall &c, const float *pa, const float *pb,
-                         int vec, int min_len = -1) {
+                         int vec, int min_len = -1, int over_len = 0) {
     const int D = (int)p->D, G = (D + 3) / 4;
     int blocks = blocks_for(c.V * G);
     if ((int64_t)blocks * kThreads < G) blocks = (G + kThreads - 1) / kThreads;
@@ -118,7 +121,7 @@ static void launch_float(bifeat_params *p, const MeanCall &c, const float *pa, c
 #define BF_FK(B, VECV, IT)                                                                        \
     gather_mean_float_kernel<KIND, B, VECV, IT><<<blocks, kThreads, 0, c.s>>>(                    \
         c.codes, p->rb, c.indptr, (const IT *)c.indices, c.V, D, pa, pb, w, len, c.agg_sum,       \
-        min_len, c.out)
+        min_len, over_len, c.status, c.out)
 #define BF_FL(B)                                                                                  \
     do {                                                                                          \
         if (vec) {                                                                                \
@@ -383,6 +386,8 @@ hipError_t launch_gather_mean(bifeat_params *p, const MeanCall &c) {
         if (!all_short) launch_float<MK_LOG>(p, c, p->d_V, nullptr, vec, tiled ? thr : -1);
     } else if (kind == BIFEAT_SQ_LOG) {
         launch_float<MK_LOG>(p, c, p->d_V, nullptr, vec);
+    } else if (int over_len = 0; p->opt_vq_sliced == 1 && vq_mean_from_l2(p, c, &over_len)) {
+        launch_float<MK_VQ4>(p, c, p->d_cb, nullptr, vec, -1, over_len);
     } else if (p->opt_vq_sliced && launch_gather_mean_vq_sliced(p, c)) {
         // vector codes, codebook slices in LDS
     } else if (p->scheme.vq_width % 4 == 0 && vec) {

@@ -644,6 +644,20 @@ bool launch_gather_dequant_vq_sliced(bifeat_params *p, const uint8_t *codes, con
     return true;
 }
 
+// The sliced mean is two launches with the requested codes through the workspace in between; the
+// general kernel is one, and fetches 4 D bytes per list entry from L2 in pieces of an entry's
+// 16..64 bytes, 6 TB/s of them at best.  8 x 2048 x 16 (slices of 64 bytes a row): 23 000 list
+// entries 7.5 against 12.4 us, 201 000 (103 MB) 15.4 against 20.7, 852 000 (436 MB) 69 against 55.
+// 96 x 256 x 8 (slices of 256 bytes): 5 900 entries (18 MB) 8.0 against 13, 50 900 (156 MB) 25
+// against 19.  16 x 2048 x 16: 207 MB 28 against 30.  So the line lies lower where the slices are
+// wide enough for whole lines of output.
+bool vq_mean_from_l2(const bifeat_params *p, const MeanCall &c, int *over_len) {
+    const VqGeom g = vq_geometry(p);
+    if (!g.ok || (uintptr_t)c.out % 16 || p->payload / 16 > 64) return false;
+    *over_len = c.max_degree > 0 && c.max_degree <= kRun ? kRun : 0;  // as the sliced kernels have it
+    return c.E <= (((int64_t)(g.LPS < 16 ? 192 : 64) << 20) / (4 * p->D));
+}
+
 // With the caller's bound on the list lengths at most kRun, the long-list pass is not
 // launched at all (a longer list then gets a row of NaNs and raises the status word).
 bool launch_gather_mean_vq_sliced(bifeat_params *p, const MeanCall &c) {
