@@ -211,6 +211,17 @@ __device__ inline float4 load4(const __half *p) {
     float2 fa = __half22float2(a), fb = __half22float2(b);
     return make_float4(fa.x, fa.y, fb.x, fb.y);
 }
+// 8 consecutive elements (16 bytes of half precision)
+__device__ inline void load8(const __half *p, float (&v)[8]) {
+    const uint4 u = *reinterpret_cast<const uint4 *>(p);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&w[k]));
+        v[2 * k] = f.x;
+        v[2 * k + 1] = f.y;
+    }
+}
 // Output rows are written once and not read again by these kernels: streaming
 // (non-temporal) stores keep them from evicting the packed table from the
 // caches the gathers depend on.

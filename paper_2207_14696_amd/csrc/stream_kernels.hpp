@@ -15,11 +15,14 @@
 //       __device__ float4 load4(const Ctx &, int64_t r, int col0) const;  // columns col0..col0+3 of row r
 //       __device__ float load1(const Ctx &, int64_t r, int col) const;    // one column of row r
 //   };
+// (the chunk source has load8 as well, for half-precision chunks)
 //
 // In all kernels a thread owns a fixed group of consecutive columns for its whole life (the
 // grid's row stride is a multiple of the groups per row), so per-column parameters live in
 // registers while consecutive lanes still touch consecutive addresses.
 #pragma once
+
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -34,29 +37,73 @@ struct ChunkSrc {
     __device__ void prepare(Ctx &, int, int) const {}
     __device__ float4 load4(const Ctx &, int64_t r, int col0) const { return bf::load4(x + r * D + col0); }
     __device__ float load1(const Ctx &, int64_t r, int col) const { return bf::load1(x + r * D + col); }
+    __device__ void load8(const Ctx &, int64_t r, int col0, float (&v)[8]) const { bf::load8(x + r * D + col0, v); }
 };
 
+template <class Src>
+constexpr bool kHalfChunk = std::is_same<Src, ChunkSrc<__half>>::value;
+
+// The fit kernels end with atomics on a few words (2*D of them, or two), and the workgroups of a
+// launch come to that end together: 2048 workgroups of 256 threads spent 80 of 210 us there (a
+// 524 288 x 768 half-precision chunk; the read alone takes 130).  So there are few workgroups, of
+// 1024 threads: two per CU.  That chunk's range with its reset: 245 -> 168 us; the extreme
+// magnitudes of 1 M x 128 floats 234 -> 102 us, of half-precision values 210 -> 51 us (4 atomics a
+// workgroup on two words before, at most 2 now).
+constexpr int kFitThreads = 1024;
+constexpr int kFitBlocks = 512;
+
+inline int fit_blocks(int64_t threads) {
+    const int64_t b = (threads + kFitThreads - 1) / kFitThreads;
+    return (int)(b < 1 ? 1 : b > kFitBlocks ? kFitBlocks : b);
+}
+
+// smallest nonzero and largest finite magnitude seen by a workgroup merged into state[0], [1]: one
+// atomic each, and none that would change nothing (positive floats order like their bits)
+__device__ inline void merge_magnitudes(uint32_t mmin, uint32_t mmax, int32_t *state) {
+    __shared__ uint32_t s_mm[2];
+    if (threadIdx.x == 0) {
+        s_mm[0] = 0x7F800000u;
+        s_mm[1] = 0u;
+    }
+    __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+        mmin = min(mmin, (uint32_t)__shfl_xor((int)mmin, o));
+        mmax = max(mmax, (uint32_t)__shfl_xor((int)mmax, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMin(&s_mm[0], mmin);
+        atomicMax(&s_mm[1], mmax);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t *st = reinterpret_cast<uint32_t *>(state);
+        if (s_mm[0] < __builtin_nontemporal_load(&st[0])) atomicMin(&st[0], s_mm[0]);
+        if (s_mm[1] > __builtin_nontemporal_load(&st[1])) atomicMax(&st[1], s_mm[1]);
+    }
+}
+
 // per-column min / max of the rows [0, rows) of `src` merged into the running state.
-// VEC = 4 needs D % 4 == 0 (and, for a chunk in memory, 16-byte / 8-byte alignment).
+// VEC = 4 needs D % 4 == 0 (and, for a chunk in memory, 16-byte / 8-byte alignment), VEC = 8 (half
+// precision in memory) D % 8 == 0 and 16 bytes.
 template <class Src, int VEC>
-__global__ __launch_bounds__(kThreads) void fit_minmax_kernel(Src src, int64_t rows, int D, int G,
+__global__ __launch_bounds__(kFitThreads) void fit_minmax_kernel(Src src, int64_t rows, int D, int G,
                                                              int32_t *state, int use_lds) {
     extern __shared__ int32_t lds[];
     if (use_lds) {
-        for (int i = threadIdx.x; i < D; i += kThreads) {
+        for (int i = threadIdx.x; i < D; i += kFitThreads) {
             lds[i] = kKeyPosInf;
             lds[D + i] = kKeyNegInf;
         }
         __syncthreads();
     }
-    // A workgroup streams one contiguous piece of the chunk: kThreads/G whole rows per
+    // A workgroup streams one contiguous piece of the chunk: kFitThreads/G whole rows per
     // iteration when a row's G column groups fit a workgroup (a wave's lanes then read
     // consecutive 16 bytes), else groups of G threads across the grid walk consecutive rows.
-    const bool by_block = G <= kThreads;
-    const int rpi = by_block ? kThreads / G : 0;  // rows per iteration of a workgroup
-    const uint32_t total = gridDim.x * kThreads;
+    const bool by_block = G <= kFitThreads;
+    const int rpi = by_block ? kFitThreads / G : 0;  // rows per iteration of a workgroup
+    const uint32_t total = gridDim.x * kFitThreads;
     const uint32_t rows_per_pass = total / (uint32_t)G;
-    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t t = blockIdx.x * kFitThreads + threadIdx.x;
     const bool active = by_block ? (int)threadIdx.x < rpi * G : t < rows_per_pass * (uint32_t)G;
     if (active) {
         const int g = by_block ? (int)threadIdx.x % G : (int)(t % (uint32_t)G);
@@ -80,10 +127,13 @@ __global__ __launch_bounds__(kThreads) void fit_minmax_kernel(Src src, int64_t r
             rend = min(rows, rbeg + K);
             rstep = 1;
         }
+        // fminf / fmaxf pass over a NaN like the comparisons they stand for
 #pragma unroll 4
         for (int64_t r = rbeg; r < rend; r += rstep) {
             float v[VEC];
-            if constexpr (VEC == 4) {
+            if constexpr (VEC == 8) {
+                src.load8(ctx, r, g * VEC, v);
+            } else if constexpr (VEC == 4) {
                 float4 q = src.load4(ctx, r, g * VEC);
                 v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
             } else {
@@ -91,16 +141,23 @@ __global__ __launch_bounds__(kThreads) void fit_minmax_kernel(Src src, int64_t r
             }
 #pragma unroll
             for (int k = 0; k < VEC; k++) {
-                if (v[k] < mn[k]) mn[k] = v[k];  // NaN compares false: skipped
-                if (v[k] > mx[k]) mx[k] = v[k];
+                mn[k] = fminf(mn[k], v[k]);
+                mx[k] = fmaxf(mx[k], v[k]);
             }
         }
-        int32_t *lo = use_lds ? lds : state;
+        // (two loops: through one pointer to either the atomics would be flat ones)
+        if (use_lds) {
 #pragma unroll
-        for (int k = 0; k < VEC; k++) {
-            int col = g * VEC + k;
-            atomicMin(&lo[col], float_key(mn[k]));
-            atomicMax(&lo[D + col], float_key(mx[k]));
+            for (int k = 0; k < VEC; k++) {
+                atomicMin(&lds[g * VEC + k], float_key(mn[k]));
+                atomicMax(&lds[D + g * VEC + k], float_key(mx[k]));
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < VEC; k++) {
+                atomicMin(&state[g * VEC + k], float_key(mn[k]));
+                atomicMax(&state[D + g * VEC + k], float_key(mx[k]));
+            }
         }
     }
     if (use_lds) {
@@ -108,7 +165,7 @@ __global__ __launch_bounds__(kThreads) void fit_minmax_kernel(Src src, int64_t r
         // thousands of workgroups would hammer the same 2*D words: only those that improve
         // on the value already there (read without ordering: a stale read merely costs one
         // atomic that changes nothing) issue the atomic
-        for (int i = threadIdx.x; i < D; i += kThreads) {
+        for (int i = threadIdx.x; i < D; i += kFitThreads) {
             const int32_t lo_k = lds[i], hi_k = lds[D + i];
             if (lo_k < __builtin_nontemporal_load(&state[i])) atomicMin(&state[i], lo_k);
             if (hi_k > __builtin_nontemporal_load(&state[D + i])) atomicMax(&state[D + i], hi_k);
@@ -120,7 +177,7 @@ __global__ __launch_bounds__(kThreads) void fit_minmax_kernel(Src src, int64_t r
 // scheme); positive floats order like their bit patterns.  Thread = one group of VEC columns,
 // rows interleaved across the grid.
 template <class Src, int VEC>
-__global__ __launch_bounds__(kThreads) void fit_log_rows_kernel(Src src, int64_t rows, int D, int G,
+__global__ __launch_bounds__(kFitThreads) void fit_log_rows_kernel(Src src, int64_t rows, int D, int G,
                                                                int32_t *state) {
     uint32_t mmin = 0x7F800000u, mmax = 0u;
     auto take = [&](float v) {
@@ -130,9 +187,9 @@ __global__ __launch_bounds__(kThreads) void fit_log_rows_kernel(Src src, int64_t
             if (m > mmax) mmax = m;
         }
     };
-    const uint32_t total = gridDim.x * kThreads;
+    const uint32_t total = gridDim.x * kFitThreads;
     const uint32_t rows_per_pass = total / (uint32_t)G;
-    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t t = blockIdx.x * kFitThreads + threadIdx.x;
     if (t < rows_per_pass * (uint32_t)G) {
         const int g = (int)(t % (uint32_t)G);
         typename Src::Ctx ctx;
@@ -150,14 +207,7 @@ __global__ __launch_bounds__(kThreads) void fit_log_rows_kernel(Src src, int64_t
             }
         }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        mmin = min(mmin, (uint32_t)__shfl_xor((int)mmin, o));
-        mmax = max(mmax, (uint32_t)__shfl_xor((int)mmax, o));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicMin((uint32_t *)&state[0], mmin);
-        atomicMax((uint32_t *)&state[1], mmax);
-    }
+    merge_magnitudes(mmin, mmax, state);
 }
 
 // ------------------------------------------------------------ scalar encoders
@@ -165,10 +215,11 @@ struct UniformCoder {
     static constexpr bool kEdges = false;
     const float *mn, *inv;
     float L;
-    struct Ctx { float mn[4], inv[4]; };
-    __device__ void prepare(Ctx &c, int col0, int D) const {
+    template <int NC> struct Ctx { float mn[NC], inv[NC]; };
+    template <int NC>
+    __device__ void prepare(Ctx<NC> &c, int col0, int D) const {
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
+        for (int k = 0; k < NC; k++) {
             bool ok = col0 + k < D;
             c.mn[k] = ok ? mn[col0 + k] : 0.0f;
             c.inv[k] = ok ? inv[col0 + k] : 0.0f;
@@ -176,7 +227,8 @@ struct UniformCoder {
     }
     // q = clamp(rne((x - min) * inv), 0, L); sub, mul, round are separate fp32
     // operations; max/min discard NaN, so NaN -> 0
-    __device__ uint32_t code(const Ctx &c, float x, int k) const {
+    template <int NC>
+    __device__ uint32_t code(const Ctx<NC> &c, float x, int k) const {
         float d = __fsub_rn(x, c.mn[k]);
         float t = __fmul_rn(d, c.inv[k]);
         float r = rintf(t);
@@ -189,10 +241,12 @@ struct LogCoder {
     static constexpr bool kEdges = true;
     const float *T;  // global, H-1 edges
     int H;
-    struct Ctx { const float *edges; };
-    __device__ void prepare(Ctx &c, int, int) const { c.edges = nullptr; }
+    template <int NC> struct Ctx { const float *edges; };
+    template <int NC>
+    __device__ void prepare(Ctx<NC> &c, int, int) const { c.edges = nullptr; }
     // l = #{i : |x| >= T_i} by bisection over the sorted edges (in LDS)
-    __device__ uint32_t code(const Ctx &c, float x, int) const {
+    template <int NC>
+    __device__ uint32_t code(const Ctx<NC> &c, float x, int) const {
         float m = fabsf(x);
         int lo = 0, hi = H - 1;
         while (lo < hi) {
@@ -203,17 +257,21 @@ struct LogCoder {
     }
 };
 
-// One thread encodes 4 consecutive columns (4*BITS bits); 8/BITS neighbouring
-// lanes OR their pieces into one 32-bit word and one of them stores it.  Every
-// word of the padded row is written (columns >= D encode as 0).
-template <class Src, int BITS, typename Coder, bool VEC>
+// One thread encodes NC consecutive columns (NC*BITS bits): 4, or 8 of a half-precision chunk (one
+// 16-byte load).  Where that is less than a 32-bit word, neighbouring lanes OR their pieces
+// together and one of them stores it.  Every word of the padded row is written (columns >= D
+// encode as 0).  Bound by memory (a plain copy moves 4.9 TB/s here): 524 288 x 768 half-precision
+// values to 4 bits 207 us, 4.86 TB/s (8-byte loads: 221), to 1 bit 177 (206).
+template <class Src, int BITS, typename Coder, bool VEC, int NC>
 __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t rows, int D, int64_t rb,
                                                               Coder coder,
                                                               uint8_t *__restrict__ codes) {
     __shared__ float s_edges[128];
-    typename Coder::Ctx ctx;
-    constexpr int LG = 8 / BITS;  // lanes per 32-bit word
-    const int GW = (int)(2 * rb / BITS);  // 4-column groups per padded row; multiple of 4*LG
+    typename Coder::template Ctx<NC> ctx;
+    constexpr int LG = NC * BITS >= 32 ? 1 : 32 / (NC * BITS);  // lanes per 32-bit word
+    constexpr int NW = NC * BITS > 32 ? NC * BITS / 32 : 1;     // words per lane
+    constexpr int CPW = NC / NW;                                // columns of a lane per word
+    const int GW = (int)(8 * rb / (NC * BITS));  // NC-column groups per padded row; a multiple of LG
     if constexpr (Coder::kEdges) {
         for (int i = threadIdx.x; i < coder.H - 1; i += kThreads) s_edges[i] = coder.T[i];
         __syncthreads();
@@ -223,52 +281,78 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
     const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
     if (t >= rows_per_pass * (uint32_t)GW) return;
     const int g = (int)(t % (uint32_t)GW);
-    const int col0 = 4 * g;
+    const int col0 = NC * g;
     coder.prepare(ctx, col0, D);
     if constexpr (Coder::kEdges) ctx.edges = s_edges;
     typename Src::Ctx sctx;
     src.prepare(sctx, col0, D);
     const int sub = g % LG;
-    uint32_t *dst_word = reinterpret_cast<uint32_t *>(codes) + (g / LG);
+    uint32_t *dst_word = reinterpret_cast<uint32_t *>(codes) + (int64_t)(g / LG) * NW;
     const int64_t rw = rb / 4;
     // rows interleaved across the grid: a wave's stores stay contiguous (consecutive rows
-    // per thread, as in the fit kernel, measured 15 % slower here)
+    // per thread, as in the fit kernel, measured 15 % slower here; four rows of a thread loaded
+    // ahead of their stores: 10-25 % slower)
     for (int64_t r = t / GW; r < rows; r += rows_per_pass) {
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        if (VEC) {
+        float v[NC];
+#pragma unroll
+        for (int k = 0; k < NC; k++) v[k] = 0.0f;
+        if constexpr (VEC && NC == 8) {
+            if (col0 < D) src.load8(sctx, r, col0, v);
+        } else if constexpr (VEC) {
             if (col0 < D) {
                 float4 q = src.load4(sctx, r, col0);
                 v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < 4; k++)
+            for (int k = 0; k < NC; k++)
                 if (col0 + k < D) v[k] = src.load1(sctx, r, col0 + k);
         }
-        uint32_t piece = 0;
+        uint32_t word[NW];
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            uint32_t q = (col0 + k < D) ? coder.code(ctx, v[k], k) : 0u;
-            piece |= q << (BITS * k);
+        for (int n = 0; n < NW; n++) {
+            word[n] = 0u;
+#pragma unroll
+            for (int k = 0; k < CPW; k++) {
+                const int j = n * CPW + k;
+                const uint32_t q = (col0 + j < D) ? coder.code(ctx, v[j], j) : 0u;
+                word[n] |= q << (BITS * k);
+            }
         }
-        piece <<= (4 * BITS) * sub;
+        if constexpr (LG > 1) {
+            word[0] <<= (NC * BITS) * sub;
 #pragma unroll
-        for (int o = 1; o < LG; o <<= 1) piece |= (uint32_t)__shfl_xor((int)piece, o);
-        if (sub == 0) dst_word[r * rw] = piece;
+            for (int o = 1; o < LG; o <<= 1) word[0] |= (uint32_t)__shfl_xor((int)word[0], o);
+        }
+        if (sub == 0) {
+            if constexpr (NW == 2) *reinterpret_cast<uint2 *>(dst_word + r * rw) = make_uint2(word[0], word[1]);
+            else dst_word[r * rw] = word[0];
+        }
     }
 }
 
 template <class Src, typename Coder>
 inline void launch_sq(const Src &src, int64_t rows, int D, int64_t rb, int bits, Coder coder,
                       uint8_t *codes, bool vec, hipStream_t s) {
-    const int GW = (int)(2 * rb / bits);
-    int64_t want = (rows * GW + 3) / 4;
+    bool vec8 = false;
+    if constexpr (kHalfChunk<Src>) vec8 = vec && D % 8 == 0 && (uintptr_t)src.x % 16 == 0;
+    const int GW = (int)(8 * rb / ((vec8 ? 8 : 4) * bits));
+    int64_t want = (rows * GW + 1) / 2;
     if (want < GW) want = GW;
     int blocks = blocks_for(want);
     if ((int64_t)blocks * kThreads < GW) blocks = (GW + kThreads - 1) / kThreads;
+#define BF_QK(B, VECV, NC) quantize_sq_kernel<Src, B, Coder, VECV, NC><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes)
 #define BF_Q(B)                                                                                 \
-    if (vec) quantize_sq_kernel<Src, B, Coder, true><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes); \
-    else quantize_sq_kernel<Src, B, Coder, false><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes)
+    do {                                                                                        \
+        if constexpr (kHalfChunk<Src>) {                                                        \
+            if (vec8) {                                                                         \
+                BF_QK(B, true, 8);                                                              \
+                break;                                                                          \
+            }                                                                                   \
+        }                                                                                       \
+        if (vec) BF_QK(B, true, 4);                                                             \
+        else BF_QK(B, false, 4);                                                                \
+    } while (0)
     switch (bits) {
         case 1: BF_Q(1); break;
         case 2: BF_Q(2); break;
@@ -276,6 +360,7 @@ inline void launch_sq(const Src &src, int64_t rows, int D, int64_t rb, int bits,
         default: BF_Q(8); break;
     }
 #undef BF_Q
+#undef BF_QK
 }
 
 // ---- launchers over a row source (scalar kinds)
@@ -284,16 +369,24 @@ template <class Src>
 inline hipError_t launch_fit_minmax_src(bifeat_params *p, const Src &src, int64_t rows, bool vec,
                                         hipStream_t s) {
     const int D = (int)p->D;
-    const int VEC = vec ? 4 : 1;
+    bool vec8 = false;
+    if constexpr (kHalfChunk<Src>) vec8 = vec && D % 8 == 0 && (uintptr_t)src.x % 16 == 0;
+    const int VEC = vec8 ? 8 : vec ? 4 : 1;
     const int G = (D + VEC - 1) / VEC;
     int64_t want = (rows * G + 7) / 8;  // about 8 rows per thread
     if (want < G) want = G;
-    int blocks = blocks_for(want);
-    if ((int64_t)blocks * kThreads < G) blocks = (G + kThreads - 1) / kThreads;
+    int blocks = fit_blocks(want);
+    if ((int64_t)blocks * kFitThreads < G) blocks = (G + kFitThreads - 1) / kFitThreads;
     const int use_lds = D <= 8192;
     const size_t shm = use_lds ? sizeof(int32_t) * 2 * (size_t)D : 0;
-    if (vec) fit_minmax_kernel<Src, 4><<<blocks, kThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
-    else fit_minmax_kernel<Src, 1><<<blocks, kThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
+    if constexpr (kHalfChunk<Src>) {
+        if (vec8) {
+            fit_minmax_kernel<Src, 8><<<blocks, kFitThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
+            return hipGetLastError();
+        }
+    }
+    if (vec) fit_minmax_kernel<Src, 4><<<blocks, kFitThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
+    else fit_minmax_kernel<Src, 1><<<blocks, kFitThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
     return hipGetLastError();
 }
 
@@ -306,10 +399,10 @@ inline hipError_t launch_fit_log_src(bifeat_params *p, const Src &src, int64_t r
     const int G = (D + VEC - 1) / VEC;
     int64_t want = (rows * G + 7) / 8;
     if (want < G) want = G;
-    int blocks = blocks_for(want);
-    if ((int64_t)blocks * kThreads < G) blocks = (G + kThreads - 1) / kThreads;
-    if (vec) fit_log_rows_kernel<Src, 4><<<blocks, kThreads, 0, s>>>(src, rows, D, G, p->d_fit);
-    else fit_log_rows_kernel<Src, 1><<<blocks, kThreads, 0, s>>>(src, rows, D, G, p->d_fit);
+    int blocks = fit_blocks(want);
+    if ((int64_t)blocks * kFitThreads < G) blocks = (G + kFitThreads - 1) / kFitThreads;
+    if (vec) fit_log_rows_kernel<Src, 4><<<blocks, kFitThreads, 0, s>>>(src, rows, D, G, p->d_fit);
+    else fit_log_rows_kernel<Src, 1><<<blocks, kFitThreads, 0, s>>>(src, rows, D, G, p->d_fit);
     return hipGetLastError();
 }
 
