@@ -13,9 +13,13 @@ constexpr int kAggInFlight = 4;  // rows in flight per lane
 constexpr int kItemsPerGroup = 4;  // (destination, tile) items a lane group works through
 // A list longer than kLong is not walked by one lane group (a hub's thousands of rows,
 // one latency after the other, would outlast the rest of the launch): it is cut into
-// pieces of kSub list entries that many groups sum side by side and add into the output
-// row with atomics.  A workgroup of that kernel looks after kRange consecutive list
-// entries, which at most kRange / kLong + 2 long lists can overlap.
+// pieces of kSub list entries that many groups sum side by side.  A workgroup of that
+// kernel looks after kRange consecutive list entries, which at most kRange / kLong + 2
+// long lists can overlap: it adds its pieces up in LDS, per list, and only then to the
+// output row with atomics.  (Every piece's own atomics, 10 M of them where a third of 16 M
+// list entries sits in long lists, took a tenth of the launch: 1252 us, see the end of
+// long_lists().  Pieces of 256 entries instead are as fast there and half as fast at 100 000
+// rows.  64-bit sums: an LDS float add takes 196 cycles per wave here, a double add 22.)
 constexpr int kLong = 256;
 constexpr int kRange = 2048;
 constexpr int kSub = 64;
@@ -53,13 +57,12 @@ struct Acc<4> {
         }
         store_stream(reinterpret_cast<float4 *>(p), o);
     }
-    // this piece's share of the row: partial sum (divided by the whole list's length)
-    __device__ void add_to(float *p, int n, bool sum) const {
-        const float d = (float)n;
-        unsafeAtomicAdd(p + 0, sum ? v.x : v.x / d);
-        unsafeAtomicAdd(p + 1, sum ? v.y : v.y / d);
-        unsafeAtomicAdd(p + 2, sum ? v.z : v.z / d);
-        unsafeAtomicAdd(p + 3, sum ? v.w : v.w / d);
+    // this piece's sum (c holds what the additions so far put on top of it)
+    __device__ void add_to(double *p) const {
+        unsafeAtomicAdd(p + 0, (double)v.x - (double)c.x);
+        unsafeAtomicAdd(p + 1, (double)v.y - (double)c.y);
+        unsafeAtomicAdd(p + 2, (double)v.z - (double)c.z);
+        unsafeAtomicAdd(p + 3, (double)v.w - (double)c.w);
     }
 };
 template <>
@@ -71,9 +74,7 @@ struct Acc<1> {
     __device__ void store(float *p, int n, bool sum) const {
         __builtin_nontemporal_store(sum ? v : (n > 0 ? v / (float)n : 0.f), p);
     }
-    __device__ void add_to(float *p, int n, bool sum) const {
-        unsafeAtomicAdd(p, sum ? v : v / (float)n);
-    }
+    __device__ void add_to(double *p) const { unsafeAtomicAdd(p, (double)v - (double)c); }
 };
 
 // rows of `pieces` consecutive list entries [e, end) added into acc, U loads in flight
@@ -121,8 +122,9 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
 // The long lists: a workgroup looks after kRange consecutive list entries at a time.  It
 // finds the first destination whose list reaches into that range (a 64-way search in
 // indptr by one wave), walks on from there, notes the long lists with the part that
-// falls inside the range, and its lane groups sum pieces of kSub entries of those parts,
-// each piece added to the output row, which aggregate_zero_long_kernel has zeroed.
+// falls inside the range, and its lane groups sum pieces of kSub entries of those parts.
+// The lists' sums over the range go to the output rows, which aggregate_zero_long_kernel
+// has zeroed.
 template <int VEC>
 __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
                                   const int64_t *__restrict__ indptr,
@@ -131,6 +133,7 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
                                   int64_t block, int64_t nblocks) {
     __shared__ int64_t s_v[kMaxLong], s_beg[kMaxLong], s_end[kMaxLong], s_first;
     __shared__ int s_deg[kMaxLong], s_n;
+    extern __shared__ double s_sum[];  // [kMaxLong][lpr * VEC]
     const int lpr = 1 << lpr_log2;
     const int t = threadIdx.x & (lpr - 1);
     const int group = threadIdx.x >> lpr_log2, groups = kThreads >> lpr_log2;
@@ -182,19 +185,29 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
             if (__syncthreads_or(past)) break;
         }
         const int n_long = s_n < kMaxLong ? s_n : kMaxLong;
-        const int work = n_long * kPieces * tiles;
-        for (int it = group; it < work; it += groups) {
-            const int tile = it % tiles;
-            const int piece = (it / tiles) % kPieces;
-            const int k = it / (tiles * kPieces);
-            const int64_t b = s_beg[k] + (int64_t)piece * kSub;
-            const int64_t col = (int64_t)VEC * (tile * lpr + t);
-            if (b >= s_end[k] || col >= D) continue;
-            const int64_t end = b + kSub < s_end[k] ? b + kSub : s_end[k];
-            Acc<VEC> acc;
-            acc.zero();
-            add_rows<VEC, 2 * kAggInFlight>(acc, x + col, D, indices, b, end);
-            acc.add_to(out + s_v[k] * D + col, s_deg[k], sum != 0);
+        const int width = lpr * VEC;  // columns of a tile
+        for (int tile = 0; tile < tiles && n_long > 0; tile++) {
+            for (int i = threadIdx.x; i < n_long * width; i += kThreads) s_sum[i] = 0.0;
+            __syncthreads();
+            for (int it = group; it < n_long * kPieces; it += groups) {
+                const int piece = it % kPieces, k = it / kPieces;
+                const int64_t b = s_beg[k] + (int64_t)piece * kSub;
+                const int64_t col = (int64_t)VEC * (tile * lpr + t);
+                if (b >= s_end[k] || col >= D) continue;
+                const int64_t end = b + kSub < s_end[k] ? b + kSub : s_end[k];
+                Acc<VEC> acc;
+                acc.zero();
+                add_rows<VEC, 2 * kAggInFlight>(acc, x + col, D, indices, b, end);
+                acc.add_to(s_sum + k * width + VEC * t);
+            }
+            __syncthreads();
+            for (int i = threadIdx.x; i < n_long * width; i += kThreads) {
+                const int k = i / width;
+                const int64_t col = (int64_t)tile * width + (i - k * width);
+                if (col < D)
+                    unsafeAtomicAdd(out + s_v[k] * D + col, (float)(sum ? s_sum[i] : s_sum[i] / (double)s_deg[k]));
+            }
+            __syncthreads();
         }
         __syncthreads();
     }
@@ -298,11 +311,12 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
         aggregate_zero_long_kernel<<<blocks_for(V, 8 * 256), kThreads, 0, s>>>(indptr, V, D, out);
     }
     const int blocks = short_blocks + long_blocks;
+    const size_t shm = long_blocks > 0 ? sizeof(double) * kMaxLong * ((vec ? 4 : 1) << lpr_log2) : 0;
     if (vec)
-        aggregate_rows_kernel<4><<<blocks, kThreads, 0, s>>>(x, D, indptr, indices, V, E, lpr_log2,
+        aggregate_rows_kernel<4><<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
                                                             (int)tiles, sum, long_blocks, out);
     else
-        aggregate_rows_kernel<1><<<blocks, kThreads, 0, s>>>(x, D, indptr, indices, V, E, lpr_log2,
+        aggregate_rows_kernel<1><<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
                                                             (int)tiles, sum, long_blocks, out);
     return hipGetLastError();
 }

@@ -89,7 +89,7 @@ hipError_t launch_log_hist_update(bifeat_params *p, const void *chunk, int dtype
     const size_t esz = dtype == BIFEAT_F32 ? 4 : 2;
     const bool vec = (uintptr_t)chunk % (4 * esz) == 0;
     int64_t want = (n / 32 + kHistThreads - 1) / kHistThreads;
-    const int blocks = (int)(want < 1 ? 1 : (want > 1024 ? 1024 : want));  // 2 workgroups per CU (LDS), two rounds
+    const int blocks = (int)(want < 1 ? 1 : (want > 512 ? 512 : want));  // 2 per CU (LDS): more would only add their histograms to the same words
 #define BF_LH(T, V)                                                                          \
     log_hist_kernel<T, V><<<blocks, kHistThreads, 0, s>>>((const T *)chunk, n, p->fit_pass,     \
                                                       p->clip_prefix[0], p->clip_prefix[1], p->d_hist)
