@@ -241,17 +241,33 @@ struct LogCoder {
     static constexpr bool kEdges = true;
     const float *T;  // global, H-1 edges
     int H;
+    // level l lies near a*log2|x| + b; a = 0: the range is too narrow or too extreme for that
+    float a, b;
     template <int NC> struct Ctx { const float *edges; };
     template <int NC>
     __device__ void prepare(Ctx<NC> &c, int, int) const { c.edges = nullptr; }
-    // l = #{i : |x| >= T_i} by bisection over the sorted edges (in LDS)
+    // l = #{i : |x| >= T_i}: the level the hardware's logarithm gives, put right against the edges
+    // on both sides of it.  With a <= 1024 and magnitudes whose logarithm is no denormal's, the
+    // logarithm (an ulp, 2^-17 at most) and b (2^-6) are off by far less than a level, the
+    // fp32 edges by 2^-23, so one step either way is enough.  Otherwise by bisection.
+    // edges (in LDS): [-1, T_1 .. T_{H-1}, NaN]; a NaN takes level 0 both ways.
+    // 524 288 x 768 half-precision values to 4 bits: 257 us, bisection 374; 262 144 x 768 to 8 bits:
+    // 129 us, bisection 361.
     template <int NC>
     __device__ uint32_t code(const Ctx<NC> &c, float x, int) const {
         float m = fabsf(x);
-        int lo = 0, hi = H - 1;
-        while (lo < hi) {
-            int mid = (lo + hi) >> 1;
-            if (m >= c.edges[mid]) lo = mid + 1; else hi = mid;
+        int lo = 0;
+        if (a > 0.0f) {
+            const int l = (int)fmaf(__builtin_amdgcn_logf(m), a, b);
+            lo = min(max(l, 0), H - 1);
+            const float below = c.edges[lo], above = c.edges[lo + 1];
+            lo += (m >= above ? 1 : 0) - (m < below ? 1 : 0);
+        } else {
+            int hi = H - 1;
+            while (lo < hi) {
+                int mid = (lo + hi) >> 1;
+                if (m >= c.edges[mid + 1]) lo = mid + 1; else hi = mid;
+            }
         }
         return (uint32_t)((x > 0.0f) ? H + lo : H - 1 - lo);
     }
@@ -266,14 +282,15 @@ template <class Src, int BITS, typename Coder, bool VEC, int NC>
 __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t rows, int D, int64_t rb,
                                                               Coder coder,
                                                               uint8_t *__restrict__ codes) {
-    __shared__ float s_edges[128];
+    __shared__ float s_edges[130];
     typename Coder::template Ctx<NC> ctx;
     constexpr int LG = NC * BITS >= 32 ? 1 : 32 / (NC * BITS);  // lanes per 32-bit word
     constexpr int NW = NC * BITS > 32 ? NC * BITS / 32 : 1;     // words per lane
     constexpr int CPW = NC / NW;                                // columns of a lane per word
     const int GW = (int)(8 * rb / (NC * BITS));  // NC-column groups per padded row; a multiple of LG
     if constexpr (Coder::kEdges) {
-        for (int i = threadIdx.x; i < coder.H - 1; i += kThreads) s_edges[i] = coder.T[i];
+        for (int i = threadIdx.x; i <= coder.H; i += kThreads)
+            s_edges[i] = i == 0 ? -1.0f : i < coder.H ? coder.T[i - 1] : __builtin_nanf("");
         __syncthreads();
     }
     const uint32_t total = gridDim.x * kThreads;
@@ -415,7 +432,11 @@ inline hipError_t launch_quantize_sq_src(bifeat_params *p, const Src &src, int64
         UniformCoder c{p->d_min, p->d_inv, (float)((1u << p->scheme.bits) - 1u)};
         launch_sq(src, rows, D, p->rb, p->scheme.bits, c, codes_row0, vec, s);
     } else {
-        LogCoder c{p->d_T, 1 << (p->scheme.bits - 1)};
+        const int H = 1 << (p->scheme.bits - 1);
+        const double a = H / (p->e_max - p->e_min);  // levels per factor of two
+        // (2-bit codes have a single edge: one comparison, 105 us for 1 M x 128 floats against 110)
+        const bool near = H > 2 && a <= 1024.0 && p->e_min >= -120.0 && p->e_max <= 127.0;  // (not NaN, not inf)
+        LogCoder c{p->d_T, H, near ? (float)a : 0.0f, near ? (float)(-a * p->e_min) : 0.0f};
         launch_sq(src, rows, D, p->rb, p->scheme.bits, c, codes_row0, vec, s);
     }
     return hipGetLastError();

@@ -50,3 +50,27 @@ def test_half_chunk_codes(bits, D, rows, offset):
     assert q.params_get_log()[:2] == (e_min, e_max)
     q.quantize(chunk, codes, 0)
     assert np.array_equal(codes.cpu().numpy(), orc.pack(orc.log_encode(x32, bits, T), bits))
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("e_min,e_max", [(-6.0, 1.75), (-0.3, 0.4), (0.999, 1.001), (-149.0, 3.0), (-126.0, 127.9),
+                                         (3.0, 3.0), (-119.5, 126.9), (100.0, 101.0)])
+def test_log_levels_at_their_edges(bits, e_min, e_max):
+    # every edge, the floats next to it and values all over the range, for ranges whose level follows
+    # from the logarithm and for those that are searched
+    import torch
+    import paper_2207_14696_amd as bf
+    T, _ = orc.log_tables(e_min, e_max, bits)
+    rng = np.random.default_rng(bits)
+    with np.errstate(all="ignore"):
+        near = np.concatenate([T, np.nextafter(T, np.float32(0)), np.nextafter(T, np.float32(np.inf)),
+                               np.exp2(rng.uniform(e_min - 2, e_max + 2, 4000)).astype(np.float32),
+                               np.array([0.0, -0.0, np.nan, np.inf, -np.inf, 1e-45, 1e-38, 3e38], np.float32)])
+    x = np.resize(np.concatenate([near, -near]), (600, 24)).astype(np.float32)
+    q = bf.Quantizer(scheme_of("log", bits), 24)
+    q.params_set_log(e_min, e_max)
+    codes = torch.zeros((600, q.row_bytes), dtype=torch.uint8, device="cuda")
+    q.quantize(torch.from_numpy(x).cuda(), codes, 0)
+    want = orc.pack(orc.log_encode(x, bits, T), bits)
+    bad = codes.cpu().numpy() != want
+    assert not bad.any(), np.nonzero(bad.any(1))[0][:5]
