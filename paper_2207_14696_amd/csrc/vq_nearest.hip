@@ -31,6 +31,8 @@
 // round over 65 536 rows of that shape: 200 us, before (plain search, fp32 adds) 1030 us.
 #include "vq_nearest.hpp"
 
+#include <math.h>
+
 #include <algorithm>
 
 namespace bf {
@@ -48,12 +50,10 @@ struct VqNearestArgs {
     int vec;                // 4 columns of a part can be loaded at once
     int NT;                 // tiles of 32 entries in LDS at a time
     int ny;                 // workgroups per part
-    const float *cb;        // [P][len][w]
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
     uint32_t cell_mask;     // low bits of a score that hold a cell's number
-    uint8_t *codes;         // (the encoder)
-    int64_t rb;
+    int64_t rb;             // (the encoder)
     float *sums;            // (training) [ny][P][w][len]
     uint32_t *counts;       // [ny][P][len]
     double *distortion;
@@ -94,7 +94,8 @@ __device__ inline float rule_value(const float (&x)[WP], const float (&c)[WP], f
 }
 
 template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
-__global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_kernel(VqNearestArgs<T> a) {
+__global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_kernel(
+    VqNearestArgs<T> a, const float *__restrict__ cb, uint8_t *__restrict__ codes) {
     constexpr int WP = 8 * G;          // columns of a part, padded with zeros
     constexpr int TH = ENT ? 256 : 512;
     constexpr int WAVES = TH / 64;
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5;
     const int w = a.w, len = a.len;
-    const float *part_cb = a.cb + (int64_t)part * len * w;
+    const float *part_cb = cb + (int64_t)part * len * w;
     const float *part_rn = COS ? a.rnorm + (int64_t)part * len : nullptr;
 
     // ---- the part's scale: a power of two that brings its largest magnitude to [2^10, 2^11)
@@ -467,6 +468,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             if (__popcll(todo) >= kLaneSearch) {
                 int bc = 0;
                 float bv = INFINITY;
+#pragma unroll 4
                 for (int e = 0; e < len; e++) {
                     float c[WP], rn;
                     entry(e, c, rn);
@@ -517,7 +519,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
 #pragma unroll
             for (int d = 0; d < WP; d++) asm volatile("" : "+v"(xn[d]));
             if (valid) {
-                uint8_t *row = a.codes + r * a.rb;
+                uint8_t *row = codes + r * a.rb;
                 if (a.cbytes == 1) row[part] = (uint8_t)code;
                 else reinterpret_cast<uint16_t *>(row)[part] = (uint16_t)code;
                 if (part == 0)
@@ -569,8 +571,9 @@ __global__ __launch_bounds__(kThreads) void vq_means_kernel(const float *__restr
 //   the cell number in the low bits: 2^(bits - 23) M
 //   the rule: distances (w + 2) u relative, i.e. (w + 2) u M per score
 // twice that for two scores, and a quarter on top.
-float vq_margin(int w, int groups, int cell_bits) {
+float vq_margin(int w, int len) {
     const double u = ldexp(1.0, -24);
+    const int groups = (w + 7) / 8, cell_bits = ilog2(4 * ((len + 63) / 64));
     const double score = ldexp(1.0, -19) + 2.0 * u * (32.0 * groups + 2.0) + ldexp(1.0, cell_bits - 23) +
                          2.0 * u * (w + 4.0);
     return (float)(1.25 * 2.0 * score);
@@ -591,8 +594,17 @@ size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) 
     return n;
 }
 
+// Entries in LDS next to their pieces when as many workgroups share a CU as their registers allow
+// (training: when it fits at all); else as many pieces as a CU holds, the rule reading its few
+// entries from L2.
+bool entries_in_lds(const bifeat_params *p, bool train) {
+    const int G = (p->scheme.vq_width + 7) / 8, tiles = (p->scheme.vq_length + 63) / 64 * 2;
+    const int64_t limit = train ? kCuLds - 1024 : kCuLds / (G == 1 ? 4 : G == 2 ? 3 : 2);
+    return (int64_t)nearest_lds(p, G, tiles, true, train) <= limit;
+}
+
 template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
-bool launch_one(bifeat_params *p, VqNearestArgs<T> a, size_t lds, hipStream_t s) {
+bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds, hipStream_t s) {
     auto kern = vq_nearest_kernel<T, G, METRIC, ENT, TRAIN>;
     // (the kernel's few static words count too)
     if (lds > 65536 - 64 &&
@@ -624,40 +636,35 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, size_t lds, hipStream_t s)
     }
     a.ny = (int)ny;
     const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
-    kern<<<(unsigned)blocks, TH, lds, s>>>(a);
-    if constexpr (TRAIN)
-        vq_means_kernel<<<blocks_for((int64_t)a.P * a.len * a.w), kThreads, 0, s>>>(a.sums, a.counts, a.ny, a.P, a.w,
-                                                                                   a.len, p->d_cb);
+    kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
+    if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.ny, s);
     return true;
 }
 
 template <typename T, int G, int METRIC>
-bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t s) {
+bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStream_t s) {
+    const bool train = codes == nullptr;
     const int tiles = (a.len + 63) / 64 * 2;
-    // entries in LDS next to their pieces when as many workgroups share a CU as their registers
-    // allow (training: when it fits at all); else as many pieces as a CU holds, the rule reading
-    // its few entries from L2
-    const bool ent = nearest_lds(p, G, tiles, true, train) <= (size_t)(train ? kCuLds - 1024 : kCuLds / (G == 1 ? 4 : G == 2 ? 3 : 2));
-    if (train && !ent) return false;
+    const bool ent = entries_in_lds(p, train);
     const int fit = (int)(152 * 1024 / (G * 1024 + 128)) & ~1;
     a.NT = ent || tiles < fit ? tiles : fit;
     const size_t lds = nearest_lds(p, G, a.NT, ent, train);
     if (train) {
-        if constexpr (METRIC == BIFEAT_VQ_L2) return launch_one<T, G, METRIC, true, true>(p, a, lds, s);
+        if constexpr (METRIC == BIFEAT_VQ_L2) return launch_one<T, G, METRIC, true, true>(p, a, codes, lds, s);
         else return false;  // the rounds of a cosine codebook go through its codes
     }
-    return ent ? launch_one<T, G, METRIC, true, false>(p, a, lds, s)
-               : launch_one<T, G, METRIC, false, false>(p, a, lds, s);
+    return ent ? launch_one<T, G, METRIC, true, false>(p, a, codes, lds, s)
+               : launch_one<T, G, METRIC, false, false>(p, a, codes, lds, s);
 }
 
 template <typename T, int G>
-bool launch_groups(bifeat_params *p, VqNearestArgs<T> a, bool train, hipStream_t s) {
+bool launch_groups(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStream_t s) {
     const int cell_bits = ilog2(4 * ((a.len + 63) / 64));
-    a.margin = vq_margin(a.w, G, cell_bits);
+    a.margin = vq_margin(a.w, a.len);
     a.cell_margin = vq_cell_margin(a.w);
     a.cell_mask = (1u << cell_bits) - 1u;
-    return p->scheme.vq_metric == BIFEAT_VQ_COSINE ? launch_metric<T, G, BIFEAT_VQ_COSINE>(p, a, train, s)
-                                                   : launch_metric<T, G, BIFEAT_VQ_L2>(p, a, train, s);
+    return p->scheme.vq_metric == BIFEAT_VQ_COSINE ? launch_metric<T, G, BIFEAT_VQ_COSINE>(p, a, codes, s)
+                                                   : launch_metric<T, G, BIFEAT_VQ_L2>(p, a, codes, s);
 }
 
 // codes == nullptr: training
@@ -665,7 +672,7 @@ template <typename T>
 bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, double *distortion,
                     hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    if (w > kNearestMaxWidth || len <= kNearestMinLength) return false;
+    if (!vq_nearest_takes(p, !codes)) return false;
     VqNearestArgs<T> a{};
     a.x = x;
     a.rows = rows;
@@ -675,20 +682,36 @@ bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, 
     a.P = p->P;
     a.cbytes = p->cbytes;
     a.vec = w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
-    a.cb = p->d_cb;
     a.rnorm = p->d_rnorm;
-    a.codes = codes;
     a.rb = rb;
     a.distortion = distortion;
     switch ((w + 7) / 8) {
-        case 1: return launch_groups<T, 1>(p, a, !codes, s);
-        case 2: return launch_groups<T, 2>(p, a, !codes, s);
-        case 3: return launch_groups<T, 3>(p, a, !codes, s);
-        default: return launch_groups<T, 4>(p, a, !codes, s);
+        case 1: return launch_groups<T, 1>(p, a, codes, s);
+        case 2: return launch_groups<T, 2>(p, a, codes, s);
+        case 3: return launch_groups<T, 3>(p, a, codes, s);
+        default: return launch_groups<T, 4>(p, a, codes, s);
     }
 }
 
 }  // namespace
+
+// Entries that lie too densely for the margin leave most rows open, and those are searched by the
+// rule one entry after the other.  The distance to the nearest of `len` entries in w dimensions is
+// about len^(-2/w) of M, and the gap to the next about 2/w of that: with the margin above a
+// twentieth of it (16384 entries of 4 columns: 154 ms of training against 32; any one-column
+// codebook of some size) the plain search is the better one.
+bool vq_nearest_takes(const bifeat_params *p, bool train) {
+    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    if (w > kNearestMaxWidth || len <= kNearestMinLength) return false;
+    const double gap = pow((double)len, -2.0 / w) * std::min(1.0, 2.0 / w);
+    if (vq_margin(w, len) > 0.05 * gap) return false;
+    return !train || (p->scheme.vq_metric == BIFEAT_VQ_L2 && entries_in_lds(p, true));
+}
+
+void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts, int ny, hipStream_t s) {
+    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    vq_means_kernel<<<blocks_for((int64_t)p->P * len * w), kThreads, 0, s>>>(sums, counts, ny, p->P, w, len, p->d_cb);
+}
 
 template <typename T>
 bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,

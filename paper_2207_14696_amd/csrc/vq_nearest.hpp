@@ -5,9 +5,11 @@
 
 namespace bf {
 
-// Both return false (nothing launched) for shapes that stay with the plain search: parts of more
-// than 32 columns, codebooks of up to 16 entries, and in training codebooks whose sums do not fit
-// LDS next to the entries.
+// Whether the matrix-core search takes the handle's shape: not parts of more than 32 columns,
+// codebooks of up to 16 entries or of entries too dense for its margin, nor in training cosine
+// codebooks and those whose sums do not fit LDS next to the entries.  (The two calls below return
+// false, with nothing launched, when it does not.)
+bool vq_nearest_takes(const bifeat_params *p, bool train);
 
 // the index of every part's nearest entry into the rows at `codes` (row stride rb bytes, indices
 // of p->cbytes bytes, the bytes behind them zeroed)
@@ -19,5 +21,8 @@ bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t
 // nearest to it, their squared distances are added to *distortion
 template <typename T>
 bool launch_vq_nearest_round(bifeat_params *p, const T *x, int64_t rows, double *distortion, hipStream_t s);
+
+// every entry with members becomes their mean, from ny sets of sums [P][w][len] and counts [P][len]
+void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts, int ny, hipStream_t s);
 
 }  // namespace bf

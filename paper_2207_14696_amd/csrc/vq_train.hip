@@ -13,8 +13,8 @@
 // with the accumulation (vq_nearest.hip; parts of more than 32 columns and codebooks
 // of up to 16 entries: the plain search here, sums first in LDS per workgroup, then
 // global atomics); everything else (cosine metric, up to 16384 entries) runs the
-// encoder's own kernel into a scratch code array and accumulates from that with
-// global atomics.
+// encoder's own kernel into a scratch code array and accumulates from that, again in
+// LDS and per workgroup.
 #include "common.hpp"
 #include "vq_nearest.hpp"
 
@@ -149,48 +149,112 @@ __global__ void vq_rnorm_kernel(const float *__restrict__ cb, int64_t entries, i
     }
 }
 
-// sums / counts / squared distance from a dense code array codes[r][p]
+// Sums, counts and squared distance from a dense code array codes[r][p].  A workgroup takes one
+// part, as many of its columns (the count is one more) as LDS holds sums for - 64-bit ones, see
+// vq_nearest.hip - and every ny-th strip of rows, and writes its sums to the workspace:
+// sums [ny][P][w][len], counts [ny][P][len].
+// Before, every value was an atomic on memory (1.1 M per part and round at 65 536 rows of 16
+// columns) and every wave one on the distortion: 1.7 ms of a round's 2.8 at 8 x 2048 x 16.
+constexpr int kAccThreads = 1024;
+constexpr int64_t kAccLds = 144 * 1024;
+
 template <typename T, typename CODE>
-__global__ __launch_bounds__(kThreads) void vq_accumulate_codes_kernel(
-    const T *__restrict__ x, int64_t rows, int D, int w, int len, int P,
-    const CODE *__restrict__ codes, const float *__restrict__ cb, float *__restrict__ sums,
-    float *__restrict__ counts, double *__restrict__ distortion) {
-    const int64_t items = rows * P;
+__global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
+    const T *__restrict__ x, int64_t rows, int D, int w, int len, int P, const CODE *__restrict__ codes,
+    const float *__restrict__ cb, int DG, int groups, int ny, float *__restrict__ sums,
+    uint32_t *__restrict__ counts, double *__restrict__ distortion) {
+    extern __shared__ double s_acc[];  // [DG][len]
+    __shared__ double s_dist;
+    const int grp = blockIdx.x % groups, p = blockIdx.x / groups % P, by = blockIdx.x / (groups * P);
+    const int c0 = grp * DG, nc = min(DG, w + 1 - c0);  // columns c0.. ; column w counts
+    for (int i = threadIdx.x; i < nc * len; i += kAccThreads) s_acc[i] = 0.0;
+    if (threadIdx.x == 0) s_dist = 0.0;
+    __syncthreads();
     float dsum = 0.0f;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < items;
-         i += (int64_t)gridDim.x * kThreads) {
-        const int64_t r = i / P;
-        const int p = (int)(i - r * P);
-        const int64_t e = (int64_t)p * len + codes[i], ent = e * w;
-        for (int d = 0; d < w; d++) {
-            const int col = p * w + d;
-            const float xv = col < D ? load1(x + r * D + col) : 0.0f;
-            atomicAdd(&sums[ent + d], xv);
-            const float diff = xv - cb[ent + d];
-            dsum += diff * diff;
+    for (int64_t r = (int64_t)by * kAccThreads + threadIdx.x; r < rows; r += (int64_t)ny * kAccThreads) {
+        const int code = codes[r * P + p];
+        const float *ent = cb + ((int64_t)p * len + code) * w;
+#pragma unroll 4
+        for (int j = 0; j < nc; j++) {
+            const int d = c0 + j, col = p * w + d;
+            if (d < w) {
+                const float xv = col < D ? load1(x + r * D + col) : 0.0f;
+                unsafeAtomicAdd(&s_acc[(int64_t)j * len + code], (double)xv);
+                const float diff = xv - ent[d];
+                dsum += diff * diff;
+            } else {
+                unsafeAtomicAdd(&s_acc[(int64_t)j * len + code], 1.0);
+            }
         }
-        atomicAdd(&counts[e], 1.0f);
     }
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
-    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(distortion, (double)dsum);
+    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
+    __syncthreads();
+    if (threadIdx.x == 0) unsafeAtomicAdd(distortion, s_dist);
+    for (int i = threadIdx.x; i < nc * len; i += kAccThreads) {
+        const int j = i / len, e = i - j * len, d = c0 + j;
+        if (d < w) sums[(((int64_t)by * P + p) * w + d) * len + e] = (float)s_acc[i];
+        else counts[((int64_t)by * P + p) * len + e] = (uint32_t)s_acc[i];
+    }
+}
+
+// The generic round's workspace: the codes, then the workgroups' sums.
+struct GenericPlan {
+    int DG, groups, ny;
+    int64_t codes_bytes, set_bytes;  // codes (rounded up), sums and counts of one workgroup row
+};
+
+GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
+    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    GenericPlan g;
+    g.DG = (int)(kAccLds / (8 * len));  // at least one: 16384 entries take 128 KB
+    if (g.DG > w + 1) g.DG = w + 1;
+    g.groups = (w + g.DG) / g.DG;
+    g.DG = (w + g.groups) / g.groups;
+    // about two workgroups per CU, no more than there are strips, the sums within 256 MB
+    const int64_t strips = (rows + kAccThreads - 1) / kAccThreads;
+    g.codes_bytes = (rows * p->P * p->cbytes + 255) / 256 * 256;
+    g.set_bytes = (int64_t)4 * p->P * len * (w + 1);
+    int64_t ny = 512 / ((int64_t)p->P * g.groups);
+    if (ny > ((int64_t)256 << 20) / g.set_bytes) ny = ((int64_t)256 << 20) / g.set_bytes;
+    if (ny > strips) ny = strips;
+    g.ny = (int)(ny < 1 ? 1 : ny);
+    return g;
+}
+
+template <typename T, typename CODE>
+bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, int ny, float *sums,
+                      uint32_t *counts, double *dist_slot, hipStream_t s) {
+    const size_t shm = sizeof(double) * (size_t)g.DG * p->scheme.vq_length;
+    auto kern = vq_accumulate_codes_kernel<T, CODE>;
+    if (shm > 65536 - 64 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)shm) != hipSuccess)
+        return false;
+    kern<<<(unsigned)(g.groups * p->P * ny), kAccThreads, shm, s>>>(
+        x, rows, (int)p->D, p->scheme.vq_width, p->scheme.vq_length, p->P, (const CODE *)p->d_scratch, p->d_cb, g.DG,
+        g.groups, ny, sums, counts, dist_slot);
+    return true;
 }
 
 template <typename T>
-void lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, double *dist_slot, hipStream_t s) {
+hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, double *dist_slot, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
-    const int64_t n = (int64_t)P * len * w;
-    float *sums = p->d_train, *counts = p->d_train + n;
-    vq_zero_kernel<<<1024, 256, 0, s>>>(p->d_train, n + (int64_t)P * len);
+    const int64_t books = (int64_t)P * len * w;
+    const GenericPlan g = generic_plan(p, rows);
+    // without room for every workgroup's sums: one workgroup per part and group of columns, and
+    // the handle's own block of one set (the codes' part of the workspace is there, see below)
+    const bool all = (int64_t)p->scratch_bytes >= g.codes_bytes + g.ny * g.set_bytes;
+    const int ny = all ? g.ny : 1;
+    float *sums = all ? (float *)(p->d_scratch + g.codes_bytes) : p->d_train;
+    uint32_t *counts = (uint32_t *)(sums + ny * books);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
     launch_vq_assign(p, x, rows, p->d_scratch, (int64_t)P * p->cbytes, s);
-    const int blocks = blocks_for(rows * P, 8192);
-    if (p->cbytes == 1)
-        vq_accumulate_codes_kernel<T, uint8_t><<<blocks, kThreads, 0, s>>>(
-            x, rows, (int)p->D, w, len, P, (const uint8_t *)p->d_scratch, p->d_cb, sums, counts, dist_slot);
-    else
-        vq_accumulate_codes_kernel<T, uint16_t><<<blocks, kThreads, 0, s>>>(
-            x, rows, (int)p->D, w, len, P, (const uint16_t *)p->d_scratch, p->d_cb, sums, counts, dist_slot);
-    vq_lloyd_update_kernel<<<1024, 256, 0, s>>>(p->d_cb, sums, counts, w, n);
+    const bool ok = p->cbytes == 1 ? accumulate_codes<T, uint8_t>(p, x, rows, g, ny, sums, counts, dist_slot, s)
+                                   : accumulate_codes<T, uint16_t>(p, x, rows, g, ny, sums, counts, dist_slot, s);
+    if (!ok) return hipGetLastError();
+    launch_vq_means(p, sums, counts, ny, s);
+    return hipSuccess;
 }
 
 }  // namespace
@@ -234,7 +298,16 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
     const bool fused = p->scheme.vq_metric == BIFEAT_VQ_L2 && p->cbytes == 1 &&
                        sizeof(float) * ((size_t)2 * len * w + len) <= 65536;
-    if (!fused && !ensure_scratch(p, (size_t)rows * P * p->cbytes, s)) return hipErrorOutOfMemory;
+    // What the fused search does not take goes through the codes as well; the plain fused kernel,
+    // which needs no workspace, is left for streams under capture (16 384 rows of 64 columns, 64
+    // entries: 42 ms with it).
+    bool through_codes = !fused;
+    if (!fused || !vq_nearest_takes(p, true)) {
+        const GenericPlan g = generic_plan(p, rows);
+        through_codes = ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s) ||
+                        ensure_scratch(p, (size_t)rows * P * p->cbytes, s);
+        if (!fused && !through_codes) return hipErrorOutOfMemory;
+    }
     if (init) {
         if (dtype == BIFEAT_F32)
             vq_init_kernel<float><<<256, 256, 0, s>>>((const float *)chunk, (int)p->D, w, len, P, p->d_cb);
@@ -243,12 +316,14 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
     }
     vq_zero_kernel<<<1, 128, 0, s>>>(reinterpret_cast<float *>(p->d_dist), 2 * rounds);
     for (int k = 0; k < rounds; k++) {
-        if (fused) {
+        if (!through_codes) {
             if (dtype == BIFEAT_F32) lloyd_round(p, (const float *)chunk, rows, p->d_dist + k, s);
             else lloyd_round(p, (const __half *)chunk, rows, p->d_dist + k, s);
         } else {
-            if (dtype == BIFEAT_F32) lloyd_round_generic(p, (const float *)chunk, rows, p->d_dist + k, s);
-            else lloyd_round_generic(p, (const __half *)chunk, rows, p->d_dist + k, s);
+            const hipError_t e = dtype == BIFEAT_F32
+                                     ? lloyd_round_generic(p, (const float *)chunk, rows, p->d_dist + k, s)
+                                     : lloyd_round_generic(p, (const __half *)chunk, rows, p->d_dist + k, s);
+            if (e != hipSuccess) return e;
         }
     }
     return hipGetLastError();
