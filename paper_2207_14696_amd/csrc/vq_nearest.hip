@@ -48,7 +48,7 @@ struct VqNearestArgs {
     int64_t rows;
     int D, w, len, P, cbytes;
     int vec;                // 4 columns of a part can be loaded at once
-    int NT;                 // tiles of 32 entries in LDS at a time
+    int NT;                 // tiles of 32 entries, a whole number of pairs: a cell spans two
     int ny;                 // workgroups per part
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
@@ -59,8 +59,8 @@ struct VqNearestArgs {
     double *distortion;
 };
 
-// codebooks of up to this many entries and wider parts stay with the plain search
-constexpr int kNearestMinLength = 16;
+// codebooks of fewer values (entries x columns) and wider parts stay with the plain search
+constexpr int kNearestMinBook = 512;
 constexpr int kNearestMaxWidth = 32;
 constexpr int kCuLds = 160 * 1024;
 // rows of a wave that need the whole codebook searched by the rule: from this many on every lane
@@ -158,10 +158,10 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
         for (int i = threadIdx.x; i < len; i += TH) s_cnt[i] = 0u;
     }
 
-    // tiles [t0, t0 + nt) of 32 entries into LDS; a thread prepares one entry
-    auto stage = [&](int t0, int nt) {
-        for (int i = threadIdx.x; i < nt * 32; i += TH) {
-            const int e = t0 * 32 + i;
+    // the entries into LDS, a thread prepares one at a time
+    {
+        for (int e = threadIdx.x; e < a.NT * 32; e += TH) {
+            const int i = e;
             const bool real = e < len;
             const float rn = COS ? (real ? part_rn[e] : 0.0f) : 0.0f;
             float s2 = 0.0f;
@@ -188,20 +188,6 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             s_half[i] = real ? (COS ? 0.0f : 0.5f * s2) : kPadScore;
             if constexpr (ENT && COS) s_rn[i] = rn;
             if (!COS) atomicMax(&s_c2max, __float_as_uint(s2));
-        }
-    };
-    const int tiles = ((len + 63) >> 6) << 1;  // in pairs: a cell spans two tiles
-    const bool single = tiles <= a.NT;
-    if (single) stage(0, tiles);
-    if (!single && !COS) {
-        // the largest norm over the whole codebook bounds every chunk's scores
-        for (int e = threadIdx.x; e < len; e += TH) {
-            float s2 = 0.0f;
-            for (int d = 0; d < w; d++) {
-                const float cs = part_cb[(int64_t)e * w + d] * scale;
-                s2 += cs * cs;
-            }
-            atomicMax(&s_c2max, __float_as_uint(s2));
         }
     }
     __syncthreads();
@@ -231,7 +217,16 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
     };
 
     float dsum = 0.0f;
-    // every wave of the workgroup walks the same strips (staging a chunk synchronises)
+    // Rows whose entries tie (0/1 features) are open more often than not.  When a quarter of a
+    // workgroup's first strip is, the workgroup searches those and all of its other strips by the
+    // rule, every lane for its own row, the entries read from LDS (a codebook without a copy
+    // there takes the place of the pieces: 32 x 8G floats are as large as a tile's pieces).
+    // Every wave of the workgroup walks the same strips.
+    bool plain = false;
+    const float *s_plain = reinterpret_cast<const float *>(s_frag);
+    auto plain_book = [&](int e) {  // entries e .. e + 3, e a multiple of 4
+        return ENT ? s_ent + (e >> 6) * PAIR + ((e >> 2) & 15) * CELL : s_plain + e * WP;
+    };
     constexpr int ROWS = WAVES * 64;
     // a row past the last one reads the last one
     auto load_row = [&](int64_t row, float (&v)[WP]) {
@@ -258,6 +253,38 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
         float xr[WP];
 #pragma unroll
         for (int d = 0; d < WP; d++) xr[d] = xn[d];
+        int code = 0;
+        float value = INFINITY;
+        int all_code = 0;
+        float all_value = INFINITY;
+        auto search_all = [&]() {
+            // four entries at a time from one address (those past the last one are in bounds and not used)
+            for (int e0 = 0; e0 < len; e0 += 4) {
+                const float *src = plain_book(e0);
+                float4 q[4][WP / 4];
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+#pragma unroll
+                    for (int i = 0; i < WP / 4; i++) q[k][i] = reinterpret_cast<const float4 *>(src + k * WP)[i];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    if (e0 + k >= len) break;
+                    float c[WP];
+#pragma unroll
+                    for (int i = 0; i < WP / 4; i++) {
+                        c[4 * i] = q[k][i].x; c[4 * i + 1] = q[k][i].y; c[4 * i + 2] = q[k][i].z; c[4 * i + 3] = q[k][i].w;
+                    }
+                    const float v = rule_value<WP, METRIC>(xr, c, COS ? (ENT ? s_rn[e0 + k] : part_rn[e0 + k]) : 0.0f);
+                    if (v < all_value) { all_value = v; all_code = e0 + k; }
+                }
+            }
+        };
+        if (plain) {
+            load_row(r + (int64_t)a.ny * ROWS, xn);
+            search_all();
+            code = all_code;
+            value = all_value;
+        } else {
         float f = scale;
         bool bad = part_bad, zero = false;
         if constexpr (COS) {  // the best entry does not depend on the row's length
@@ -311,13 +338,8 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
         // the next strip's rows travel during this strip's search
         load_row(r + (int64_t)a.ny * ROWS, xn);
         float best[2] = {3e38f, 3e38f}, second[2] = {3e38f, 3e38f};
-        for (int t0 = 0; t0 < tiles; t0 += a.NT) {
-            const int nt = min(a.NT, tiles - t0);
-            if (!single) {
-                __syncthreads();
-                stage(t0, nt);
-                __syncthreads();
-            }
+        {
+            const int nt = a.NT;
             // A set's minima are taken while the matrix cores work on the other set: the next tile's
             // product is started as soon as its accumulators are free, its operands having been
             // read from LDS one half-step earlier.
@@ -351,7 +373,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             auto minima = [&](int s, int t) {
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    uint32_t number = (uint32_t)(2 * (t0 + t) + q);
+                    uint32_t number = (uint32_t)(2 * t + q);
                     asm volatile("" : "+s"(number));  // one scalar: the compiler would add it up per lane
                     const float m = minimum(minimum(minimum(minimum(part4[s][q], acc[s][4 * q]), acc[s][4 * q + 1]),
                                                     acc[s][4 * q + 2]), acc[s][4 * q + 3]);
@@ -408,8 +430,6 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
         bool open = !(gap > margin);  // the rule has to look at all entries
         // ---- the cell's 8 entries in fp32, again with the second best; rows too close to call join
         // the open ones
-        int code = 0;
-        float value = 0.0f;
         {
             // cell number = 2 * (first tile) + q; entries 8q + 4h .. + 3 of both tiles
             const uint32_t e0 = open ? 0u : (cell >> 2) * 64u + (cell & 3u) * 8u + 4u * (uint32_t)h_of;
@@ -463,9 +483,23 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             open = false;
             code = 0;
         }
+        if (r0 == (int64_t)by * ROWS && __syncthreads_count(open && valid) > TH / 4) {
+            plain = true;
+            if constexpr (!ENT) {  // (the barrier above: no wave reads the pieces any more)
+                float *dst = reinterpret_cast<float *>(s_frag);
+                for (int i = threadIdx.x; i < len * WP; i += TH) {
+                    const int e = i / WP, d = i - e * WP;
+                    dst[i] = d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
+                }
+                __syncthreads();
+            }
+        }
         uint64_t todo = __ballot(open && valid);
         if (todo) {
-            if (__popcll(todo) >= kLaneSearch) {
+            if (plain) {
+                search_all();
+                if (open) { code = all_code; value = all_value; }
+            } else if (__popcll(todo) >= kLaneSearch) {
                 int bc = 0;
                 float bv = INFINITY;
 #pragma unroll 4
@@ -505,6 +539,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
                 }
             }
         }
+        }  // !plain
         if constexpr (TRAIN) {
             if (valid) {
 #pragma unroll
@@ -619,7 +654,8 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
     // (staging the codebook is about as long as one strip, so a workgroup should have many); in
     // training, where each also adds its sums to memory, as many as the chip holds
     const int64_t resident = 256 * std::min<int64_t>(ENT ? (G == 1 ? 4 : 2) : 1, kCuLds / (int64_t)lds);
-    int64_t ny = (TRAIN ? 1 : 4) * resident / a.P;
+    // (without a copy of the entries: the codebook is large, and once is enough there too)
+    int64_t ny = (TRAIN || !ENT ? 1 : 4) * resident / a.P;
     if (ny < 1) ny = 1;
     if (ny > strips) ny = strips;
     if constexpr (TRAIN) {
@@ -646,8 +682,7 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
     const bool train = codes == nullptr;
     const int tiles = (a.len + 63) / 64 * 2;
     const bool ent = entries_in_lds(p, train);
-    const int fit = (int)(152 * 1024 / (G * 1024 + 128)) & ~1;
-    a.NT = ent || tiles < fit ? tiles : fit;
+    a.NT = tiles;
     const size_t lds = nearest_lds(p, G, a.NT, ent, train);
     if (train) {
         if constexpr (METRIC == BIFEAT_VQ_L2) return launch_one<T, G, METRIC, true, true>(p, a, codes, lds, s);
@@ -698,13 +733,17 @@ bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, 
 // Entries that lie too densely for the margin leave most rows open, and those are searched by the
 // rule one entry after the other.  The distance to the nearest of `len` entries in w dimensions is
 // about len^(-2/w) of M, and the gap to the next about 2/w of that: with the margin above a
-// twentieth of it (16384 entries of 4 columns: 154 ms of training against 32; any one-column
-// codebook of some size) the plain search is the better one.
+// hundredth of it (4096 entries of 4 columns: 1857 us against 1499; any one-column codebook of
+// some size) the plain search is the better one.  So it is for codebooks of under 512 values
+// (65 536 x 12 parts of 8 columns, 32 entries: 28 us against 33; 4 columns, 64 entries: 40 against
+// 54) and for those whose pieces do not fit LDS at once (16384 x 16: 2.7 ms against 4.9).
 bool vq_nearest_takes(const bifeat_params *p, bool train) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    if (w > kNearestMaxWidth || len <= kNearestMinLength) return false;
+    const int G = (w + 7) / 8, tiles = (len + 63) / 64 * 2;
+    if (w > kNearestMaxWidth || w * len < kNearestMinBook) return false;
+    if (nearest_lds(p, G, tiles, false, false) > kCuLds - 4096) return false;
     const double gap = pow((double)len, -2.0 / w) * std::min(1.0, 2.0 / w);
-    if (vq_margin(w, len) > 0.05 * gap) return false;
+    if (vq_margin(w, len) > 0.01 * gap) return false;
     return !train || (p->scheme.vq_metric == BIFEAT_VQ_L2 && entries_in_lds(p, true));
 }
 

@@ -6,9 +6,9 @@
 namespace bf {
 
 // Whether the matrix-core search takes the handle's shape: not parts of more than 32 columns,
-// codebooks of up to 16 entries or of entries too dense for its margin, nor in training cosine
-// codebooks and those whose sums do not fit LDS next to the entries.  (The two calls below return
-// false, with nothing launched, when it does not.)
+// codebooks of under 512 values, of entries too dense for its margin or too large for LDS, nor in
+// training cosine codebooks and those whose sums do not fit LDS next to the entries.  (The two
+// calls below return false, with nothing launched, when it does not.)
 bool vq_nearest_takes(const bifeat_params *p, bool train);
 
 // the index of every part's nearest entry into the rows at `codes` (row stride rb bytes, indices

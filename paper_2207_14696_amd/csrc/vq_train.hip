@@ -10,11 +10,10 @@
 // the result depend on the order of additions in the last bits; it is judged on
 // distortion, not bit for bit.
 // Two forms: Euclidean one-byte codebooks small enough for LDS fuse the search
-// with the accumulation (vq_nearest.hip; parts of more than 32 columns and codebooks
-// of up to 16 entries: the plain search here, sums first in LDS per workgroup, then
-// global atomics); everything else (cosine metric, up to 16384 entries) runs the
-// encoder's own kernel into a scratch code array and accumulates from that, again in
-// LDS and per workgroup.
+// with the accumulation (vq_nearest.hip); everything else (cosine metric, up to 16384
+// entries, wide parts, tiny codebooks) runs the encoder's own kernel into a scratch code
+// array and accumulates from that, again in LDS and per workgroup.  (A plain fused kernel,
+// sums in LDS and then global atomics, is left for streams under capture without workspace.)
 #include "common.hpp"
 #include "vq_nearest.hpp"
 

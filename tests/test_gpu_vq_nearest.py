@@ -46,11 +46,12 @@ def _codebook(rng, D, w, length):
 
 
 # w: one to four groups of 8 columns, 4-column loads or not, a short last part; length: either side of
-# the plain search's limit, of a tile and of a cell, up to several chunks of LDS (4500 x 32)
+# the plain search's limit, of a tile and of a cell, with a copy of the entries in LDS and without, and too large for it (4500 x 32)
 @pytest.mark.parametrize("metric", ["l2", "cosine"])
 @pytest.mark.parametrize("D,w,length,rows,dtype", [
     (24, 8, 16, 300, np.float32), (24, 8, 17, 300, np.float32), (24, 8, 32, 64, np.float32),
-    (24, 8, 33, 65, np.float32), (64, 8, 256, 1000, np.float32), (64, 8, 255, 1000, np.float16),
+    (24, 8, 33, 65, np.float32), (24, 8, 63, 65, np.float32), (24, 8, 64, 300, np.float32), (24, 8, 65, 129, np.float32),
+    (64, 32, 1000, 700, np.float32), (64, 8, 256, 1000, np.float32), (64, 8, 255, 1000, np.float16),
     (22, 5, 64, 257, np.float32), (23, 4, 100, 257, np.float32), (3, 1, 20, 500, np.float32),
     (48, 12, 130, 511, np.float16), (50, 16, 256, 513, np.float32), (64, 16, 2048, 600, np.float32),
     (40, 20, 64, 129, np.float32), (64, 32, 256, 300, np.float32), (33, 32, 70, 300, np.float32),
@@ -86,6 +87,18 @@ def test_ties_and_near_ties_go_by_the_rule(bf, torch, metric):
     cb = np.concatenate([base, near, base + np.float32(1e-6), rng.normal(size=base.shape).astype(np.float32) * 3], 1)
     x = (rng.normal(size=(2000, 32)) * 2).astype(np.float32)
     _check(bf, torch, x, cb, 32, 8, 256, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("P,w,length,rows", [(96, 8, 256, 11000), (96, 16, 600, 2100)])
+def test_workgroups_whose_rows_tie_search_by_the_rule(bf, torch, P, w, length, rows, metric):
+    # more rows than one strip per workgroup (42 x 256, 2 x 512), the entries with and without a copy
+    # in LDS; the last rows are ordinary ones
+    rng = np.random.default_rng(P + w)
+    cb = rng.integers(0, 2, size=(P, length, w)).astype(np.float32)
+    x = rng.integers(0, 2, size=(rows, P * w)).astype(np.float32)
+    x[-300:] = rng.normal(size=(300, P * w))
+    _check(bf, torch, x, cb, P * w, w, length, metric)
 
 
 @pytest.mark.parametrize("metric", ["l2", "cosine"])
