@@ -147,8 +147,10 @@ int64_t bifeat_codes_per_row(const bifeat_params *p);
  *   encoder's rule for the scheme's metric, entry = mean of its members, an
  *   entry without members keeps its value.  Sums are accumulated with atomics,
  *   so the codebooks are reproducible in distortion, not bit for bit.
- *   Training uses library scratch: two bytes per part and sample row for a large or
- *   cosine codebook, otherwise partial sums (a few times the codebooks).  finalize synchronises `stream` for the cosine metric
+ *   Training uses library scratch: workgroups' partial sums of the codebooks, and for a large
+ *   or cosine codebook also a code per part and sample row (one byte up to 256 entries, else
+ *   two), with the sums there within 256 MB, or one set of them if that is larger.
+ *   finalize synchronises `stream` for the cosine metric
  *   (the entry norms are evaluated on the host in fp64).
  * finalize without any update returns BIFEAT_ENOTFIT. */
 int bifeat_fit_reset(bifeat_params *p, void *stream);
