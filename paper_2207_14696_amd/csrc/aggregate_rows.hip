@@ -36,6 +36,12 @@ __device__ inline void kahan_add(float &s, float &c, const float r) {
     s = t;
 }
 
+// What has been added up so far: c holds what the additions put on top of it.  Right after an
+// infinite term, or one whose addition overflowed, c is not finite; the sum then is s alone.
+__device__ inline double kahan_sum(const float s, const float c) {
+    return __builtin_isfinite(c) ? (double)s - (double)c : (double)s;
+}
+
 template <int VEC>
 struct Acc;
 template <>
@@ -57,12 +63,12 @@ struct Acc<4> {
         }
         store_stream(reinterpret_cast<float4 *>(p), o);
     }
-    // this piece's sum (c holds what the additions so far put on top of it)
+    // this piece's sum
     __device__ void add_to(double *p) const {
-        unsafeAtomicAdd(p + 0, (double)v.x - (double)c.x);
-        unsafeAtomicAdd(p + 1, (double)v.y - (double)c.y);
-        unsafeAtomicAdd(p + 2, (double)v.z - (double)c.z);
-        unsafeAtomicAdd(p + 3, (double)v.w - (double)c.w);
+        unsafeAtomicAdd(p + 0, kahan_sum(v.x, c.x));
+        unsafeAtomicAdd(p + 1, kahan_sum(v.y, c.y));
+        unsafeAtomicAdd(p + 2, kahan_sum(v.z, c.z));
+        unsafeAtomicAdd(p + 3, kahan_sum(v.w, c.w));
     }
 };
 template <>
@@ -74,7 +80,7 @@ struct Acc<1> {
     __device__ void store(float *p, int n, bool sum) const {
         __builtin_nontemporal_store(sum ? v : (n > 0 ? v / (float)n : 0.f), p);
     }
-    __device__ void add_to(double *p) const { unsafeAtomicAdd(p, (double)v - (double)c); }
+    __device__ void add_to(double *p) const { unsafeAtomicAdd(p, kahan_sum(v, c)); }
 };
 
 // rows of `pieces` consecutive list entries [e, end) added into acc, U loads in flight

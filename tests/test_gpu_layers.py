@@ -302,3 +302,20 @@ def test_aggregate_rows_random(bf, torch, case):
                       torch.from_numpy(indices).cuda(), out=out, sum=as_sum)
     _assert_rows_close(out.cpu().numpy(), orc.aggregate_rows(x, indptr, indices, sum=as_sum), x, indptr,
                        indices, as_sum, f"case {case}: D={D} N={N} V={V} sum={as_sum}")
+
+
+@pytest.mark.parametrize("as_sum", [False, True])
+@pytest.mark.parametrize("D", [8, 5])
+def test_infinities_at_the_end_of_a_long_lists_piece(bf, torch, D, as_sum):
+    # a list of more than 256 entries is summed in compensated pieces of 64; a term that is infinite,
+    # or whose addition overflows, in the last place of a piece leaves the compensation not a number
+    n = 320
+    x = np.ones((n, D), np.float32)
+    x[63, 0], x[127, 1], x[319, 2] = np.inf, -np.inf, np.inf
+    x[62:64, 3] = 3e38           # overflows when the piece's last row is added
+    x[128:131, 4] = 1.5          # an ordinary column
+    ptr = torch.tensor([0, n, n + 1], device="cuda")
+    idx = torch.cat([torch.arange(n, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")])
+    got = bf.aggregate_rows(torch.from_numpy(x).cuda(), ptr, idx, sum=as_sum).cpu().numpy()[0]
+    assert got[0] == np.inf and got[1] == -np.inf and got[2] == np.inf and got[3] == np.inf, got
+    np.testing.assert_allclose(got[4], 321.5 if as_sum else 321.5 / n, rtol=1e-6)
