@@ -24,6 +24,15 @@ constexpr int kLong = 256;
 constexpr int kRange = 2048;
 constexpr int kSub = 64;
 constexpr int kMaxLong = kRange / kLong + 2;
+// Columns that a workgroup adds up at a time, and the sums it has room for: a tile of 16-byte lanes
+// (20 KB); where rows allow 4-byte lanes only, four tiles, one for each of the workgroup's four lane
+// groups - one at a time takes barriers every 64 columns and the groups apart: 100 000 rows of 601
+// columns with hubs 843 us against 666 (every piece with atomics of its own, in 32 bits: 624) - or three where more than 7 lists
+// overlap a range (15 KB; with 20 a CU holds one workgroup less, 1.5 % on launches of short lists).
+template <int VEC>
+constexpr int kSums = kMaxLong * (VEC == 4 ? 256 : 192);
+template <int VEC>
+__device__ inline int pass_tiles(int n_long) { return VEC == 4 ? 1 : n_long <= 7 ? 4 : 3; }
 
 // Compensated (Kahan) running sums: the rounding error of a sum stays at a couple of
 // ulps of the mean magnitude whatever the list length; the kernel waits on memory, so
@@ -139,7 +148,7 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
                                   int64_t block, int64_t nblocks) {
     __shared__ int64_t s_v[kMaxLong], s_beg[kMaxLong], s_end[kMaxLong], s_first;
     __shared__ int s_deg[kMaxLong], s_n;
-    extern __shared__ double s_sum[];  // [kMaxLong][lpr * VEC]
+    extern __shared__ double s_sum[];  // [long lists][columns of a pass]
     const int lpr = 1 << lpr_log2;
     const int t = threadIdx.x & (lpr - 1);
     const int group = threadIdx.x >> lpr_log2, groups = kThreads >> lpr_log2;
@@ -191,25 +200,29 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
             if (__syncthreads_or(past)) break;
         }
         const int n_long = s_n < kMaxLong ? s_n : kMaxLong;
-        const int width = lpr * VEC;  // columns of a tile
-        for (int tile = 0; tile < tiles && n_long > 0; tile++) {
+        const int tile_cols = lpr * VEC;
+        // neighbouring groups work on neighbouring tiles of a pass
+        const int pass = pass_tiles<VEC>(n_long);
+        for (int t0 = 0; t0 < tiles && n_long > 0; t0 += pass) {
+            const int nt = min(tiles - t0, pass);
+            const int width = nt * tile_cols;
             for (int i = threadIdx.x; i < n_long * width; i += kThreads) s_sum[i] = 0.0;
             __syncthreads();
-            for (int it = group; it < n_long * kPieces; it += groups) {
-                const int piece = it % kPieces, k = it / kPieces;
+            for (int it = group; it < n_long * kPieces * nt; it += groups) {
+                const int tile = it % nt, piece = it / nt % kPieces, k = it / (nt * kPieces);
                 const int64_t b = s_beg[k] + (int64_t)piece * kSub;
-                const int64_t col = (int64_t)VEC * (tile * lpr + t);
+                const int64_t col = (int64_t)VEC * ((t0 + tile) * lpr + t);
                 if (b >= s_end[k] || col >= D) continue;
                 const int64_t end = b + kSub < s_end[k] ? b + kSub : s_end[k];
                 Acc<VEC> acc;
                 acc.zero();
                 add_rows<VEC, 2 * kAggInFlight>(acc, x + col, D, indices, b, end);
-                acc.add_to(s_sum + k * width + VEC * t);
+                acc.add_to(s_sum + k * width + tile * tile_cols + VEC * t);
             }
             __syncthreads();
             for (int i = threadIdx.x; i < n_long * width; i += kThreads) {
                 const int k = i / width;
-                const int64_t col = (int64_t)tile * width + (i - k * width);
+                const int64_t col = (int64_t)t0 * tile_cols + (i - k * width);
                 if (col < D)
                     unsafeAtomicAdd(out + s_v[k] * D + col, (float)(sum ? s_sum[i] : s_sum[i] / (double)s_deg[k]));
             }
@@ -223,10 +236,9 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
 // pieces are the longest single chains of the launch) take the long lists, the rest
 // the short ones.  The two write disjoint rows.
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void aggregate_rows_kernel(
-    const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
-    const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int tiles, int sum,
-    int long_blocks, float *__restrict__ out) {
+__device__ inline void aggregate(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
+                                 const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int tiles,
+                                 int sum, int long_blocks, float *__restrict__ out) {
     if ((int)blockIdx.x < long_blocks)
         long_lists<VEC>(x, D, indptr, indices, V, E, lpr_log2, tiles, sum, out, blockIdx.x,
                         long_blocks);
@@ -234,6 +246,17 @@ __global__ __launch_bounds__(kThreads) void aggregate_rows_kernel(
         short_lists<VEC>(x, D, indptr, indices, V, lpr_log2, tiles, sum, out,
                          (int64_t)blockIdx.x - long_blocks, (int64_t)gridDim.x - long_blocks);
 }
+#define BF_AGG(NAME, VEC)                                                                            \
+    void NAME(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,             \
+              const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int tiles,     \
+              int sum, int long_blocks, float *__restrict__ out) {                                    \
+        aggregate<VEC>(x, D, indptr, indices, V, E, lpr_log2, tiles, sum, long_blocks, out);          \
+    }
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_kernel4, 4)
+// (with the 96 SGPRs it would take a SIMD holds 7 waves instead of 8, and launches without a long
+// list, 200 000 rows of 101 columns, take 289 us instead of 268)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_sgpr(80))) BF_AGG(aggregate_rows_kernel1, 1)
+#undef BF_AGG
 
 // Output rows of the long lists set to zero ahead of the launch above: a lane per
 // destination looks at its list length, the wave then clears each long one's row.
@@ -317,12 +340,14 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
         aggregate_zero_long_kernel<<<blocks_for(V, 8 * 256), kThreads, 0, s>>>(indptr, V, D, out);
     }
     const int blocks = short_blocks + long_blocks;
-    const size_t shm = long_blocks > 0 ? sizeof(double) * kMaxLong * ((vec ? 4 : 1) << lpr_log2) : 0;
+    const int64_t tile_cols = (int64_t)(vec ? 4 : 1) << lpr_log2;
+    const int64_t most = vec ? kSums<4> : kSums<1>, all = kMaxLong * tiles * tile_cols;
+    const size_t shm = long_blocks > 0 ? sizeof(double) * (size_t)(all < most ? all : most) : 0;
     if (vec)
-        aggregate_rows_kernel<4><<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
+        aggregate_rows_kernel4<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
                                                             (int)tiles, sum, long_blocks, out);
     else
-        aggregate_rows_kernel<1><<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
+        aggregate_rows_kernel1<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
                                                             (int)tiles, sum, long_blocks, out);
     return hipGetLastError();
 }
