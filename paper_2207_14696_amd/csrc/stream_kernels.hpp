@@ -216,13 +216,28 @@ struct UniformCoder {
     const float *mn, *inv;
     float L;
     template <int NC> struct Ctx { float mn[NC], inv[NC]; };
-    template <int NC>
+    // VEC: D % 4 == 0
+    template <bool VEC, int NC>
     __device__ void prepare(Ctx<NC> &c, int col0, int D) const {
+        // 16 bytes a load where that goes: by 4 bytes the lanes' loads, NC columns apart, cross so many
+        // lines that 8 columns' parameters took 8 us at the head of a launch (25 MB of half-precision
+        // values 6.9 us, 18.5 before; 4 columns a lane that way: 10)
+        if constexpr (VEC) {
 #pragma unroll
-        for (int k = 0; k < NC; k++) {
-            bool ok = col0 + k < D;
-            c.mn[k] = ok ? mn[col0 + k] : 0.0f;
-            c.inv[k] = ok ? inv[col0 + k] : 0.0f;
+            for (int k = 0; k < NC; k += 4) {
+                const int j = min(col0 + k, D - 4);  // (past D: not used)
+                const float4 m = *reinterpret_cast<const float4 *>(mn + j);
+                const float4 s = *reinterpret_cast<const float4 *>(inv + j);
+                c.mn[k] = m.x; c.mn[k + 1] = m.y; c.mn[k + 2] = m.z; c.mn[k + 3] = m.w;
+                c.inv[k] = s.x; c.inv[k + 1] = s.y; c.inv[k + 2] = s.z; c.inv[k + 3] = s.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < NC; k++) {
+                const int j = min(col0 + k, D - 1);
+                c.mn[k] = mn[j];
+                c.inv[k] = inv[j];
+            }
         }
     }
     // q = clamp(rne((x - min) * inv), 0, L); sub, mul, round are separate fp32
@@ -244,7 +259,7 @@ struct LogCoder {
     // level l lies near a*log2|x| + b; a = 0: the range is too narrow or too extreme for that
     float a, b;
     template <int NC> struct Ctx { const float *edges; };
-    template <int NC>
+    template <bool VEC, int NC>
     __device__ void prepare(Ctx<NC> &c, int, int) const { c.edges = nullptr; }
     // l = #{i : |x| >= T_i}: the level the hardware's logarithm gives, put right against the edges
     // on both sides of it.  With a <= 1024 and magnitudes whose logarithm is no denormal's, the
@@ -299,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
     if (t >= rows_per_pass * (uint32_t)GW) return;
     const int g = (int)(t % (uint32_t)GW);
     const int col0 = NC * g;
-    coder.prepare(ctx, col0, D);
+    coder.template prepare<VEC>(ctx, col0, D);
     if constexpr (Coder::kEdges) ctx.edges = s_edges;
     typename Src::Ctx sctx;
     src.prepare(sctx, col0, D);
@@ -332,7 +347,7 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
 #pragma unroll
             for (int k = 0; k < CPW; k++) {
                 const int j = n * CPW + k;
-                const uint32_t q = (col0 + j < D) ? coder.code(ctx, v[j], j) : 0u;
+                const uint32_t q = (VEC ? col0 < D : col0 + j < D) ? coder.code(ctx, v[j], j) : 0u;
                 word[n] |= q << (BITS * k);
             }
         }
@@ -352,7 +367,9 @@ template <class Src, typename Coder>
 inline void launch_sq(const Src &src, int64_t rows, int D, int64_t rb, int bits, Coder coder,
                       uint8_t *codes, bool vec, hipStream_t s) {
     bool vec8 = false;
-    if constexpr (kHalfChunk<Src>) vec8 = vec && D % 8 == 0 && (uintptr_t)src.x % 16 == 0;
+    // (8-bit uniform codes, whose stores then take 8 bytes a lane: 1.6 GB 476 us by 4 columns, 505 by 8)
+    if constexpr (kHalfChunk<Src>)
+        vec8 = vec && D % 8 == 0 && (uintptr_t)src.x % 16 == 0 && (bits < 8 || Coder::kEdges);
     const int GW = (int)(8 * rb / ((vec8 ? 8 : 4) * bits));
     int64_t want = (rows * GW + 1) / 2;
     if (want < GW) want = GW;
