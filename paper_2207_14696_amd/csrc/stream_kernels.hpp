@@ -242,7 +242,7 @@ struct UniformCoder {
     }
     // q = clamp(rne((x - min) * inv), 0, L); sub, mul, round are separate fp32
     // operations; max/min discard NaN, so NaN -> 0
-    template <int NC>
+    template <int BITS, int NC>
     __device__ uint32_t code(const Ctx<NC> &c, float x, int k) const {
         float d = __fsub_rn(x, c.mn[k]);
         float t = __fmul_rn(d, c.inv[k]);
@@ -268,11 +268,15 @@ struct LogCoder {
     // edges (in LDS): [-1, T_1 .. T_{H-1}, NaN]; a NaN takes level 0 both ways.
     // 524 288 x 768 half-precision values to 4 bits: 257 us, bisection 374; 262 144 x 768 to 8 bits:
     // 129 us, bisection 361.
-    template <int NC>
+    // (a single edge, 2 bits, is a comparison: 105 us for 1 M x 128 floats, by the logarithm 110)
+    template <int BITS, int NC>
     __device__ uint32_t code(const Ctx<NC> &c, float x, int) const {
+        constexpr int H = 1 << (BITS - 1);
         float m = fabsf(x);
         int lo = 0;
-        if (a > 0.0f) {
+        if constexpr (BITS <= 2) {
+            if (BITS == 2 && m >= c.edges[1]) lo = 1;
+        } else if (a > 0.0f) {
             const int l = (int)fmaf(__builtin_amdgcn_logf(m), a, b);
             lo = min(max(l, 0), H - 1);
             const float below = c.edges[lo], above = c.edges[lo + 1];
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
 #pragma unroll
             for (int k = 0; k < CPW; k++) {
                 const int j = n * CPW + k;
-                const uint32_t q = (VEC ? col0 < D : col0 + j < D) ? coder.code(ctx, v[j], j) : 0u;
+                const uint32_t q = (VEC ? col0 < D : col0 + j < D) ? coder.template code<BITS>(ctx, v[j], j) : 0u;
                 word[n] |= q << (BITS * k);
             }
         }
@@ -451,8 +455,7 @@ inline hipError_t launch_quantize_sq_src(bifeat_params *p, const Src &src, int64
     } else {
         const int H = 1 << (p->scheme.bits - 1);
         const double a = H / (p->e_max - p->e_min);  // levels per factor of two
-        // (2-bit codes have a single edge: one comparison, 105 us for 1 M x 128 floats against 110)
-        const bool near = H > 2 && a <= 1024.0 && p->e_min >= -120.0 && p->e_max <= 127.0;  // (not NaN, not inf)
+        const bool near = a <= 1024.0 && p->e_min >= -120.0 && p->e_max <= 127.0;  // (not NaN, not inf)
         LogCoder c{p->d_T, H, near ? (float)a : 0.0f, near ? (float)(-a * p->e_min) : 0.0f};
         launch_sq(src, rows, D, p->rb, p->scheme.bits, c, codes_row0, vec, s);
     }
