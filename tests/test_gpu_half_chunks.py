@@ -74,3 +74,17 @@ def test_log_levels_at_their_edges(bits, e_min, e_max):
     want = orc.pack(orc.log_encode(x, bits, T), bits)
     bad = codes.cpu().numpy() != want
     assert not bad.any(), np.nonzero(bad.any(1))[0][:5]
+
+
+@pytest.mark.parametrize("D,rows", [(8192, 37), (8200, 37), (9000, 300)])
+def test_wide_half_chunks(D, rows):
+    # either side of the columns whose range is merged in LDS
+    import torch
+    import paper_2207_14696_amd as bf
+    x = (np.random.default_rng(D).normal(size=(rows, D)) * 2).astype(np.float16)
+    q = bf.Quantizer(scheme_of("uniform", 4), D)
+    q.fit_update(torch.from_numpy(x).cuda())
+    q.fit_finalize()
+    mn, mx = orc.fit_minmax(x.astype(np.float32))
+    for got, ref in zip(q.params_get_uniform(), (mn, mx)):
+        assert np.array_equal(got, ref)
