@@ -84,26 +84,29 @@ __device__ inline void merge_magnitudes(uint32_t mmin, uint32_t mmax, int32_t *s
 
 // per-column min / max of the rows [0, rows) of `src` merged into the running state.
 // VEC = 4 needs D % 4 == 0 (and, for a chunk in memory, 16-byte / 8-byte alignment), VEC = 8 (half
-// precision in memory) D % 8 == 0 and 16 bytes.
-template <class Src, int VEC>
-__global__ __launch_bounds__(kFitThreads) void fit_minmax_kernel(Src src, int64_t rows, int D, int G,
-                                                             int32_t *state, int use_lds) {
+// precision in memory) D % 8 == 0 and 16 bytes.  TH: threads of a workgroup, see the launcher.
+template <class Src, int VEC, int TH>
+__global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, int D, int G, int32_t *state,
+                                                        int use_lds) {
     extern __shared__ int32_t lds[];
     if (use_lds) {
-        for (int i = threadIdx.x; i < D; i += kFitThreads) {
+        for (int i = threadIdx.x; i < D; i += TH) {
             lds[i] = kKeyPosInf;
             lds[D + i] = kKeyNegInf;
         }
         __syncthreads();
     }
-    // A workgroup streams one contiguous piece of the chunk: kFitThreads/G whole rows per
+    // A workgroup streams one contiguous piece of the chunk: TH/G whole rows per
     // iteration when a row's G column groups fit a workgroup (a wave's lanes then read
-    // consecutive 16 bytes), else groups of G threads across the grid walk consecutive rows.
-    const bool by_block = G <= kFitThreads;
-    const int rpi = by_block ? kFitThreads / G : 0;  // rows per iteration of a workgroup
-    const uint32_t total = gridDim.x * kFitThreads;
+    // consecutive 16 bytes), else groups of G threads across the grid walk consecutive rows - also
+    // where single columns would leave more than a quarter of the workgroup idle (601 half-precision
+    // columns, 700 000 rows: 176 us so, 223 with one row per workgroup of 1024), and wider groups two
+    // fifths (204 400 rows of 2052 floats 278 us, 300; but 4 194 of 3000 12.1, 10.1).
+    const bool by_block = G <= TH && TH % G <= (VEC > 1 ? 2 * TH / 5 : TH / 4);
+    const int rpi = by_block ? TH / G : 0;  // rows per iteration of a workgroup
+    const uint32_t total = gridDim.x * TH;
     const uint32_t rows_per_pass = total / (uint32_t)G;
-    const uint32_t t = blockIdx.x * kFitThreads + threadIdx.x;
+    const uint32_t t = blockIdx.x * TH + threadIdx.x;
     const bool active = by_block ? (int)threadIdx.x < rpi * G : t < rows_per_pass * (uint32_t)G;
     if (active) {
         const int g = by_block ? (int)threadIdx.x % G : (int)(t % (uint32_t)G);
@@ -145,14 +148,27 @@ __global__ __launch_bounds__(kFitThreads) void fit_minmax_kernel(Src src, int64_
                 mx[k] = fmaxf(mx[k], v[k]);
             }
         }
+        // one or two column groups: the lanes of a wave that share one merge first (the same few
+        // words of LDS for all of a workgroup's atomics: 3 M rows of 4 half-precision columns 17 us, 9 so)
+        bool merged = false;
+        if (by_block && G <= 2) {
+            for (int m = 32; m >= G; m >>= 1) {
+#pragma unroll
+                for (int k = 0; k < VEC; k++) {
+                    mn[k] = fminf(mn[k], __shfl_xor(mn[k], m));
+                    mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], m));
+                }
+            }
+            merged = (int)(threadIdx.x & 63) >= G;
+        }
         // (two loops: through one pointer to either the atomics would be flat ones)
-        if (use_lds) {
+        if (!merged && use_lds) {
 #pragma unroll
             for (int k = 0; k < VEC; k++) {
                 atomicMin(&lds[g * VEC + k], float_key(mn[k]));
                 atomicMax(&lds[D + g * VEC + k], float_key(mx[k]));
             }
-        } else {
+        } else if (!merged) {
 #pragma unroll
             for (int k = 0; k < VEC; k++) {
                 atomicMin(&state[g * VEC + k], float_key(mn[k]));
@@ -165,7 +181,7 @@ __global__ __launch_bounds__(kFitThreads) void fit_minmax_kernel(Src src, int64_
         // thousands of workgroups would hammer the same 2*D words: only those that improve
         // on the value already there (read without ordering: a stale read merely costs one
         // atomic that changes nothing) issue the atomic
-        for (int i = threadIdx.x; i < D; i += kFitThreads) {
+        for (int i = threadIdx.x; i < D; i += TH) {
             const int32_t lo_k = lds[i], hi_k = lds[D + i];
             if (lo_k < __builtin_nontemporal_load(&state[i])) atomicMin(&state[i], lo_k);
             if (hi_k > __builtin_nontemporal_load(&state[D + i])) atomicMax(&state[D + i], hi_k);
@@ -409,24 +425,37 @@ inline hipError_t launch_fit_minmax_src(bifeat_params *p, const Src &src, int64_
     const int D = (int)p->D;
     const int use_lds = D <= 8192;
     // (columns merged without LDS, an atomic per thread and column: twice as many of them by 8 columns,
-    // 5 242 rows of 20 000 half-precision columns 63 us, 185 by 8)
+    // 5 242 rows of 20 000 half-precision columns 63 us, 185 by 8; few columns, merged in few words of
+    // LDS: 524 288 rows of 24 6.4 us, 8.9 by 8)
     bool vec8 = false;
-    if constexpr (kHalfChunk<Src>) vec8 = use_lds && vec && D % 8 == 0 && (uintptr_t)src.x % 16 == 0;
+    if constexpr (kHalfChunk<Src>)
+        vec8 = use_lds && D >= 64 && vec && D % 8 == 0 && (uintptr_t)src.x % 16 == 0;
     const int VEC = vec8 ? 8 : vec ? 4 : 1;
     const int G = (D + VEC - 1) / VEC;
     int64_t want = (rows * G + 7) / 8;  // about 8 rows per thread
     if (want < G) want = G;
-    int blocks = fit_blocks(want);
-    if ((int64_t)blocks * kFitThreads < G) blocks = (G + kFitThreads - 1) / kFitThreads;
+    // few large workgroups for the sake of their merge (see above), but not where there is none, nor,
+    // with few columns to merge, for chunks that would occupy a fraction of the CUs (300 x 768 half-
+    // precision 6.5 us, 4.9 so; 300 x 4096 floats 4.9, 7.3 with small ones)
+    const bool large = use_lds && (want >= kThreads * 256 || G > kThreads);
+    const int threads = large ? kFitThreads : kThreads;
+    int blocks = large ? fit_blocks(want) : blocks_for(want);
+    if ((int64_t)blocks * threads < G) blocks = (G + threads - 1) / threads;
     const size_t shm = use_lds ? sizeof(int32_t) * 2 * (size_t)D : 0;
+#define BF_FM(V)                                                                                               \
+    do {                                                                                                       \
+        if (large) fit_minmax_kernel<Src, V, kFitThreads><<<blocks, threads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds); \
+        else fit_minmax_kernel<Src, V, kThreads><<<blocks, threads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds); \
+    } while (0)
     if constexpr (kHalfChunk<Src>) {
         if (vec8) {
-            fit_minmax_kernel<Src, 8><<<blocks, kFitThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
+            BF_FM(8);
             return hipGetLastError();
         }
     }
-    if (vec) fit_minmax_kernel<Src, 4><<<blocks, kFitThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
-    else fit_minmax_kernel<Src, 1><<<blocks, kFitThreads, shm, s>>>(src, rows, D, G, p->d_fit, use_lds);
+    if (vec) BF_FM(4);
+    else BF_FM(1);
+#undef BF_FM
     return hipGetLastError();
 }
 
