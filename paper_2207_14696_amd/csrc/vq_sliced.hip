@@ -645,17 +645,26 @@ bool launch_gather_dequant_vq_sliced(bifeat_params *p, const uint8_t *codes, con
 }
 
 // The sliced mean is two launches with the requested codes through the workspace in between; the
-// general kernel is one, and fetches 4 D bytes per list entry from L2 in pieces of an entry's
-// 16..64 bytes, 6 TB/s of them at best.  8 x 2048 x 16 (slices of 64 bytes a row): 23 000 list
-// entries 7.5 against 12.4 us, 201 000 (103 MB) 15.4 against 20.7, 852 000 (436 MB) 69 against 55.
-// 96 x 256 x 8 (slices of 256 bytes): 5 900 entries (18 MB) 8.0 against 13, 50 900 (156 MB) 25
-// against 19.  16 x 2048 x 16: 207 MB 28 against 30.  So the line lies lower where the slices are
-// wide enough for whole lines of output.
+// general kernel is one, and fetches 4 D bytes per list entry in pieces of an entry's 4 w bytes, at
+// 7 TB/s where they come from L2.  Sliced against that, us, at so many bytes of looked-up entries:
+//   entries of 64 bytes and more   8 x 2048 x 16: 16 MB 11.3 / 6.9, 128 MB 20.8 / 16.9, 256 MB 30 / 29
+//                                  48 x 256 x 16: 128 MB 14.9 / 13.4, 192 MB 14.5 / 17.9
+//   32 bytes                       96 x 256 x 8: 16 MB 9.9 / 6.7, 48 MB 10.8 / 10.1, 64 MB 10.5 / 12.2
+//   16 bytes                       32 x 256 x 4: 16 MB 10.4 / 7.1, 32 MB 11.3 / 10.7, 64 MB 14.0 / 17.4
+//   codebooks an XCD's 4 MB of L2 does not hold with the rest: 48 x 2048 x 16 (6.3 MB), 32 MB
+//                                  11.4 / 9.0, 48 MB 11.4 / 11.1, 128 MB 19.1 / 22.1
+// And only under the caller's bound on the list lengths: a lane group walks a list four entries a
+// step, code after row id after entry, and one list of 10 000 entries among short ones takes 2.1 ms
+// where the sliced kernels need 0.73 (32 x 2048 x 16).  Lists of 60: 30 - 60 % faster than sliced.
 bool vq_mean_from_l2(const bifeat_params *p, const MeanCall &c, int *over_len) {
     const VqGeom g = vq_geometry(p);
     if (!g.ok || (uintptr_t)c.out % 16 || p->payload / 16 > 64) return false;
-    *over_len = c.max_degree > 0 && c.max_degree <= kRun ? kRun : 0;  // as the sliced kernels have it
-    return c.E <= (((int64_t)(g.LPS < 16 ? 192 : 64) << 20) / (4 * p->D));
+    if (c.max_degree <= 0 || c.max_degree > 64) return false;
+    *over_len = c.max_degree <= kRun ? kRun : 0;  // as the sliced kernels have it
+    const int w = p->scheme.vq_width;
+    const int64_t book = (int64_t)p->P * p->scheme.vq_length * w * 4;
+    const int64_t mb = w >= 16 ? (book <= (3 << 20) ? 128 : 48) : w >= 8 ? 48 : 24;
+    return c.E <= (mb << 20) / (4 * p->D);
 }
 
 // With the caller's bound on the list lengths at most kRun, the long-list pass is not

@@ -189,6 +189,7 @@ def test_vector_code_workspace_reserve_growth_and_capture(bf, torch):
     small = block(300)
     out_small = torch.empty((300, 64), device="cuda")
     q.set_option("mean_max_degree", 9)
+    q.set_option("vq_sliced", 2)  # (by itself a bounded call this small needs no workspace)
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
         q.gather_mean(dcodes, small[2], small[3], out_small)          # sizes the workspace
