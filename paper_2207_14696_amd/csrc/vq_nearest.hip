@@ -14,7 +14,9 @@
 // the errors of both evaluations together (derived at vq_margin and vq_cell_margin below); a row
 // for which it is not - near ties, values outside the range the split holds - is searched by the
 // rule over the whole codebook, by the wave together, or lane by lane when many rows of a wave
-// need it.  The codes are therefore the same as the plain search gives, for any input.
+// need it; where most rows do, the scores are left out (search_costs below: at no share of such
+// rows is that dearer than the plain search by more than a tenth).  The codes are therefore the
+// same as the plain search gives, for any input.
 //
 // What bounds it: vector instructions - of ~570 per 64 rows and part 272 are the running minima
 // over 256 entries, 133 the scores inside the cell, 59 the split of x - at 75 % of the issue rate,
@@ -47,7 +49,8 @@ struct VqNearestArgs {
     const T *x;             // [rows x D]
     int64_t rows;
     int D, w, len, P, cbytes;
-    int vec;                // 4 columns of a part can be loaded at once
+    int vec, bvec;          // 4 columns of a part, of an entry can be loaded at once
+    int lane_rows, plain_rows;  // see search_costs
     int NT;                 // tiles of 32 entries, a whole number of pairs: a cell spans two
     int ny;                 // workgroups per part
     const float *rnorm;     // [P][len], cosine metric
@@ -63,10 +66,8 @@ struct VqNearestArgs {
 constexpr int kNearestMinBook = 512;
 constexpr int kNearestMaxWidth = 32;
 constexpr int kCuLds = 160 * 1024;
-// rows of a wave that need the whole codebook searched by the rule: from this many on every lane
-// searches for its own row (one pass over the codebook for all), below it the wave works on one
-// row at a time with its lanes sharing the codebook
-constexpr int kLaneSearch = 24;
+// strips that a wave searches by the rule once its rows tie, before it tries the scores again
+constexpr int kPlainStrips = 7;
 
 constexpr float kPadScore = 1e30f;   // score of the entries that fill up the last tile
 constexpr int kScaleExp = 11;        // largest magnitude of a part's codebook: [2^10, 2^11)
@@ -76,25 +77,30 @@ constexpr float kMaxNorm2 = 1073741824.0f;  // rows with a scaled |x|^2 of 2^30 
 // NaN wins, which the caller's comparison with the margin then sees.
 __device__ inline float minimum(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 
+// The rule, column by column.
+template <int METRIC>
+__device__ inline float rule_step(float acc, float x, float c) {
+    if constexpr (METRIC == BIFEAT_VQ_COSINE) return __fadd_rn(acc, __fmul_rn(x, c));
+    const float diff = __fsub_rn(x, c);
+    return __fadd_rn(acc, __fmul_rn(diff, diff));
+}
+
 // One row's distance to one entry by the rule (smaller = better; cosine: the negated score).
 template <int WP, int METRIC>
 __device__ inline float rule_value(const float (&x)[WP], const float (&c)[WP], float rn) {
     float acc = 0.0f;
 #pragma unroll
-    for (int d = 0; d < WP; d++) {
-        if constexpr (METRIC == BIFEAT_VQ_COSINE) {
-            acc = __fadd_rn(acc, __fmul_rn(x[d], c[d]));
-        } else {
-            const float diff = __fsub_rn(x[d], c[d]);
-            acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-        }
-    }
+    for (int d = 0; d < WP; d++) acc = rule_step<METRIC>(acc, x[d], c[d]);
     if constexpr (METRIC == BIFEAT_VQ_COSINE) return -__fmul_rn(acc, rn);
     else return acc;
 }
 
+// waves of a SIMD, workgroups of a CU with a copy of the entries in LDS (9 to 16 columns: with 2 waves
+// the whole search by the rule, 48 x 256 x 16, took 846 us instead of 770, the scores 181 instead of 166)
+constexpr int nearest_waves(int G, bool ent) { return G == 1 ? 4 : G == 2 && ent ? 3 : 2; }
+
 template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
-__global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_kernel(
+__global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nearest_kernel(
     VqNearestArgs<T> a, const float *__restrict__ cb, uint8_t *__restrict__ codes) {
     constexpr int WP = 8 * G;          // columns of a part, padded with zeros
     constexpr int TH = ENT ? 256 : 512;
@@ -210,19 +216,30 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             rn = COS ? s_rn[e] : 0.0f;
         } else {
             const float *src = part_cb + (int64_t)e * w;
+            if (a.bvec) {
 #pragma unroll
-            for (int d = 0; d < WP; d++) c[d] = d < w ? src[d] : 0.0f;
+                for (int k = 0; k < WP / 4; k++) {
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (4 * k < w) v = reinterpret_cast<const float4 *>(src)[k];
+                    c[4 * k] = v.x; c[4 * k + 1] = v.y; c[4 * k + 2] = v.z; c[4 * k + 3] = v.w;
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < WP; d++) c[d] = d < w ? src[d] : 0.0f;
+            }
             rn = COS ? part_rn[e] : 0.0f;
         }
     };
 
     float dsum = 0.0f;
-    // Rows whose entries tie (0/1 features) are open more often than not.  When a quarter of a
-    // workgroup's first strip is, the workgroup searches those and all of its other strips by the
-    // rule, every lane for its own row, the entries read from LDS (a codebook without a copy
-    // there takes the place of the pieces: 32 x 8G floats are as large as a tile's pieces).
-    // Every wave of the workgroup walks the same strips.
+    // Rows whose entries tie (0/1 features) are open more often than not; from a share on where the
+    // scores and the rows searched one by one cost more than all rows by the rule, each lane for its
+    // own, they are searched that way.  The entries for that come from LDS.  With a copy of them there
+    // a wave decides for itself, and tries the scores again every so many strips.  Without one they
+    // take the place of the pieces (32 x 8G floats are as large as a tile's pieces), so the workgroup
+    // decides, now and then, and for good; every wave of it walks the same strips.
     bool plain = false;
+    int plain_left = 0;
     const float *s_plain = reinterpret_cast<const float *>(s_frag);
     auto plain_book = [&](int e) {  // entries e .. e + 3, e a multiple of 4
         return ENT ? s_ent + (e >> 6) * PAIR + ((e >> 2) & 15) * CELL : s_plain + e * WP;
@@ -244,6 +261,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
         }
     };
     float xn[WP];
+    [[maybe_unused]] int strip = 0;
     load_row((int64_t)by * ROWS + wave * 64 + lane, xn);
     for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += (int64_t)a.ny * ROWS) {
         // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which both halves of
@@ -258,28 +276,55 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
         int all_code = 0;
         float all_value = INFINITY;
         auto search_all = [&]() {
-            // four entries at a time from one address (those past the last one are in bounds and not used)
-            for (int e0 = 0; e0 < len; e0 += 4) {
-                const float *src = plain_book(e0);
-                float4 q[4][WP / 4];
+            // EP entries at a time, each read by all lanes from one address, the next ones while
+            // these are evaluated (those past the last one are in bounds and not used)
+            constexpr int EP = WP <= 16 ? 4 : 2;
+            float4 q[2][EP][WP / 4];
+            auto read = [&](float4 (&to)[EP][WP / 4], int e0) {
+                const float *src = plain_book(e0 & ~3) + (EP < 4 ? (e0 & 3) * WP : 0);
 #pragma unroll
-                for (int k = 0; k < 4; k++)
+                for (int k = 0; k < EP; k++)
 #pragma unroll
-                    for (int i = 0; i < WP / 4; i++) q[k][i] = reinterpret_cast<const float4 *>(src + k * WP)[i];
+                    for (int i = 0; i < WP / 4; i++) to[k][i] = reinterpret_cast<const float4 *>(src + k * WP)[i];
+            };
+            // (the entries' sums side by side: with two waves a SIMD nothing else hides an addition)
+            auto take = [&](const float4 (&of)[EP][WP / 4], int e0, int n) {
+                float v[EP];
 #pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    if (e0 + k >= len) break;
-                    float c[WP];
+                for (int k = 0; k < EP; k++) v[k] = 0.0f;
 #pragma unroll
-                    for (int i = 0; i < WP / 4; i++) {
-                        c[4 * i] = q[k][i].x; c[4 * i + 1] = q[k][i].y; c[4 * i + 2] = q[k][i].z; c[4 * i + 3] = q[k][i].w;
+                for (int i = 0; i < WP / 4; i++)
+#pragma unroll
+                    for (int k = 0; k < EP; k++) {
+                        v[k] = rule_step<METRIC>(v[k], xr[4 * i], of[k][i].x);
+                        v[k] = rule_step<METRIC>(v[k], xr[4 * i + 1], of[k][i].y);
+                        v[k] = rule_step<METRIC>(v[k], xr[4 * i + 2], of[k][i].z);
+                        v[k] = rule_step<METRIC>(v[k], xr[4 * i + 3], of[k][i].w);
                     }
-                    const float v = rule_value<WP, METRIC>(xr, c, COS ? (ENT ? s_rn[e0 + k] : part_rn[e0 + k]) : 0.0f);
-                    if (v < all_value) { all_value = v; all_code = e0 + k; }
+#pragma unroll
+                for (int k = 0; k < EP; k++) {
+                    if (k >= n) break;
+                    if constexpr (COS) v[k] = -__fmul_rn(v[k], ENT ? s_rn[e0 + k] : part_rn[e0 + k]);
+                    if (v[k] < all_value) { all_value = v[k]; all_code = e0 + k; }
                 }
+            };
+            const int last = a.NT * 32 - EP;
+            int e0 = 0;
+            read(q[0], 0);
+            for (; e0 + 2 * EP <= len; e0 += 2 * EP) {
+                read(q[1], e0 + EP);
+                take(q[0], e0, EP);
+                read(q[0], min(e0 + 2 * EP, last));
+                take(q[1], e0 + EP, EP);
+            }
+            if (e0 < len) take(q[0], e0, len - e0);
+            if (e0 + EP < len) {
+                read(q[1], e0 + EP);
+                take(q[1], e0 + EP, len - e0 - EP);
             }
         };
-        if (plain) {
+        if (plain || plain_left > 0) {
+            plain_left--;
             load_row(r + (int64_t)a.ny * ROWS, xn);
             search_all();
             code = all_code;
@@ -483,9 +528,15 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
             open = false;
             code = 0;
         }
-        if (r0 == (int64_t)by * ROWS && __syncthreads_count(open && valid) > TH / 4) {
-            plain = true;
-            if constexpr (!ENT) {  // (the barrier above: no wave reads the pieces any more)
+        uint64_t todo = __ballot(open && valid);
+        if constexpr (ENT) {
+            if (__popcll(todo) > a.plain_rows) plain_left = kPlainStrips;
+        } else {
+            // (strips 0, 1 and 3, then every eighth)
+            const bool look = strip < 4 ? strip != 2 : (strip & 7) == 7;
+            strip++;
+            if (look && __syncthreads_count(open && valid) > a.plain_rows * WAVES) {
+                plain = true;  // (the barrier: no wave reads the pieces any more)
                 float *dst = reinterpret_cast<float *>(s_frag);
                 for (int i = threadIdx.x; i < len * WP; i += TH) {
                     const int e = i / WP, d = i - e * WP;
@@ -494,47 +545,50 @@ __global__ __launch_bounds__(ENT ? 256 : 512, G == 1 ? 4 : 2) void vq_nearest_ke
                 __syncthreads();
             }
         }
-        uint64_t todo = __ballot(open && valid);
         if (todo) {
-            if (plain) {
+            if ((ENT || plain) && __popcll(todo) >= a.lane_rows) {
                 search_all();
                 if (open) { code = all_code; value = all_value; }
-            } else if (__popcll(todo) >= kLaneSearch) {
-                int bc = 0;
-                float bv = INFINITY;
-#pragma unroll 4
-                for (int e = 0; e < len; e++) {
-                    float c[WP], rn;
-                    entry(e, c, rn);
-                    const float v = rule_value<WP, METRIC>(xr, c, rn);
-                    if (v < bv) { bv = v; bc = e; }
-                }
-                if (open) { code = bc; value = bv; }
             } else {
+                // two rows at a time, which halves the fetches of entries and has two reductions side by
+                // side, where there are registers for it (8 columns, entries in LDS, 4 waves a SIMD: the
+                // scores would lose 3 %)
+                constexpr int NR = WP == 16 || (WP == 8 && !ENT) ? 2 : 1;
                 while (todo) {
-                    const int j = __ffsll((unsigned long long)todo) - 1;
-                    todo &= todo - 1;
-                    float xj[WP];
+                    int j[NR];
+                    float xj[NR][WP], bv[NR];
+                    int bc[NR];
 #pragma unroll
-                    for (int d = 0; d < WP; d++)
-                        xj[d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xr[d]), j));
-                    int bc = 0x7FFFFFFF;
-                    float bv = INFINITY;
+                    for (int n = 0; n < NR; n++) {
+                        j[n] = todo ? __ffsll((unsigned long long)todo) - 1 : j[0];
+                        todo &= todo - 1;
+#pragma unroll
+                        for (int d = 0; d < WP; d++)
+                            xj[n][d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xr[d]), j[n]));
+                        bv[n] = INFINITY;
+                        bc[n] = 0x7FFFFFFF;
+                    }
                     for (int e = lane; e < len; e += 64) {
                         float c[WP], rn;
                         entry(e, c, rn);
-                        const float v = rule_value<WP, METRIC>(xj, c, rn);
-                        if (v < bv) { bv = v; bc = e; }
+#pragma unroll
+                        for (int n = 0; n < NR; n++) {
+                            const float v = rule_value<WP, METRIC>(xj[n], c, rn);
+                            if (v < bv[n]) { bv[n] = v; bc[n] = e; }
+                        }
                     }
 #pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) {
-                        const float ov = __shfl_xor(bv, o);
-                        const int oc = __shfl_xor(bc, o);
-                        if (ov < bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
-                    }
-                    if (lane == j) {
-                        code = bc == 0x7FFFFFFF ? 0 : bc;
-                        value = bv;
+                    for (int n = 0; n < NR; n++) {
+#pragma unroll
+                        for (int o = 32; o > 0; o >>= 1) {
+                            const float ov = __shfl_xor(bv[n], o);
+                            const int oc = __shfl_xor(bc[n], o);
+                            if (ov < bv[n] || (ov == bv[n] && oc < bc[n])) { bv[n] = ov; bc[n] = oc; }
+                        }
+                        if (lane == j[n]) {
+                            code = bc[n] == 0x7FFFFFFF ? 0 : bc[n];
+                            value = bv[n];
+                        }
                     }
                 }
             }
@@ -634,8 +688,25 @@ size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) 
 // entries from L2.
 bool entries_in_lds(const bifeat_params *p, bool train) {
     const int G = (p->scheme.vq_width + 7) / 8, tiles = (p->scheme.vq_length + 63) / 64 * 2;
-    const int64_t limit = train ? kCuLds - 1024 : kCuLds / (G == 1 ? 4 : G == 2 ? 3 : 2);
+    const int64_t limit = train ? kCuLds - 1024 : kCuLds / nearest_waves(G, true);
     return (int64_t)nearest_lds(p, G, tiles, true, train) <= limit;
+}
+
+// Rows of a wave that the scores leave open are searched by the rule two at a time, the lanes sharing
+// the codebook, or, from `lane_rows` of 64 on, all in one pass over it; and from `plain_rows` on the
+// scores do not pay at all.  The costs in vector instructions, from times at shares of open rows
+// between 0 and 1 (65 536 rows; us with none open, per share of 1, all by the rule):
+//   96 x 256 x 8  193, 1930, 748      48 x 256 x 16  181, 2120, 846     24 x 64 x 32  112, 884, 262
+//   without the entries in LDS: 8 x 2048 x 16  214, 2280, 969   32 x 2048 x 8  424, 5040, 2127
+//   2 x 1000 x 32  134, 1960, 300     10 x 1000 x 13  204, 4430, 700
+template <typename T>
+void search_costs(VqNearestArgs<T> &a, int G, bool ent) {
+    const double entry = 3.0 * 8 * G + 3.0, all = a.len * entry;
+    const double apart = ent ? (G == 1 ? 1.1 : 1.7) : G <= 2 && a.bvec ? 2.2 : 6.0;  // each lane its own entry
+    const double one = (a.len + 63) / 64 * entry * apart + 170.0;
+    const double scores = 5.5 * a.len * G + 400.0;
+    a.lane_rows = (int)std::min(64.0, all / one);
+    a.plain_rows = (int)std::max(1.0, std::min(60.0, (all - scores) / one));
 }
 
 template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
@@ -653,7 +724,7 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
     // workgroups: four times what the chip holds at once, a little less rather than a little more
     // (staging the codebook is about as long as one strip, so a workgroup should have many); in
     // training, where each also adds its sums to memory, as many as the chip holds
-    const int64_t resident = 256 * std::min<int64_t>(ENT ? (G == 1 ? 4 : 2) : 1, kCuLds / (int64_t)lds);
+    const int64_t resident = 256 * std::min<int64_t>(ENT ? nearest_waves(G, true) : 1, kCuLds / (int64_t)lds);
     // (without a copy of the entries: the codebook is large, and once is enough there too)
     int64_t ny = (TRAIN || !ENT ? 1 : 4) * resident / a.P;
     if (ny < 1) ny = 1;
@@ -671,6 +742,7 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         a.counts = (uint32_t *)(a.sums + ny * books);
     }
     a.ny = (int)ny;
+    search_costs(a, G, ENT);
     const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
     kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
     if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.ny, s);
@@ -716,6 +788,7 @@ bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, 
     a.len = len;
     a.P = p->P;
     a.cbytes = p->cbytes;
+    a.bvec = w % 4 == 0;
     a.vec = w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
     a.rnorm = p->d_rnorm;
     a.rb = rb;

@@ -133,3 +133,50 @@ def test_rounds_of_training_agree_with_the_oracle(bf, torch):
     _, want = orc.vq_train(x, 8, 200, iters=10)
     np.testing.assert_allclose(q.vq_distortion(10)[:3], want[:3], rtol=1e-5)
     assert np.all(np.diff(q.vq_distortion(10)) <= 1e-6 * want[0])
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("P,w,length,rows", [(8, 8, 65, 700), (8, 8, 71, 700), (3, 16, 255, 900), (3, 12, 259, 900),
+                                             (2, 24, 130, 500), (2, 32, 67, 500), (8, 16, 2047, 9000), (8, 8, 2045, 9000),
+                                             (2, 13, 1001, 3000), (2, 32, 1003, 3000)])
+@pytest.mark.parametrize("share", [0.2, 0.5, 1.0])
+def test_rows_that_the_scores_cannot_decide(bf, torch, P, w, length, rows, metric, share):
+    # rows far outside the codebook (cosine: beyond what the scores are trusted with): one by one, by
+    # lanes and by whole workgroups, over entries of every remainder; the first and last rows ordinary
+    rng = np.random.default_rng(P * 100 + w + length)
+    cb = _codebook(rng, P * w, w, length)
+    x = rng.normal(size=(rows, P * w)).astype(np.float32)
+    x[rng.random(rows) < share] *= np.float32(1e18)
+    x[:60], x[-40:] = rng.normal(size=(60, P * w)), rng.normal(size=(40, P * w))
+    _check(bf, torch, x, cb, P * w, w, length, metric)
+
+
+@pytest.mark.parametrize("P,w,length", [(8, 16, 2048), (32, 8, 2048), (48, 16, 256), (96, 8, 256)])
+def test_a_share_of_open_rows_costs_no_more_than_all(bf, torch, P, w, length):
+    # 30 % of the rows open, spread or in the later half only, where the first strips do not show them:
+    # no dearer than the search by the rule for all rows
+    rows = 131072
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P)
+    x = torch.randn(rows, P * w, generator=g, device="cuda")
+    q = bf.Quantizer(scheme_of("vq", 8, w, length), P * w)
+    q.params_set_codebooks(torch.randn(P, length, w, generator=g, device="cuda").cpu().numpy())
+    codes = torch.empty((rows, q.row_bytes), dtype=torch.uint8, device="cuda")
+    spread = torch.randperm(rows, generator=g, device="cuda") < rows * 3 // 10
+    late = torch.arange(rows, device="cuda") >= rows * 7 // 10
+
+    def us(open_rows):
+        y = torch.where(open_rows[:, None], x * 1e20, x)
+        q.quantize(y, codes, 0)
+        best = 1e9
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            q.quantize(y, codes, 0)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        return best
+    everything = us(torch.ones_like(late))
+    for name, rows_ in (("spread", spread), ("late", late)):
+        assert us(rows_) <= 1.25 * everything, (name, us(rows_), everything)
