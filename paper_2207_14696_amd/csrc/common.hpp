@@ -68,7 +68,7 @@ struct bifeat_params {
     int opt_mean_lean = 1;        // 0: never use the short-list kernel
     int opt_mean_max_degree = 0;  // caller's promise: no neighbour list is longer (0 = unknown)
     int opt_vq_iters = 10;        // Lloyd rounds per training chunk
-    int opt_vq_sliced = 1;        // 0: vector codes decode from L2 instead of LDS-resident slices; 2: never
+    int opt_vq_sliced = 1;        // 0: vector codes decode from L2, not from LDS-resident slices; 2: never from L2
     int opt_dequant_flat = 0;  // 1: gather_dequant without the LDS-staged tile kernel
     int opt_mean_generic = 0;  // 1: route uniform tables through the float-accumulate kernel
     int opt_validate = 0;      // 1: check indices / list bounds on the GPU before every gather (synchronises)
@@ -131,6 +131,7 @@ size_t vq_gather_scratch_bytes(const bifeat_params *p, int64_t M);
 size_t static_scratch_bytes();
 hipError_t static_scratch_ptr(uint8_t **out);
 // 1/|entry| for every codebook entry, fp64 inside (cosine metric)
+void launch_vq_zero(float *a, int64_t n, hipStream_t s);
 void launch_vq_rnorm(bifeat_params *p, hipStream_t s);
 // nearest-entry search of `rows` rows into codes_row0 (row stride rb bytes, indices of
 // `cbytes` bytes; bytes from P*cbytes to rb are zeroed)

@@ -219,8 +219,8 @@ template <typename T>
 void launch_vq_assign(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
                       hipStream_t s) {
     const int w = p->scheme.vq_width;
-    // the matrix-core search gives the same codes; what it leaves (wide parts, tiny codebooks)
-    // takes the plain search
+    // the matrix-core search gives the same codes; what it leaves (wide parts, tiny codebooks, dense
+    // ones and those that do not fit LDS) takes the plain search
     if (launch_vq_nearest_codes<T>(p, x, rows, codes, rb, s)) return;
     switch (w) {
         case 1: launch_vq_w<T, 1, 1>(p, x, rows, codes, rb, s); break;

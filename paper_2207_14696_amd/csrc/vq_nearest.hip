@@ -57,7 +57,8 @@ struct VqNearestArgs {
     float margin, cell_margin;  // see vq_margin
     uint32_t cell_mask;     // low bits of a score that hold a cell's number
     int64_t rb;             // (the encoder)
-    float *sums;            // (training) [ny][P][w][len]
+    int one_set;            // (training) every workgroup adds to one set of sums, all zeros
+    float *sums;            // [ny][P][w][len]
     uint32_t *counts;       // [ny][P][len]
     double *distortion;
 };
@@ -618,10 +619,18 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     }
     if constexpr (TRAIN) {
         __syncthreads();
-        float *sums = a.sums + ((int64_t)by * a.P + part) * len * w;
-        uint32_t *counts = a.counts + ((int64_t)by * a.P + part) * len;
-        for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
-        for (int i = threadIdx.x; i < len; i += TH) counts[i] = s_cnt[i];
+        const int64_t set = a.one_set ? 0 : by;
+        float *sums = a.sums + (set * a.P + part) * len * w;
+        uint32_t *counts = a.counts + (set * a.P + part) * len;
+        if (a.one_set) {
+            for (int i = threadIdx.x; i < len * w; i += TH)
+                if (s_sum[i] != 0.0) unsafeAtomicAdd(&sums[i], (float)s_sum[i]);
+            for (int i = threadIdx.x; i < len; i += TH)
+                if (s_cnt[i]) atomicAdd(&counts[i], s_cnt[i]);
+        } else {
+            for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
+            for (int i = threadIdx.x; i < len; i += TH) counts[i] = s_cnt[i];
+        }
         for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
         if (lane == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
         __syncthreads();
@@ -730,22 +739,24 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
     if (ny < 1) ny = 1;
     if (ny > strips) ny = strips;
     if constexpr (TRAIN) {
-        // every workgroup's sums; without room for them (a stream that is being captured) one
-        // workgroup per part and the handle's own block of one set
+        // every workgroup's sums; without room for them (a stream that is being captured) they add to
+        // the handle's own block of one set (10 rounds on 65 536 rows, with workspace / so: 8 x 256 x 16
+        // 690 / 560 us, 96 x 256 x 8 1910 / 1930; one workgroup per part 8790 and 6370)
         const int64_t books = (int64_t)a.P * a.len * a.w, ents = (int64_t)a.P * a.len;
         if (ensure_scratch(p, sizeof(float) * (size_t)(ny * (books + ents)), s)) {
             a.sums = (float *)p->d_scratch;
         } else {
-            ny = 1;
+            a.one_set = 1;
             a.sums = p->d_train;
+            launch_vq_zero(p->d_train, books + ents, s);
         }
-        a.counts = (uint32_t *)(a.sums + ny * books);
+        a.counts = (uint32_t *)(a.sums + (a.one_set ? 1 : ny) * books);
     }
     a.ny = (int)ny;
     search_costs(a, G, ENT);
     const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
     kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
-    if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.ny, s);
+    if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.ny, s);
     return true;
 }
 

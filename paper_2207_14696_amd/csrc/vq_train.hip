@@ -6,14 +6,18 @@
 // sub-vector to its nearest entry (the same fp32 rule as the encoder, so a
 // trained codebook encodes exactly as it was fitted), accumulates per-entry
 // sums and counts and replaces each non-empty entry by the mean of its members
-// (an entry without members keeps its value).  fp32 atomic accumulation makes
-// the result depend on the order of additions in the last bits; it is judged on
-// distortion, not bit for bit.
-// Two forms: Euclidean one-byte codebooks small enough for LDS fuse the search
-// with the accumulation (vq_nearest.hip); everything else (cosine metric, up to 16384
-// entries, wide parts, tiny codebooks) runs the encoder's own kernel into a scratch code
-// array and accumulates from that, again in LDS and per workgroup.  (A plain fused kernel,
-// sums in LDS and then global atomics, is left for streams under capture without workspace.)
+// (an entry without members keeps its value).  Sums are added with atomics, so the result
+// depends on the order of additions in the last bits; it is judged on distortion, not bit
+// for bit.
+// Three forms:
+// - Euclidean one-byte codebooks that the matrix-core search takes: search and sums in one
+//   kernel (vq_nearest.hip);
+// - everything else that the plain fused kernel cannot do (cosine metric, two-byte codes) or
+//   does badly runs the encoder's own kernel into a scratch code array and
+//   adds up from that, in LDS and per workgroup;
+// - the plain fused kernel (sums in LDS in 32 bits, then global atomics) for the rest, and
+//   for those of the second form's codebooks that it can do where a stream under capture
+//   leaves no room for the codes.
 #include "common.hpp"
 #include "vq_nearest.hpp"
 
@@ -113,7 +117,7 @@ __global__ void vq_lloyd_update_kernel(float *__restrict__ cb, const float *__re
 template <typename T>
 void lloyd_round(bifeat_params *p, const T *x, int64_t rows, double *dist_slot, hipStream_t s) {
     if (launch_vq_nearest_round<T>(p, x, rows, dist_slot, s)) return;
-    // what the matrix-core search leaves: wide parts and tiny codebooks
+    // codebooks that the matrix-core search leaves and codes do not pay for, or have no workspace for
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
     const int64_t n = (int64_t)P * len * w;
     float *sums = p->d_train, *counts = p->d_train + n;
@@ -151,7 +155,7 @@ __global__ void vq_rnorm_kernel(const float *__restrict__ cb, int64_t entries, i
 // Sums, counts and squared distance from a dense code array codes[r][p].  A workgroup takes one
 // part, as many of its columns (the count is one more) as LDS holds sums for - 64-bit ones, see
 // vq_nearest.hip - and every ny-th strip of rows, and writes its sums to the workspace:
-// sums [ny][P][w][len], counts [ny][P][len].
+// sums [ny][P][w][len], counts [ny][P][len]; or adds them to the one (zeroed) set there is room for.
 // Before, every value was an atomic on memory (1.1 M per part and round at 65 536 rows of 16
 // columns) and every wave one on the distortion: 1.7 ms of a round's 2.8 at 8 x 2048 x 16.
 constexpr int kAccThreads = 1024;
@@ -160,7 +164,7 @@ constexpr int64_t kAccLds = 144 * 1024;
 template <typename T, typename CODE>
 __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w, int len, int P, const CODE *__restrict__ codes,
-    const float *__restrict__ cb, int DG, int groups, int ny, float *__restrict__ sums,
+    const float *__restrict__ cb, int DG, int groups, int ny, int one_set, float *__restrict__ sums,
     uint32_t *__restrict__ counts, double *__restrict__ distortion) {
     extern __shared__ double s_acc[];  // [DG][len]
     __shared__ double s_dist;
@@ -192,8 +196,15 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     if (threadIdx.x == 0) unsafeAtomicAdd(distortion, s_dist);
     for (int i = threadIdx.x; i < nc * len; i += kAccThreads) {
         const int j = i / len, e = i - j * len, d = c0 + j;
-        if (d < w) sums[(((int64_t)by * P + p) * w + d) * len + e] = (float)s_acc[i];
-        else counts[((int64_t)by * P + p) * len + e] = (uint32_t)s_acc[i];
+        if (one_set) {
+            if (s_acc[i] == 0.0) continue;
+            if (d < w) unsafeAtomicAdd(&sums[((int64_t)p * w + d) * len + e], (float)s_acc[i]);
+            else atomicAdd(&counts[(int64_t)p * len + e], (uint32_t)s_acc[i]);
+        } else if (d < w) {
+            sums[(((int64_t)by * P + p) * w + d) * len + e] = (float)s_acc[i];
+        } else {
+            counts[((int64_t)by * P + p) * len + e] = (uint32_t)s_acc[i];
+        }
     }
 }
 
@@ -222,7 +233,7 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
 }
 
 template <typename T, typename CODE>
-bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, int ny, float *sums,
+bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, bool one_set, float *sums,
                       uint32_t *counts, double *dist_slot, hipStream_t s) {
     const size_t shm = sizeof(double) * (size_t)g.DG * p->scheme.vq_length;
     auto kern = vq_accumulate_codes_kernel<T, CODE>;
@@ -230,9 +241,9 @@ bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericP
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)shm) != hipSuccess)
         return false;
-    kern<<<(unsigned)(g.groups * p->P * ny), kAccThreads, shm, s>>>(
+    kern<<<(unsigned)(g.groups * p->P * g.ny), kAccThreads, shm, s>>>(
         x, rows, (int)p->D, p->scheme.vq_width, p->scheme.vq_length, p->P, (const CODE *)p->d_scratch, p->d_cb, g.DG,
-        g.groups, ny, sums, counts, dist_slot);
+        g.groups, g.ny, one_set, sums, counts, dist_slot);
     return true;
 }
 
@@ -241,18 +252,20 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
     const int64_t books = (int64_t)P * len * w;
     const GenericPlan g = generic_plan(p, rows);
-    // without room for every workgroup's sums: one workgroup per part and group of columns, and
-    // the handle's own block of one set (the codes' part of the workspace is there, see below)
+    // without room for every workgroup's sums (a stream under capture) they add to the handle's own
+    // block of one set (the codes' part of the workspace is there, see below): 8 x 2048 x 16 cosine,
+    // 10 rounds 2890 us so, with workspace 2980; one workgroup per part and group of columns 8690
     const bool all = (int64_t)p->scratch_bytes >= g.codes_bytes + g.ny * g.set_bytes;
-    const int ny = all ? g.ny : 1;
+    const int sets = all ? g.ny : 1;
     float *sums = all ? (float *)(p->d_scratch + g.codes_bytes) : p->d_train;
-    uint32_t *counts = (uint32_t *)(sums + ny * books);
+    uint32_t *counts = (uint32_t *)(sums + sets * books);
+    if (!all) launch_vq_zero(p->d_train, books + (int64_t)P * len, s);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
     launch_vq_assign(p, x, rows, p->d_scratch, (int64_t)P * p->cbytes, s);
-    const bool ok = p->cbytes == 1 ? accumulate_codes<T, uint8_t>(p, x, rows, g, ny, sums, counts, dist_slot, s)
-                                   : accumulate_codes<T, uint16_t>(p, x, rows, g, ny, sums, counts, dist_slot, s);
+    const bool ok = p->cbytes == 1 ? accumulate_codes<T, uint8_t>(p, x, rows, g, !all, sums, counts, dist_slot, s)
+                                   : accumulate_codes<T, uint16_t>(p, x, rows, g, !all, sums, counts, dist_slot, s);
     if (!ok) return hipGetLastError();
-    launch_vq_means(p, sums, counts, ny, s);
+    launch_vq_means(p, sums, counts, sets, s);
     return hipSuccess;
 }
 
@@ -283,6 +296,10 @@ bool ensure_scratch(bifeat_params *p, size_t bytes, hipStream_t s) {
     return true;
 }
 
+void launch_vq_zero(float *a, int64_t n, hipStream_t s) {
+    vq_zero_kernel<<<blocks_for(n, 1024), kThreads, 0, s>>>(a, n);
+}
+
 void launch_vq_rnorm(bifeat_params *p, hipStream_t s) {
     const int64_t entries = (int64_t)p->P * p->scheme.vq_length;
     vq_rnorm_kernel<<<blocks_for(entries), kThreads, 0, s>>>(p->d_cb, entries, p->scheme.vq_width,
@@ -297,15 +314,15 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
     const int w = p->scheme.vq_width, len = p->scheme.vq_length, P = p->P;
     const bool fused = p->scheme.vq_metric == BIFEAT_VQ_L2 && p->cbytes == 1 &&
                        sizeof(float) * ((size_t)2 * len * w + len) <= 65536;
-    // What the fused search does not take goes through the codes as well; the plain fused kernel,
-    // which needs no workspace, is left for streams under capture (16 384 rows of 64 columns, 64
-    // entries: 42 ms with it).
     bool through_codes = !fused;
-    if (!fused || !vq_nearest_takes(p, true)) {
-        const GenericPlan g = generic_plan(p, rows);
-        through_codes = ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s) ||
-                        ensure_scratch(p, (size_t)rows * P * p->cbytes, s);
-        if (!fused && !through_codes) return hipErrorOutOfMemory;
+    const GenericPlan g = generic_plan(p, rows);
+    if (!fused) {
+        // (codes without the sums: see lloyd_round_generic)
+        if (!ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s) &&
+            !ensure_scratch(p, (size_t)rows * P * p->cbytes, s))
+            return hipErrorOutOfMemory;
+    } else if (!vq_nearest_takes(p, true)) {
+        through_codes = ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s);
     }
     if (init) {
         if (dtype == BIFEAT_F32)

@@ -1,0 +1,117 @@
+"""Codebook training in each of its forms against the oracle's rounds: the column groups of large
+codebooks, codebooks on both sides of the choice between codes and the plain fused kernel, and streams
+under capture that have no workspace, or not enough, to offer."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from helpers import scheme_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _train(torch, bf, x, w, length, metric, iters):
+    q = bf.Quantizer(scheme_of("vq", 8, w, length, metric), x.shape[1])
+    q.set_option("vq_iters", iters)
+    q.fit_update(torch.from_numpy(x).cuda())
+    q.fit_finalize()
+    return q
+
+
+# sums of 8 * length * (w + 1) bytes: 278 528 and 1.1 M for 2048 x 16 and 8000 x 16, in 144 KB a group;
+# 16 384 entries leave room for one column a group (Euclidean: the directions of so many entries of two
+# columns differ by 2 pi / 16 384, their cosines by 7e-8, what fp32 resolves: rounding picks the entry);
+# a last part of 5 columns
+@pytest.mark.parametrize("D,w,length,rows,metric", [
+    (32, 16, 2048, 5000, "l2"), (32, 16, 2048, 5000, "cosine"), (21, 16, 1300, 4000, "l2"),
+    (21, 16, 1300, 4000, "cosine"), (16, 16, 8000, 9000, "l2"), (16, 16, 8000, 9000, "cosine"),
+    (3, 2, 16384, 17000, "l2"), (48, 48, 400, 3000, "l2"), (48, 48, 400, 3000, "cosine")])
+def test_column_groups(D, w, length, rows, metric):
+    import torch
+    import paper_2207_14696_amd as bf
+    x = np.random.default_rng(D + length).normal(size=(rows, D)).astype(np.float32)
+    q = _train(torch, bf, x, w, length, metric, 2)
+    cb, want = orc.vq_train(x, w, length, iters=2, metric=metric)
+    # (rows between entries may change sides with the last bits of the first round's means)
+    np.testing.assert_allclose(q.vq_distortion(2), want[:2], rtol=1e-4)
+    assert q.vq_distortion(1)[0] == pytest.approx(want[0], rel=1e-5)
+    np.testing.assert_allclose(np.abs(q.params_get_codebooks()).mean(), np.abs(cb).mean(), rtol=1e-3)
+
+
+# widths 1, 2 and 4 on both sides of 128 values, of 4096 rows and of 2^21 sample values; other widths
+@pytest.mark.parametrize("P,w,length,rows", [(3, 1, 64, 5000), (3, 1, 200, 5000), (3, 1, 64, 4096), (5, 4, 31, 4097),
+                                             (5, 4, 32, 4097), (130, 4, 64, 4100), (8, 2, 64, 131_200),
+                                             (8, 2, 65, 131_200), (4, 5, 40, 700), (1, 64, 30, 900)])
+def test_small_codebooks(P, w, length, rows):
+    import torch
+    import paper_2207_14696_amd as bf
+    x = np.random.default_rng(P * w + length).normal(size=(rows, P * w)).astype(np.float32)
+    q = _train(torch, bf, x, w, length, "l2", 2)
+    _, want = orc.vq_train(x, w, length, iters=2)
+    np.testing.assert_allclose(q.vq_distortion(2), want[:2], rtol=2e-5)
+
+
+@pytest.mark.parametrize("P,w,length,metric,reserve", [
+    (4, 16, 256, "l2", 0),         # no room: one set of sums
+    (4, 8, 32, "l2", 0), (4, 8, 32, "l2", 20_000), (2, 5, 40, "l2", 20_000),  # the plain fused kernel
+    (2, 16, 700, "cosine", 20_000)])  # room for the codes only: one set of sums
+def test_training_under_capture(P, w, length, metric, reserve):
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(length)
+    x = rng.normal(size=(20_000, P * w)).astype(np.float32)
+    dx = torch.from_numpy(x).cuda()
+    eager = bf.Quantizer(scheme_of("vq", 8, w, length, metric), P * w)
+    eager.fit_update(dx)
+    want = eager.vq_distortion(10)
+    q = bf.Quantizer(scheme_of("vq", 8, w, length, metric), P * w)
+    q.fit_reset()
+    if reserve:
+        q.reserve(reserve)
+    g, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=stream):
+        q.fit_update(dx)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        got = q.vq_distortion(10)
+        assert got[0] == pytest.approx(want[0], rel=1e-5)
+        np.testing.assert_allclose(got, want, rtol=2e-3)   # ten rounds from sums in another order
+        dx.mul_(1.0)                                       # the program's own work between replays
+    eager.fit_update(dx)
+
+
+def _us(torch, f):
+    f()
+    best = 1e9
+    for _ in range(3):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("P,w,length,reserve", [(8, 16, 256, 0), (12, 8, 32, 65_536)])
+def test_training_under_capture_fills_the_chip(P, w, length, reserve):
+    # 0.9 and 1.7 times an eager call's time; with a workgroup per part it was 13 and 6 times
+    import torch
+    import paper_2207_14696_amd as bf
+    x = torch.randn(65_536, P * w, device="cuda")
+    q = bf.Quantizer(scheme_of("vq", 8, w, length), P * w)
+    q.fit_reset()
+    if reserve:
+        q.reserve(reserve)
+    g, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=stream):
+        q.fit_update(x)
+    captured = _us(torch, g.replay)
+    eager = bf.Quantizer(scheme_of("vq", 8, w, length), P * w)
+
+    def call():
+        eager.fit_reset()
+        eager.fit_update(x)
+    t = _us(torch, call)
+    assert captured <= 3 * t, (captured, t)
