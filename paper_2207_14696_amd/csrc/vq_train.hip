@@ -13,7 +13,7 @@
 // - Euclidean one-byte codebooks that the matrix-core search takes: search and sums in one
 //   kernel (vq_nearest.hip);
 // - everything else that the plain fused kernel cannot do (cosine metric, two-byte codes) or
-//   does badly runs the encoder's own kernel into a scratch code array and
+//   does badly (codes_pay below) runs the encoder's own kernel into a scratch code array and
 //   adds up from that, in LDS and per workgroup;
 // - the plain fused kernel (sums in LDS in 32 bits, then global atomics) for the rest, and
 //   for those of the second form's codebooks that it can do where a stream under capture
@@ -232,6 +232,22 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
     return g;
 }
 
+// Whether a codebook that the plain fused kernel can train, and the matrix-core search does not take,
+// goes through codes.  The fused kernel reads the sample once a round and is bound by its LDS float
+// adds; the other way searches faster, reads twice, and the second time a workgroup has one part's
+// columns of all its rows, which only a sample that the caches hold allows.  10 rounds, us, fused /
+// codes: 16 384 x 1 x 64 x 64 41 700 / 2600, 65 536 x 8 x 64 x 5 4369 / 1142 (widths the fused kernel
+// does not have at compile time); 65 536 x 1 x 32 x 8 522 / 354, 1000 x 96 x 32 x 8 341 / 217;
+// 65 536 x 8 x 16 x 1 279 / 343, 65 536 x 8 x 16 x 4 403 / 544, 65 536 x 192 x 64 x 4 5110 / 8760.
+// One and two columns are so little to read that small codebooks go through codes at any size
+// (65 536 x 96 x 64 x 1 1931 / 1433; 256 entries 2393 / 2958).
+bool codes_pay(const bifeat_params *p, int64_t rows) {
+    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    if (w > 16 || (w & (w - 1))) return true;
+    if (rows * p->P * w < (1 << 21)) return len * w >= 128 || rows <= 4096;
+    return w <= 2 && len <= 64;
+}
+
 template <typename T, typename CODE>
 bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, bool one_set, float *sums,
                       uint32_t *counts, double *dist_slot, hipStream_t s) {
@@ -321,7 +337,7 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
         if (!ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s) &&
             !ensure_scratch(p, (size_t)rows * P * p->cbytes, s))
             return hipErrorOutOfMemory;
-    } else if (!vq_nearest_takes(p, true)) {
+    } else if (!vq_nearest_takes(p, true) && codes_pay(p, rows)) {
         through_codes = ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s);
     }
     if (init) {
