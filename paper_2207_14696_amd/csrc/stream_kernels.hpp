@@ -435,9 +435,10 @@ inline hipError_t launch_fit_minmax_src(bifeat_params *p, const Src &src, int64_
     int64_t want = (rows * G + 7) / 8;  // about 8 rows per thread
     if (want < G) want = G;
     // few large workgroups for the sake of their merge (see above), but not where there is none, nor,
-    // with few columns to merge, for chunks that would occupy a fraction of the CUs (300 x 768 half-
-    // precision 6.5 us, 4.9 so; 300 x 4096 floats 4.9, 7.3 with small ones)
-    const bool large = use_lds && (want >= kThreads * 256 || G > kThreads);
+    // with few columns to merge, for chunks that would not occupy the CUs (half precision, large / small
+    // ones: 300 x 768 6.5 / 4.9 us, 40 000 x 128 5.8 / 4.6, 15 000 x 768 6.8 / 7.5; but 300 x 4096
+    // floats 4.9 / 7.3)
+    const bool large = use_lds && (want > kThreads * 640 || G > kThreads);
     const int threads = large ? kFitThreads : kThreads;
     int blocks = large ? fit_blocks(want) : blocks_for(want);
     if ((int64_t)blocks * threads < G) blocks = (G + threads - 1) / threads;
