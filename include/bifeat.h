@@ -149,7 +149,10 @@ int64_t bifeat_codes_per_row(const bifeat_params *p);
  *   so the codebooks are reproducible in distortion, not bit for bit.
  *   Training uses library scratch: workgroups' partial sums of the codebooks, and for a large
  *   or cosine codebook also a code per part and sample row (one byte up to 256 entries, else
- *   two), with the sums there within 256 MB, or one set of them if that is larger.
+ *   two), with the sums there within 256 MB, or one set of them if that is larger.  On a stream
+ *   that is being captured nothing is allocated: sums that find no room are added to the
+ *   handle's own set, and a large or cosine codebook needs room for its codes from an earlier
+ *   update or bifeat_reserve (BIFEAT_EHIP otherwise).
  *   finalize synchronises `stream` for the cosine metric
  *   (the entry norms are evaluated on the host in fp64).
  * finalize without any update returns BIFEAT_ENOTFIT. */
@@ -366,8 +369,9 @@ const char *bifeat_strerror(int status);
  * "mean_generic" = 1 routes uniform tables through the float-accumulate
  * kernel; "mean_lean" = 0 disables the short-list kernel; "max_blocks" caps the
  * gather_dequant grid; "dequant_flat" = 1 / "vq_sliced" = 0 select the
- * unstaged decode kernels ("vq_sliced" = 2: the staged ones for small gather_mean
- * calls too).  Two options carry information rather than tuning:
+ * unstaged decode kernels ("vq_sliced" = 2: the staged ones also for the small
+ * gather_mean / gather_sum calls that "mean_max_degree" lets go without).
+ * Two options carry information rather than tuning:
  * "mean_max_degree" = d is the caller's promise that no neighbour list of the
  * following bifeat_gather_mean calls is longer than d (0 = unknown; a sampler
  * knows its fan-out), which lets the library skip the pass that looks for
