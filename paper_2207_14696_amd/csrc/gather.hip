@@ -119,19 +119,18 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
     const int r = lane / c16, c = lane - r * c16;
     const int64_t tiles = (M + RT - 1) / RT;
     const int64_t n_waves = (int64_t)gridDim.x * (kThreads / 64);
-    // the packed rows of a tile, one 16-byte piece per lane (lane = r*c16 + c); the first tile's
-    // travel while the parameters are staged
-    auto fetch = [&](int64_t tile) {
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (tile < tiles && r < RT && tile * RT + r < M) v = codes16[idx[tile * RT + r] * s16 + c];
-        return v;
-    };
+    // the packed rows of a tile, one 16-byte piece per lane (lane = r*c16 + c); of the first tile's the
+    // row ids travel while the parameters are staged (the rows too: 8 bits, 100 000 rows of 768 columns
+    // 61 us, 57 so - the staging's loads would queue behind ids and rows)
+    auto mine = [&](int64_t tile) { return tile < tiles && r < RT && tile * RT + r < M; };
     int64_t tile = (int64_t)blockIdx.x * (kThreads / 64) + wave;
-    uint4 next = fetch(tile);
+    int64_t id = mine(tile) ? idx[tile * RT + r] : 0;
     for (int i = threadIdx.x; i < npar; i += kThreads) {
         if constexpr (DEC == DEC_UNIFORM) s_par[i] = i < D ? pb[i] : pa[i - D];  // [scale | min]
         else s_par[i] = pa[i];
     }
+    uint4 next = make_uint4(0u, 0u, 0u, 0u);
+    if (mine(tile)) next = codes16[id * s16 + c];
     __syncthreads();
 
     const int nf4 = D >> 2;
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
                 d++;
             }
         }
-        next = fetch(tile + n_waves);
+        if (mine(tile + n_waves)) next = codes16[idx[(tile + n_waves) * RT + r] * s16 + c];
         wave_sync();  // raw is rewritten by the next tile
     }
 }
