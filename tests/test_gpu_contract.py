@@ -271,6 +271,8 @@ def test_line_aligned_table_layout(bf, torch, kind, bits, D, payload, stride):
         q.set_option(opt, 1)
     indptr, indices = random_csr(500, 2003, 9, rng)
     q.set_option("mean_max_degree", 9)
-    got = q.gather_mean(table, torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda())
-    assert_close(got.cpu().numpy(), orc.gather_mean(s, codes, indptr, indices), s, "mean, bounded lists")
+    for sliced in (1, 2):  # (vector codes: from L2 and through the codebook slices)
+        q.set_option("vq_sliced", sliced)
+        got = q.gather_mean(table, torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda())
+        assert_close(got.cpu().numpy(), orc.gather_mean(s, codes, indptr, indices), s, f"mean, bounded lists {sliced}")
     assert q.poll_status()

@@ -144,15 +144,19 @@ def test_small_requests_and_fanout_bounds(bf, torch, case):
         indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
         indices = rng.integers(0, N, int(indptr[-1])).astype(np.int64)
         dptr, dind = torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda()
-        q.set_option("mean_max_degree", f)
-        got = q.gather_mean(dcodes, dptr, dind).cpu().numpy()
-        gsum = q.gather_sum(dcodes, dptr, dind).cpu().numpy().astype(np.float64)
-        q.set_option("mean_max_degree", 0)
-        assert_close(got, orc.gather_mean(s, codes, indptr, indices), s, f"mean V={V} f={f} {c}")
+        mean_want = orc.gather_mean(s, codes, indptr, indices)
         want = orc.gather_sum(s, codes, indptr, indices).astype(np.float64)
         n = np.maximum(deg, 1)[:, None]
         bound = REL_TOL * np.maximum(np.abs(want), column_magnitude(s).astype(np.float64)[None, :] * n)
-        assert not (np.abs(gsum - want) > bound).any(), f"sum V={V} f={f} {c}"
+        # vector codes: from L2, as a bounded call this small goes, and through the codebook slices
+        for sliced in ((1, 2) if c["kind"] == "vq" else (1,)):
+            q.set_option("vq_sliced", sliced)
+            q.set_option("mean_max_degree", f)
+            got = q.gather_mean(dcodes, dptr, dind).cpu().numpy()
+            gsum = q.gather_sum(dcodes, dptr, dind).cpu().numpy().astype(np.float64)
+            q.set_option("mean_max_degree", 0)
+            assert_close(got, mean_want, s, f"mean V={V} f={f} sliced={sliced} {c}")
+            assert not (np.abs(gsum - want) > bound).any(), f"sum V={V} f={f} sliced={sliced} {c}"
     # every list empty, with and without the bound
     V = int(rng.integers(1, 70))
     zptr = torch.zeros(V + 1, dtype=torch.int64, device="cuda")
