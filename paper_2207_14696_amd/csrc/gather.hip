@@ -120,17 +120,20 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
     const int64_t tiles = (M + RT - 1) / RT;
     const int64_t n_waves = (int64_t)gridDim.x * (kThreads / 64);
     // the packed rows of a tile, one 16-byte piece per lane (lane = r*c16 + c); of the first tile's the
-    // row ids travel while the parameters are staged (the rows too: 8 bits, 100 000 rows of 768 columns
-    // 61 us, 57 so - the staging's loads would queue behind ids and rows)
+    // row ids travel while the parameters are staged, and where those are few the rows too (4 bits,
+    // 20 000 rows of 100 columns 4.56 us by ids only, 4.44; but 8 bits, 100 000 rows of 768 56 and 61 -
+    // the staging's loads queue behind ids and rows)
     auto mine = [&](int64_t tile) { return tile < tiles && r < RT && tile * RT + r < M; };
     int64_t tile = (int64_t)blockIdx.x * (kThreads / 64) + wave;
-    int64_t id = mine(tile) ? idx[tile * RT + r] : 0;
+    const int64_t id = mine(tile) ? idx[tile * RT + r] : 0;
+    const bool early = npar <= 2 * kThreads;
+    uint4 next = make_uint4(0u, 0u, 0u, 0u);
+    if (early && mine(tile)) next = codes16[id * s16 + c];
     for (int i = threadIdx.x; i < npar; i += kThreads) {
         if constexpr (DEC == DEC_UNIFORM) s_par[i] = i < D ? pb[i] : pa[i - D];  // [scale | min]
         else s_par[i] = pa[i];
     }
-    uint4 next = make_uint4(0u, 0u, 0u, 0u);
-    if (mine(tile)) next = codes16[id * s16 + c];
+    if (!early && mine(tile)) next = codes16[id * s16 + c];
     __syncthreads();
 
     const int nf4 = D >> 2;
