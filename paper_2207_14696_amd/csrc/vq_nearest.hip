@@ -6,42 +6,47 @@
 // product times the entry's reciprocal norm).  Evaluating that rule for every entry costs 3
 // vector instructions per column and entry and leaves the matrix cores idle.  Here they do the
 // search: s = |c|^2/2 - x.c (cosine: -x.c/|c|) for 32 rows x 32 entries at a time, both factors
-// split into two half-precision pieces (hi + lo, 22 bits) so that all four piece products are
-// two MFMAs of K = 16 per 8 columns.  A lane keeps, per row, the best and the second best *cell*
-// (8 entries: the accumulator registers 4q..4q+3 of two neighbouring tiles), which costs 7 vector
-// instructions per 8 scores; the 8 entries of the winning cell are then scored in fp32.  Each of
-// the two decisions is certain to be the rule's own when the second best is further away than
-// the errors of both evaluations together (derived at vq_margin and vq_cell_margin below); a row
-// for which it is not - near ties, values outside the range the split holds - is searched by the
-// rule over the whole codebook, by the wave together, or lane by lane when many rows of a wave
-// need it; where most rows do, the scores are left out (search_costs below: at no share of such
-// rows is that dearer than the plain search by more than a tenth).  The codes are therefore the
-// same as the plain search gives, for any input.
+// split into two half-precision pieces (hi + lo, 22 bits).  Per 8 columns x.c_hi is one MFMA of
+// K = 16 (the row's high pieces in the lower lanes, its low ones in the upper) and x_hi.c_lo half of
+// one; the other half of an odd last one carries |c|^2/2 in three pieces (with an even number of
+// groups of 8 columns, or without the entries in LDS, the accumulators start from it).  A lane
+// keeps, per row, the best and the second best *cell* (8 entries: half of the accumulators of a
+// tile), which costs 6 vector instructions per 8 scores; the 8 entries of the winning cell are then
+// scored in fp32.  Each of the two decisions is certain to be the rule's own when the second best is
+// further away than the errors of both evaluations together (derived at vq_margin and
+// vq_cell_margin below); a row for which it is not - near ties, values outside the range the split
+// holds - is searched by the rule over the whole codebook, by the wave together, or lane by lane
+// when many rows of a wave need it; where most rows do, the scores are left out (search_costs below:
+// at no share of such rows is that dearer than the plain search by more than a tenth).  The codes
+// are therefore the same as the plain search gives, for any input.
 //
-// What bounds it: vector instructions - of ~570 per 64 rows and part 272 are the running minima
-// over 256 entries, 133 the scores inside the cell, 59 the split of x - at 75 % of the issue rate,
-// next to LDS (entry pieces, constants and cells: 430 cycles per 64 rows) and 18 cycles of MFMA
-// per row and part.  64 rows per wave reuse each 1 KB of entry pieces read from LDS four times.
-// Cells of 4 entries decided by the rule itself: 660 instructions, 680 us; one tile at a time
-// instead of a set's minima under the other set's product: 706 us.  262 144 rows of 96 parts x 256
-// entries x 8 columns: 661 us, the plain search 3111 us.
+// What bounds it: vector instructions and power.  Of ~470 per 64 rows and part 200 are the running
+// minima over 256 entries, 100 the scores inside the cell, 45 the split of x, 32 the products, at
+// 77 % of the issue rate; the clock falls to 1.8 GHz under it, so that every instruction and LDS
+// read taken out counts, and a better overlap alone does not.  262 144 rows of 96 parts x 256 entries
+// x 8 columns: 542 us; with all four products of the pieces, |c|^2/2 read from LDS for every tile
+// and cells across two tiles (570 instructions, 77 LDS reads instead of 39) 650; the plain search
+// 3111 us.  Cells of 4 entries cost as much more in minima as they save in scores, of 16 more.
 //
 // Training adds each part to its entry's sum in LDS.  The sums are kept in 64 bits: an LDS
 // float add takes 196 cycles per wave here whatever the addresses, a double add 22 (integer: 8).
 // A workgroup writes its sums to the workspace and a second kernel adds them up in a fixed order
 // (global float adds onto the same few addresses ran at 22.6 G/s, a quarter of the round).  One
-// round over 65 536 rows of that shape: 200 us, before (plain search, fp32 adds) 1030 us.
+// round over 65 536 rows of that shape: 165 us (with the search as it was, see above, 200; plain search
+// and fp32 adds 1030).
 #include "vq_nearest.hpp"
 
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace bf {
 
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 
 template <typename T>
@@ -51,7 +56,7 @@ struct VqNearestArgs {
     int D, w, len, P, cbytes;
     int vec, bvec;          // 4 columns of a part, of an entry can be loaded at once
     int lane_rows, plain_rows;  // see search_costs
-    int NT;                 // tiles of 32 entries, a whole number of pairs: a cell spans two
+    int NT;                 // tiles of 32 entries
     int ny;                 // workgroups per part
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
@@ -71,12 +76,36 @@ constexpr int kCuLds = 160 * 1024;
 constexpr int kPlainStrips = 7;
 
 constexpr float kPadScore = 1e30f;   // score of the entries that fill up the last tile
+// Layout in LDS.  Entry pieces of a tile, in units of 8 halves: [high pieces: G x 32 | low pieces:
+// G x 32 | with NORM |c|^2/2 in three pieces and a fourth that only padding entries have, 4 halves
+// an entry].  Entries: 4 of them, then 4 floats (|c|^2/2; cosine: 1/|c|); after 4 such groups 4
+// floats of padding, so that lanes that read different ones meet in few banks.
+__host__ __device__ constexpr bool norm_slot(int G, bool ent) { return ent && G % 2 == 1; }
+__host__ __device__ constexpr int tile_units(int G, bool ent) { return 64 * G + (norm_slot(G, ent) ? 16 : 0); }
+__host__ __device__ constexpr int group_floats(int G) { return 4 * 8 * G + 4; }
+__host__ __device__ constexpr int groups4_floats(int G) { return 4 * group_floats(G) + 4; }
+// what the pieces of |c|^2/2 (at most 2^26) are multiplied with; the fourth makes 2^31
+constexpr float kNormUnit1 = 4096.0f, kNormUnit2 = 2.0f, kPadUnit = 32768.0f, kPadPiece = 65504.0f;
+constexpr float kMinHalf = 0x1p-14f;  // smallest normal half
 constexpr int kScaleExp = 11;        // largest magnitude of a part's codebook: [2^10, 2^11)
 constexpr float kMaxNorm2 = 1073741824.0f;  // rows with a scaled |x|^2 of 2^30 or more go by the rule
 
 // One instruction for up to three operands, and none to quiet NaNs first (fminf needs one each); a
 // NaN wins, which the caller's comparison with the margin then sees.
 __device__ inline float minimum(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+
+// a minus the half in the low / high bits of h: exact where that is a's high piece, and one instruction
+// (the compiler makes a conversion and a subtraction of it)
+__device__ inline float less_low(float a, uint32_t h) {
+    float d;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(d) : "v"(h), "v"(a));
+    return d;
+}
+__device__ inline float less_high(float a, uint32_t h) {
+    float d;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(h), "v"(a));
+    return d;
+}
 
 // The rule, column by column.
 template <int METRIC>
@@ -106,19 +135,19 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     constexpr int WP = 8 * G;          // columns of a part, padded with zeros
     constexpr int TH = ENT ? 256 : 512;
     constexpr int WAVES = TH / 64;
-    // floats of 4 entries in LDS and of the 16 such groups of two tiles: the padding spreads the
-    // groups, which different lanes read at the same time, over the banks
-    constexpr int CELL = 4 * WP + 4, PAIR = 16 * CELL + 4;
+    constexpr int GROUP = group_floats(G), GROUPS4 = groups4_floats(G), UNITS = tile_units(G, ENT);
     constexpr bool COS = METRIC == BIFEAT_VQ_COSINE;
+    // whether |c|^2/2 comes with the product or is what the accumulators start from
+    constexpr bool NORM = norm_slot(G, ENT);
+    constexpr int LO = (G + 1) / 2;    // products with low pieces, two groups of columns at a time
     extern __shared__ uint4 s_raw[];
-    // [entry pieces: NT x G x 64 lanes x 16 bytes | scores' constant: NT x 32 | entries | rnorm |
-    // sums by column, counts]
+    // [entry pieces: NT x UNITS x 16 bytes, NORM: 16 more of zeros, else the scores' constant: NT x 32
+    // floats | entries | sums by column, counts]
     half8 *s_frag = reinterpret_cast<half8 *>(s_raw);
-    float *s_half = reinterpret_cast<float *>(s_frag + (size_t)a.NT * G * 64);
-    float *s_ent = s_half + a.NT * 32;
-    float *s_rn = s_ent + (ENT ? a.NT / 2 * PAIR : 0);
+    float *s_half = reinterpret_cast<float *>(s_frag + (size_t)a.NT * UNITS);
+    float *s_ent = s_half + (NORM ? 4 : a.NT * 32);
     // (every piece above is a multiple of 4 floats)
-    double *s_sum = reinterpret_cast<double *>(s_rn + (ENT && COS ? a.NT * 32 : 0));
+    double *s_sum = reinterpret_cast<double *>(s_ent + (ENT ? a.NT * 2 * GROUPS4 : 0));
     uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s_sum + (TRAIN ? a.len * a.w : 0));
     __shared__ unsigned s_cmax, s_c2max;
     __shared__ int s_bad;
@@ -130,7 +159,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     const unsigned id = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (id >= (unsigned)(a.P * a.ny)) return;
     const int part = (int)(id % (unsigned)a.P), by = (int)(id / (unsigned)a.P);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     const int half = lane >> 5;
     const int w = a.w, len = a.len;
     const float *part_cb = cb + (int64_t)part * len * w;
@@ -165,13 +194,18 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         for (int i = threadIdx.x; i < len; i += TH) s_cnt[i] = 0u;
     }
 
+    // entry e in LDS, and its |c|^2/2 (cosine: 1/|c|); from a multiple of 4 on 4 follow each other
+    auto ent_at = [&](int e) { return s_ent + (e >> 4) * GROUPS4 + ((e >> 2) & 3) * GROUP + (e & 3) * WP; };
+    auto norm_at = [&](int e) { return s_ent + (e >> 4) * GROUPS4 + ((e >> 2) & 3) * GROUP + 4 * WP + (e & 3); };
+    const float unscale = 1.0f / (scale * scale);
     // the entries into LDS, a thread prepares one at a time
     {
+        if (NORM && threadIdx.x < 4) s_half[threadIdx.x] = 0.0f;
         for (int e = threadIdx.x; e < a.NT * 32; e += TH) {
-            const int i = e;
             const bool real = e < len;
             const float rn = COS ? (real ? part_rn[e] : 0.0f) : 0.0f;
             float s2 = 0.0f;
+            half8 *tile = s_frag + (e >> 5) * UNITS;
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 half8 hi, lo;
@@ -179,7 +213,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                 for (int j = 0; j < 8; j++) {
                     const int d = 8 * g + j;
                     const float c = real && d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
-                    if constexpr (ENT) s_ent[(i >> 6) * PAIR + ((i >> 2) & 15) * CELL + (i & 3) * WP + d] = c;
+                    if constexpr (ENT) ent_at(e)[d] = c;
                     float cs = COS ? c * (rn * 1024.0f) : c * scale;
                     // one fp32 value for both pieces: the compiler may otherwise fold the product
                     // into one of the conversions and round the pieces from different values
@@ -188,33 +222,46 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                     hi[j] = (_Float16)(-cs);
                     lo[j] = (_Float16)(-cs - (float)hi[j]);
                 }
-                half8 *f = s_frag + ((i >> 5) * G + g) * 64 + (i & 31);
-                f[0] = hi;
-                f[32] = lo;
+                tile[32 * g + (e & 31)] = hi;
+                tile[32 * (G + g) + (e & 31)] = lo;
             }
-            s_half[i] = real ? (COS ? 0.0f : 0.5f * s2) : kPadScore;
-            if constexpr (ENT && COS) s_rn[i] = rn;
+            const float half2 = COS ? 0.0f : 0.5f * s2;
+            if constexpr (NORM) {
+                // a piece that would not be a normal half is left to the next one
+                const float n1 = half2 * (1.0f / kNormUnit1);
+                const _Float16 p1 = n1 < kMinHalf ? (_Float16)0.0f : (_Float16)n1;
+                const float r1 = half2 - (float)p1 * kNormUnit1, n2 = r1 * (1.0f / kNormUnit2);
+                const _Float16 p2 = fabsf(n2) < kMinHalf ? (_Float16)0.0f : (_Float16)n2;
+                const _Float16 p3 = (_Float16)(r1 - (float)p2 * kNormUnit2);
+                _Float16 *norm = reinterpret_cast<_Float16 *>(tile + 64 * G) + 4 * (e & 31);
+                norm[0] = real ? p1 : (_Float16)0.0f;
+                norm[1] = real ? p2 : (_Float16)0.0f;
+                norm[2] = real ? p3 : (_Float16)0.0f;
+                norm[3] = real ? (_Float16)0.0f : (_Float16)kPadPiece;
+            } else {
+                s_half[e] = real ? half2 : kPadScore;
+            }
+            if constexpr (ENT)
+                *norm_at(e) = COS ? rn : real ? half2 * unscale : kPadScore;
             if (!COS) atomicMax(&s_c2max, __float_as_uint(s2));
         }
     }
     __syncthreads();
     const bool part_bad = s_bad != 0;
     const float c2max = __uint_as_float(s_c2max) * 1.0001f;
-    const float unscale = 1.0f / (scale * scale);
     uint32_t keep = ~a.cell_mask;
     asm volatile("" : "+v"(keep));  // in a vector register: mask and cell number are then one instruction
 
     // entry e as the rule sees it (columns past w: zeros)
     auto entry = [&](int e, float (&c)[WP], float &rn) {
         if constexpr (ENT) {
-            const float4 *src = reinterpret_cast<const float4 *>(s_ent + (e >> 6) * PAIR +
-                                                                      ((e >> 2) & 15) * CELL + (e & 3) * WP);
+            const float4 *src = reinterpret_cast<const float4 *>(ent_at(e));
 #pragma unroll
             for (int k = 0; k < WP / 4; k++) {
                 const float4 v = src[k];
                 c[4 * k] = v.x; c[4 * k + 1] = v.y; c[4 * k + 2] = v.z; c[4 * k + 3] = v.w;
             }
-            rn = COS ? s_rn[e] : 0.0f;
+            rn = COS ? *norm_at(e) : 0.0f;
         } else {
             const float *src = part_cb + (int64_t)e * w;
             if (a.bvec) {
@@ -232,6 +279,10 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         }
     };
 
+    [[maybe_unused]] const half8 norm_units = {(_Float16)kNormUnit1, (_Float16)kNormUnit2, (_Float16)1.0f,
+                                               (_Float16)kPadUnit, 0, 0, 0, 0};
+    // (in units of 8 bytes, from the last group's low pieces)
+    [[maybe_unused]] const int last_piece = half ? 32 + lane : 2 * lane;
     float dsum = 0.0f;
     // Rows whose entries tie (0/1 features) are open more often than not; from a share on where the
     // scores and the rows searched one by one cost more than all rows by the rule, each lane for its
@@ -243,12 +294,10 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     int plain_left = 0;
     const float *s_plain = reinterpret_cast<const float *>(s_frag);
     auto plain_book = [&](int e) {  // entries e .. e + 3, e a multiple of 4
-        return ENT ? s_ent + (e >> 6) * PAIR + ((e >> 2) & 15) * CELL : s_plain + e * WP;
+        return ENT ? ent_at(e) : s_plain + e * WP;
     };
     constexpr int ROWS = WAVES * 64;
-    // a row past the last one reads the last one
-    auto load_row = [&](int64_t row, float (&v)[WP]) {
-        const T *src = a.x + (row < a.rows ? row : a.rows - 1) * a.D + (int64_t)part * w;
+    auto load_row = [&](const T *src, float (&v)[WP]) {
         if (a.vec) {  // w % 4 == 0, D % 4 == 0, 4 columns aligned
 #pragma unroll
             for (int k = 0; k < WP / 4; k++) {
@@ -261,14 +310,26 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             for (int d = 0; d < WP; d++) v[d] = d < w && part * w + d < a.D ? load1(src + d) : 0.0f;
         }
     };
+    // (a row past the last one reads the last one; 64-bit products only where a strip is not whole)
+    const int64_t step = (int64_t)a.ny * ROWS;
+    const T *const first_row = a.x + (int64_t)part * w;
+    auto clamped = [&](int64_t r0) {
+        const int64_t row = r0 + threadIdx.x;
+        return first_row + (row < a.rows ? row : a.rows - 1) * a.D;
+    };
+    const T *next = clamped((int64_t)by * ROWS);
+    auto load_next = [&](int64_t r0, float (&v)[WP]) {
+        next = r0 + step + ROWS <= a.rows ? next + step * a.D : clamped(r0 + step);
+        load_row(next, v);
+    };
     float xn[WP];
     [[maybe_unused]] int strip = 0;
-    load_row((int64_t)by * ROWS + wave * 64 + lane, xn);
-    for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += (int64_t)a.ny * ROWS) {
-        // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which both halves of
+    load_row(next, xn);
+    [[maybe_unused]] uint8_t *out = codes + ((int64_t)by * ROWS + threadIdx.x) * a.rb + part * a.cbytes;
+    for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += step) {
+        // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which the halves of
         // the wave then hold for both sets of 32 rows
-        const int64_t r = r0 + wave * 64 + lane;
-        const bool valid = r < a.rows;
+        const bool valid = (int64_t)threadIdx.x < a.rows - r0;
         float xr[WP];
 #pragma unroll
         for (int d = 0; d < WP; d++) xr[d] = xn[d];
@@ -291,8 +352,14 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             // (the entries' sums side by side: with two waves a SIMD nothing else hides an addition)
             auto take = [&](const float4 (&of)[EP][WP / 4], int e0, int n) {
                 float v[EP];
+                [[maybe_unused]] float rn[EP];
 #pragma unroll
                 for (int k = 0; k < EP; k++) v[k] = 0.0f;
+                if constexpr (COS) {
+                    const float *src = ENT ? norm_at(e0) : part_rn + e0;
+#pragma unroll
+                    for (int k = 0; k < EP; k++) rn[k] = src[ENT || k < n ? k : 0];
+                }
 #pragma unroll
                 for (int i = 0; i < WP / 4; i++)
 #pragma unroll
@@ -305,7 +372,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
 #pragma unroll
                 for (int k = 0; k < EP; k++) {
                     if (k >= n) break;
-                    if constexpr (COS) v[k] = -__fmul_rn(v[k], ENT ? s_rn[e0 + k] : part_rn[e0 + k]);
+                    if constexpr (COS) v[k] = -__fmul_rn(v[k], rn[k]);
                     if (v[k] < all_value) { all_value = v[k]; all_code = e0 + k; }
                 }
             };
@@ -326,7 +393,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         };
         if (plain || plain_left > 0) {
             plain_left--;
-            load_row(r + (int64_t)a.ny * ROWS, xn);
+            load_next(r0, xn);
             search_all();
             code = all_code;
             value = all_value;
@@ -344,35 +411,44 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             f = zero || bad ? 1.0f : ldexpf(1.0f, kScaleExp - e);
         }
         float s2 = 0.0f;
-        half8 xh[2][G], xl[2][G];
+        // products with the high pieces of the entries: the lower lanes multiply them with the row's high
+        // pieces, the upper ones with its low pieces; with their low pieces: two groups of columns side by
+        // side, of an odd last group beside |c|^2/2 (or the low pieces once more)
+        half8 xh[2][G], xl[2][LO];
+        {
+            uint32_t hi[4 * G], lo[4 * G];
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            uint32_t hi[4], lo[4];
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const float u = xr[8 * g + 2 * j] * f, v = xr[8 * g + 2 * j + 1] * f;
-                s2 = fmaf(u, u, s2);
-                s2 = fmaf(v, v, s2);
+            for (int j = 0; j < 4 * G; j++) {
+                const float u = xr[2 * j] * f, v = xr[2 * j + 1] * f;
                 const auto h = __builtin_amdgcn_cvt_pkrtz(u, v);
-                const auto l = __builtin_amdgcn_cvt_pkrtz(u - (float)h[0], v - (float)h[1]);
                 hi[j] = __builtin_bit_cast(uint32_t, h);
-                lo[j] = __builtin_bit_cast(uint32_t, l);
+                // |x|^2 from the high pieces, short of it by less than 2^-9 of itself (vq_margin)
+                s2 = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, h), __builtin_bit_cast(half2v, h), s2, false);
+                lo[j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(less_low(u, hi[j]), less_high(v, hi[j])));
             }
-            uint32_t set[2][2][4];
+            // one exchange of halves of two registers: [rows 0..31 of both], [rows 32..63 of both]
+            auto both = [&](half8 (&x0), half8 (&x1), const uint32_t *p, const uint32_t *q) {
+                uint32_t set[2][4];
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                // one exchange of halves: [rows 0..31 twice], [rows 32..63 twice]
-                const auto h = __builtin_amdgcn_permlane32_swap(hi[j], hi[j], false, false);
-                const auto l = __builtin_amdgcn_permlane32_swap(lo[j], lo[j], false, false);
-                set[0][0][j] = h[0];
-                set[0][1][j] = h[1];
-                set[1][0][j] = l[0];
-                set[1][1][j] = l[1];
-            }
+                for (int j = 0; j < 4; j++) {
+                    const auto e = __builtin_amdgcn_permlane32_swap(p[j], q[j], false, false);
+                    set[0][j] = e[0];
+                    set[1][j] = e[1];
+                }
+                __builtin_memcpy(&x0, set[0], 16);
+                __builtin_memcpy(&x1, set[1], 16);
+            };
 #pragma unroll
-            for (int s = 0; s < 2; s++) {
-                __builtin_memcpy(&xh[s][g], set[0][s], 16);
-                __builtin_memcpy(&xl[s][g], set[1][s], 16);
+            for (int g = 0; g + 1 < G; g += 2) both(xl[0][g / 2], xl[1][g / 2], hi + 4 * g, hi + 4 * g + 4);
+#pragma unroll
+            for (int g = 0; g < G; g++) both(xh[0][g], xh[1][g], hi + 4 * g, lo + 4 * g);
+            if constexpr (G % 2 == 1) {
+#pragma unroll
+                for (int s = 0; s < 2; s++) {
+                    xl[s][LO - 1] = xh[s][G - 1];
+                    if constexpr (NORM)
+                        if (half) xl[s][LO - 1] = norm_units;
+                }
             }
         }
         bad |= !(s2 < kMaxNorm2);  // also NaN
@@ -382,120 +458,158 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         const float cell_margin = COS ? sqrtf(s2) * a.cell_margin / f : big * unscale * a.cell_margin;
         if constexpr (COS) zero = zero && s2 == 0.0f && !part_bad;  // not a NaN that fmaxf passed over
         // the next strip's rows travel during this strip's search
-        load_row(r + (int64_t)a.ny * ROWS, xn);
+        load_next(r0, xn);
         float best[2] = {3e38f, 3e38f}, second[2] = {3e38f, 3e38f};
         {
             const int nt = a.NT;
             // A set's minima are taken while the matrix cores work on the other set: the next tile's
             // product is started as soon as its accumulators are free, its operands having been
             // read from LDS one half-step earlier.
-            half8 ent[G];
+            half8 eh[G], el[LO];
             float16v c;
             auto fetch = [&](int t) {
+                const half8 *tile = s_frag + t * UNITS;
+                if constexpr (!NORM) {
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const float4 n = *reinterpret_cast<const float4 *>(s_half + t * 32 + 8 * q + 4 * half);
-                    c[4 * q] = n.x; c[4 * q + 1] = n.y; c[4 * q + 2] = n.z; c[4 * q + 3] = n.w;
+                    for (int q = 0; q < 4; q++) {
+                        const float4 n = *reinterpret_cast<const float4 *>(s_half + t * 32 + 8 * q + 4 * half);
+                        c[4 * q] = n.x; c[4 * q + 1] = n.y; c[4 * q + 2] = n.z; c[4 * q + 3] = n.w;
+                    }
                 }
 #pragma unroll
-                for (int g = 0; g < G; g++) ent[g] = s_frag[(t * G + g) * 64 + lane];
+                for (int g = 0; g < G; g++) eh[g] = tile[32 * g + (lane & 31)];
+#pragma unroll
+                for (int g = 0; g < G / 2; g++) el[g] = tile[32 * G + 64 * g + lane];
+                if constexpr (NORM) {
+                    // (the upper lanes: their entry's 8 bytes and the 8 after them, which meet zeros)
+                    const uint2 *p = reinterpret_cast<const uint2 *>(tile + 32 * (2 * G - 1)) + last_piece;
+                    const uint2 v0 = p[0], v1 = p[1];
+                    const uint4 v = make_uint4(v0.x, v0.y, v1.x, v1.y);
+                    __builtin_memcpy(&el[LO - 1], &v, 16);
+                } else if constexpr (G % 2 == 1) {
+                    el[LO - 1] = tile[32 * (2 * G - 1) + (lane & 31)];
+                }
             };
             float16v acc[2];
             auto product = [&](int s) {
-                acc[s] = c;
+                if constexpr (NORM) {
 #pragma unroll
-                for (int g = 0; g < G; g++) {
-                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent[g], xh[s][g], acc[s], 0, 0, 0);
-                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ent[g], xl[s][g], acc[s], 0, 0, 0);
+                    for (int i = 0; i < 16; i++) acc[s][i] = 0.0f;
+                } else {
+                    acc[s] = c;
                 }
-            };
-            float part4[2][4];  // of the pair's first tile
-            auto first = [&](int s) {
 #pragma unroll
-                for (int q = 0; q < 4; q++)
-                    part4[s][q] = minimum(minimum(minimum(acc[s][4 * q], acc[s][4 * q + 1]), acc[s][4 * q + 2]),
-                                          acc[s][4 * q + 3]);
-            };
-            auto minima = [&](int s, int t) {
+                for (int g = 0; g < G; g++)
+                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(eh[g], xh[s][g], acc[s], 0, 0, 0);
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
+                for (int g = 0; g < LO; g++)
+                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(el[g], xl[s][g], acc[s], 0, 0, 0);
+            };
+            // (the runner-up of a tile's two keys waits for the next tile's: one instruction for both; with
+            // more columns the registers are missed elsewhere)
+            constexpr bool PAIRED = G == 1;
+            float runner[2] = {3e38f, 3e38f};
+            auto minima = [&](int s, int t, auto odd) {
+                float key[2];
+#pragma unroll
+                for (int q = 0; q < 2; q++) {
                     uint32_t number = (uint32_t)(2 * t + q);
                     asm volatile("" : "+s"(number));  // one scalar: the compiler would add it up per lane
-                    const float m = minimum(minimum(minimum(minimum(part4[s][q], acc[s][4 * q]), acc[s][4 * q + 1]),
-                                                    acc[s][4 * q + 2]), acc[s][4 * q + 3]);
+                    float m = acc[s][8 * q];
+#pragma unroll
+                    for (int i = 1; i < 7; i += 2) m = minimum(minimum(m, acc[s][8 * q + i]), acc[s][8 * q + i + 1]);
+                    m = minimum(m, acc[s][8 * q + 7]);
                     // the cell's number replaces the low bits of its score
-                    const float key = __uint_as_float((__float_as_uint(m) & keep) | number);
-                    second[s] = __builtin_amdgcn_fmed3f(best[s], second[s], key);
-                    best[s] = minimum(best[s], key);
+                    key[q] = __uint_as_float((__float_as_uint(m) & keep) | number);
                 }
+                const float r = __builtin_amdgcn_fmed3f(best[s], key[0], key[1]);
+                if constexpr (!PAIRED) second[s] = minimum(second[s], r);
+                else if constexpr (odd.value) second[s] = minimum(minimum(second[s], runner[s]), r);
+                else runner[s] = r;
+                best[s] = minimum(minimum(best[s], key[0]), key[1]);
             };
             fetch(0);
             product(0);
             product(1);
-            fetch(1);
-            for (int t = 0; t < nt; t += 2) {
-                // (past the last tile its product is computed once more and dropped; c outlives both
-                // products of a step: one of them would otherwise take over its registers, and 32
-                // copies would put things back in place)
+            if constexpr (!NORM) asm volatile("" : : "v"(c));
+            fetch(min(1, nt - 1));
+            auto tile = [&](int t, auto odd) {
+                // (c outlives both products of a step: one of them would otherwise take over its
+                // registers, and 32 copies would put things back in place)
                 __builtin_amdgcn_sched_barrier(0);
-                first(0);
+                minima(0, t, odd);
                 __builtin_amdgcn_sched_barrier(0);
                 product(0);
-                first(1);
+                minima(1, t, odd);
                 __builtin_amdgcn_sched_barrier(0);
                 product(1);
-                asm volatile("" : : "v"(c));
+                if constexpr (!NORM) asm volatile("" : : "v"(c));
                 fetch(min(t + 2, nt - 1));
+            };
+            int t = 0;
+            if constexpr (!PAIRED)
+                for (; t + 1 < nt; t++) tile(t, std::false_type());
+            for (; PAIRED && t + 2 < nt; t += 2) {
+                tile(t, std::false_type());
+                tile(t + 1, std::true_type());
+            }
+            if (PAIRED && t + 1 < nt) {
+                tile(t, std::false_type());
+                t++;
                 __builtin_amdgcn_sched_barrier(0);
-                minima(0, t);
+                minima(0, t, std::true_type());
+                minima(1, t, std::true_type());
+            } else {
                 __builtin_amdgcn_sched_barrier(0);
-                product(0);
-                minima(1, t);
-                __builtin_amdgcn_sched_barrier(0);
-                product(1);
-                asm volatile("" : : "v"(c));
-                fetch(min(t + 3, nt - 1));
+                minima(0, t, std::false_type());
+                minima(1, t, std::false_type());
+#pragma unroll
+                for (int s = 0; s < 2; s++) second[s] = PAIRED ? minimum(second[s], runner[s]) : second[s];
             }
         }
-        // ---- the two halves of the wave hold different cells of the same rows; afterwards lane
-        // half h decides the rows of set h
-        float b = 0.0f, gap = 0.0f;
-        int h_of = 0;
-#pragma unroll
-        for (int s = 0; s < 2; s++) {
-            const float ob = __shfl_xor(best[s], 32), os = __shfl_xor(second[s], 32);
-            const float lo = minimum(best[s], ob), hi = fmaxf(best[s], ob);
-            const float g = minimum(hi, minimum(second[s], os)) - lo;
-            if (half == s) {
-                b = lo;
-                gap = g;
-                h_of = best[s] <= ob ? half : 1 - half;
-            }
+        // ---- the two halves of the wave hold different cells of the same rows; one exchange gives lane
+        // half h both cells of the rows of set h, which it then decides
+        float b, gap;
+        int h_of;
+        {
+            const auto eb = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[0]), __float_as_uint(best[1]),
+                                                             false, false);
+            const auto es = __builtin_amdgcn_permlane32_swap(__float_as_uint(second[0]), __float_as_uint(second[1]),
+                                                             false, false);
+            const float b0 = __uint_as_float(eb[0]), b1 = __uint_as_float(eb[1]);
+            b = minimum(b0, b1);
+            gap = minimum(minimum(__builtin_elementwise_maximum(b0, b1), __uint_as_float(es[0])),
+                          __uint_as_float(es[1])) - b;
+            h_of = b0 <= b1 ? 0 : 1;
         }
         const uint32_t cell = __float_as_uint(b) & a.cell_mask;
         bool open = !(gap > margin);  // the rule has to look at all entries
         // ---- the cell's 8 entries in fp32, again with the second best; rows too close to call join
         // the open ones
         {
-            // cell number = 2 * (first tile) + q; entries 8q + 4h .. + 3 of both tiles
-            const uint32_t e0 = open ? 0u : (cell >> 2) * 64u + (cell & 3u) * 8u + 4u * (uint32_t)h_of;
-            // (in LDS the two runs of 4 entries are 8 cells of 4 apart)
-            const float *near_ent = s_ent + (e0 >> 6) * (uint32_t)PAIR + ((e0 >> 2) & 15u) * (uint32_t)CELL;
-            const float *near_half = s_half + e0, *near_rn = s_rn + e0;
-            float b1 = 3e38f, b2 = 3e38f;
+            // the cell's entries are those from 16 * its number + 4h on, 4 of them and 4 from 8 further on
+            const uint32_t c0 = open ? 0u : cell, h4 = open ? 0u : 4u * (uint32_t)h_of, e0 = c0 * 16u + h4;
+            const float *near_ent = s_ent + __umul24(c0, GROUPS4) + __umul24(h4, GROUP / 4);
+            float4 near_norm[2];
+            if constexpr (ENT) {
+                near_norm[0] = *reinterpret_cast<const float4 *>(near_ent + 4 * WP);
+                near_norm[1] = *reinterpret_cast<const float4 *>(near_ent + 2 * GROUP + 4 * WP);
+            }
+            float b1 = 3e38f, b2 = 3e38f, key[2];
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                const int e = (int)e0 + (k & 3) + 32 * (k >> 2);
+                const int e = (int)e0 + (k & 3) + 8 * (k >> 2);
+                [[maybe_unused]] const float4 nn = near_norm[k >> 2];
+                [[maybe_unused]] const float norm = (k & 3) == 0 ? nn.x : (k & 3) == 1 ? nn.y : (k & 3) == 2 ? nn.z : nn.w;
                 float c[WP], rn, sc = 0.0f;
                 if constexpr (ENT) {
-                    const float4 *src =
-                        reinterpret_cast<const float4 *>(near_ent + (k >> 2) * 8 * CELL + (k & 3) * WP);
+                    const float4 *src = reinterpret_cast<const float4 *>(near_ent + (k >> 2) * 2 * GROUP + (k & 3) * WP);
 #pragma unroll
                     for (int i = 0; i < WP / 4; i++) {
                         const float4 v = src[i];
                         c[4 * i] = v.x; c[4 * i + 1] = v.y; c[4 * i + 2] = v.z; c[4 * i + 3] = v.w;
                     }
-                    rn = COS ? near_rn[(k & 3) + 32 * (k >> 2)] : 0.0f;
+                    rn = norm;
                 } else {
                     entry(min(e, len - 1), c, rn);
                 }
@@ -504,7 +618,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                     for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
                     sc *= rn;
                 } else if constexpr (ENT) {
-                    sc = near_half[(k & 3) + 32 * (k >> 2)] * unscale;
+                    sc = norm;
 #pragma unroll
                     for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
                 } else {
@@ -512,13 +626,15 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                     for (int d = 0; d < WP; d++) sc = fmaf(c[d], fmaf(0.5f, c[d], -xr[d]), sc);
                 }
                 if ((!ENT || COS) && e >= len) sc = 3e38f;
-                const float key = __uint_as_float((__float_as_uint(sc) & ~7u) | (uint32_t)k);
-                b2 = __builtin_amdgcn_fmed3f(b1, b2, key);
-                b1 = minimum(b1, key);
+                key[k & 1] = __uint_as_float((__float_as_uint(sc) & ~7u) | (uint32_t)k);
+                if (k & 1) {
+                    b2 = minimum(b2, __builtin_amdgcn_fmed3f(b1, key[0], key[1]));
+                    b1 = minimum(minimum(b1, key[0]), key[1]);
+                }
             }
             const int k = (int)(__float_as_uint(b1) & 7u);
             open |= !(b2 - b1 > cell_margin);
-            code = (int)e0 + (k & 3) + 32 * (k >> 2);
+            code = (int)e0 + (k & 3) + 8 * (k >> 2);
             if constexpr (TRAIN) {  // the rule's distance; an open row's is found below
                 float c[WP], rn;
                 entry(min(code, len - 1), c, rn);
@@ -609,12 +725,12 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
 #pragma unroll
             for (int d = 0; d < WP; d++) asm volatile("" : "+v"(xn[d]));
             if (valid) {
-                uint8_t *row = codes + r * a.rb;
-                if (a.cbytes == 1) row[part] = (uint8_t)code;
-                else reinterpret_cast<uint16_t *>(row)[part] = (uint16_t)code;
+                if (a.cbytes == 1) *out = (uint8_t)code;
+                else *reinterpret_cast<uint16_t *>(out) = (uint16_t)code;
                 if (part == 0)
-                    for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) row[k] = 0;  // padding
+                    for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) out[k] = 0;  // padding
             }
+            out += step * a.rb;
         }
     }
     if constexpr (TRAIN) {
@@ -661,17 +777,19 @@ __global__ __launch_bounds__(kThreads) void vq_means_kernel(const float *__restr
 // Bound on how far the difference of two scores can be from what the rule decides on, relative to
 // M = |x|^2 + max|c|^2 (scaled; every |score| and half of every squared distance is at most M;
 // cosine: M = |x||c|).  u = 2^-24.
-//   pieces: x rounded towards zero twice (2^-20 of each column), c to nearest twice (2^-22); by
-//     Cauchy at most (2^-20 + 2^-22) M/2 per score, and what is lost below the smallest normal
-//     half (2^-14 of codebooks scaled to 2^10) at most 2^-20 M: 2^-19 M per score
-//   sums: 32 products per 8 columns and the constant added in fp32, each addition to 2u M;
-//     the constant itself (w + 2) u M
+//   pieces: x rounded towards zero twice (2^-20 of each column), c to nearest twice (2^-22), the
+//     product of the low pieces left out (2^-10 . 2^-11); by Cauchy at most 7 . 2^-22 M/2 per score,
+//     and what is lost below the smallest normal half (2^-14 of codebooks scaled to 2^10) at most
+//     2^-20 M: 2^-19 M per score
+//   sums: at most 32 products per 8 columns and the constant added in fp32, each addition to 2u M;
+//     the constant itself (w + 2) u M and, in pieces, 2^-33 of it
 //   the cell number in the low bits: 2^(bits - 23) M
 //   the rule: distances (w + 2) u relative, i.e. (w + 2) u M per score
-// twice that for two scores, and a quarter on top.
+// twice that for two scores, and a quarter on top (in which |x|^2 from the high pieces, short of it by
+// less than 2^-9 of itself, is covered).
 float vq_margin(int w, int len) {
     const double u = ldexp(1.0, -24);
-    const int groups = (w + 7) / 8, cell_bits = ilog2(4 * ((len + 63) / 64));
+    const int groups = (w + 7) / 8, cell_bits = ilog2(2 * ((len + 31) / 32));
     const double score = ldexp(1.0, -19) + 2.0 * u * (32.0 * groups + 2.0) + ldexp(1.0, cell_bits - 23) +
                          2.0 * u * (w + 4.0);
     return (float)(1.25 * 2.0 * score);
@@ -685,9 +803,8 @@ float vq_cell_margin(int w) {
 
 size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    const bool cosine = p->scheme.vq_metric == BIFEAT_VQ_COSINE;
-    size_t n = (size_t)NT * G * 1024 + sizeof(float) * NT * 32;
-    if (ent) n += sizeof(float) * ((size_t)NT / 2 * (16 * (32 * G + 4) + 4) + (cosine ? NT * 32 : 0));
+    size_t n = (size_t)NT * tile_units(G, ent) * 16 + (norm_slot(G, ent) ? 16 : sizeof(float) * NT * 32);
+    if (ent) n += sizeof(float) * (size_t)NT * 2 * groups4_floats(G);
     if (train) n += (size_t)len * (sizeof(double) * w + sizeof(uint32_t));
     return n;
 }
@@ -696,7 +813,7 @@ size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) 
 // (training: when it fits at all); else as many pieces as a CU holds, the rule reading its few
 // entries from L2.
 bool entries_in_lds(const bifeat_params *p, bool train) {
-    const int G = (p->scheme.vq_width + 7) / 8, tiles = (p->scheme.vq_length + 63) / 64 * 2;
+    const int G = (p->scheme.vq_width + 7) / 8, tiles = (p->scheme.vq_length + 31) / 32;
     const int64_t limit = train ? kCuLds - 1024 : kCuLds / nearest_waves(G, true);
     return (int64_t)nearest_lds(p, G, tiles, true, train) <= limit;
 }
@@ -763,7 +880,7 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
 template <typename T, int G, int METRIC>
 bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStream_t s) {
     const bool train = codes == nullptr;
-    const int tiles = (a.len + 63) / 64 * 2;
+    const int tiles = (a.len + 31) / 32;
     const bool ent = entries_in_lds(p, train);
     a.NT = tiles;
     const size_t lds = nearest_lds(p, G, a.NT, ent, train);
@@ -777,7 +894,7 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
 
 template <typename T, int G>
 bool launch_groups(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStream_t s) {
-    const int cell_bits = ilog2(4 * ((a.len + 63) / 64));
+    const int cell_bits = ilog2(2 * ((a.len + 31) / 32));
     a.margin = vq_margin(a.w, a.len);
     a.cell_margin = vq_cell_margin(a.w);
     a.cell_mask = (1u << cell_bits) - 1u;
@@ -823,7 +940,7 @@ bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, 
 // 54) and for those whose pieces do not fit LDS at once (16384 x 16: 2.7 ms against 4.9).
 bool vq_nearest_takes(const bifeat_params *p, bool train) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    const int G = (w + 7) / 8, tiles = (len + 63) / 64 * 2;
+    const int G = (w + 7) / 8, tiles = (len + 31) / 32;
     if (w > kNearestMaxWidth || w * len < kNearestMinBook) return false;
     if (nearest_lds(p, G, tiles, false, false) > kCuLds - 4096) return false;
     const double gap = pow((double)len, -2.0 / w) * std::min(1.0, 2.0 / w);

@@ -63,6 +63,20 @@ def test_codes_equal_the_plain_search(bf, torch, D, w, length, rows, dtype, metr
     _check(bf, torch, x, cb, D, w, length, metric)
 
 
+# every entry of every cell wins, in odd and even numbers of tiles; entries of very different lengths (their
+# squares in pieces next to the product, or the accumulators' start), padding entries beside real ones
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("w,length", [(8, 96), (8, 160), (8, 289), (5, 97), (16, 96), (16, 65), (24, 97), (24, 33), (32, 31),
+                                      (32, 96), (8, 1056), (24, 480)])
+def test_every_entry_of_every_tile(bf, torch, w, length, metric):
+    rng = np.random.default_rng(w * 1000 + length)
+    cb = _codebook(rng, 2 * w, w, length) * np.float32(10.0) ** -rng.uniform(0, 4, size=(2, length, 1)).astype(np.float32)
+    cb = cb.astype(np.float32)
+    x = np.concatenate([cb[0], cb[1][::-1]], 1)
+    x = np.concatenate([x, x * np.float32(1.0001), x + rng.normal(size=x.shape).astype(np.float32) * np.float32(1e-4)])
+    _check(bf, torch, x.astype(np.float32), cb, 2 * w, w, length, metric)
+
+
 @pytest.mark.parametrize("metric", ["l2", "cosine"])
 @pytest.mark.parametrize("scale", [1e-30, 1e-6, 1.0, 1e5, 1e18])
 def test_scale_of_the_data(bf, torch, scale, metric):
