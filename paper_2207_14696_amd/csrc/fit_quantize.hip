@@ -129,7 +129,7 @@ template <typename T, int W, int WMAX, int METRIC, typename CODE>
 __global__ __launch_bounds__(kThreads) void vq_assign_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w_rt, int len, int P, int EC,
     const float *__restrict__ cb, const float *__restrict__ rnorm, uint8_t *__restrict__ codes,
-    int64_t rb) {
+    int64_t rb, int64_t pb) {
     extern __shared__ float s_cb[];
     const int w = W > 0 ? W : w_rt;
     float *s_rn = s_cb + EC * w;
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void vq_assign_kernel(
             }
         }
         if (valid) {
-            reinterpret_cast<CODE *>(codes + r * rb)[p] = (CODE)best;
+            *reinterpret_cast<CODE *>(codes + r * rb + p * pb) = (CODE)best;
             if (p == 0)
                 for (int64_t b = (int64_t)P * sizeof(CODE); b < rb; b++) codes[r * rb + b] = 0;  // row padding
         }
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kThreads) void vq_assign_kernel(
 }
 
 template <typename T, int W, int WMAX>
-static void launch_vq_w(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
+static void launch_vq_w(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                         hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const bool cosine = p->scheme.vq_metric == BIFEAT_VQ_COSINE;
@@ -204,7 +204,7 @@ static void launch_vq_w(bifeat_params *p, const T *x, int64_t rows, uint8_t *cod
     const size_t shm = sizeof(float) * ((size_t)EC * w + (cosine ? EC : 0));
 #define BF_VQ(M, CODE)                                                                   \
     vq_assign_kernel<T, W, WMAX, M, CODE><<<grid, kThreads, shm, s>>>(                  \
-        x, rows, (int)p->D, w, len, p->P, EC, p->d_cb, p->d_rnorm, codes, rb)
+        x, rows, (int)p->D, w, len, p->P, EC, p->d_cb, p->d_rnorm, codes, rb, pb)
     if (p->cbytes == 1) {
         if (cosine) BF_VQ(BIFEAT_VQ_COSINE, uint8_t);
         else BF_VQ(BIFEAT_VQ_L2, uint8_t);
@@ -216,29 +216,29 @@ static void launch_vq_w(bifeat_params *p, const T *x, int64_t rows, uint8_t *cod
 }
 
 template <typename T>
-void launch_vq_assign(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
+void launch_vq_assign(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                       hipStream_t s) {
     const int w = p->scheme.vq_width;
     // the matrix-core search gives the same codes; what it leaves (wide parts, tiny codebooks, dense
     // ones and those that do not fit LDS) takes the plain search
-    if (launch_vq_nearest_codes<T>(p, x, rows, codes, rb, s)) return;
+    if (launch_vq_nearest_codes<T>(p, x, rows, codes, rb, pb, s)) return;
     switch (w) {
-        case 1: launch_vq_w<T, 1, 1>(p, x, rows, codes, rb, s); break;
-        case 2: launch_vq_w<T, 2, 2>(p, x, rows, codes, rb, s); break;
-        case 4: launch_vq_w<T, 4, 4>(p, x, rows, codes, rb, s); break;
-        case 8: launch_vq_w<T, 8, 8>(p, x, rows, codes, rb, s); break;
-        case 16: launch_vq_w<T, 16, 16>(p, x, rows, codes, rb, s); break;
+        case 1: launch_vq_w<T, 1, 1>(p, x, rows, codes, rb, pb, s); break;
+        case 2: launch_vq_w<T, 2, 2>(p, x, rows, codes, rb, pb, s); break;
+        case 4: launch_vq_w<T, 4, 4>(p, x, rows, codes, rb, pb, s); break;
+        case 8: launch_vq_w<T, 8, 8>(p, x, rows, codes, rb, pb, s); break;
+        case 16: launch_vq_w<T, 16, 16>(p, x, rows, codes, rb, pb, s); break;
         default:
-            if (w <= 32) launch_vq_w<T, 0, 32>(p, x, rows, codes, rb, s);
-            else if (w <= 64) launch_vq_w<T, 0, 64>(p, x, rows, codes, rb, s);
-            else launch_vq_w<T, 0, 128>(p, x, rows, codes, rb, s);
+            if (w <= 32) launch_vq_w<T, 0, 32>(p, x, rows, codes, rb, pb, s);
+            else if (w <= 64) launch_vq_w<T, 0, 64>(p, x, rows, codes, rb, pb, s);
+            else launch_vq_w<T, 0, 128>(p, x, rows, codes, rb, pb, s);
             break;
     }
 }
-template void launch_vq_assign<float>(bifeat_params *, const float *, int64_t, uint8_t *, int64_t,
+template void launch_vq_assign<float>(bifeat_params *, const float *, int64_t, uint8_t *, int64_t, int64_t,
                                       hipStream_t);
-template void launch_vq_assign<__half>(bifeat_params *, const __half *, int64_t, uint8_t *, int64_t,
-                                       hipStream_t);
+template void launch_vq_assign<__half>(bifeat_params *, const __half *, int64_t, uint8_t *, int64_t, int64_t,
+                                      hipStream_t);
 
 hipError_t launch_quantize(bifeat_params *p, const void *chunk, int dtype, int64_t rows,
                            uint8_t *codes, hipStream_t s) {
@@ -246,8 +246,8 @@ hipError_t launch_quantize(bifeat_params *p, const void *chunk, int dtype, int64
     const size_t esz = dtype == BIFEAT_F32 ? 4 : 2;
     const bool vec = (D % 4 == 0) && ((uintptr_t)chunk % (4 * esz) == 0);
     if (p->scheme.kind == BIFEAT_VQ) {
-        if (dtype == BIFEAT_F32) launch_vq_assign(p, (const float *)chunk, rows, codes, p->rb, s);
-        else launch_vq_assign(p, (const __half *)chunk, rows, codes, p->rb, s);
+        if (dtype == BIFEAT_F32) launch_vq_assign(p, (const float *)chunk, rows, codes, p->rb, p->cbytes, s);
+        else launch_vq_assign(p, (const __half *)chunk, rows, codes, p->rb, p->cbytes, s);
     } else if (dtype == BIFEAT_F32) {
         return launch_quantize_sq_src(p, ChunkSrc<float>{(const float *)chunk, D}, rows, codes, vec, s);
     } else {

@@ -61,7 +61,7 @@ struct VqNearestArgs {
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
     uint32_t cell_mask;     // low bits of a score that hold a cell's number
-    int64_t rb;             // (the encoder)
+    int64_t rb, pb;         // (the encoder) from one row's index, one part's to the next
     int one_set;            // (training) every workgroup adds to one set of sums, all zeros
     float *sums;            // [ny][P][w][len]
     uint32_t *counts;       // [ny][P][len]
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     float xn[WP];
     [[maybe_unused]] int strip = 0;
     load_row(next, xn);
-    [[maybe_unused]] uint8_t *out = codes + ((int64_t)by * ROWS + threadIdx.x) * a.rb + part * a.cbytes;
+    [[maybe_unused]] uint8_t *out = codes + ((int64_t)by * ROWS + threadIdx.x) * a.rb + part * a.pb;
     for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += step) {
         // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which the halves of
         // the wave then hold for both sets of 32 rows
@@ -904,8 +904,8 @@ bool launch_groups(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
 
 // codes == nullptr: training
 template <typename T>
-bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, double *distortion,
-                    hipStream_t s) {
+bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
+                    double *distortion, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     if (!vq_nearest_takes(p, !codes)) return false;
     VqNearestArgs<T> a{};
@@ -920,6 +920,7 @@ bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, 
     a.vec = w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
     a.rnorm = p->d_rnorm;
     a.rb = rb;
+    a.pb = pb;
     a.distortion = distortion;
     switch ((w + 7) / 8) {
         case 1: return launch_groups<T, 1>(p, a, codes, s);
@@ -954,18 +955,19 @@ void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts
 }
 
 template <typename T>
-bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
+bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                              hipStream_t s) {
-    return launch_nearest<T>(p, x, rows, codes, rb, nullptr, s);
+    return launch_nearest<T>(p, x, rows, codes, rb, pb, nullptr, s);
 }
 
 template <typename T>
 bool launch_vq_nearest_round(bifeat_params *p, const T *x, int64_t rows, double *distortion, hipStream_t s) {
-    return launch_nearest<T>(p, x, rows, nullptr, 0, distortion, s);
+    return launch_nearest<T>(p, x, rows, nullptr, 0, 0, distortion, s);
 }
 
 #define BF_VN(T)                                                                                              \
-    template bool launch_vq_nearest_codes<T>(bifeat_params *, const T *, int64_t, uint8_t *, int64_t, hipStream_t); \
+    template bool launch_vq_nearest_codes<T>(bifeat_params *, const T *, int64_t, uint8_t *, int64_t, int64_t,       \
+                                             hipStream_t);                                                     \
     template bool launch_vq_nearest_round<T>(bifeat_params *, const T *, int64_t, double *, hipStream_t);
 BF_VN(float)
 BF_VN(__half)

@@ -11,10 +11,9 @@ namespace bf {
 // calls below return false, with nothing launched, when it does not.)
 bool vq_nearest_takes(const bifeat_params *p, bool train);
 
-// the index of every part's nearest entry into the rows at `codes` (row stride rb bytes, indices
-// of p->cbytes bytes, the bytes behind them zeroed)
+// the index of every part's nearest entry, see launch_vq_assign
 template <typename T>
-bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb,
+bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                              hipStream_t s);
 
 // one Lloyd round over the rows (Euclidean codebooks): every entry becomes the mean of the parts

@@ -21,6 +21,8 @@
 #include "common.hpp"
 #include "vq_nearest.hpp"
 
+#include <algorithm>
+
 namespace bf {
 
 namespace {
@@ -152,80 +154,145 @@ __global__ void vq_rnorm_kernel(const float *__restrict__ cb, int64_t entries, i
     }
 }
 
-// Sums, counts and squared distance from a dense code array codes[r][p].  A workgroup takes one
-// part, as many of its columns (the count is one more) as LDS holds sums for - 64-bit ones, see
+// Sums, counts and squared distance from the codes, one part's after the other.  A workgroup takes
+// one part, as many of its columns (the count is one more) as LDS holds sums for - 64-bit ones, see
 // vq_nearest.hip - and every ny-th strip of rows, and writes its sums to the workspace:
 // sums [ny][P][w][len], counts [ny][P][len]; or adds them to the one (zeroed) set there is room for.
-// Before, every value was an atomic on memory (1.1 M per part and round at 65 536 rows of 16
-// columns) and every wave one on the distortion: 1.7 ms of a round's 2.8 at 8 x 2048 x 16.
+// What bounds it: the LDS adds (22 cycles a wave, 36 us for 65 536 rows of 96 x 8 columns) and reading
+// the sample once more (40 us).  For that 4 columns are loaded at a time (VEC) and lanes share a row
+// (a load of one lane per row touches 64 lines), workgroups of the same rows run at the same time on one
+// XCD (four parts of 8 columns share a line), and a wave's codes are consecutive.  A round's sums of
+// that shape: 68 us; one lane per row 89; with 4-byte loads, codes row by row and the parts dealt over
+// the XCDs 475.
 constexpr int kAccThreads = 1024;
-constexpr int64_t kAccLds = 144 * 1024;
+constexpr int64_t kAccLds = 145 * 1024;
+constexpr int kAccRows = 2;
+// from one column's sums to the next: odd, so that lanes that add columns of one row meet different banks
+__host__ __device__ constexpr int acc_stride(int len) { return len | 1; }
 
-template <typename T, typename CODE>
+template <typename T, typename CODE, bool VEC>
 __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w, int len, int P, const CODE *__restrict__ codes,
-    const float *__restrict__ cb, int DG, int groups, int ny, int one_set, float *__restrict__ sums,
+    const float *__restrict__ cb, int DG, int more, int groups, int ny, int lanes, int one_set, float *__restrict__ sums,
     uint32_t *__restrict__ counts, double *__restrict__ distortion) {
-    extern __shared__ double s_acc[];  // [DG][len]
+    extern __shared__ double s_acc[];  // [columns][acc_stride]
+    const int ls = acc_stride(len);
     __shared__ double s_dist;
-    const int grp = blockIdx.x % groups, p = blockIdx.x / groups % P, by = blockIdx.x / (groups * P);
-    const int c0 = grp * DG, nc = min(DG, w + 1 - c0);  // columns c0.. ; column w counts
-    for (int i = threadIdx.x; i < nc * len; i += kAccThreads) s_acc[i] = 0.0;
+    // workgroups are dealt to the XCDs in turn: consecutive logical ids belong on one XCD
+    const int id = (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)), TH = blockDim.x;
+    if (id >= groups * P * ny) return;
+    const int grp = id % groups, p = id / groups % P, by = id / (groups * P);
+    const int c0 = grp * DG, nc = min(DG + (grp == groups - 1 ? more : 0), w + 1 - c0);  // column w counts
+    const int nd = min(nc, w - c0);
+    for (int i = threadIdx.x; i < nc * ls; i += TH) s_acc[i] = 0.0;
     if (threadIdx.x == 0) s_dist = 0.0;
     __syncthreads();
     float dsum = 0.0f;
-    for (int64_t r = (int64_t)by * kAccThreads + threadIdx.x; r < rows; r += (int64_t)ny * kAccThreads) {
-        const int code = codes[r * P + p];
-        const float *ent = cb + ((int64_t)p * len + code) * w;
-#pragma unroll 4
-        for (int j = 0; j < nc; j++) {
-            const int d = c0 + j, col = p * w + d;
-            if (d < w) {
-                const float xv = col < D ? load1(x + r * D + col) : 0.0f;
-                unsafeAtomicAdd(&s_acc[(int64_t)j * len + code], (double)xv);
-                const float diff = xv - ent[d];
-                dsum += diff * diff;
-            } else {
-                unsafeAtomicAdd(&s_acc[(int64_t)j * len + code], 1.0);
+    const CODE *part_codes = codes + p * rows;
+    const int left = D - (p * w + c0);  // columns that the table has
+    auto add = [&](double *acc, int j, float xv, float ev) {
+        unsafeAtomicAdd(acc + j * ls, (double)xv);
+        const float diff = xv - ev;
+        dsum += diff * diff;
+    };
+    if constexpr (VEC) {
+        // `lanes` lanes (a power of two that divides the fours of columns) share a row: fewer lines an
+        // instruction; a lane has kAccRows rows in flight
+        const int lq = threadIdx.x & (lanes - 1), at = threadIdx.x / lanes, step = TH / lanes;
+        for (int64_t r0 = (int64_t)by * TH * kAccRows; r0 < rows; r0 += (int64_t)ny * TH * kAccRows) {
+            const int64_t end = min(rows, r0 + (int64_t)TH * kAccRows);
+            for (int64_t r = r0 + at; r < end; r += (int64_t)step * kAccRows) {
+                int code[kAccRows];
+#pragma unroll
+                for (int k = 0; k < kAccRows; k++) code[k] = r + k * step < end ? part_codes[r + k * step] : -1;
+                for (int j = 4 * lq; j < nd; j += 4 * lanes) {
+                    float4 v[kAccRows], e[kAccRows];
+#pragma unroll
+                    for (int k = 0; k < kAccRows; k++) {
+                        v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        if (code[k] < 0) continue;
+                        if (j < left) v[k] = load4(x + (r + k * step) * D + (int64_t)p * w + c0 + j);
+                        e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
+                    }
+#pragma unroll
+                    for (int k = 0; k < kAccRows; k++) {
+                        if (code[k] < 0) continue;
+                        double *acc = s_acc + code[k];
+                        add(acc, j, v[k].x, e[k].x);
+                        add(acc, j + 1, v[k].y, e[k].y);
+                        add(acc, j + 2, v[k].z, e[k].z);
+                        add(acc, j + 3, v[k].w, e[k].w);
+                    }
+                }
+                if (nc > nd && lq == 0) {
+#pragma unroll
+                    for (int k = 0; k < kAccRows; k++)
+                        if (code[k] >= 0) unsafeAtomicAdd(s_acc + code[k] + nd * ls, 1.0);
+                }
             }
+        }
+    } else {
+        for (int64_t r = (int64_t)by * TH + threadIdx.x; r < rows; r += (int64_t)ny * TH) {
+            const int code = part_codes[r];
+            const T *src = x + r * D + (int64_t)p * w + c0;
+            const float *ent = cb + ((int64_t)p * len + code) * w + c0;
+            double *acc = s_acc + code;
+#pragma unroll 4
+            for (int j = 0; j < nd; j++) add(acc, j, j < left ? load1(src + j) : 0.0f, ent[j]);
+            if (nc > nd) unsafeAtomicAdd(acc + nd * ls, 1.0);
         }
     }
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
     if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
     __syncthreads();
     if (threadIdx.x == 0) unsafeAtomicAdd(distortion, s_dist);
-    for (int i = threadIdx.x; i < nc * len; i += kAccThreads) {
+    for (int i = threadIdx.x; i < nc * len; i += TH) {
         const int j = i / len, e = i - j * len, d = c0 + j;
+        const double sum = s_acc[j * ls + e];
         if (one_set) {
-            if (s_acc[i] == 0.0) continue;
-            if (d < w) unsafeAtomicAdd(&sums[((int64_t)p * w + d) * len + e], (float)s_acc[i]);
-            else atomicAdd(&counts[(int64_t)p * len + e], (uint32_t)s_acc[i]);
+            if (sum == 0.0) continue;
+            if (d < w) unsafeAtomicAdd(&sums[((int64_t)p * w + d) * len + e], (float)sum);
+            else atomicAdd(&counts[(int64_t)p * len + e], (uint32_t)sum);
         } else if (d < w) {
-            sums[(((int64_t)by * P + p) * w + d) * len + e] = (float)s_acc[i];
+            sums[(((int64_t)by * P + p) * w + d) * len + e] = (float)sum;
         } else {
-            counts[((int64_t)by * P + p) * len + e] = (uint32_t)s_acc[i];
+            counts[((int64_t)by * P + p) * len + e] = (uint32_t)sum;
         }
     }
 }
 
 // The generic round's workspace: the codes, then the workgroups' sums.
 struct GenericPlan {
-    int DG, groups, ny;
+    int DG, more, groups, ny;        // columns a group, 1: the last one counts on top of them
+    int threads;
     int64_t codes_bytes, set_bytes;  // codes (rounded up), sums and counts of one workgroup row
 };
 
 GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     GenericPlan g;
-    g.DG = (int)(kAccLds / (8 * len));  // at least one: 16384 entries take 128 KB
-    if (g.DG > w + 1) g.DG = w + 1;
-    g.groups = (w + g.DG) / g.DG;
-    g.DG = (w + g.groups) / g.groups;
-    // about two workgroups per CU, no more than there are strips, the sums within 256 MB
-    const int64_t strips = (rows + kAccThreads - 1) / kAccThreads;
+    g.DG = (int)(kAccLds / (8 * acc_stride(len)));  // at least one: 16384 entries take 128 KB
+    g.more = 0;
+    if (w % 4 == 0 && g.DG > 4) {  // whole fours of columns, for wide loads
+        g.more = 1;
+        g.DG = std::min((g.DG - 1) / 4 * 4, w);
+        g.groups = (w + g.DG - 1) / g.DG;
+        g.DG = (w / 4 + g.groups - 1) / g.groups * 4;
+    } else {
+        if (g.DG > w + 1) g.DG = w + 1;
+        g.groups = (w + g.DG) / g.DG;
+        g.DG = (w + g.groups) / g.groups;
+    }
+    // as many workgroups as the chip holds at once, no more than there are strips, the sums within
+    // 256 MB; smaller ones where a sample is too short to fill the chip with large ones, unless a
+    // workgroup's sums outnumber its rows then (3000 rows of 8 x 2048 x 16: 930 us against 980)
+    const int64_t lds = (int64_t)8 * (g.DG + g.more) * acc_stride(len), cols = (int64_t)p->P * g.groups;
+    g.threads = kAccThreads;
+    while (g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
+    const int64_t strips = (rows + g.threads - 1) / g.threads;
     g.codes_bytes = (rows * p->P * p->cbytes + 255) / 256 * 256;
     g.set_bytes = (int64_t)4 * p->P * len * (w + 1);
-    int64_t ny = 512 / ((int64_t)p->P * g.groups);
+    int64_t ny = 256 * std::min<int64_t>(2 * kAccThreads / g.threads, 160 * 1024 / (lds + 64)) / cols;
     if (ny > ((int64_t)256 << 20) / g.set_bytes) ny = ((int64_t)256 << 20) / g.set_bytes;
     if (ny > strips) ny = strips;
     g.ny = (int)(ny < 1 ? 1 : ny);
@@ -248,18 +315,21 @@ bool codes_pay(const bifeat_params *p, int64_t rows) {
     return w <= 2 && len <= 64;
 }
 
-template <typename T, typename CODE>
+template <typename T, typename CODE, bool VEC>
 bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, bool one_set, float *sums,
                       uint32_t *counts, double *dist_slot, hipStream_t s) {
-    const size_t shm = sizeof(double) * (size_t)g.DG * p->scheme.vq_length;
-    auto kern = vq_accumulate_codes_kernel<T, CODE>;
+    const size_t shm = sizeof(double) * (size_t)(g.DG + g.more) * acc_stride(p->scheme.vq_length);
+    auto kern = vq_accumulate_codes_kernel<T, CODE, VEC>;
     if (shm > 65536 - 64 &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)shm) != hipSuccess)
         return false;
-    kern<<<(unsigned)(g.groups * p->P * g.ny), kAccThreads, shm, s>>>(
+    const int blocks = (g.groups * p->P * g.ny + 7) / 8 * 8;
+    int lanes = 1;
+    while (VEC && lanes < 16 && g.DG % (8 * lanes) == 0) lanes *= 2;
+    kern<<<(unsigned)blocks, g.threads, shm, s>>>(
         x, rows, (int)p->D, p->scheme.vq_width, p->scheme.vq_length, p->P, (const CODE *)p->d_scratch, p->d_cb, g.DG,
-        g.groups, g.ny, one_set, sums, counts, dist_slot);
+        g.more, g.groups, g.ny, lanes, one_set, sums, counts, dist_slot);
     return true;
 }
 
@@ -277,9 +347,14 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     uint32_t *counts = (uint32_t *)(sums + sets * books);
     if (!all) launch_vq_zero(p->d_train, books + (int64_t)P * len, s);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
-    launch_vq_assign(p, x, rows, p->d_scratch, (int64_t)P * p->cbytes, s);
-    const bool ok = p->cbytes == 1 ? accumulate_codes<T, uint8_t>(p, x, rows, g, !all, sums, counts, dist_slot, s)
-                                   : accumulate_codes<T, uint16_t>(p, x, rows, g, !all, sums, counts, dist_slot, s);
+    launch_vq_assign(p, x, rows, p->d_scratch, p->cbytes, rows * p->cbytes, s);
+    // 4 columns at a time: whole fours everywhere, and where they lie
+    const bool vec = g.DG % 4 == 0 && w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
+    const bool ok = p->cbytes == 1
+                        ? (vec ? accumulate_codes<T, uint8_t, true>(p, x, rows, g, !all, sums, counts, dist_slot, s)
+                               : accumulate_codes<T, uint8_t, false>(p, x, rows, g, !all, sums, counts, dist_slot, s))
+                        : (vec ? accumulate_codes<T, uint16_t, true>(p, x, rows, g, !all, sums, counts, dist_slot, s)
+                               : accumulate_codes<T, uint16_t, false>(p, x, rows, g, !all, sums, counts, dist_slot, s));
     if (!ok) return hipGetLastError();
     launch_vq_means(p, sums, counts, sets, s);
     return hipSuccess;

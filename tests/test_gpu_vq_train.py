@@ -38,6 +38,31 @@ def test_column_groups(D, w, length, rows, metric):
     np.testing.assert_allclose(np.abs(q.params_get_codebooks()).mean(), np.abs(cb).mean(), rtol=1e-3)
 
 
+# the sums from codes, 4 columns at a time and one at a time: 1 to 16 lanes a row, column groups that are and
+# are not whole fours, a last part that the table cuts short, half precision, a base that is not aligned
+@pytest.mark.parametrize("D,w,length,rows,metric,half,offset", [
+    (40, 8, 300, 2100, "cosine", False, 0), (36, 12, 257, 1025, "cosine", False, 0), (64, 32, 700, 1500, "l2", True, 0),
+    (64, 64, 300, 1027, "l2", False, 0), (72, 24, 500, 2049, "cosine", True, 0), (40, 16, 1800, 4100, "l2", False, 0),
+    (44, 16, 1800, 4100, "l2", False, 0), (40, 8, 3000, 5000, "cosine", False, 0), (40, 8, 4000, 5000, "cosine", False, 0),
+    (40, 8, 1500, 2000, "l2", False, 1), (38, 8, 1500, 2000, "l2", False, 0), (128, 128, 260, 600, "cosine", False, 0)])
+def test_sums_from_codes(D, w, length, rows, metric, half, offset):
+    import torch
+    import paper_2207_14696_amd as bf
+    x = np.random.default_rng(D + length).normal(size=(rows, D)).astype(np.float16 if half else np.float32)
+    q = bf.Quantizer(scheme_of("vq", 8, w, length, metric), D)
+    q.set_option("vq_iters", 1)
+    dx = torch.zeros(rows * D + offset, dtype=torch.float16 if half else torch.float32, device="cuda")
+    dx = dx[offset:].view(rows, D)
+    dx.copy_(torch.from_numpy(x))
+    q.fit_update(dx)
+    q.fit_finalize()
+    x = x.astype(np.float32)
+    cb, want = orc.vq_train(x, w, length, iters=1, metric=metric)
+    assert q.vq_distortion(1)[0] == pytest.approx(want[0], rel=1e-5)
+    # one round: the same members in every entry, their mean rounded once (a workgroup's sums to 32 bits)
+    np.testing.assert_allclose(q.params_get_codebooks(), cb, rtol=2e-6, atol=1e-6)
+
+
 # widths 1, 2 and 4 on both sides of 128 values, of 4096 rows and of 2^21 sample values; other widths
 @pytest.mark.parametrize("P,w,length,rows", [(3, 1, 64, 5000), (3, 1, 200, 5000), (3, 1, 64, 4096), (5, 4, 31, 4097),
                                              (5, 4, 32, 4097), (130, 4, 64, 4100), (8, 2, 64, 131_200),
