@@ -24,7 +24,7 @@
 // minima over 256 entries, 100 the scores inside the cell, 45 the split of x, 32 the products, at
 // 77 % of the issue rate; the clock falls to 1.8 GHz under it, so that every instruction and LDS
 // read taken out counts, and a better overlap alone does not.  262 144 rows of 96 parts x 256 entries
-// x 8 columns: 542 us; with all four products of the pieces, |c|^2/2 read from LDS for every tile
+// x 8 columns: 535 us; with all four products of the pieces, |c|^2/2 read from LDS for every tile
 // and cells across two tiles (570 instructions, 77 LDS reads instead of 39) 650; the plain search
 // 3111 us.  Cells of 4 entries cost as much more in minima as they save in scores, of 16 more.
 //
@@ -58,6 +58,7 @@ struct VqNearestArgs {
     int lane_rows, plain_rows;  // see search_costs
     int NT;                 // tiles of 32 entries
     int ny;                 // workgroups per part
+    int64_t chunk;          // rows of each, a whole number of waves
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
     uint32_t cell_mask;     // low bits of a score that hold a cell's number
@@ -127,13 +128,13 @@ __device__ inline float rule_value(const float (&x)[WP], const float (&c)[WP], f
 
 // waves of a SIMD, workgroups of a CU with a copy of the entries in LDS (9 to 16 columns: with 2 waves
 // the whole search by the rule, 48 x 256 x 16, took 846 us instead of 770, the scores 181 instead of 166)
-constexpr int nearest_waves(int G, bool ent) { return G == 1 ? 4 : G == 2 && ent ? 3 : 2; }
+// (one workgroup of 512 threads: 2)
+constexpr int nearest_waves(int G, bool ent, int TH = 256) { return G == 1 ? 4 : G == 2 && ent && TH == 256 ? 3 : 2; }
 
-template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
-__global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nearest_kernel(
+template <typename T, int G, int METRIC, bool ENT, bool TRAIN, int TH>
+__global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kernel(
     VqNearestArgs<T> a, const float *__restrict__ cb, uint8_t *__restrict__ codes) {
     constexpr int WP = 8 * G;          // columns of a part, padded with zeros
-    constexpr int TH = ENT ? 256 : 512;
     constexpr int WAVES = TH / 64;
     constexpr int GROUP = group_floats(G), GROUPS4 = groups4_floats(G), UNITS = tile_units(G, ENT);
     constexpr bool COS = METRIC == BIFEAT_VQ_COSINE;
@@ -172,10 +173,17 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     {
         float m = 0.0f;
         bool bad = false;
-        for (int i = threadIdx.x; i < len * w; i += TH) {
-            const float c = fabsf(part_cb[i]);
-            bad |= !(c <= 0x1p40f);
-            m = fmaxf(m, c);
+        auto take = [&](float c) {
+            bad |= !(fabsf(c) <= 0x1p40f);
+            m = fmaxf(m, fabsf(c));
+        };
+        if (a.bvec) {
+            for (int i = threadIdx.x; i < len * w / 4; i += TH) {
+                const float4 c = reinterpret_cast<const float4 *>(part_cb)[i];
+                take(c.x); take(c.y); take(c.z); take(c.w);
+            }
+        } else {
+            for (int i = threadIdx.x; i < len * w; i += TH) take(part_cb[i]);
         }
         if constexpr (COS)
             for (int i = threadIdx.x; i < len; i += TH) bad |= !(part_rn[i] <= 0x1p40f);
@@ -197,6 +205,21 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
     // entry e in LDS, and its |c|^2/2 (cosine: 1/|c|); from a multiple of 4 on 4 follow each other
     auto ent_at = [&](int e) { return s_ent + (e >> 4) * GROUPS4 + ((e >> 2) & 3) * GROUP + (e & 3) * WP; };
     auto norm_at = [&](int e) { return s_ent + (e >> 4) * GROUPS4 + ((e >> 2) & 3) * GROUP + 4 * WP + (e & 3); };
+    // entry e from memory (columns past w: zeros)
+    auto read_entry = [&](int e, float (&c)[WP]) {
+        const float *src = part_cb + (int64_t)e * w;
+        if (a.bvec) {
+#pragma unroll
+            for (int k = 0; k < WP / 4; k++) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (4 * k < w) v = reinterpret_cast<const float4 *>(src)[k];
+                c[4 * k] = v.x; c[4 * k + 1] = v.y; c[4 * k + 2] = v.z; c[4 * k + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int d = 0; d < WP; d++) c[d] = d < w ? src[d] : 0.0f;
+        }
+    };
     const float unscale = 1.0f / (scale * scale);
     // the entries into LDS, a thread prepares one at a time
     {
@@ -206,14 +229,17 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             const float rn = COS ? (real ? part_rn[e] : 0.0f) : 0.0f;
             float s2 = 0.0f;
             half8 *tile = s_frag + (e >> 5) * UNITS;
+            float cv[WP];
+#pragma unroll
+            for (int d = 0; d < WP; d++) cv[d] = 0.0f;
+            if (real) read_entry(e, cv);
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 half8 hi, lo;
 #pragma unroll
                 for (int j = 0; j < 8; j++) {
                     const int d = 8 * g + j;
-                    const float c = real && d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
-                    if constexpr (ENT) ent_at(e)[d] = c;
+                    const float c = cv[d];
                     float cs = COS ? c * (rn * 1024.0f) : c * scale;
                     // one fp32 value for both pieces: the compiler may otherwise fold the product
                     // into one of the conversions and round the pieces from different values
@@ -224,6 +250,11 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                 }
                 tile[32 * g + (e & 31)] = hi;
                 tile[32 * (G + g) + (e & 31)] = lo;
+            }
+            if constexpr (ENT) {
+#pragma unroll
+                for (int d = 0; d < WP; d += 4)
+                    *reinterpret_cast<float4 *>(ent_at(e) + d) = make_float4(cv[d], cv[d + 1], cv[d + 2], cv[d + 3]);
             }
             const float half2 = COS ? 0.0f : 0.5f * s2;
             if constexpr (NORM) {
@@ -263,18 +294,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             }
             rn = COS ? *norm_at(e) : 0.0f;
         } else {
-            const float *src = part_cb + (int64_t)e * w;
-            if (a.bvec) {
-#pragma unroll
-                for (int k = 0; k < WP / 4; k++) {
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (4 * k < w) v = reinterpret_cast<const float4 *>(src)[k];
-                    c[4 * k] = v.x; c[4 * k + 1] = v.y; c[4 * k + 2] = v.z; c[4 * k + 3] = v.w;
-                }
-            } else {
-#pragma unroll
-                for (int d = 0; d < WP; d++) c[d] = d < w ? src[d] : 0.0f;
-            }
+            read_entry(e, c);
             rn = COS ? part_rn[e] : 0.0f;
         }
     };
@@ -311,30 +331,32 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         }
     };
     // (a row past the last one reads the last one; 64-bit products only where a strip is not whole)
-    const int64_t step = (int64_t)a.ny * ROWS;
     const T *const first_row = a.x + (int64_t)part * w;
     auto clamped = [&](int64_t r0) {
         const int64_t row = r0 + threadIdx.x;
         return first_row + (row < a.rows ? row : a.rows - 1) * a.D;
     };
-    const T *next = clamped((int64_t)by * ROWS);
+    const int64_t begin = by * a.chunk, end = min(a.rows, begin + a.chunk);
+    const T *next = clamped(begin);
     auto load_next = [&](int64_t r0, float (&v)[WP]) {
-        next = r0 + step + ROWS <= a.rows ? next + step * a.D : clamped(r0 + step);
+        next = r0 + 2 * ROWS <= a.rows ? next + (int64_t)ROWS * a.D : clamped(r0 + ROWS);
         load_row(next, v);
     };
     float xn[WP];
     [[maybe_unused]] int strip = 0;
     load_row(next, xn);
-    [[maybe_unused]] uint8_t *out = codes + ((int64_t)by * ROWS + threadIdx.x) * a.rb + part * a.pb;
-    for (int64_t r0 = (int64_t)by * ROWS; r0 < a.rows; r0 += step) {
+    [[maybe_unused]] uint8_t *out = codes + (begin + threadIdx.x) * a.rb + part * a.pb;
+    for (int64_t r0 = begin; r0 < end; r0 += ROWS) {
         // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which the halves of
         // the wave then hold for both sets of 32 rows
-        const bool valid = (int64_t)threadIdx.x < a.rows - r0;
+        const bool valid = (int64_t)threadIdx.x < end - r0;
+        // (a wave without rows has nothing to do, but the workgroup decides together without a copy of
+        // the entries)
+        if (ENT && __builtin_amdgcn_readfirstlane(threadIdx.x) >= end - r0) break;
         float xr[WP];
 #pragma unroll
         for (int d = 0; d < WP; d++) xr[d] = xn[d];
         int code = 0;
-        float value = INFINITY;
         int all_code = 0;
         float all_value = INFINITY;
         auto search_all = [&]() {
@@ -396,7 +418,6 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             load_next(r0, xn);
             search_all();
             code = all_code;
-            value = all_value;
         } else {
         float f = scale;
         bool bad = part_bad, zero = false;
@@ -635,11 +656,6 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
             const int k = (int)(__float_as_uint(b1) & 7u);
             open |= !(b2 - b1 > cell_margin);
             code = (int)e0 + (k & 3) + 8 * (k >> 2);
-            if constexpr (TRAIN) {  // the rule's distance; an open row's is found below
-                float c[WP], rn;
-                entry(min(code, len - 1), c, rn);
-                value = rule_value<WP, METRIC>(xr, c, rn);
-            }
         }
         if (COS && zero) {  // all scores are zero: the first entry
             open = false;
@@ -665,7 +681,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         if (todo) {
             if ((ENT || plain) && __popcll(todo) >= a.lane_rows) {
                 search_all();
-                if (open) { code = all_code; value = all_value; }
+                if (open) code = all_code;
             } else {
                 // two rows at a time, which halves the fetches of entries and has two reductions side by
                 // side, where there are registers for it (8 columns, entries in LDS, 4 waves a SIMD: the
@@ -702,10 +718,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                             const int oc = __shfl_xor(bc[n], o);
                             if (ov < bv[n] || (ov == bv[n] && oc < bc[n])) { bv[n] = ov; bc[n] = oc; }
                         }
-                        if (lane == j[n]) {
-                            code = bc[n] == 0x7FFFFFFF ? 0 : bc[n];
-                            value = bv[n];
-                        }
+                        if (lane == j[n]) code = bc[n] == 0x7FFFFFFF ? 0 : bc[n];
                     }
                 }
             }
@@ -713,11 +726,13 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
         }  // !plain
         if constexpr (TRAIN) {
             if (valid) {
+                float c[WP], rn;
+                entry(code, c, rn);
+                dsum += rule_value<WP, BIFEAT_VQ_L2>(xr, c, rn);
 #pragma unroll
                 for (int d = 0; d < WP; d++)
                     if (d < w) unsafeAtomicAdd(&s_sum[d * len + code], (double)xr[d]);
                 atomicAdd(&s_cnt[code], 1u);
-                dsum += value;
             }
         } else {
             // the next rows have arrived by now; waiting for them here keeps that wait from covering
@@ -730,7 +745,7 @@ __global__ __launch_bounds__(ENT ? 256 : 512, nearest_waves(G, ENT)) void vq_nea
                 if (part == 0)
                     for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) out[k] = 0;  // padding
             }
-            out += step * a.rb;
+            out += ROWS * a.rb;
         }
     }
     if constexpr (TRAIN) {
@@ -809,12 +824,11 @@ size_t nearest_lds(const bifeat_params *p, int G, int NT, bool ent, bool train) 
     return n;
 }
 
-// Entries in LDS next to their pieces when as many workgroups share a CU as their registers allow
-// (training: when it fits at all); else as many pieces as a CU holds, the rule reading its few
+// Entries in LDS next to their pieces when they fit; else the pieces alone, the rule reading its few
 // entries from L2.
 bool entries_in_lds(const bifeat_params *p, bool train) {
     const int G = (p->scheme.vq_width + 7) / 8, tiles = (p->scheme.vq_length + 31) / 32;
-    const int64_t limit = train ? kCuLds - 1024 : kCuLds / nearest_waves(G, true);
+    const int64_t limit = kCuLds - 1024;
     return (int64_t)nearest_lds(p, G, tiles, true, train) <= limit;
 }
 
@@ -835,9 +849,9 @@ void search_costs(VqNearestArgs<T> &a, int G, bool ent) {
     a.plain_rows = (int)std::max(1.0, std::min(60.0, (all - scores) / one));
 }
 
-template <typename T, int G, int METRIC, bool ENT, bool TRAIN>
+template <typename T, int G, int METRIC, bool ENT, bool TRAIN, int TH>
 bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds, hipStream_t s) {
-    auto kern = vq_nearest_kernel<T, G, METRIC, ENT, TRAIN>;
+    auto kern = vq_nearest_kernel<T, G, METRIC, ENT, TRAIN, TH>;
     // (the kernel's few static words count too)
     if (lds > 65536 - 64 &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -845,16 +859,26 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         (void)hipGetLastError();
         return false;
     }
-    constexpr int TH = ENT ? 256 : 512;
     const int64_t strips = (a.rows + TH - 1) / TH;
-    // workgroups: four times what the chip holds at once, a little less rather than a little more
-    // (staging the codebook is about as long as one strip, so a workgroup should have many); in
-    // training, where each also adds its sums to memory, as many as the chip holds
-    const int64_t resident = 256 * std::min<int64_t>(ENT ? nearest_waves(G, true) : 1, kCuLds / (int64_t)lds);
-    // (without a copy of the entries: the codebook is large, and once is enough there too)
-    int64_t ny = (TRAIN || !ENT ? 1 : 4) * resident / a.P;
+    // Workgroups per part: one to four times what the chip holds at once, as the slots that stay empty
+    // and the staging of the codebook, about as long as a strip, cost least (24 x 270 x 32, all rows
+    // open: 845 us with one workgroup a CU, 1022 with two rounds of two).  In training, where each also
+    // adds its sums to memory, as many as the chip holds.
+    const int64_t resident =
+        256 * std::min<int64_t>(ENT ? nearest_waves(G, true, TH) * 256 / TH : 1, kCuLds / (int64_t)lds);
+    int64_t ny = resident / a.P;
+    double least = 0.0;
+    for (int m = 1; m <= (TRAIN ? 1 : 4); m++) {
+        const int64_t n = m * resident / a.P;
+        if (n < 1) continue;
+        const double rows_long = m * ((double)a.rows / (double)n + 0.8 * TH);
+        if (least == 0.0 || rows_long < least) { least = rows_long; ny = n; }
+    }
     if (ny < 1) ny = 1;
     if (ny > strips) ny = strips;
+    // (whole strips instead would leave the chip waiting for the workgroups with one more)
+    a.chunk = ((a.rows + ny - 1) / ny + 63) / 64 * 64;
+    ny = (a.rows + a.chunk - 1) / a.chunk;
     if constexpr (TRAIN) {
         // every workgroup's sums; without room for them (a stream that is being captured) they add to
         // the handle's own block of one set (10 rounds on 65 536 rows, with workspace / so: 8 x 256 x 16
@@ -884,12 +908,20 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
     const bool ent = entries_in_lds(p, train);
     a.NT = tiles;
     const size_t lds = nearest_lds(p, G, a.NT, ent, train);
-    if (train) {
-        if constexpr (METRIC == BIFEAT_VQ_L2) return launch_one<T, G, METRIC, true, true>(p, a, codes, lds, s);
-        else return false;  // the rounds of a cosine codebook go through its codes
-    }
-    return ent ? launch_one<T, G, METRIC, true, false>(p, a, codes, lds, s)
-               : launch_one<T, G, METRIC, false, false>(p, a, codes, lds, s);
+    if (!ent) return train ? false : launch_one<T, G, METRIC, false, false, 512>(p, a, codes, lds, s);
+#define BF_VNL(TH) (train ? launch_one<T, G, METRIC, true, true, TH>(p, a, codes, lds, s) \
+                          : launch_one<T, G, METRIC, true, false, TH>(p, a, codes, lds, s))
+    // Workgroups of 256 threads while a CU holds three or more.  Larger codebooks would leave it with few
+    // waves, so they are shared by as many as the registers allow: 65 536 rows of 96 x 1000 x 8 459 us (512
+    // threads that read the entries from L2: 726), 48 x 512 x 16 207 (358), 24 x 270 x 32 124 (447); training
+    // 96 x 1000 x 8 4610 us (search and sums apart 7420).  9 to 16 columns: with three waves a SIMD in mind the
+    // plain search spills, which workgroups of 512 do not have (48 x 512 x 16 244 in two of 256).
+    // (the kernel's few static words count too)
+    const int64_t fit = kCuLds / ((int64_t)lds + 64);
+    if (fit >= 3) return BF_VNL(256);
+    if constexpr (G == 1) return fit == 2 ? BF_VNL(512) : BF_VNL(1024);
+    else return BF_VNL(512);
+#undef BF_VNL
 }
 
 template <typename T, int G>
@@ -946,7 +978,7 @@ bool vq_nearest_takes(const bifeat_params *p, bool train) {
     if (nearest_lds(p, G, tiles, false, false) > kCuLds - 4096) return false;
     const double gap = pow((double)len, -2.0 / w) * std::min(1.0, 2.0 / w);
     if (vq_margin(w, len) > 0.01 * gap) return false;
-    return !train || (p->scheme.vq_metric == BIFEAT_VQ_L2 && entries_in_lds(p, true));
+    return !train || entries_in_lds(p, true);
 }
 
 void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts, int ny, hipStream_t s) {

@@ -7,7 +7,7 @@ namespace bf {
 
 // Whether the matrix-core search takes the handle's shape: not parts of more than 32 columns,
 // codebooks of under 512 values, of entries too dense for its margin or too large for LDS, nor in
-// training cosine codebooks and those whose sums do not fit LDS next to the entries.  (The two
+// training those whose sums do not fit LDS next to the entries.  (The two
 // calls below return false, with nothing launched, when it does not.)
 bool vq_nearest_takes(const bifeat_params *p, bool train);
 
@@ -16,8 +16,8 @@ template <typename T>
 bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                              hipStream_t s);
 
-// one Lloyd round over the rows (Euclidean codebooks): every entry becomes the mean of the parts
-// nearest to it, their squared distances are added to *distortion
+// one Lloyd round over the rows: every entry becomes the mean of the parts nearest to it (cosine: by
+// the reciprocal norms in p->d_rnorm), their squared distances are added to *distortion
 template <typename T>
 bool launch_vq_nearest_round(bifeat_params *p, const T *x, int64_t rows, double *distortion, hipStream_t s);
 

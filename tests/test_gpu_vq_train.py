@@ -38,6 +38,46 @@ def test_column_groups(D, w, length, rows, metric):
     np.testing.assert_allclose(np.abs(q.params_get_codebooks()).mean(), np.abs(cb).mean(), rtol=1e-3)
 
 
+# search and sums in one kernel: workgroups of 256, 512 and 1024 threads, up to the most entries that fit and one
+# more, rows that tie (searched by the rule in strips), two-byte codes, both metrics
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("D,w,length,rows,kind", [
+    (24, 8, 256, 3000, "normal"), (24, 8, 300, 3000, "normal"), (40, 8, 470, 3001, "normal"), (24, 8, 1000, 2100, "normal"),
+    (8, 8, 1120, 2500, "normal"), (8, 8, 1121, 2500, "normal"), (32, 16, 256, 1500, "normal"), (44, 16, 500, 1500, "normal"),
+    (24, 24, 150, 900, "normal"), (48, 24, 400, 1500, "normal"), (32, 32, 130, 700, "normal"), (32, 32, 290, 700, "normal"),
+    (13, 13, 300, 900, "normal"), (24, 8, 900, 9000, "ties"), (32, 16, 300, 9000, "ties")])
+def test_search_and_sums_in_one_kernel(D, w, length, rows, kind, metric):
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(D + length)
+    x = rng.normal(size=(rows, D)).astype(np.float32)
+    if kind == "ties":
+        x = rng.integers(-3, 4, size=(rows, D)).astype(np.float32)
+    q = _train(torch, bf, x, w, length, metric, 1)
+    cb, want = orc.vq_train(x, w, length, iters=1, metric=metric)
+    if kind == "ties":      # (the oracle starts from distinct rows: its own first entries differ)
+        codes = orc.vq_assign(x, w, _first_entries(x, w, length), metric=metric)
+        cb, want = _one_round(x, w, length, codes)
+    assert q.vq_distortion(1)[0] == pytest.approx(want[0], rel=1e-5)
+    np.testing.assert_allclose(q.params_get_codebooks(), cb, rtol=2e-6, atol=1e-6)
+
+
+def _first_entries(x, w, length):
+    P = x.shape[1] // w
+    return np.ascontiguousarray(x[:length, :P * w].reshape(length, P, w).transpose(1, 0, 2))
+
+
+def _one_round(x, w, length, codes):
+    cb = _first_entries(x, w, length).astype(np.float64)
+    parts = x.reshape(len(x), -1, w).astype(np.float64)
+    dist = 0.0
+    for p in range(parts.shape[1]):
+        dist += ((parts[:, p] - cb[p][codes[:, p]]) ** 2).sum()
+        for e in np.unique(codes[:, p]):
+            cb[p, e] = parts[codes[:, p] == e, p].mean(0)
+    return cb, [dist / len(x)]
+
+
 # the sums from codes, 4 columns at a time and one at a time: 1 to 16 lanes a row, column groups that are and
 # are not whole fours, a last part that the table cuts short, half precision, a base that is not aligned
 @pytest.mark.parametrize("D,w,length,rows,metric,half,offset", [
