@@ -69,8 +69,10 @@ struct VqNearestArgs {
     double *distortion;
 };
 
-// codebooks of fewer values (entries x columns) and wider parts stay with the plain search
-constexpr int kNearestMinBook = 512;
+// codebooks of fewer values (entries x columns; parts of 4 columns or more; with few rows x parts) and
+// wider parts stay with the plain search, see vq_nearest_takes
+constexpr int kNearestMinBook = 512, kNearestMinBookAny = 64, kNearestMinBookFew = 384;
+constexpr int64_t kNearestManyParts = 1 << 18;
 constexpr int kNearestMaxWidth = 32;
 constexpr int kCuLds = 160 * 1024;
 // strips that a wave searches by the rule once its rows tie, before it tries the scores again
@@ -770,22 +772,46 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
 }
 
 // An entry becomes the mean of its members (one without members keeps its value) from the
-// workgroups' sums; a thread per column of an entry, in the sums' order.
+// workgroups' sums; GROUPS threads per column of an entry, each adding every GROUPS-th set in the sets'
+// order.  One thread to all of the sets that few parts give (64 of 6 x 64 x 4) waits for one load after
+// the other: 20 us of a round's 35.
+template <int GROUPS>
 __global__ __launch_bounds__(kThreads) void vq_means_kernel(const float *__restrict__ sums,
                                                             const uint32_t *__restrict__ counts, int ny, int P, int w,
                                                             int len, float *__restrict__ cb) {
+    constexpr int OUT = kThreads / GROUPS;
+    __shared__ double s_sum[GROUPS > 1 ? kThreads : 1];
+    __shared__ uint64_t s_count[GROUPS > 1 ? kThreads : 1];
     const int64_t n = (int64_t)P * w * len;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+    const int o = threadIdx.x % OUT, g = threadIdx.x / OUT;
+    for (int64_t i0 = (int64_t)blockIdx.x * OUT; i0 < n; i0 += (int64_t)gridDim.x * OUT) {
+        const int64_t i = i0 + o;
         const int e = (int)(i % len);
         const int64_t pd = i / len, p = pd / w;
         const int d = (int)(pd - p * w);
         double sum = 0.0;
         uint64_t count = 0;
-        for (int k = 0; k < ny; k++) {
-            sum += (double)sums[k * n + i];
-            count += counts[((int64_t)k * P + p) * len + e];
+        if (i < n) {
+#pragma unroll 4
+            for (int k = g; k < ny; k += GROUPS) {
+                sum += (double)sums[k * n + i];
+                count += counts[((int64_t)k * P + p) * len + e];
+            }
         }
-        if (count > 0) cb[(p * len + e) * w + d] = (float)(sum / (double)count);
+        if constexpr (GROUPS > 1) {
+            s_sum[threadIdx.x] = sum;
+            s_count[threadIdx.x] = count;
+            __syncthreads();
+            if (g == 0) {
+#pragma unroll
+                for (int k = 1; k < GROUPS; k++) {
+                    sum += s_sum[k * OUT + o];
+                    count += s_count[k * OUT + o];
+                }
+            }
+            __syncthreads();
+        }
+        if (g == 0 && i < n && count > 0) cb[(p * len + e) * w + d] = (float)(sum / (double)count);
     }
 }
 
@@ -939,7 +965,7 @@ template <typename T>
 bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                     double *distortion, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    if (!vq_nearest_takes(p, !codes)) return false;
+    if (!vq_nearest_takes(p, !codes, rows)) return false;
     VqNearestArgs<T> a{};
     a.x = x;
     a.rows = rows;
@@ -968,13 +994,20 @@ bool launch_nearest(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, 
 // rule one entry after the other.  The distance to the nearest of `len` entries in w dimensions is
 // about len^(-2/w) of M, and the gap to the next about 2/w of that: with the margin above a
 // hundredth of it (4096 entries of 4 columns: 1857 us against 1499; any one-column codebook of
-// some size) the plain search is the better one.  So it is for codebooks of under 512 values
-// (65 536 x 12 parts of 8 columns, 32 entries: 28 us against 33; 4 columns, 64 entries: 40 against
-// 54) and for those whose pieces do not fit LDS at once (16384 x 16: 2.7 ms against 4.9).
-bool vq_nearest_takes(const bifeat_params *p, bool train) {
+// some size) the plain search is the better one.  So it is for codebooks whose pieces do not fit LDS
+// at once (16384 x 16: 2.7 ms against 4.9), for those of under 64 values, of under 512 in parts of
+// under 4 columns (65 536 x 24 parts of 2 columns, 64 entries: 29 us against 38), and for those of under
+// 384 (512 in fewer than 48 entries) where rows x parts are so few that staging is most of the call
+// and the plain search has the width at compile time (4096 x 24 parts of 4 columns, 32 entries: 6.8 us
+// against 8.0; 65 536 x 24: 37 against 24; 4096 x 24 parts of 12 columns, 32 entries: 27.6 against 11.9;
+// 4096 x 6 parts of 16 columns, 31 entries: 9.7 against 10.6; of 8 columns, 60 entries: 10.8 against 9.6).
+bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const int G = (w + 7) / 8, tiles = (len + 31) / 32;
-    if (w > kNearestMaxWidth || w * len < kNearestMinBook) return false;
+    const bool few = rows * p->P < kNearestManyParts && (w == 4 || w == 8 || w == 16);
+    if (w > kNearestMaxWidth || w * len < (w < 4 ? kNearestMinBook : few ? kNearestMinBookFew : kNearestMinBookAny))
+        return false;
+    if (few && len < 48 && w * len < kNearestMinBook) return false;
     if (nearest_lds(p, G, tiles, false, false) > kCuLds - 4096) return false;
     const double gap = pow((double)len, -2.0 / w) * std::min(1.0, 2.0 / w);
     if (vq_margin(w, len) > 0.01 * gap) return false;
@@ -983,7 +1016,10 @@ bool vq_nearest_takes(const bifeat_params *p, bool train) {
 
 void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts, int ny, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    vq_means_kernel<<<blocks_for((int64_t)p->P * len * w), kThreads, 0, s>>>(sums, counts, ny, p->P, w, len, p->d_cb);
+    const int64_t n = (int64_t)p->P * len * w;
+    // (a thread each where that fills the chip: 10 sets of 96 x 256 x 8 take 6.5 us so, 13 by groups)
+    if (ny > 8 && n < (1 << 16)) vq_means_kernel<8><<<blocks_for(8 * n), kThreads, 0, s>>>(sums, counts, ny, p->P, w, len, p->d_cb);
+    else vq_means_kernel<1><<<blocks_for(n), kThreads, 0, s>>>(sums, counts, ny, p->P, w, len, p->d_cb);
 }
 
 template <typename T>

@@ -5,11 +5,11 @@
 
 namespace bf {
 
-// Whether the matrix-core search takes the handle's shape: not parts of more than 32 columns,
-// codebooks of under 512 values, of entries too dense for its margin or too large for LDS, nor in
+// Whether the matrix-core search takes the handle's shape for so many rows: not parts of more than 32 columns,
+// codebooks of few values, of entries too dense for its margin or too large for LDS, nor in
 // training those whose sums do not fit LDS next to the entries.  (The two
 // calls below return false, with nothing launched, when it does not.)
-bool vq_nearest_takes(const bifeat_params *p, bool train);
+bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows);
 
 // the index of every part's nearest entry, see launch_vq_assign
 template <typename T>

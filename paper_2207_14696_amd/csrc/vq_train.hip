@@ -156,7 +156,7 @@ __global__ void vq_rnorm_kernel(const float *__restrict__ cb, int64_t entries, i
 
 // Sums, counts and squared distance from the codes, one part's after the other.  A workgroup takes
 // one part, as many of its columns (the count is one more) as LDS holds sums for - 64-bit ones, see
-// vq_nearest.hip - and every ny-th strip of rows, and writes its sums to the workspace:
+// vq_nearest.hip - and an ny-th of the rows, and writes its sums to the workspace:
 // sums [ny][P][w][len], counts [ny][P][len]; or adds them to the one (zeroed) set there is room for.
 // What bounds it: the LDS adds (22 cycles a wave, 36 us for 65 536 rows of 96 x 8 columns) and reading
 // the sample once more (40 us).  For that 4 columns are loaded at a time (VEC) and lanes share a row
@@ -189,6 +189,8 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     __syncthreads();
     float dsum = 0.0f;
     const CODE *part_codes = codes + p * rows;
+    // an even share of the rows, whole waves of them
+    const int64_t share = ((rows + ny - 1) / ny + 63) / 64 * 64, begin = by * share, end = min(rows, begin + share);
     const int left = D - (p * w + c0);  // columns that the table has
     auto add = [&](double *acc, int j, float xv, float ev) {
         unsafeAtomicAdd(acc + j * ls, (double)xv);
@@ -199,40 +201,37 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
         // `lanes` lanes (a power of two that divides the fours of columns) share a row: fewer lines an
         // instruction; a lane has kAccRows rows in flight
         const int lq = threadIdx.x & (lanes - 1), at = threadIdx.x / lanes, step = TH / lanes;
-        for (int64_t r0 = (int64_t)by * TH * kAccRows; r0 < rows; r0 += (int64_t)ny * TH * kAccRows) {
-            const int64_t end = min(rows, r0 + (int64_t)TH * kAccRows);
-            for (int64_t r = r0 + at; r < end; r += (int64_t)step * kAccRows) {
-                int code[kAccRows];
+        for (int64_t r = begin + at; r < end; r += (int64_t)step * kAccRows) {
+            int code[kAccRows];
 #pragma unroll
-                for (int k = 0; k < kAccRows; k++) code[k] = r + k * step < end ? part_codes[r + k * step] : -1;
-                for (int j = 4 * lq; j < nd; j += 4 * lanes) {
-                    float4 v[kAccRows], e[kAccRows];
+            for (int k = 0; k < kAccRows; k++) code[k] = r + k * step < end ? part_codes[r + k * step] : -1;
+            for (int j = 4 * lq; j < nd; j += 4 * lanes) {
+                float4 v[kAccRows], e[kAccRows];
 #pragma unroll
-                    for (int k = 0; k < kAccRows; k++) {
-                        v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (code[k] < 0) continue;
-                        if (j < left) v[k] = load4(x + (r + k * step) * D + (int64_t)p * w + c0 + j);
-                        e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
-                    }
-#pragma unroll
-                    for (int k = 0; k < kAccRows; k++) {
-                        if (code[k] < 0) continue;
-                        double *acc = s_acc + code[k];
-                        add(acc, j, v[k].x, e[k].x);
-                        add(acc, j + 1, v[k].y, e[k].y);
-                        add(acc, j + 2, v[k].z, e[k].z);
-                        add(acc, j + 3, v[k].w, e[k].w);
-                    }
+                for (int k = 0; k < kAccRows; k++) {
+                    v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (code[k] < 0) continue;
+                    if (j < left) v[k] = load4(x + (r + k * step) * D + (int64_t)p * w + c0 + j);
+                    e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
                 }
-                if (nc > nd && lq == 0) {
 #pragma unroll
-                    for (int k = 0; k < kAccRows; k++)
-                        if (code[k] >= 0) unsafeAtomicAdd(s_acc + code[k] + nd * ls, 1.0);
+                for (int k = 0; k < kAccRows; k++) {
+                    if (code[k] < 0) continue;
+                    double *acc = s_acc + code[k];
+                    add(acc, j, v[k].x, e[k].x);
+                    add(acc, j + 1, v[k].y, e[k].y);
+                    add(acc, j + 2, v[k].z, e[k].z);
+                    add(acc, j + 3, v[k].w, e[k].w);
                 }
+            }
+            if (nc > nd && lq == 0) {
+#pragma unroll
+                for (int k = 0; k < kAccRows; k++)
+                    if (code[k] >= 0) unsafeAtomicAdd(s_acc + code[k] + nd * ls, 1.0);
             }
         }
     } else {
-        for (int64_t r = (int64_t)by * TH + threadIdx.x; r < rows; r += (int64_t)ny * TH) {
+        for (int64_t r = begin + threadIdx.x; r < end; r += TH) {
             const int code = part_codes[r];
             const T *src = x + r * D + (int64_t)p * w + c0;
             const float *ent = cb + ((int64_t)p * len + code) * w + c0;
@@ -285,10 +284,11 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
     }
     // as many workgroups as the chip holds at once, no more than there are strips, the sums within
     // 256 MB; smaller ones where a sample is too short to fill the chip with large ones, unless a
-    // workgroup's sums outnumber its rows then (3000 rows of 8 x 2048 x 16: 930 us against 980)
+    // workgroup's sums outnumber its rows then (3000 rows of 8 x 2048 x 16: 930 us against 980) or there
+    // are few columns to add (4096 rows of 96 x 64 x 1: 222 us against 259)
     const int64_t lds = (int64_t)8 * (g.DG + g.more) * acc_stride(len), cols = (int64_t)p->P * g.groups;
     g.threads = kAccThreads;
-    while (g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
+    while (w >= 8 && g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
     const int64_t strips = (rows + g.threads - 1) / g.threads;
     g.codes_bytes = (rows * p->P * p->cbytes + 255) / 256 * 256;
     g.set_bytes = (int64_t)4 * p->P * len * (w + 1);
@@ -301,18 +301,12 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
 
 // Whether a codebook that the plain fused kernel can train, and the matrix-core search does not take,
 // goes through codes.  The fused kernel reads the sample once a round and is bound by its LDS float
-// adds; the other way searches faster, reads twice, and the second time a workgroup has one part's
-// columns of all its rows, which only a sample that the caches hold allows.  10 rounds, us, fused /
-// codes: 16 384 x 1 x 64 x 64 41 700 / 2600, 65 536 x 8 x 64 x 5 4369 / 1142 (widths the fused kernel
-// does not have at compile time); 65 536 x 1 x 32 x 8 522 / 354, 1000 x 96 x 32 x 8 341 / 217;
-// 65 536 x 8 x 16 x 1 279 / 343, 65 536 x 8 x 16 x 4 403 / 544, 65 536 x 192 x 64 x 4 5110 / 8760.
-// One and two columns are so little to read that small codebooks go through codes at any size
-// (65 536 x 96 x 64 x 1 1931 / 1433; 256 entries 2393 / 2958).
+// adds; the other way reads twice and adds in 64 bits at a ninth of the cost.  10 rounds, us, fused /
+// codes: 65 536 x 24 x 64 x 1 654 / 379, 16 384 x 96 x 250 x 2 1230 / 1030, 65 536 x 6 x 16 x 4 350 / 310.
+// Of one or two columns there is little to add, and at millions of parts with more than 64 entries the
+// search is all that counts, which reads the sample as it lies in both (65 536 x 96 x 256 x 1 2390 / 2630).
 bool codes_pay(const bifeat_params *p, int64_t rows) {
-    const int w = p->scheme.vq_width, len = p->scheme.vq_length;
-    if (w > 16 || (w & (w - 1))) return true;
-    if (rows * p->P * w < (1 << 21)) return len * w >= 128 || rows <= 4096;
-    return w <= 2 && len <= 64;
+    return p->scheme.vq_width > 2 || p->scheme.vq_length <= 64 || rows * p->P < (1 << 22);
 }
 
 template <typename T, typename CODE, bool VEC>
@@ -411,7 +405,7 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
         return ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s) ||
                ensure_scratch(p, (size_t)rows * P * p->cbytes, s);
     };
-    bool nearest = vq_nearest_takes(p, true), through_codes = false;
+    bool nearest = vq_nearest_takes(p, true, rows), through_codes = false;
     if (!nearest) {
         through_codes = fused ? codes_pay(p, rows) && ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s)
                               : room_for_codes();

@@ -63,6 +63,21 @@ def test_codes_equal_the_plain_search(bf, torch, D, w, length, rows, dtype, metr
     _check(bf, torch, x, cb, D, w, length, metric)
 
 
+# codebooks of under 512 values: on both sides of 64 values, of rows x parts (2^18), of 384 values and 48 entries
+# where those are few, widths that the plain search has at compile time and that it has not
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("D,w,length,rows", [
+    (256, 4, 16, 4097), (256, 4, 15, 4097), (256, 4, 16, 4095), (512, 8, 8, 4100), (512, 8, 33, 4100), (24, 4, 96, 300),
+    (24, 4, 95, 300), (32, 16, 31, 300), (32, 16, 30, 300), (24, 8, 48, 300), (24, 8, 47, 300), (36, 12, 6, 300),
+    (36, 12, 5, 300), (50, 5, 13, 300), (64, 32, 2, 300), (66, 33, 12, 300), (1024, 16, 20, 4100)])
+def test_small_codebooks(bf, torch, D, w, length, rows, metric):
+    rng = np.random.default_rng(D + w * 100 + length)
+    cb = _codebook(rng, D, w, length)
+    x = (rng.normal(size=(rows, D)) * 1.3).astype(np.float32)
+    x[::97] = cb.transpose(1, 0, 2).reshape(length, -1)[0, :D]
+    _check(bf, torch, x, cb, D, w, length, metric)
+
+
 # every entry of every cell wins, in odd and even numbers of tiles; entries of very different lengths (their
 # squares in pieces next to the product, or the accumulators' start), padding entries beside real ones
 @pytest.mark.parametrize("metric", ["l2", "cosine"])

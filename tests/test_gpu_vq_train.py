@@ -45,7 +45,7 @@ def test_column_groups(D, w, length, rows, metric):
     (24, 8, 256, 3000, "normal"), (24, 8, 300, 3000, "normal"), (40, 8, 470, 3001, "normal"), (24, 8, 1000, 2100, "normal"),
     (8, 8, 1120, 2500, "normal"), (8, 8, 1121, 2500, "normal"), (32, 16, 256, 1500, "normal"), (44, 16, 500, 1500, "normal"),
     (24, 24, 150, 900, "normal"), (48, 24, 400, 1500, "normal"), (32, 32, 130, 700, "normal"), (32, 32, 290, 700, "normal"),
-    (13, 13, 300, 900, "normal"), (24, 8, 900, 9000, "ties"), (32, 16, 300, 9000, "ties")])
+    (13, 13, 300, 900, "normal"), (256, 4, 16, 4100, "normal"), (12, 12, 8, 3000, "normal"), (32, 8, 8, 3000, "normal"), (24, 8, 900, 9000, "ties"), (32, 16, 300, 9000, "ties")])
 def test_search_and_sums_in_one_kernel(D, w, length, rows, kind, metric):
     import torch
     import paper_2207_14696_amd as bf
@@ -84,6 +84,7 @@ def _one_round(x, w, length, codes):
     (40, 8, 300, 2100, "cosine", False, 0), (36, 12, 257, 1025, "cosine", False, 0), (64, 32, 700, 1500, "l2", True, 0),
     (64, 64, 300, 1027, "l2", False, 0), (72, 24, 500, 2049, "cosine", True, 0), (40, 16, 1800, 4100, "l2", False, 0),
     (44, 16, 1800, 4100, "l2", False, 0), (40, 8, 3000, 5000, "cosine", False, 0), (40, 8, 4000, 5000, "cosine", False, 0),
+    (6, 1, 64, 4100, "l2", False, 0), (12, 2, 250, 4100, "l2", False, 0), (8, 4, 30, 70, "l2", False, 0),
     (40, 8, 1500, 2000, "l2", False, 1), (38, 8, 1500, 2000, "l2", False, 0), (128, 128, 260, 600, "cosine", False, 0)])
 def test_sums_from_codes(D, w, length, rows, metric, half, offset):
     import torch
