@@ -1,6 +1,7 @@
 """ctypes binding of the C ABI in ``include/bifeat.h``: same names, argument
 marshalling only.  Tensors are torch CUDA tensors; their ``data_ptr()`` and the
-current stream's handle are what crosses the boundary."""
+current stream's handle are what crosses the boundary.  ``gather_dequant``, ``gather_mean`` and
+``gather_sum`` without ``out`` go through a native module (``csrc/calls.cpp``) to the same entry points."""
 from __future__ import annotations
 
 import ctypes as C
@@ -111,6 +112,23 @@ def load_library():
     return _lib
 
 
+_calls = None
+
+
+def _load_calls():
+    """The native module for the per-iteration calls.  No fallback either."""
+    global _calls
+    if _calls is None:
+        import torch  # noqa: F401  (its libraries are what the module links against)
+        from . import _calls as module
+        _calls = module
+    return _calls
+
+
+def _address(fn) -> int:
+    return C.cast(fn, C.c_void_p).value
+
+
 def _check(status: int) -> None:
     if status != OK:
         raise BifeatError(status, load_library().bifeat_strerror(status).decode())
@@ -152,6 +170,9 @@ class Quantizer:
         cs = _CScheme(scheme.kind, scheme.bits, scheme.vq_width, scheme.vq_length, scheme.vq_metric)
         _check(self._lib.bifeat_params_create(C.byref(cs), self.D, C.byref(h)))
         self._h = h
+        self._native = (h.value, _address(self._lib.bifeat_gather_dequant),
+                        (_address(self._lib.bifeat_gather_mean), _address(self._lib.bifeat_gather_mean_i32)),
+                        (_address(self._lib.bifeat_gather_sum), _address(self._lib.bifeat_gather_sum_i32)))
         if row_align != 16:
             self.set_option("row_align", row_align)
 
@@ -264,6 +285,13 @@ class Quantizer:
         return out
 
     def gather_dequant(self, codes, idx, out=None):
+        if out is None:
+            handle, fn = self._native[:2]
+            r = (_calls or _load_calls()).gather_dequant(fn, handle, codes, idx, self.D)
+            if r is not None:
+                if r.__class__ is int:
+                    _check(r)
+                return r
         import torch
         M = idx.shape[0]
         if out is None:
@@ -301,11 +329,26 @@ class Quantizer:
                   indices.shape[0], _dev_ptr(out, (torch.float32,)), _stream()))
         return out
 
+    def _aggregate_native(self, fns, codes, indptr, indices):
+        """The output, or None where _aggregate has to look at the arguments."""
+        r = (_calls or _load_calls()).aggregate(fns[0], fns[1], self._native[0], codes, indptr, indices, self.D)
+        if r.__class__ is int:
+            _check(r)
+        return r
+
     def gather_mean(self, codes, indptr, indices, out=None):
+        if out is None:
+            r = self._aggregate_native(self._native[2], codes, indptr, indices)
+            if r is not None:
+                return r
         return self._aggregate(self._lib.bifeat_gather_mean, self._lib.bifeat_gather_mean_i32,
                                codes, indptr, indices, out)
 
     def gather_sum(self, codes, indptr, indices, out=None):
+        if out is None:
+            r = self._aggregate_native(self._native[3], codes, indptr, indices)
+            if r is not None:
+                return r
         return self._aggregate(self._lib.bifeat_gather_sum, self._lib.bifeat_gather_sum_i32,
                                codes, indptr, indices, out)
 
