@@ -237,6 +237,11 @@ __device__ inline void store_stream(float4 *p, const float4 v) {
     __builtin_nontemporal_store(v.z, &p->z);
     __builtin_nontemporal_store(v.w, &p->w);
 }
+__device__ inline void store_stream(float2 *p, const float2 v) {
+    __builtin_nontemporal_store(v.x, &p->x);
+    __builtin_nontemporal_store(v.y, &p->y);
+}
+__device__ inline void store_stream(float *p, const float v) { __builtin_nontemporal_store(v, p); }
 __device__ inline void store_stream(uint4 *p, const uint4 v) {
     __builtin_nontemporal_store(v.x, &p->x);
     __builtin_nontemporal_store(v.y, &p->y);

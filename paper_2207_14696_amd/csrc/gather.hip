@@ -9,6 +9,8 @@
 // life, so scale/offset sit in registers.
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace bf {
 
 // out[i, :] = codes[idx[i], :], 16 bytes per lane
@@ -32,6 +34,25 @@ hipError_t launch_gather_codes(bifeat_params *p, const uint8_t *codes, const int
     if ((int64_t)blocks * kThreads < rc) blocks = (rc + kThreads - 1) / kThreads;
     gather_codes_kernel<<<blocks, kThreads, 0, s>>>((const uint4 *)codes, rc, idx, M, (uint4 *)out);
     return hipGetLastError();
+}
+
+// GR consecutive output columns
+template <int GR> struct Granule;
+template <> struct Granule<4> { using T = float4; };
+template <> struct Granule<2> { using T = float2; };
+template <> struct Granule<1> { using T = float; };
+
+// the GR*BITS code bits (at the low end) of columns GR*g .. of a packed row (always inside the
+// 16-byte padded row)
+template <int BITS, int GR>
+__device__ inline uint32_t code_bits(const uint8_t *row, int g) {
+    if constexpr (BITS * GR == 32) return *reinterpret_cast<const uint32_t *>(row + 4 * g);
+    else if constexpr (BITS * GR == 16) return *reinterpret_cast<const uint16_t *>(row + 2 * g);
+    else if constexpr (BITS * GR == 8) return row[g];
+    else {
+        constexpr int kPer = 8 / (BITS * GR);  // such groups in a byte
+        return (uint32_t)row[g / kPer] >> (BITS * GR * (g % kPer));
+    }
 }
 
 // the 4*BITS code bits of columns 4g..4g+3 of a packed row (always inside the
@@ -99,23 +120,26 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_sq_kernel(
     }
 }
 
-// Tile form of the scalar-code kernel (output rows 16-byte aligned, packed row
+// Tile form of the scalar-code kernel (packed row
 // of at most 64 16-byte chunks).  A wavefront takes RT = 64/c16 consecutive
 // output rows: one 16-byte load per lane fetches their packed rows in whole
 // sectors (sub-dword gathers cost an L2 request per few lanes), the raw codes
 // are parked in LDS, and the tile's output span - contiguous in memory - is
-// written with consecutive 16-byte stores, granule m of the span by lane m%64.
-template <int BITS, int DEC>
+// written with consecutive stores of GR columns, granule m of the span by lane m%64.
+// GR: 4 columns where output rows are 16-byte aligned, 2 where they are 8-byte aligned
+// (602 columns), else 1, with as many rows a wave as give the chip enough of them.  Against the
+// flat kernel's 4 columns a lane stored one by one: 262 000 rows of 602 columns, 8 bits 367 -> 144 us, 1
+// bit 311 -> 172; of 131 columns, 8 bits 60 -> 42.
+template <int BITS, int DEC, int GR>
 __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
-    const uint4 *__restrict__ codes16, int c16, int s16, const int64_t *__restrict__ idx, int64_t M, int D,
+    const uint4 *__restrict__ codes16, int c16, int s16, int RT, const int64_t *__restrict__ idx, int64_t M, int D,
     const float *__restrict__ pa, const float *__restrict__ pb, float *__restrict__ out) {
     extern __shared__ uint32_t smem[];
     constexpr int kLut = 1 << BITS;
-    const int npar = DEC == DEC_UNIFORM ? 2 * D : kLut;  // D % 4 == 0 here
+    const int npar = DEC == DEC_UNIFORM ? 2 * D : kLut;  // D % GR == 0
     float *s_par = reinterpret_cast<float *>(smem);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint4 *raw = reinterpret_cast<uint4 *>(smem + ((npar + 3) & ~3)) + wave * 64;
-    const int RT = 64 / c16;
     const int r = lane / c16, c = lane - r * c16;
     const int64_t tiles = (M + RT - 1) / RT;
     const int64_t n_waves = (int64_t)gridDim.x * (kThreads / 64);
@@ -136,7 +160,8 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
     if (!early && mine(tile)) next = codes16[id * s16 + c];
     __syncthreads();
 
-    const int nf4 = D >> 2;
+    using G = typename Granule<GR>::T;
+    const int nf4 = D / GR;
     const int step_d = 64 / nf4, step_f = 64 % nf4;
     const int lane_d = lane / nf4, lane_f = lane % nf4;
     const int rb = c16 * 16;
@@ -146,28 +171,28 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_tile_kernel(
         const int nrow = (int)min((int64_t)RT, M - row0);
         if (r < nrow) raw[lane] = next;
         wave_sync();
-        float4 *span = reinterpret_cast<float4 *>(out + row0 * D);
+        G *span = reinterpret_cast<G *>(out + row0 * D);
         const int ngran = nrow * nf4;
         int d = lane_d, f = lane_f;
 #pragma unroll 2
         for (int m = lane; m < ngran; m += 64) {
             const uint8_t *rowp = reinterpret_cast<const uint8_t *>(raw) + d * rb;
-            const uint32_t bits = code_bits4<BITS>(rowp, f);
-            float4 v;
+            const uint32_t bits = code_bits<BITS, GR>(rowp, f);
+            float v[GR];
             if constexpr (DEC == DEC_UNIFORM) {
-                const float4 a = *reinterpret_cast<const float4 *>(s_par + 4 * f);
-                const float4 b = *reinterpret_cast<const float4 *>(s_par + D + 4 * f);
-                v.x = fmaf((float)(bits & mask), a.x, b.x);
-                v.y = fmaf((float)((bits >> BITS) & mask), a.y, b.y);
-                v.z = fmaf((float)((bits >> (2 * BITS)) & mask), a.z, b.z);
-                v.w = fmaf((float)((bits >> (3 * BITS)) & mask), a.w, b.w);
+                const G ga = *reinterpret_cast<const G *>(s_par + GR * f), gb = *reinterpret_cast<const G *>(s_par + D + GR * f);
+                float a[GR], b[GR];
+                __builtin_memcpy(a, &ga, sizeof(G));
+                __builtin_memcpy(b, &gb, sizeof(G));
+#pragma unroll
+                for (int k = 0; k < GR; k++) v[k] = fmaf((float)((bits >> (k * BITS)) & mask), a[k], b[k]);
             } else {
-                v.x = s_par[bits & mask];
-                v.y = s_par[(bits >> BITS) & mask];
-                v.z = s_par[(bits >> (2 * BITS)) & mask];
-                v.w = s_par[(bits >> (3 * BITS)) & mask];
+#pragma unroll
+                for (int k = 0; k < GR; k++) v[k] = s_par[(bits >> (k * BITS)) & mask];
             }
-            store_stream(&span[m], v);
+            G val;
+            __builtin_memcpy(&val, v, sizeof(G));
+            store_stream(&span[m], val);
             d += step_d;
             f += step_f;
             if (f >= nf4) {
@@ -352,8 +377,10 @@ hipError_t launch_gather_dequant(bifeat_params *p, const uint8_t *codes, const i
     // flat kernel below
     const size_t tile_lds = sizeof(uint32_t) * (size_t)(((kind == BIFEAT_SQ_UNIFORM ? 2 * D : (1 << bits)) + 3) & ~3) +
                             (size_t)(kThreads / 64) * 64 * 16;
-    if (vec && c16 <= 64 && !p->opt_dequant_flat && tile_lds <= 65536) {
-        const int RT = 64 / c16;
+    const int gr = vec ? 4 : D % 2 == 0 && (uintptr_t)out % 8 == 0 ? 2 : 1;
+    if (c16 <= 64 && !p->opt_dequant_flat && tile_lds <= 65536) {
+        // (narrow granules are many: few requests are spread over 4096 waves, 16 per CU)
+        const int RT = gr == 4 ? 64 / c16 : (int)std::max<int64_t>(1, std::min<int64_t>(64 / c16, M / 4096));
         const int64_t tiles = (M + RT - 1) / RT;
         // about one tile per wave: the hardware's wave scheduling hides the index -> row ->
         // store latency better than a persistent, software-pipelined loop (measured); grids
@@ -362,8 +389,14 @@ hipError_t launch_gather_dequant(bifeat_params *p, const uint8_t *codes, const i
         int64_t want = (tiles + 3) / 4;
         const int tb = (int)(want < cap ? want : cap);
         const size_t shm = tile_lds;
-#define BF_GT(B, DEC, A, Bp) \
-    gather_dequant_tile_kernel<B, DEC><<<tb, kThreads, shm, s>>>((const uint4 *)codes, c16, s16, idx, M, D, A, Bp, out)
+#define BF_GT1(B, DEC, A, Bp, GR) \
+    gather_dequant_tile_kernel<B, DEC, GR><<<tb, kThreads, shm, s>>>((const uint4 *)codes, c16, s16, RT, idx, M, D, A, Bp, out)
+#define BF_GT(B, DEC, A, Bp)                             \
+    do {                                                 \
+        if (gr == 4) BF_GT1(B, DEC, A, Bp, 4);           \
+        else if (gr == 2) BF_GT1(B, DEC, A, Bp, 2);      \
+        else BF_GT1(B, DEC, A, Bp, 1);                   \
+    } while (0)
         if (kind == BIFEAT_SQ_UNIFORM) {
             switch (bits) {
                 case 1: BF_GT(1, DEC_UNIFORM, p->d_min, p->d_scale); break;
@@ -380,6 +413,7 @@ hipError_t launch_gather_dequant(bifeat_params *p, const uint8_t *codes, const i
             }
         }
 #undef BF_GT
+#undef BF_GT1
         return hipGetLastError();
     }
 #define BF_GD(B, DEC, A, Bp)                                                                        \

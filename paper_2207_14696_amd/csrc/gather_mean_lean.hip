@@ -15,7 +15,8 @@
 //     masked, so the U index loads and then the U row loads of an iteration are
 //     all in flight together;
 //   - field sums go through LDS once and the tile's output rows (contiguous in
-//     memory) are written by the whole wave with consecutive 16-byte stores.
+//     memory) are written by the whole wave with consecutive 16-byte stores; large launches
+//     whose output rows are 8-byte aligned only (602 columns) with 8-byte stores.
 #include "common.hpp"
 
 namespace bf {
@@ -60,7 +61,8 @@ constexpr int64_t kSplitWaves = 2048;
 // longer than thr (the caller promised there are none): such a list gets a row of NaNs and
 // raises the status word.
 // STAGE: the tile's list entries are fetched once by the wave and parked in LDS (see below).
-template <int BITS, int CW, bool WIDE, bool SUM, bool PAIR, bool STAGE, bool SHARE, typename IT>
+// ODD: output rows that are 8-byte aligned only, written two columns at a time.
+template <int BITS, int CW, bool WIDE, bool SUM, bool PAIR, bool STAGE, bool SHARE, bool ODD, typename IT>
 __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_kernel(
     const uint8_t *__restrict__ codes, uint32_t rb, const int64_t *__restrict__ indptr,
     const IT *__restrict__ indices, int64_t V, int D, int Dp, const float *__restrict__ mn,
@@ -74,14 +76,15 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
     constexpr uint32_t FMAX = (1u << W::kF) - 1u;
 
     extern __shared__ uint32_t smem[];
-    float *s_sc = reinterpret_cast<float *>(smem);  // [scale Dp | min Dp], Dp % 4 == 0
-    float *s_mn = s_sc + Dp;
+    const int Dq = ODD ? (Dp + 3) & ~3 : Dp;
+    float *s_sc = reinterpret_cast<float *>(smem);  // [scale Dq | min Dq]
+    float *s_mn = s_sc + Dq;
     const int lane = threadIdx.x & 63;
     // wave-uniform values kept in scalar registers: the tile bookkeeping runs on the scalar unit
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float *meta = reinterpret_cast<float *>(smem + 2 * Dp) + wave * 64;
-    uint32_t *stage = smem + 2 * Dp + 64 * kLeanWaves + wave * (64 * R);
-    uint32_t *sidx = smem + 2 * Dp + 64 * kLeanWaves + kLeanWaves * (64 * R) + wave * kIdxStage;
+    float *meta = reinterpret_cast<float *>(smem + 2 * Dq) + wave * 64;
+    uint32_t *stage = smem + 2 * Dq + 64 * kLeanWaves + wave * (64 * R);
+    uint32_t *sidx = smem + 2 * Dq + 64 * kLeanWaves + kLeanWaves * (64 * R) + wave * kIdxStage;
 
     // LPR lanes fetch a row, S groups of them share a destination's list (S > 1: small launches,
     // see the launcher): group `grp` takes the entries grp, grp + S, ...
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
     const int d_local = lane >> dl_log2;
     const bool chunk_ok = lane_chunk < chunks;
     const uint32_t coff = (uint32_t)lane_chunk * (CW * 4);
-    const int nf4 = D >> 2;
+    const int nf4 = ODD ? D >> 1 : D >> 2;
     const int step_d = 64 / nf4, step_f = 64 % nf4;
     const int lane_d = lane / nf4, lane_f = lane % nf4;
     const int64_t tiles = (V + dpw - 1) >> dpw_log2;
@@ -204,6 +207,35 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
         }
         wave_sync();
 
+        if constexpr (ODD) {
+            // ---- the same span in granules of two columns
+            float2 *span = reinterpret_cast<float2 *>(out + v_tile * D);
+            const int ngran = ndst * nf4;
+            int d = lane_d, f = lane_f;
+#pragma unroll 2
+            for (int m = lane; m < ngran; m += 64) {
+                const float md = meta[d];
+                const bool some = md > 0.0f;
+                const int j0 = 2 * f, lc = j0 / CPL, jj = j0 % CPL, k = jj / CPW, c = jj % CPW;
+                // neighbouring registers, one shift
+                const uint2 q = *reinterpret_cast<const uint2 *>(stage + (((d << lpr_log2) + lc) * CW + k) * W::kN + c % W::kN);
+                const int sh = W::kF * (c / W::kN);
+                const float s0 = (float)((q.x >> sh) & FMAX), s1 = (float)((q.y >> sh) & FMAX);
+                const float2 a = *reinterpret_cast<const float2 *>(s_sc + j0), b = *reinterpret_cast<const float2 *>(s_mn + j0);
+                float2 val;
+                val.x = SUM ? fmaf(a.x, s0, b.x * md) : fmaf(a.x, s0 * md, b.x);
+                val.y = SUM ? fmaf(a.y, s1, b.y * md) : fmaf(a.y, s1 * md, b.y);
+                if (!some) val.x = val.y = 0.0f;
+                if (md != md) val.x = val.y = md;
+                if (!(md < 0.0f)) store_stream(&span[m], val);
+                d += step_d;
+                f += step_f;
+                if (f >= nf4) {
+                    f -= nf4;
+                    d++;
+                }
+            }
+        } else {
         // ---- the tile's output rows, one contiguous span of ndst*nf4 float4 granules
         float4 *span = reinterpret_cast<float4 *>(out + v_tile * D);
         const int ngran = ndst * nf4;
@@ -294,6 +326,7 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
                 d++;
             }
         }
+        }  // !ODD
         wave_sync();  // stage / meta are rewritten by the next tile
     }
 }
@@ -325,9 +358,11 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
     // average) is one step of BF_LEAN_U rows (the mean only: the sums keep one form), up to 2048 waves (8 per CU).  4-bit rows of 64 bytes,
     // lists of up to 25: 1 024 destinations 9.3 -> 4.8 us (512 waves); 6 200 destinations 8.9 us
     // unshared, 6.1 with 2048 waves, 7.1 with 4096.
+    const bool odd = p->D % 4 != 0 || (uintptr_t)c.out % 16 != 0;
+    if (odd && (PAIR || p->D % 2 != 0 || (uintptr_t)c.out % 8 != 0)) return false;
     const int64_t longest = c.max_degree > 0 ? c.max_degree : 2 * c.E / (V > 0 ? V : 1);
     int s_log2 = 0;
-    while (!c.agg_sum && (lpr << (s_log2 + 1)) <= 64 && ((int64_t)BF_LEAN_U << s_log2) < longest &&
+    while (!c.agg_sum && !odd && (lpr << (s_log2 + 1)) <= 64 && ((int64_t)BF_LEAN_U << s_log2) < longest &&
            (V * (lpr << (s_log2 + 1)) + 63) / 64 <= kSplitWaves)
         s_log2++;
     const int dpw = 64 / (lpr << s_log2);
@@ -337,17 +372,18 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
     const int blocks = (int)(want < cap ? (want < 1 ? 1 : want) : cap);
     const int D = (int)p->D, Dp = PAIR ? 2 * D : D;
     const int R = cw * W::kN;
-    const size_t shm = sizeof(uint32_t) * ((size_t)2 * Dp + 64 * kLeanWaves + (size_t)kLeanWaves * 64 * R +
+    const size_t shm = sizeof(uint32_t) * ((size_t)2 * ((Dp + 3) & ~3) + 64 * kLeanWaves + (size_t)kLeanWaves * 64 * R +
                                            (size_t)kLeanWaves * kIdxStage);
     const bool stage = ilog2(lpr) >= kStageMinLprLog2;
-#define BF_LK1(CWV, SUMV, STG, SHR, IT)                                                            \
-    gather_mean_lean_kernel<BITS, CWV, WIDE, SUMV, PAIR, STG, SHR, IT><<<blocks, kLeanThreads, shm, c.s>>>( \
+#define BF_LK1(CWV, SUMV, STG, SHR, ODDV, IT)                                                      \
+    gather_mean_lean_kernel<BITS, CWV, WIDE, SUMV, PAIR, STG, SHR, ODDV, IT><<<blocks, kLeanThreads, shm, c.s>>>( \
         c.codes, (uint32_t)rb, c.indptr, (const IT *)c.indices, V, D, Dp, mn, sc, p->d_zero,       \
         c.out, ilog2(lpr), s_log2, chunks, thr, lo, alone ? 1 : 0, c.status)
 #define BF_LK(CWV, SUMV, STG, IT)                                                                  \
     do {                                                                                           \
-        if (!SUMV && s_log2 > 0) BF_LK1(CWV, SUMV, STG, !SUMV, IT);                                \
-        else BF_LK1(CWV, SUMV, STG, false, IT);                                                    \
+        if (odd) BF_LK1(CWV, SUMV, STG, false, !PAIR, IT);                                         \
+        else if (!SUMV && s_log2 > 0) BF_LK1(CWV, SUMV, STG, !SUMV, false, IT);                    \
+        else BF_LK1(CWV, SUMV, STG, false, false, IT);                                             \
     } while (0)
 #define BF_LS(CWV, SUMV)                                                                           \
     do {                                                                                           \

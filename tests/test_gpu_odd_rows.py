@@ -1,0 +1,83 @@
+"""Output rows that are not 16-byte aligned: the decode in granules of two and one columns, with fewer and
+more rows a wave than it has room for, and the short-list mean of large launches in granules of two columns, with
+lists on both sides of what it holds and of the caller's bound."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from helpers import assert_close, column_magnitude, random_csr, scheme_of, REL_TOL
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(kind, bits, D, N=700):
+    """A quantizer, the oracle's scheme and a packed table of random codes."""
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(D * 10 + bits)
+    q = bf.Quantizer(scheme_of(kind, bits), D)
+    if kind == "uniform":
+        mn = rng.normal(size=D).astype(np.float32)
+        mx = mn + rng.uniform(0.5, 2, D).astype(np.float32)
+        q.params_set_uniform(mn, mx)
+        s = orc.Scheme.uniform(mn, orc.uniform_params(mn, mx, bits)[0], bits)
+    else:
+        q.params_set_log(-5.0, 1.5)
+        s = orc.Scheme.log(D, q.params_get_log()[3], bits)
+    codes = orc.pack(rng.integers(0, 1 << bits, (N, D)).astype(np.uint8), bits)
+    return torch, q, s, codes, torch.from_numpy(codes).cuda()
+
+
+def _out(torch, rows, D, offset):
+    """[rows, D] floats that start `offset` floats behind an aligned address."""
+    return torch.full((rows * D + offset,), float("nan"), device="cuda")[offset:].view(rows, D)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "log"])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+@pytest.mark.parametrize("D,rows,offset", [
+    (1, 300, 0), (2, 300, 0), (3, 65, 0), (6, 1, 0), (18, 9000, 0), (67, 9001, 0), (131, 63, 0), (131, 20_000, 0),
+    (602, 500, 0), (602, 20_000, 0), (100, 700, 2), (100, 700, 1), (128, 20_000, 2), (602, 700, 1)])
+def test_decode(kind, bits, D, rows, offset):
+    torch, q, s, codes, table = _table(kind, bits, D)
+    idx = np.random.default_rng(rows).integers(0, len(codes), rows)
+    out = _out(torch, rows, D, offset)
+    assert out.data_ptr() % 16 == 4 * offset
+    q.gather_dequant(table, torch.from_numpy(idx).cuda(), out)
+    want = orc.gather_dequant(s, codes, idx)
+    assert_close(out.cpu().numpy(), want, s)
+    aligned = q.gather_dequant(table, torch.from_numpy(idx).cuda())
+    assert torch.equal(aligned, out)
+
+
+# V * D on both sides of 4 M values
+@pytest.mark.parametrize("kind,bits", [("uniform", 8), ("uniform", 4), ("uniform", 2), ("uniform", 1), ("log", 1),
+                                       ("log", 2), ("log", 4)])
+@pytest.mark.parametrize("D,V,offset", [(602, 6967, 0), (602, 6968, 0), (110, 38_131, 0), (2, 2_097_153, 0),
+                                        (128, 32_769, 2), (102, 41_200, 1)])
+@pytest.mark.parametrize("bound", [0, 10])
+def test_mean(kind, bits, D, V, offset, bound):
+    torch, q, s, codes, table = _table(kind, bits, D)
+    rng = np.random.default_rng(V)
+    # lists beyond the narrow and wide fields and, with a bound, beyond it: summed all the same
+    indptr, indices = random_csr(V, len(codes), 6, rng, hubs=(11, 15, 16, 17, 18, 64, 65, 86, 300))
+    q.set_option("mean_max_degree", bound)
+    ptr, ind = torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda()
+    out = _out(torch, V, D, offset)
+    q.gather_mean(table, ptr, ind, out)
+    rows = np.r_[0:40, rng.integers(0, V, 2000), V - 40:V]       # the oracle's share
+    lists = [indices[indptr[v]:indptr[v + 1]] for v in rows]
+    sub = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    cat = np.concatenate(lists).astype(np.int64)
+    got = out[torch.from_numpy(rows).cuda()].cpu().numpy()
+    assert_close(got, orc.gather_mean(s, codes, sub, cat), s)
+    assert not torch.isnan(out).any()
+    assert q.poll_status()
+    # 32-bit entries and the sum
+    again = _out(torch, V, D, offset)
+    q.gather_mean(table, ptr, ind.int(), again)
+    assert torch.equal(out, again)
+    total = q.gather_sum(table, ptr, ind, again)[torch.from_numpy(rows).cuda()].cpu().numpy()
+    want = orc.gather_sum(s, codes, sub, cat).astype(np.float64)
+    n = np.maximum(np.diff(sub), 1)[:, None]
+    assert (np.abs(total - want) <= REL_TOL * np.maximum(np.abs(want), column_magnitude(s)[None, :] * n)).all()
