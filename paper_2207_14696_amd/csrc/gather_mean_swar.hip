@@ -53,6 +53,7 @@ template <> struct Swar<1> {
 enum : uint32_t { F_SKIP = 1u, F_MORE = 2u, F_PREV = 4u, F_EMPTY = 8u };
 
 constexpr int kWaves = kThreads / 64;
+constexpr int64_t kSlotWaves = 4096;
 #ifndef BF_SWAR_WPE
 #define BF_SWAR_WPE 4
 #endif
@@ -416,6 +417,14 @@ static void launch_swar(bifeat_params *p, const MeanCall &c, int vec, int min_le
         S = pow2ceil((int)((avg + 15) / 16 > 64 ? 64 : (avg + 15) / 16));
     }
     S = pow2ceil(S);
+    // Few destinations whose rows are not 16-byte aligned: each group writes its own row there, four
+    // values a lane at a time, and a narrow row's single lane all of it.  More slots, up to one per entry
+    // of the longest list to be expected, give such launches lanes and waves (1472 lists of up to 10 rows
+    // of 110 columns, 1 bit 37 -> 8 us, 4 bits 9.2 -> 5.9; of 602, 1 bit 22 -> 11; 46 546 of 131, 1 bit 37 -> 31).
+    const int64_t longest = c.max_degree > 0 ? c.max_degree : 2 * E / (V > 0 ? V : 1);
+    while (!vec && min_len < 0 && p->opt_mean_slots <= 0 && S < longest && lpr * S * 2 <= 64 &&
+           V * lpr * S * 2 <= 64 * kSlotWaves)
+        S *= 2;
     while (lpr * S > 64) S >>= 1;
     int long_thr = 32 * S;
     if (long_thr > W::kCap1) long_thr = W::kCap1;
