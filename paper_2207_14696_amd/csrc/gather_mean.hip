@@ -149,29 +149,38 @@ static void launch_float(bifeat_params *p, const MeanCall &c, const float *pa, c
 
 // ------------------------------------------------ two rounds, general form
 // out[v] = mean over the seed list of v of the means over the outer lists of decoded rows, for
-// every kind of code and any list length.  A wave owns a destination; its lanes take 4 output
-// columns each (in rounds of 256 columns); an outer list is summed in fp32 runs of kRun rows
-// combined in fp64, and the rounds' divisions and the seed list's sum are fp64.
+// every kind of code and any list length.  A wave, or where it pays all four of a workgroup (WPS),
+// own a destination; 2^gl_log2 lanes take 4 output columns each (in rounds of 256 columns), and the
+// groups that a wave then has room for share the seed list's entries.  An outer list is summed in fp32
+// runs of kRun rows combined in fp64, and the rounds' divisions and the seed list's sum are fp64.
+// What bounds it: an entry is a chain of dependent fetches (entry, list bounds, row ids, rows), so
+// entries side by side are what counts, and the next entry's bounds travel during one.  A wave a seed,
+// lanes past the last column idle / now: 256 seeds of 768 columns, 4-bit logarithmic codes 121 / 38 us, of
+// 100 columns 44 / 11; 32 768 seeds of 100 columns 293 / 210, of 40 230 / 101.
 // only_over > 0: the bounded kernel ran first with that bound and left out the destinations
 // that have a list longer than it; only those are done here (the wave looks at its seed
 // list's entries 64 at a time).
-template <int KIND, int BITS, bool VEC>
+template <int KIND, int BITS, bool VEC, int WPS, bool GROUPS>
 __global__ __launch_bounds__(kThreads) void gather_mean_2hop_float_kernel(
     const uint8_t *__restrict__ codes, int64_t rb, const int64_t *__restrict__ indptr1,
     const int64_t *__restrict__ indices1, const int64_t *__restrict__ indptr2,
     const int64_t *__restrict__ indices2, int64_t V2, int D, const float *__restrict__ pa,
-    const float *__restrict__ pb, int w, int len, int only_over, float *__restrict__ out) {
+    const float *__restrict__ pb, int w, int len, int only_over, int gl_log2, float *__restrict__ out) {
     __shared__ float s_lut[KIND == MK_LOG ? (1 << (BITS & 15)) : 1];
+    constexpr int kSeeds = kThreads / 64 / WPS;  // destinations of a workgroup at a time
+    __shared__ double s_part[WPS > 1 ? (WPS - 1) * 64 * 4 : 1];
     if constexpr (KIND == MK_LOG) {
         for (int i = threadIdx.x; i < (1 << BITS); i += kThreads) s_lut[i] = pa[i];
         __syncthreads();
     }
     const int G = (D + 3) / 4;
-    const int lane = threadIdx.x & 63;
-    const int64_t n_waves = (int64_t)gridDim.x * (kThreads / 64);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // (a wave alone on its seed, one group, is compiled apart: large launches lose 12 % with the rest)
+    const int gl = GROUPS ? gl_log2 : 6, groups = 64 >> gl;
+    const int share = (wave % WPS) * groups + (lane >> gl), shares = WPS * groups;
     constexpr uint32_t mask = (1u << BITS) - 1u;
     constexpr int kRun = 32;
-    for (int64_t v = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); v < V2; v += n_waves) {
+    for (int64_t v = (int64_t)blockIdx.x * kSeeds + wave / WPS; v < V2; v += (int64_t)gridDim.x * kSeeds) {
         const int64_t beg2 = indptr2[v], end2 = indptr2[v + 1];
         if (only_over > 0) {
             bool over = end2 - beg2 > only_over;
@@ -185,7 +194,12 @@ __global__ __launch_bounds__(kThreads) void gather_mean_2hop_float_kernel(
             }
             if (!over) continue;
         }
-        for (int g = lane; g < G; g += 64) {
+        // (every lane stays in the loop; those past the last column have no entries)
+        for (int g0 = 0; g0 < G; g0 += 1 << gl) {
+            const int mine = g0 + (lane & ((1 << gl) - 1));
+            if (!GROUPS && mine >= G) break;
+            const int g = GROUPS ? min(mine, G - 1) : mine;
+            const int64_t last2 = !GROUPS || mine < G ? end2 : beg2;
             const int col0 = 4 * g;
             float mn[4], sc[4];
             int part[4], dim[4];
@@ -202,9 +216,20 @@ __global__ __launch_bounds__(kThreads) void gather_mean_2hop_float_kernel(
                 }
             }
             double outer[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int64_t e2 = beg2; e2 < end2; e2++) {
-                const int64_t u = indices2[e2];
-                const int64_t beg = indptr1[u], end = indptr1[u + 1];
+            int64_t beg_next = 0, end_next = 0;
+            auto bounds = [&](int64_t e2) {
+                if (e2 < last2) {
+                    const int64_t u = indices2[e2];
+                    beg_next = indptr1[u];
+                    end_next = indptr1[u + 1];
+                }
+            };
+            constexpr bool kAhead = WPS > 1;  // (where waves are many it costs 8 %)
+            if constexpr (kAhead) bounds(beg2 + share);
+            for (int64_t e2 = beg2 + share; e2 < last2; e2 += shares) {
+                if constexpr (!kAhead) bounds(e2);
+                const int64_t beg = beg_next, end = end_next;
+                if constexpr (kAhead) bounds(e2 + shares);
                 if (end == beg) continue;  // a zero row
                 double total1[4] = {0.0, 0.0, 0.0, 0.0};
                 for (int64_t c0 = beg; c0 < end; c0 += kRun) {
@@ -238,6 +263,23 @@ __global__ __launch_bounds__(kThreads) void gather_mean_2hop_float_kernel(
 #pragma unroll
                 for (int k = 0; k < 4; k++) outer[k] += total1[k] * inv1;
             }
+            // the shares add up: the wave's groups, then the waves
+            for (int m = 1 << gl; GROUPS && m < 64; m <<= 1)
+#pragma unroll
+                for (int k = 0; k < 4; k++) outer[k] += __shfl_xor(outer[k], m);
+            if constexpr (WPS > 1) {
+                __syncthreads();  // (the partial sums of the round before have been read)
+                if (wave % WPS > 0)
+#pragma unroll
+                    for (int k = 0; k < 4; k++) s_part[((wave % WPS - 1) * 64 + lane) * 4 + k] = outer[k];
+                __syncthreads();
+                if (wave % WPS == 0)
+#pragma unroll
+                    for (int o = 0; o < WPS - 1; o++)
+#pragma unroll
+                        for (int k = 0; k < 4; k++) outer[k] += s_part[(o * 64 + lane) * 4 + k];
+            }
+            if (GROUPS && (share > 0 || mine >= G)) continue;
             const double inv2 = end2 > beg2 ? 1.0 / (double)(end2 - beg2) : 0.0;
             float res[4];
 #pragma unroll
@@ -258,18 +300,29 @@ template <int KIND>
 static void launch_2hop_float(bifeat_params *p, const HopCall &c, const float *pa, const float *pb,
                               int vec, int only_over) {
     const int D = (int)p->D;
-    const int blocks = blocks_for(c.V2 * 64, 1 << 16);  // a wave per destination
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
+    const int gl_log2 = ilog2((D + 3) / 4 < 64 ? (D + 3) / 4 : 64);
+    // A workgroup a seed while the chip waits for chains of fetches rather than for rows: 8192 seeds, 480 000
+    // rows in all 95 -> 75 us (131 columns, 4-bit logarithmic); 7145 seeds, 790 000 rows would lose 7 %, 32 768
+    // seeds up to a fifth.
+    const double rows = (double)c.E2 * (double)c.E1 / (double)(c.V1 > 0 ? c.V1 : 1);
+    const bool wide = only_over == 0 && c.V2 <= 8192 && rows <= (1 << 19);
+    const int blocks = blocks_for(c.V2 * (wide ? kThreads : 64), 1 << 16);
+#define BF_HF1(B, VECV, WPS, GROUPS)                                                               \
+    gather_mean_2hop_float_kernel<KIND, B, VECV, WPS, GROUPS><<<blocks, kThreads, 0, c.s>>>(               \
+        c.codes, p->rb, c.indptr1, c.indices1, c.indptr2, c.indices2, c.V2, D, pa, pb, w, len,     \
+        only_over, gl_log2, c.out)
 #define BF_HF(B)                                                                                   \
     do {                                                                                           \
-        if (vec)                                                                                   \
-            gather_mean_2hop_float_kernel<KIND, B, true><<<blocks, kThreads, 0, c.s>>>(            \
-                c.codes, p->rb, c.indptr1, c.indices1, c.indptr2, c.indices2, c.V2, D, pa, pb, w,  \
-                len, only_over, c.out);                                                            \
-        else                                                                                       \
-            gather_mean_2hop_float_kernel<KIND, B, false><<<blocks, kThreads, 0, c.s>>>(           \
-                c.codes, p->rb, c.indptr1, c.indices1, c.indptr2, c.indices2, c.V2, D, pa, pb, w,  \
-                len, only_over, c.out);                                                            \
+        if (vec) {                                                                                 \
+            if (wide) BF_HF1(B, true, 4, true);                                                    \
+            else if (gl_log2 < 6) BF_HF1(B, true, 1, true);                                        \
+            else BF_HF1(B, true, 1, false);                                                        \
+        } else {                                                                                   \
+            if (wide) BF_HF1(B, false, 4, true);                                                   \
+            else if (gl_log2 < 6) BF_HF1(B, false, 1, true);                                       \
+            else BF_HF1(B, false, 1, false);                                                       \
+        }                                                                                          \
     } while (0)
     if constexpr (KIND == MK_VQ4 || KIND == MK_VQ) {
         if (p->cbytes == 2) BF_HF(16);
@@ -283,6 +336,7 @@ static void launch_2hop_float(bifeat_params *p, const HopCall &c, const float *p
         }
     }
 #undef BF_HF
+#undef BF_HF1
 }
 
 hipError_t launch_gather_mean_2hop(bifeat_params *p, const HopCall &c) {
@@ -311,8 +365,12 @@ hipError_t launch_gather_mean_2hop(bifeat_params *p, const HopCall &c) {
         launch_2hop_float<MK_LOG>(p, c, p->d_V, nullptr, vec, only_over);
     } else {
         // codebooks in LDS where the sliced kernels' shapes allow (and the workspace can be had)
-        if (vec && p->opt_vq_sliced && launch_gather_mean_2hop_vq_sliced(p, c)) return hipGetLastError();
         const int w = p->scheme.vq_width;
+        // (not for few seeds of narrow rows, where three launches and the staging of the codebooks are what
+        // counts: 256 seeds of 128 columns, 8 a part, 40 us against 11, 2048 44 against 20; 1024 of 256 columns
+        // 42 against 22, 2048 about equal)
+        const bool few = p->opt_vq_sliced == 1 && w % 4 == 0 && D <= 256 && c.V2 * D <= (1 << 18);
+        if (vec && p->opt_vq_sliced && !few && launch_gather_mean_2hop_vq_sliced(p, c)) return hipGetLastError();
         if (w % 4 == 0 && vec) launch_2hop_float<MK_VQ4>(p, c, p->d_cb, nullptr, vec, only_over);
         else launch_2hop_float<MK_VQ>(p, c, p->d_cb, nullptr, vec, only_over);
     }

@@ -319,3 +319,38 @@ def test_replays_from_a_captured_graph(bf, torch):
                 assert_close(got.cpu().numpy(), want_big, s, f"{kind}: eager between replays")
         q.set_option("mean_max_degree", 0)
         assert q.poll_status()
+
+
+# the general kernel: a workgroup and a wave a seed, 1 to 16 groups a wave, several rounds of columns, more
+# entries than shares and fewer, rows that are not 16-byte aligned
+@pytest.mark.parametrize("kind,bits,D", [("log", 4, 8), ("log", 8, 40), ("log", 4, 128), ("log", 4, 132), ("uniform", 8, 3),
+                                         ("uniform", 4, 101), ("uniform", 2, 257), ("uniform", 1, 602), ("log", 8, 516)])
+@pytest.mark.parametrize("V2,max1,max2", [(61, 70, 60), (8192, 4, 3), (8193, 4, 3)])
+def test_general_kernel_shares(bf, torch, kind, bits, D, V2, max1, max2):
+    s, codes, q = _table(bf, kind, bits, D, N=2000)
+    indptr1, indices1, indptr2, indices2 = _blocks(codes.shape[0], 500, V2, max1, max2, np.random.default_rng(D + V2))
+    dev = [torch.from_numpy(a).cuda() for a in (codes, indptr1, indices1, indptr2, indices2)]
+    got = q.gather_mean_2hop(*dev).cpu().numpy()
+    assert_close(got, orc.gather_mean_2hop(s, codes, indptr1, indices1, indptr2, indices2), s)
+
+
+# few seeds of narrow rows read the entries from L2, the slices in LDS give the same
+@pytest.mark.parametrize("D,w,length,V2", [(128, 8, 256, 2048), (128, 8, 256, 2049), (256, 16, 64, 1024), (64, 32, 300, 50),
+                                           (260, 4, 64, 50), (96, 8, 16, 203)])
+def test_vector_codes_of_few_seeds(bf, torch, D, w, length, V2):
+    s, codes, q = _table(bf, "vq", 8, D, N=2500, w=w, length=length) if length <= 256 else _vq2(bf, D, w, length)
+    indptr1, indices1, indptr2, indices2 = _blocks(codes.shape[0], 600, V2, 9, 6, np.random.default_rng(V2))
+    dev = [torch.from_numpy(a).cuda() for a in (codes, indptr1, indices1, indptr2, indices2)]
+    want = orc.gather_mean_2hop(s, codes, indptr1, indices1, indptr2, indices2)
+    assert_close(q.gather_mean_2hop(*dev).cpu().numpy(), want, s)
+    q.set_option("vq_sliced", 2)
+    assert_close(q.gather_mean_2hop(*dev).cpu().numpy(), want, s)
+
+
+def _vq2(bf, D, w, length):
+    rng = np.random.default_rng(length)
+    cb = rng.normal(size=(D // w, length, w)).astype(np.float32)
+    codes = orc.pack(rng.integers(0, length, (2500, D // w)).astype(np.uint16), orc.vq_code_bits(length))
+    q = bf.Quantizer(scheme_of("vq", 8, w, length), D)
+    q.params_set_codebooks(cb)
+    return orc.Scheme.vq(D, cb), codes, q
