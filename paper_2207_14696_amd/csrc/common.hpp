@@ -165,6 +165,7 @@ int logf_capacity();
 bool launch_gather_mean_logf(bifeat_params *p, const MeanCall &c, int thr, bool alone);
 bool launch_gather_mean_lean_log2(bifeat_params *p, const MeanCall &c, int thr, bool wide, int lo,
                                   bool alone);
+bool launch_gather_mean_lean_odd(bifeat_params *p, const MeanCall &c, int thr, bool wide, int lo, bool alone);
 bool launch_gather_mean_lean(bifeat_params *p, const MeanCall &c, int thr, bool wide, int lo,
                              bool alone);
 
