@@ -147,12 +147,14 @@ int64_t bifeat_codes_per_row(const bifeat_params *p);
  *   encoder's rule for the scheme's metric, entry = mean of its members, an
  *   entry without members keeps its value.  Sums are accumulated with atomics,
  *   so the codebooks are reproducible in distortion, not bit for bit.
- *   Training uses library scratch: workgroups' partial sums of the codebooks, and for a large
- *   or cosine codebook also a code per part and sample row (one byte up to 256 entries, else
- *   two), with the sums there within 256 MB, or one set of them if that is larger.  On a stream
- *   that is being captured nothing is allocated: sums that find no room are added to the
- *   handle's own set, and a large or cosine codebook needs room for its codes from an earlier
- *   update or bifeat_reserve (BIFEAT_EHIP otherwise).
+ *   Training uses library scratch: workgroups' partial sums of the codebooks, and for a
+ *   codebook that does not fit a compute unit's on-chip memory next to its sums (w = 8: more than
+ *   about 1100 entries, w = 16: 600, w = 32: 300), of w > 32 or too small or dense for the matrix
+ *   cores mostly also a code per part and sample row (one byte up to 256 entries, else two), with
+ *   the sums there within 256 MB, or one set of them if that is larger.  On a stream that is being
+ *   captured nothing is allocated: sums that find no room are added to the handle's own set, and a
+ *   codebook that cannot do without its codes (of those: cosine, over 256 entries or over 32 KB) has room
+ *   for them from an earlier update or bifeat_reserve (BIFEAT_EHIP otherwise).
  *   finalize synchronises `stream` for the cosine metric
  *   (the entry norms are evaluated on the host in fp64).
  * finalize without any update returns BIFEAT_ENOTFIT. */
@@ -289,7 +291,8 @@ int bifeat_gather_sum_i32(bifeat_params *p, const uint8_t *codes, int64_t N, con
  * general kernel (any list length) the others.  Vector codes of power-of-two
  * width take a kernel with the codebooks in on-chip memory (any list length;
  * uses the handle's workspace like bifeat_gather_mean, sized by E1); the
- * remaining codes take the general kernel throughout.
+ * remaining codes, and few seeds of narrow vector codes (V2 * D of up to 2^18),
+ * take the general kernel throughout.
  * Option "validate" checks both blocks first.  V2 = 0 is a no-op. */
 int bifeat_gather_mean_2hop(bifeat_params *p, const uint8_t *codes, int64_t N,
                             const int64_t *indptr1, const int64_t *indices1, int64_t V1, int64_t E1,
