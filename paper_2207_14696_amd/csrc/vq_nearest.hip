@@ -13,9 +13,9 @@ namespace {
 // order.  One thread to all of the sets that few parts give (64 of 6 x 64 x 4) waits for one load after
 // the other: 20 us of a round's 35.
 template <int GROUPS>
-__global__ __launch_bounds__(kThreads) void vq_means_kernel(const float *__restrict__ sums,
-                                                            const uint32_t *__restrict__ counts, int ny, int P, int w,
-                                                            int len, float *__restrict__ cb) {
+__global__ __launch_bounds__(kThreads) void vq_means_kernel(const void *__restrict__ sums,
+                                                            const uint32_t *__restrict__ counts, int sets, int sub, int P,
+                                                            int w, int len, float *__restrict__ cb) {
     constexpr int OUT = kThreads / GROUPS;
     __shared__ double s_sum[GROUPS > 1 ? kThreads : 1];
     __shared__ uint64_t s_count[GROUPS > 1 ? kThreads : 1];
@@ -28,11 +28,21 @@ __global__ __launch_bounds__(kThreads) void vq_means_kernel(const float *__restr
         const int d = (int)(pd - p * w);
         double sum = 0.0;
         uint64_t count = 0;
-        if (i < n) {
+        if (i < n && sub == 1) {
 #pragma unroll 4
-            for (int k = g; k < ny; k += GROUPS) {
-                sum += (double)sums[k * n + i];
+            for (int k = g; k < sets; k += GROUPS) {
+                sum += (double)static_cast<const float *>(sums)[k * n + i];
                 count += counts[((int64_t)k * P + p) * len + e];
+            }
+        } else if (i < n) {
+            for (int k = g; k < sets; k += GROUPS) {
+                double set = 0.0;
+#pragma unroll 4
+                for (int64_t j = (int64_t)k * sub; j < (int64_t)(k + 1) * sub; j++) {
+                    set += static_cast<const double *>(sums)[j * n + i];
+                    count += counts[(j * P + p) * len + e];
+                }
+                sum += (double)(float)set;
             }
         }
         if constexpr (GROUPS > 1) {
@@ -78,12 +88,15 @@ bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows) {
     return !train || entries_in_lds(p, true);
 }
 
-void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts, int ny, hipStream_t s) {
+void launch_vq_means(bifeat_params *p, const void *sums, const uint32_t *counts, int sets, int sub, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const int64_t n = (int64_t)p->P * len * w;
+#define BF_VM(GROUPS) \
+    vq_means_kernel<GROUPS><<<blocks_for(GROUPS * n), kThreads, 0, s>>>(sums, counts, sets, sub, p->P, w, len, p->d_cb)
     // (a thread each where that fills the chip: 10 sets of 96 x 256 x 8 take 6.5 us so, 13 by groups)
-    if (ny > 8 && n < (1 << 16)) vq_means_kernel<8><<<blocks_for(8 * n), kThreads, 0, s>>>(sums, counts, ny, p->P, w, len, p->d_cb);
-    else vq_means_kernel<1><<<blocks_for(n), kThreads, 0, s>>>(sums, counts, ny, p->P, w, len, p->d_cb);
+    if (sets * sub > 8 && n < (1 << 16)) BF_VM(8);
+    else BF_VM(1);
+#undef BF_VM
 }
 
 BF_VN(float)

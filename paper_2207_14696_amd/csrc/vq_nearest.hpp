@@ -21,7 +21,33 @@ bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t
 template <typename T>
 bool launch_vq_nearest_round(bifeat_params *p, const T *x, int64_t rows, double *distortion, hipStream_t s);
 
-// every entry with members becomes their mean, from ny sets of sums [P][w][len] and counts [P][len]
-void launch_vq_means(bifeat_params *p, const float *sums, const uint32_t *counts, int ny, hipStream_t s);
+// Training's sums.  A set's are added up in 64 bits and rounded to 32, and an entry's mean comes from the
+// sets in their order: which rows make up a set decides the last bits of a codebook, and after some rounds
+// which side rows between two entries fall to.  So the sets follow from the scheme and the number of rows
+// alone: strip k of 2^strip_log2 rows belongs to set k % sets.  How many workgroups there are is up to the kernel:
+// one takes every groups-th set, or `sub` share a set, whose sums stay in 64 bits until they have met.
+struct RowSets {
+    int strip_log2, sets, groups, sub;
+    int64_t share;  // rows of a set that a workgroup takes, a whole number of waves
+};
+RowSets row_sets(const bifeat_params *p, int64_t rows);
+// groups, sub and share for `cols` columns of workgroups of `threads` rows at a time, of which `room` run side by side
+void deal_sets(RowSets &r, int64_t rows, int64_t cols, int64_t room, int threads);
+inline int64_t sums_bytes(const bifeat_params *p, const RowSets &r) {
+    return (int64_t)r.sets * r.sub * p->P * p->scheme.vq_length * ((r.sub > 1 ? 8 : 4) * p->scheme.vq_width + 4);
+}
+// how many rows a set has, and its i-th one
+__device__ inline int64_t set_rows(int set, int sets, int strip_log2, int64_t rows) {
+    const int64_t strips = (rows + (1 << strip_log2) - 1) >> strip_log2, mine = (strips - set + sets - 1) / sets;
+    const int64_t past = ((set + (mine - 1) * sets + 1) << strip_log2) - rows;
+    return (mine << strip_log2) - (past > 0 ? past : 0);
+}
+__device__ inline int64_t set_row(int set, int sets, int strip_log2, int64_t i) {
+    return ((set + (i >> strip_log2) * sets) << strip_log2) + (i & ((1 << strip_log2) - 1));
+}
+
+// every entry with members becomes their mean, from the sums [sets][sub][P][w][len] (64 bits where sub > 1, else
+// 32) and counts [sets][sub][P][len]
+void launch_vq_means(bifeat_params *p, const void *sums, const uint32_t *counts, int sets, int sub, hipStream_t s);
 
 }  // namespace bf

@@ -61,13 +61,14 @@ struct VqNearestArgs {
     int NT;                 // tiles of 32 entries
     int ny;                 // workgroups per part
     int64_t chunk;          // rows of each, a whole number of waves
+    int strip_log2, sets, sub;  // (training) see RowSets
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
     uint32_t cell_mask;     // low bits of a score that hold a cell's number
     int64_t rb, pb;         // (the encoder) from one row's index, one part's to the next
     int one_set;            // (training) every workgroup adds to one set of sums, all zeros
-    float *sums;            // [ny][P][w][len]
-    uint32_t *counts;       // [ny][P][len]
+    void *sums;             // [sets][sub][P][w][len], in 64 bits where sub > 1, else 32
+    uint32_t *counts;       // [sets][sub][P][len]
     double *distortion;
 };
 
@@ -334,22 +335,30 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
             for (int d = 0; d < WP; d++) v[d] = d < w && part * w + d < a.D ? load1(src + d) : 0.0f;
         }
     };
-    // (a row past the last one reads the last one; 64-bit products only where a strip is not whole)
+    // (a row past the last one reads the last one; 64-bit products only where a strip is not whole.  In
+    // training rows are counted within a set)
     const T *const first_row = a.x + (int64_t)part * w;
+    int set = TRAIN ? by / a.sub : 0;
+    const int sub = TRAIN ? by - set * a.sub : by;
     auto clamped = [&](int64_t r0) {
-        const int64_t row = r0 + threadIdx.x;
+        int64_t row = r0 + threadIdx.x;
+        if constexpr (TRAIN) row = set_row(set, a.sets, a.strip_log2, row);
         return first_row + (row < a.rows ? row : a.rows - 1) * a.D;
     };
-    const int64_t begin = by * a.chunk, end = min(a.rows, begin + a.chunk);
-    const T *next = clamped(begin);
+    const T *next;
     auto load_next = [&](int64_t r0, float (&v)[WP]) {
-        next = r0 + 2 * ROWS <= a.rows ? next + (int64_t)ROWS * a.D : clamped(r0 + ROWS);
+        next = !TRAIN && r0 + 2 * ROWS <= a.rows ? next + (int64_t)ROWS * a.D : clamped(r0 + ROWS);
         load_row(next, v);
     };
-    float xn[WP];
     [[maybe_unused]] int strip = 0;
+    [[maybe_unused]] uint8_t *out = codes;
+    do {
+    const int64_t begin = sub * a.chunk;
+    const int64_t end = min(TRAIN ? set_rows(set, a.sets, a.strip_log2, a.rows) : a.rows, begin + a.chunk);
+    if constexpr (!TRAIN) out += (begin + threadIdx.x) * a.rb + part * a.pb;
+    next = clamped(begin);
+    float xn[WP];
     load_row(next, xn);
-    [[maybe_unused]] uint8_t *out = codes + (begin + threadIdx.x) * a.rb + part * a.pb;
     for (int64_t r0 = begin; r0 < end; r0 += ROWS) {
         // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which the halves of
         // the wave then hold for both sets of 32 rows
@@ -753,19 +762,35 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
         }
     }
     if constexpr (TRAIN) {
+        const int this_set = set;
+        set += a.sub > 1 ? a.sets : a.ny;
+        if (a.one_set && set < a.sets) continue;  // (all sets' sums together)
         __syncthreads();
-        const int64_t set = a.one_set ? 0 : by;
-        float *sums = a.sums + (set * a.P + part) * len * w;
-        uint32_t *counts = a.counts + (set * a.P + part) * len;
+        const int64_t to = (a.one_set ? 0 : ((int64_t)this_set * a.sub + sub) * a.P) + part;
+        float *sums = static_cast<float *>(a.sums) + to * len * w;
+        uint32_t *counts = a.counts + to * len;
         if (a.one_set) {
             for (int i = threadIdx.x; i < len * w; i += TH)
                 if (s_sum[i] != 0.0) unsafeAtomicAdd(&sums[i], (float)s_sum[i]);
             for (int i = threadIdx.x; i < len; i += TH)
                 if (s_cnt[i]) atomicAdd(&counts[i], s_cnt[i]);
         } else {
-            for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
+            if (a.sub > 1) {
+                double *wide = static_cast<double *>(a.sums) + to * len * w;
+                for (int i = threadIdx.x; i < len * w; i += TH) wide[i] = s_sum[i];
+            } else {
+                for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
+            }
             for (int i = threadIdx.x; i < len; i += TH) counts[i] = s_cnt[i];
         }
+        if (set < a.sets) {  // (the same thread's as read above)
+            for (int i = threadIdx.x; i < len * w; i += TH) s_sum[i] = 0.0;
+            for (int i = threadIdx.x; i < len; i += TH) s_cnt[i] = 0u;
+            __syncthreads();
+        }
+    }
+    } while (TRAIN && set < a.sets);
+    if constexpr (TRAIN) {
         for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
         if (lane == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
         __syncthreads();
@@ -845,45 +870,55 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         (void)hipGetLastError();
         return false;
     }
-    const int64_t strips = (a.rows + TH - 1) / TH;
     // Workgroups per part: one to four times what the chip holds at once, as the slots that stay empty
     // and the staging of the codebook, about as long as a strip, cost least (24 x 270 x 32, all rows
     // open: 845 us with one workgroup a CU, 1022 with two rounds of two).  In training, where each also
-    // adds its sums to memory, as many as the chip holds.
+    // writes its sums to memory, as deal_sets has it.
     const int64_t resident =
         256 * std::min<int64_t>(ENT ? nearest_waves(G, true, TH) * 256 / TH : 1, kCuLds / (int64_t)lds);
-    int64_t ny = resident / a.P;
-    double least = 0.0;
-    for (int m = 1; m <= (TRAIN ? 1 : 4); m++) {
-        const int64_t n = m * resident / a.P;
-        if (n < 1) continue;
-        const double rows_long = m * ((double)a.rows / (double)n + 0.8 * TH);
-        if (least == 0.0 || rows_long < least) { least = rows_long; ny = n; }
-    }
-    if (ny < 1) ny = 1;
-    if (ny > strips) ny = strips;
-    // (whole strips instead would leave the chip waiting for the workgroups with one more)
-    a.chunk = ((a.rows + ny - 1) / ny + 63) / 64 * 64;
-    ny = (a.rows + a.chunk - 1) / a.chunk;
+    int64_t ny = 0;
     if constexpr (TRAIN) {
-        // every workgroup's sums; without room for them (a stream that is being captured) they add to
+        RowSets r = row_sets(p, a.rows);
+        deal_sets(r, a.rows, a.P, resident, TH);
+        ny = r.groups;
+        // the sets' sums; without room for them (a stream that is being captured) they add to
         // the handle's own block of one set (10 rounds on 65 536 rows, with workspace / so: 8 x 256 x 16
         // 690 / 560 us, 96 x 256 x 8 1910 / 1930; one workgroup per part 8790 and 6370)
         const int64_t books = (int64_t)a.P * a.len * a.w, ents = (int64_t)a.P * a.len;
-        if (ensure_scratch(p, sizeof(float) * (size_t)(ny * (books + ents)), s)) {
-            a.sums = (float *)p->d_scratch;
+        if (ensure_scratch(p, (size_t)sums_bytes(p, r), s)) {
+            a.sums = p->d_scratch;
+            a.counts = (uint32_t *)(p->d_scratch + r.sets * r.sub * books * (r.sub > 1 ? 8 : 4));
         } else {
             a.one_set = 1;
             a.sums = p->d_train;
+            a.counts = (uint32_t *)(p->d_train + books);
             launch_vq_zero(p->d_train, books + ents, s);
         }
-        a.counts = (uint32_t *)(a.sums + (a.one_set ? 1 : ny) * books);
+        a.strip_log2 = r.strip_log2;
+        a.sets = r.sets;
+        a.sub = r.sub;
+        a.chunk = r.share;
+    } else {
+        const int64_t strips = (a.rows + TH - 1) / TH;
+        ny = resident / a.P;
+        double least = 0.0;
+        for (int m = 1; m <= 4; m++) {
+            const int64_t n = m * resident / a.P;
+            if (n < 1) continue;
+            const double rows_long = m * ((double)a.rows / (double)n + 0.8 * TH);
+            if (least == 0.0 || rows_long < least) { least = rows_long; ny = n; }
+        }
+        if (ny < 1) ny = 1;
+        if (ny > strips) ny = strips;
+        // (whole strips instead would leave the chip waiting for the workgroups with one more)
+        a.chunk = ((a.rows + ny - 1) / ny + 63) / 64 * 64;
+        ny = (a.rows + a.chunk - 1) / a.chunk;
     }
     a.ny = (int)ny;
     search_costs(a, G, ENT);
     const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
     kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
-    if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.ny, s);
+    if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.sets, a.one_set ? 1 : a.sub, s);
     return true;
 }
 
@@ -904,7 +939,8 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
     // plain search spills, which workgroups of 512 do not have (48 x 512 x 16 244 in two of 256).
     // (the kernel's few static words count too)
     const int64_t fit = kCuLds / ((int64_t)lds + 64);
-    if (fit >= 3) return BF_VNL(256);
+    // (training at two a CU: as many sets, with one codebook for each)
+    if (fit >= 3 || (train && fit == 2 && G == 2)) return BF_VNL(256);
     if constexpr (G == 1) return fit == 2 ? BF_VNL(512) : BF_VNL(1024);
     else return BF_VNL(512);
 #undef BF_VNL

@@ -6,9 +6,10 @@
 // sub-vector to its nearest entry (the same fp32 rule as the encoder, so a
 // trained codebook encodes exactly as it was fitted), accumulates per-entry
 // sums and counts and replaces each non-empty entry by the mean of its members
-// (an entry without members keeps its value).  Sums are added with atomics, so the result
-// depends on the order of additions in the last bits; it is judged on distortion, not bit
-// for bit.
+// (an entry without members keeps its value).  Sums are 64-bit LDS atomics, rounded to 32 bits set by
+// set (RowSets): the same sample gives the same codebook on every path that has room for its sums, up
+// to a sum that lies within 2^-53 of an edge between two 32-bit values.  The plain fused kernel, and
+// sums that find no room, depend on the order of additions in the last bits.
 // Three forms:
 // - codebooks that the matrix-core search takes and that fit LDS next to their sums: search and
 //   sums in one kernel (vq_nearest.hip; 96 x 256 x 8 cosine, 10 rounds on 65 536 rows: 1760 us,
@@ -156,8 +157,8 @@ __global__ void vq_rnorm_kernel(const float *__restrict__ cb, int64_t entries, i
 
 // Sums, counts and squared distance from the codes, one part's after the other.  A workgroup takes
 // one part, as many of its columns (the count is one more) as LDS holds sums for - 64-bit ones, see
-// vq_nearest.hip - and an ny-th of the rows, and writes its sums to the workspace:
-// sums [ny][P][w][len], counts [ny][P][len]; or adds them to the one (zeroed) set there is room for.
+// vq_nearest.hip - and the rows of a set, of several one after the other, or of part of one, and writes
+// each one's sums to the workspace; or adds them to the one (zeroed) set there is room for.
 // What bounds it: the LDS adds (22 cycles a wave, 36 us for 65 536 rows of 96 x 8 columns) and reading
 // the sample once more (40 us).  For that 4 columns are loaded at a time (VEC) and lanes share a row
 // (a load of one lane per row touches 64 lines), workgroups of the same rows run at the same time on one
@@ -167,21 +168,21 @@ __global__ void vq_rnorm_kernel(const float *__restrict__ cb, int64_t entries, i
 constexpr int kAccThreads = 1024;
 constexpr int64_t kAccLds = 145 * 1024;
 constexpr int kAccRows = 2;
+constexpr int64_t kMaxSumsBytes = (int64_t)256 << 20;
 // from one column's sums to the next: odd, so that lanes that add columns of one row meet different banks
 __host__ __device__ constexpr int acc_stride(int len) { return len | 1; }
 
 template <typename T, typename CODE, bool VEC>
 __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w, int len, int P, const CODE *__restrict__ codes,
-    const float *__restrict__ cb, int DG, int more, int groups, int ny, int lanes, int one_set, float *__restrict__ sums,
-    uint32_t *__restrict__ counts, double *__restrict__ distortion) {
+    const float *__restrict__ cb, int DG, int more, int groups, RowSets r, int lanes, int one_set, void *__restrict__ all_sums, uint32_t *__restrict__ counts, double *__restrict__ distortion) {
     extern __shared__ double s_acc[];  // [columns][acc_stride]
     const int ls = acc_stride(len);
     __shared__ double s_dist;
     // workgroups are dealt to the XCDs in turn: consecutive logical ids belong on one XCD
     const int id = (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)), TH = blockDim.x;
-    if (id >= groups * P * ny) return;
-    const int grp = id % groups, p = id / groups % P, by = id / (groups * P);
+    if (id >= groups * P * r.groups) return;
+    const int grp = id % groups, p = id / groups % P, by = id / (groups * P), sub = by % r.sub;
     const int c0 = grp * DG, nc = min(DG + (grp == groups - 1 ? more : 0), w + 1 - c0);  // column w counts
     const int nd = min(nc, w - c0);
     for (int i = threadIdx.x; i < nc * ls; i += TH) s_acc[i] = 0.0;
@@ -189,29 +190,35 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     __syncthreads();
     float dsum = 0.0f;
     const CODE *part_codes = codes + p * rows;
-    // an even share of the rows, whole waves of them
-    const int64_t share = ((rows + ny - 1) / ny + 63) / 64 * 64, begin = by * share, end = min(rows, begin + share);
     const int left = D - (p * w + c0);  // columns that the table has
     auto add = [&](double *acc, int j, float xv, float ev) {
         unsafeAtomicAdd(acc + j * ls, (double)xv);
         const float diff = xv - ev;
         dsum += diff * diff;
     };
+    // (rows are counted within the set)
+    for (int set = by / r.sub, next; set < r.sets; set = next) {
+    next = set + (r.sub > 1 ? r.sets : r.groups);
+    const int64_t begin = sub * r.share, end = min(set_rows(set, r.sets, r.strip_log2, rows), begin + r.share);
     if constexpr (VEC) {
         // `lanes` lanes (a power of two that divides the fours of columns) share a row: fewer lines an
         // instruction; a lane has kAccRows rows in flight
         const int lq = threadIdx.x & (lanes - 1), at = threadIdx.x / lanes, step = TH / lanes;
-        for (int64_t r = begin + at; r < end; r += (int64_t)step * kAccRows) {
+        for (int64_t i = begin + at; i < end; i += (int64_t)step * kAccRows) {
             int code[kAccRows];
+            int64_t row[kAccRows];
 #pragma unroll
-            for (int k = 0; k < kAccRows; k++) code[k] = r + k * step < end ? part_codes[r + k * step] : -1;
+            for (int k = 0; k < kAccRows; k++) {
+                row[k] = set_row(set, r.sets, r.strip_log2, i + k * step);
+                code[k] = i + k * step < end ? part_codes[row[k]] : -1;
+            }
             for (int j = 4 * lq; j < nd; j += 4 * lanes) {
                 float4 v[kAccRows], e[kAccRows];
 #pragma unroll
                 for (int k = 0; k < kAccRows; k++) {
                     v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (code[k] < 0) continue;
-                    if (j < left) v[k] = load4(x + (r + k * step) * D + (int64_t)p * w + c0 + j);
+                    if (j < left) v[k] = load4(x + row[k] * D + (int64_t)p * w + c0 + j);
                     e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
                 }
 #pragma unroll
@@ -231,9 +238,10 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
             }
         }
     } else {
-        for (int64_t r = begin + threadIdx.x; r < end; r += TH) {
-            const int code = part_codes[r];
-            const T *src = x + r * D + (int64_t)p * w + c0;
+        for (int64_t i = begin + threadIdx.x; i < end; i += TH) {
+            const int64_t row = set_row(set, r.sets, r.strip_log2, i);
+            const int code = part_codes[row];
+            const T *src = x + row * D + (int64_t)p * w + c0;
             const float *ent = cb + ((int64_t)p * len + code) * w + c0;
             double *acc = s_acc + code;
 #pragma unroll 4
@@ -241,30 +249,40 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
             if (nc > nd) unsafeAtomicAdd(acc + nd * ls, 1.0);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
-    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
+    if (one_set && next < r.sets) continue;  // (all sets' sums together)
     __syncthreads();
-    if (threadIdx.x == 0) unsafeAtomicAdd(distortion, s_dist);
     for (int i = threadIdx.x; i < nc * len; i += TH) {
         const int j = i / len, e = i - j * len, d = c0 + j;
         const double sum = s_acc[j * ls + e];
+        s_acc[j * ls + e] = 0.0;
+        float *sums = static_cast<float *>(all_sums);
+        const int64_t slot = (int64_t)set * r.sub + sub;
         if (one_set) {
             if (sum == 0.0) continue;
             if (d < w) unsafeAtomicAdd(&sums[((int64_t)p * w + d) * len + e], (float)sum);
             else atomicAdd(&counts[(int64_t)p * len + e], (uint32_t)sum);
         } else if (d < w) {
-            sums[(((int64_t)by * P + p) * w + d) * len + e] = (float)sum;
+            const int64_t to = ((slot * P + p) * w + d) * len + e;
+            if (r.sub > 1) static_cast<double *>(all_sums)[to] = sum;
+            else sums[to] = (float)sum;
         } else {
-            counts[((int64_t)by * P + p) * len + e] = (uint32_t)sum;
+            counts[(slot * P + p) * len + e] = (uint32_t)sum;
         }
     }
+    __syncthreads();
+    }
+    for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
+    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
+    __syncthreads();
+    if (threadIdx.x == 0) unsafeAtomicAdd(distortion, s_dist);
 }
 
 // The generic round's workspace: the codes, then the workgroups' sums.
 struct GenericPlan {
-    int DG, more, groups, ny;        // columns a group, 1: the last one counts on top of them
+    int DG, more, groups;            // columns a group, 1: the last one counts on top of them
     int threads;
-    int64_t codes_bytes, set_bytes;  // codes (rounded up), sums and counts of one workgroup row
+    RowSets sets;
+    int64_t codes_bytes, sums_bytes;  // codes (rounded up), sums and counts of every workgroup
 };
 
 GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
@@ -282,20 +300,17 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
         g.groups = (w + g.DG) / g.DG;
         g.DG = (w + g.groups) / g.groups;
     }
-    // as many workgroups as the chip holds at once, no more than there are strips, the sums within
-    // 256 MB; smaller ones where a sample is too short to fill the chip with large ones, unless a
+    // smaller workgroups where a sample is too short to fill the chip with large ones, unless a
     // workgroup's sums outnumber its rows then (3000 rows of 8 x 2048 x 16: 930 us against 980) or there
     // are few columns to add (4096 rows of 96 x 64 x 1: 222 us against 259)
     const int64_t lds = (int64_t)8 * (g.DG + g.more) * acc_stride(len), cols = (int64_t)p->P * g.groups;
     g.threads = kAccThreads;
     while (w >= 8 && g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
-    const int64_t strips = (rows + g.threads - 1) / g.threads;
     g.codes_bytes = (rows * p->P * p->cbytes + 255) / 256 * 256;
-    g.set_bytes = (int64_t)4 * p->P * len * (w + 1);
-    int64_t ny = 256 * std::min<int64_t>(2 * kAccThreads / g.threads, 160 * 1024 / (lds + 64)) / cols;
-    if (ny > ((int64_t)256 << 20) / g.set_bytes) ny = ((int64_t)256 << 20) / g.set_bytes;
-    if (ny > strips) ny = strips;
-    g.ny = (int)(ny < 1 ? 1 : ny);
+    g.sets = row_sets(p, rows);
+    deal_sets(g.sets, rows, cols, 256 * std::min<int64_t>(2 * kAccThreads / g.threads, 160 * 1024 / (lds + 64)), g.threads);
+    if (g.sets.sub > 1 && sums_bytes(p, g.sets) > kMaxSumsBytes) g.sets = row_sets(p, rows);
+    g.sums_bytes = sums_bytes(p, g.sets);
     return g;
 }
 
@@ -310,7 +325,7 @@ bool codes_pay(const bifeat_params *p, int64_t rows) {
 }
 
 template <typename T, typename CODE, bool VEC>
-bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, bool one_set, float *sums,
+bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, bool one_set, void *sums,
                       uint32_t *counts, double *dist_slot, hipStream_t s) {
     const size_t shm = sizeof(double) * (size_t)(g.DG + g.more) * acc_stride(p->scheme.vq_length);
     auto kern = vq_accumulate_codes_kernel<T, CODE, VEC>;
@@ -318,12 +333,12 @@ bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericP
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)shm) != hipSuccess)
         return false;
-    const int blocks = (g.groups * p->P * g.ny + 7) / 8 * 8;
+    const int blocks = (g.groups * p->P * g.sets.groups + 7) / 8 * 8;
     int lanes = 1;
     while (VEC && lanes < 16 && g.DG % (8 * lanes) == 0) lanes *= 2;
     kern<<<(unsigned)blocks, g.threads, shm, s>>>(
         x, rows, (int)p->D, p->scheme.vq_width, p->scheme.vq_length, p->P, (const CODE *)p->d_scratch, p->d_cb, g.DG,
-        g.more, g.groups, g.ny, lanes, one_set, sums, counts, dist_slot);
+        g.more, g.groups, g.sets, lanes, one_set, sums, counts, dist_slot);
     return true;
 }
 
@@ -335,10 +350,10 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     // without room for every workgroup's sums (a stream under capture) they add to the handle's own
     // block of one set (the codes' part of the workspace is there, see below): 8 x 2048 x 16 cosine,
     // 10 rounds 2890 us so, with workspace 2980; one workgroup per part and group of columns 8690
-    const bool all = (int64_t)p->scratch_bytes >= g.codes_bytes + g.ny * g.set_bytes;
-    const int sets = all ? g.ny : 1;
-    float *sums = all ? (float *)(p->d_scratch + g.codes_bytes) : p->d_train;
-    uint32_t *counts = (uint32_t *)(sums + sets * books);
+    const bool all = (int64_t)p->scratch_bytes >= g.codes_bytes + g.sums_bytes;
+    const int sets = all ? g.sets.sets : 1, sub = all ? g.sets.sub : 1;
+    uint8_t *sums = all ? p->d_scratch + g.codes_bytes : (uint8_t *)p->d_train;
+    uint32_t *counts = (uint32_t *)(sums + sets * sub * books * (sub > 1 ? 8 : 4));
     if (!all) launch_vq_zero(p->d_train, books + (int64_t)P * len, s);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
     launch_vq_assign(p, x, rows, p->d_scratch, p->cbytes, rows * p->cbytes, s);
@@ -350,7 +365,7 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
                         : (vec ? accumulate_codes<T, uint16_t, true>(p, x, rows, g, !all, sums, counts, dist_slot, s)
                                : accumulate_codes<T, uint16_t, false>(p, x, rows, g, !all, sums, counts, dist_slot, s));
     if (!ok) return hipGetLastError();
-    launch_vq_means(p, sums, counts, sets, s);
+    launch_vq_means(p, sums, counts, sets, sub, s);
     return hipSuccess;
 }
 
@@ -381,6 +396,52 @@ bool ensure_scratch(bifeat_params *p, size_t bytes, hipStream_t s) {
     return true;
 }
 
+// rows of the largest set
+static int64_t largest_set(const RowSets &r, int64_t rows) {
+    const int64_t strips = (rows + (1 << r.strip_log2) - 1) >> r.strip_log2;
+    return (strips + r.sets - 1) / r.sets << r.strip_log2;
+}
+
+// Sets of strips of 256 rows, as many as the chip holds workgroups of the search and its sums, for the Euclidean
+// one-byte codebooks of 512 values or more, within 64 KB, that the matrix-core search trains; else of 1024 rows, as
+// many as give two workgroups of the sums from codes a CU.
+RowSets row_sets(const bifeat_params *p, int64_t rows) {
+    const int64_t w = p->scheme.vq_width, len = p->scheme.vq_length;
+    RowSets r{};
+    int64_t sets;
+    if (p->scheme.vq_metric == BIFEAT_VQ_L2 && p->cbytes == 1 && w * len >= 512 && 4 * len * (2 * w + 1) <= 65536 &&
+        vq_nearest_takes(p, true, rows)) {
+        const int64_t G = (w + 7) / 8, pairs = (len + 63) / 64;  // of tiles of 32 entries
+        const int64_t lds = pairs * (2 * (1024 * G + 128) + 4 * (16 * (32 * G + 4) + 4)) + len * (8 * w + 4);
+        r.strip_log2 = 8;
+        sets = 256 * std::min<int64_t>(G == 1 ? 4 : G == 2 ? 3 : 2, 160 * 1024 / lds) / p->P;
+    } else {
+        const int64_t cols = std::min(144 * 1024 / (8 * len), w + 1);  // a workgroup's, one more counts
+        r.strip_log2 = 10;
+        sets = std::min(512 / (p->P * ((w + cols) / cols)), kMaxSumsBytes / (4 * p->P * len * (w + 1)));
+    }
+    r.sets = r.groups = (int)std::max<int64_t>(1, std::min(sets, (rows + (1 << r.strip_log2) - 1) >> r.strip_log2));
+    r.sub = 1;
+    r.share = largest_set(r, rows);
+    return r;
+}
+
+// Several workgroups to a set while that many are missing; else one or several sets to a workgroup, as the rows of
+// as many rounds of workgroups as it takes cost least, with staging a codebook and writing sums as long as 0.8
+// and 0.4 rows a thread.
+void deal_sets(RowSets &r, int64_t rows, int64_t cols, int64_t room, int threads) {
+    const int64_t most = largest_set(r, rows);
+    r.sub = (int)std::max<int64_t>(1, std::min(room / (cols * r.sets), (most + threads - 1) / threads));
+    r.share = ((most + r.sub - 1) / r.sub + 63) / 64 * 64;
+    r.groups = r.sets * r.sub;
+    double least = 0.0;
+    for (int m = 1; r.sub == 1 && m <= 8; m++) {
+        const int64_t n = (r.sets + m - 1) / m, rounds = (n * cols + room - 1) / room;
+        const double time = (double)rounds * (m * ((double)most + 0.4 * threads) + 0.8 * threads);
+        if (least == 0.0 || time < least) { least = time; r.groups = (int)n; }
+    }
+}
+
 void launch_vq_zero(float *a, int64_t n, hipStream_t s) {
     vq_zero_kernel<<<blocks_for(n, 1024), kThreads, 0, s>>>(a, n);
 }
@@ -402,12 +463,12 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
     const GenericPlan g = generic_plan(p, rows);
     // (codes without the sums: see lloyd_round_generic)
     auto room_for_codes = [&] {
-        return ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s) ||
+        return ensure_scratch(p, (size_t)(g.codes_bytes + g.sums_bytes), s) ||
                ensure_scratch(p, (size_t)rows * P * p->cbytes, s);
     };
     bool nearest = vq_nearest_takes(p, true, rows), through_codes = false;
     if (!nearest) {
-        through_codes = fused ? codes_pay(p, rows) && ensure_scratch(p, (size_t)(g.codes_bytes + g.ny * g.set_bytes), s)
+        through_codes = fused ? codes_pay(p, rows) && ensure_scratch(p, (size_t)(g.codes_bytes + g.sums_bytes), s)
                               : room_for_codes();
         if (!fused && !through_codes) return hipErrorOutOfMemory;
     }

@@ -104,6 +104,37 @@ def test_sums_from_codes(D, w, length, rows, metric, half, offset):
     np.testing.assert_allclose(q.params_get_codebooks(), cb, rtol=2e-6, atol=1e-6)
 
 
+# A codebook's last bits: strip k of the rows belongs to set k % sets, a set's sums are rounded to 32 bits, the
+# sets added in 64.  Sets of several strips and of one, a last strip that is short, several sets a workgroup (96 x
+# 300 x 8, 24 x 256 x 32) and several workgroups a set (12 x 64 x 32), search and sums in one kernel and apart (64 x
+# 1500 x 8, 6 x 300 x 48).  (The order of additions inside a set can move a sum over an edge between two 32-bit
+# values with a chance of 1e-7.)
+@pytest.mark.parametrize("P,w,length,rows,metric,strip,sets", [
+    (96, 8, 256, 9000, "l2", 256, 10), (96, 8, 300, 9100, "l2", 1024, 5), (20, 16, 256, 13_000, "l2", 256, 25),
+    (24, 32, 256, 33_000, "l2", 1024, 21), (40, 8, 1000, 14_000, "cosine", 1024, 12), (12, 32, 64, 4096, "cosine", 1024, 4),
+    (64, 8, 1500, 9300, "l2", 1024, 8), (6, 48, 300, 5000, "l2", 1024, 5), (5, 4, 200, 700, "l2", 256, 3)])
+def test_sets_of_rows(P, w, length, rows, metric, strip, sets):
+    import torch
+    import paper_2207_14696_amd as bf
+    x = (np.random.default_rng(P + length).normal(size=(rows, P * w)) * 1.7 + 0.4).astype(np.float32)
+    q = _train(torch, bf, x, w, length, metric, 1)
+    want = _first_entries(x, w, length)
+    codes = orc.vq_assign(x, w, want, metric=metric)
+    of = np.arange(rows) // strip % sets
+    for p in range(P):
+        total, count = np.zeros((length, w)), np.bincount(codes[:, p], minlength=length)
+        for k in range(sets):
+            rows_k = np.flatnonzero(of == k)
+            part = np.zeros((length, w))
+            np.add.at(part, codes[rows_k, p], x[rows_k, p * w:(p + 1) * w].astype(np.float64))
+            total += part.astype(np.float32)
+        want[p, count > 0] = (total[count > 0] / count[count > 0, None]).astype(np.float32)
+    got = q.params_get_codebooks()
+    other = got != want
+    assert other.sum() <= 3, f"{other.sum()} of {other.size} values differ"
+    np.testing.assert_allclose(got, want, rtol=5e-7, atol=1e-7)
+
+
 # widths 1, 2 and 4 on both sides of 128 values, of 4096 rows and of 2^21 sample values; other widths
 @pytest.mark.parametrize("P,w,length,rows", [(3, 1, 64, 5000), (3, 1, 200, 5000), (3, 1, 64, 4096), (5, 4, 31, 4097),
                                              (5, 4, 32, 4097), (130, 4, 64, 4100), (8, 2, 64, 131_200),
