@@ -183,8 +183,9 @@ int bifeat_params_set_codebooks(bifeat_params *p, const float *codebooks);
 int bifeat_params_get_codebooks(bifeat_params *p, float *codebooks);
 /* BIFEAT_VQ: mean squared Euclidean distance between a part and its assigned
  * entry (summed over parts, either metric) at each Lloyd round's assignment
- * step of the last bifeat_fit_update; out: HOST [n], n <= 64.  Synchronises
- * the device. */
+ * step of the last bifeat_fit_update; out: HOST [n], n <= 64.  A row that is
+ * near to no entry (a NaN, an infinity) makes it infinite under the Euclidean
+ * metric.  Synchronises the device. */
 int bifeat_vq_distortion(bifeat_params *p, float *out, int32_t n);
 
 /* ---- encode + pack one chunk (Sec. 3.1 Eq. (1); Sec. 3.2 nearest entry).

@@ -791,6 +791,7 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
     }
     } while (TRAIN && set < a.sets);
     if constexpr (TRAIN) {
+        if (!COS && dsum != dsum) dsum = INFINITY;  // (a row that is near to no entry)
         for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
         if (lane == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
         __syncthreads();

@@ -175,7 +175,7 @@ __host__ __device__ constexpr int acc_stride(int len) { return len | 1; }
 template <typename T, typename CODE, bool VEC>
 __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w, int len, int P, const CODE *__restrict__ codes,
-    const float *__restrict__ cb, int DG, int more, int groups, RowSets r, int lanes, int one_set, void *__restrict__ all_sums, uint32_t *__restrict__ counts, double *__restrict__ distortion) {
+    const float *__restrict__ cb, int DG, int more, int groups, RowSets r, int lanes, int one_set, int l2, void *__restrict__ all_sums, uint32_t *__restrict__ counts, double *__restrict__ distortion) {
     extern __shared__ double s_acc[];  // [columns][acc_stride]
     const int ls = acc_stride(len);
     __shared__ double s_dist;
@@ -271,6 +271,7 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     }
     __syncthreads();
     }
+    if (l2 && dsum != dsum) dsum = INFINITY;  // (a row that is near to no entry)
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
     if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
     __syncthreads();
@@ -338,7 +339,7 @@ bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericP
     while (VEC && lanes < 16 && g.DG % (8 * lanes) == 0) lanes *= 2;
     kern<<<(unsigned)blocks, g.threads, shm, s>>>(
         x, rows, (int)p->D, p->scheme.vq_width, p->scheme.vq_length, p->P, (const CODE *)p->d_scratch, p->d_cb, g.DG,
-        g.more, g.groups, g.sets, lanes, one_set, sums, counts, dist_slot);
+        g.more, g.groups, g.sets, lanes, one_set, p->scheme.vq_metric == BIFEAT_VQ_L2, sums, counts, dist_slot);
     return true;
 }
 

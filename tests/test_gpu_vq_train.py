@@ -135,6 +135,25 @@ def test_sets_of_rows(P, w, length, rows, metric, strip, sets):
     np.testing.assert_allclose(got, want, rtol=5e-7, atol=1e-7)
 
 
+# rows that are near to no entry: entry 0 takes them, the Euclidean distortion is infinite (search and sums in one
+# kernel, apart, the plain fused kernel)
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("P,w,length,rows,metric", [
+    (3, 8, 256, 3000, "l2"), (3, 8, 300, 3000, "l2"), (2, 8, 1500, 2000, "l2"), (2, 48, 300, 900, "l2"), (3, 1, 64, 900, "l2"),
+    (24, 4, 15, 900, "l2"), (16, 1, 65, 263_000, "l2"), (3, 8, 256, 3000, "cosine"), (2, 48, 300, 900, "cosine")])
+def test_rows_without_a_nearest_entry(P, w, length, rows, metric, bad):
+    import torch
+    import paper_2207_14696_amd as bf
+    x = np.random.default_rng(P + length).normal(size=(rows, P * w)).astype(np.float32)
+    x[rows - 5:rows - 2, :w] = bad
+    q = _train(torch, bf, x, w, length, metric, 1)
+    with np.errstate(all="ignore"):
+        cb, want = orc.vq_train(x, w, length, iters=1, metric=metric)
+    got = q.vq_distortion(1)[0]
+    assert np.isnan(got) if np.isnan(want[0]) else got == want[0] == np.inf
+    np.testing.assert_array_equal(np.isnan(q.params_get_codebooks()), np.isnan(cb))
+
+
 # widths 1, 2 and 4 on both sides of 128 values, of 4096 rows and of 2^21 sample values; other widths
 @pytest.mark.parametrize("P,w,length,rows", [(3, 1, 64, 5000), (3, 1, 200, 5000), (3, 1, 64, 4096), (5, 4, 31, 4097),
                                              (5, 4, 32, 4097), (130, 4, 64, 4100), (8, 2, 64, 131_200),
