@@ -10,6 +10,8 @@ namespace bf {
 // training those whose sums do not fit LDS next to the entries.  (The two
 // calls below return false, with nothing launched, when it does not.)
 bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows);
+// rows x parts from which on it takes some small codebooks
+constexpr int64_t kNearestManyParts = 1 << 18;
 
 // the index of every part's nearest entry, see launch_vq_assign
 template <typename T>

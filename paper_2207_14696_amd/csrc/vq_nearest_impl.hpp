@@ -75,7 +75,6 @@ struct VqNearestArgs {
 // codebooks of fewer values (entries x columns; parts of 4 columns or more; with few rows x parts) and
 // wider parts stay with the plain search, see vq_nearest_takes
 constexpr int kNearestMinBook = 512, kNearestMinBookAny = 64, kNearestMinBookFew = 384;
-constexpr int64_t kNearestManyParts = 1 << 18;
 constexpr int kNearestMaxWidth = 32;
 constexpr int kCuLds = 160 * 1024;
 // strips that a wave searches by the rule once its rows tie, before it tries the scores again

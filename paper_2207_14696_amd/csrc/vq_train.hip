@@ -472,6 +472,10 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
         through_codes = fused ? codes_pay(p, rows) && ensure_scratch(p, (size_t)(g.codes_bytes + g.sums_bytes), s)
                               : room_for_codes();
         if (!fused && !through_codes) return hipErrorOutOfMemory;
+    } else if (!fused && !vq_nearest_takes(p, true, 1)) {
+        // A smaller sample of this codebook goes through codes and cannot do without them: a captured update of
+        // one finds room for them after this one, as after any larger update.
+        (void)ensure_scratch(p, (size_t)std::min(rows * P, kNearestManyParts) * p->cbytes, s);
     }
     if (init) {
         if (dtype == BIFEAT_F32)

@@ -197,6 +197,29 @@ def test_training_under_capture(P, w, length, metric, reserve):
     eager.fit_update(dx)
 
 
+# a codebook that goes through codes for up to 2^18 rows x parts (513 parts: 511 rows) and cannot do without them: a larger
+# update, which needs none, leaves room for them all the same
+def test_a_smaller_update_under_capture_after_a_larger_one():
+    import torch
+    import paper_2207_14696_amd as bf
+    P, w, length = 513, 4, 16
+    x = torch.from_numpy(np.random.default_rng(5).normal(size=(600, P * w)).astype(np.float32)).cuda()
+    q, eager = (bf.Quantizer(scheme_of("vq", 8, w, length, "cosine"), P * w) for _ in range(2))
+    q.fit_update(x)
+    q.fit_reset()
+    small = x[:511].contiguous()
+    g, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=stream):
+        q.fit_update(small)
+    eager.fit_update(small)
+    want = eager.vq_distortion(10)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(q.vq_distortion(10), want, rtol=1e-5)
+        small.mul_(1.0)
+
+
 def _us(torch, f):
     f()
     best = 1e9
