@@ -50,6 +50,15 @@ bool stream(void **out) {
     return !(*out == nullptr && PyErr_Occurred());
 }
 
+// The interpreter runs other threads while this lives: an allocation may wait for the device, or for a lock that
+// another thread holds.
+struct Released {
+    PyThreadState *state = PyEval_SaveThread();
+    ~Released() { PyEval_RestoreThread(state); }
+    Released() = default;
+    Released(const Released &) = delete;
+};
+
 at::Tensor rows(const at::Tensor &like, int64_t n, int64_t D) {
     return torch::empty({n, D}, at::TensorOptions().dtype(at::kFloat).device(like.device()));
 }
@@ -75,12 +84,13 @@ PyObject *gather_dequant(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const int64_t M = idx->size(0), N = codes->size(0);
         const auto *pc = static_cast<const uint8_t *>(codes->data_ptr());
         const auto *pi = static_cast<const int64_t *>(idx->data_ptr());
-        at::Tensor out = rows(*codes, M, D);
-        auto *po = static_cast<float *>(out.data_ptr());
+        at::Tensor out;
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = fn(handle, pc, N, pi, M, po, s);
-        Py_END_ALLOW_THREADS
+        {
+            Released interpreter;
+            out = rows(*codes, M, D);
+            status = fn(handle, pc, N, pi, M, static_cast<float *>(out.data_ptr()), s);
+        }
         return finish(status, out);
     } catch (...) {
         Py_RETURN_NONE;
@@ -105,12 +115,13 @@ PyObject *aggregate(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const auto *pc = static_cast<const uint8_t *>(codes->data_ptr());
         const auto *pp = static_cast<const int64_t *>(indptr->data_ptr());
         const void *pi = indices->data_ptr();
-        at::Tensor out = rows(*codes, V, D);
-        auto *po = static_cast<float *>(out.data_ptr());
+        at::Tensor out;
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = fn(handle, pc, N, pp, pi, V, E, po, s);
-        Py_END_ALLOW_THREADS
+        {
+            Released interpreter;
+            out = rows(*codes, V, D);
+            status = fn(handle, pc, N, pp, pi, V, E, static_cast<float *>(out.data_ptr()), s);
+        }
         return finish(status, out);
     } catch (...) {
         Py_RETURN_NONE;
