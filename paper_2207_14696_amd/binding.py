@@ -1,11 +1,12 @@
 """ctypes binding of the C ABI in ``include/bifeat.h``: same names, argument
 marshalling only.  Tensors are torch CUDA tensors; their ``data_ptr()`` and the
 current stream's handle are what crosses the boundary.  ``gather_dequant``, ``gather_mean`` and
-``gather_sum`` without ``out`` go through a native module (``csrc/calls.cpp``) to the same entry points."""
+``gather_sum`` without ``out`` go through a native module (``csrc/calls.cpp``) to the same entry points where it is built."""
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 
 import numpy as np
@@ -116,12 +117,18 @@ _calls = None
 
 
 def _load_calls():
-    """The native module for the per-iteration calls.  No fallback either."""
+    """The native module for the per-iteration calls, or False where it is missing or was built for
+    another torch or Python: they then go through ctypes, to the same entry points."""
     global _calls
     if _calls is None:
         import torch  # noqa: F401  (its libraries are what the module links against)
-        from . import _calls as module
-        _calls = module
+        try:
+            from . import _calls as module
+            _calls = module
+        except ImportError as e:
+            warnings.warn(f"gather_dequant, gather_mean and gather_sum go through ctypes, 5 us a call slower ({e}); "
+                          "`python -m paper_2207_14696_amd.build` builds the native module", RuntimeWarning, stacklevel=3)
+            _calls = False
     return _calls
 
 
@@ -285,9 +292,9 @@ class Quantizer:
         return out
 
     def gather_dequant(self, codes, idx, out=None):
-        if out is None:
+        if out is None and (calls := _calls or _load_calls()):
             handle, fn = self._native[:2]
-            r = (_calls or _load_calls()).gather_dequant(fn, handle, codes, idx, self.D)
+            r = calls.gather_dequant(fn, handle, codes, idx, self.D)
             if r is not None:
                 if r.__class__ is int:
                     _check(r)
@@ -331,7 +338,10 @@ class Quantizer:
 
     def _aggregate_native(self, fns, codes, indptr, indices):
         """The output, or None where _aggregate has to look at the arguments."""
-        r = (_calls or _load_calls()).aggregate(fns[0], fns[1], self._native[0], codes, indptr, indices, self.D)
+        calls = _calls or _load_calls()
+        if not calls:
+            return None
+        r = calls.aggregate(fns[0], fns[1], self._native[0], codes, indptr, indices, self.D)
         if r.__class__ is int:
             _check(r)
         return r

@@ -38,7 +38,7 @@ def _compile_calls() -> None:
     tmp = CALLS + f".tmp{os.getpid()}"
     subprocess.check_call([
         os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-        f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+        f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DBF_TORCH_VERSION="{torch.__version__}"',
         "-isystem", os.path.join(base, "include"),
         "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
         "-I", sysconfig.get_path("include"), os.path.join(CSRC, "calls.cpp"), "-o", tmp,

@@ -16,6 +16,7 @@
 #include <torch/csrc/jit/frontend/tracer.h>
 
 #include <cstdint>
+#include <string>
 
 namespace {
 
@@ -144,5 +145,17 @@ PyMODINIT_FUNC PyInit__calls() {
     g_device = PyObject_GetAttrString(c, "_cuda_getDevice");
     g_stream = g_device ? PyObject_GetAttrString(c, "_cuda_getCurrentRawStream") : nullptr;
     Py_DECREF(c);
+    // (tensors are taken apart by their layout in the torch that this was compiled against)
+    PyObject *torch = PyImport_ImportModule("torch");
+    PyObject *version = torch ? PyObject_GetAttrString(torch, "__version__") : nullptr;
+    PyObject *text = version ? PyObject_Str(version) : nullptr;
+    const char *now = text ? PyUnicode_AsUTF8(text) : nullptr;
+    const std::string python = std::to_string(PY_MAJOR_VERSION) + "." + std::to_string(PY_MINOR_VERSION) + ".";
+    if (now && (std::string(now) != BF_TORCH_VERSION || std::string(Py_GetVersion()).rfind(python, 0) != 0))
+        PyErr_Format(PyExc_ImportError, "_calls.so was built for torch %s and Python %sx", BF_TORCH_VERSION, python.c_str());
+    Py_XDECREF(text);
+    Py_XDECREF(version);
+    Py_XDECREF(torch);
+    if (PyErr_Occurred()) return nullptr;
     return g_stream ? PyModule_Create(&module) : nullptr;
 }

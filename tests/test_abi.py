@@ -3,6 +3,8 @@ declares, and rejects bad arguments before touching the device."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -106,3 +108,28 @@ def test_product_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".hpp", ".h")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower() or f == "__init__.py" and "no CPU fallback" in text, f
+
+
+@pytest.mark.parametrize("spoil", ["sys.modules['paper_2207_14696_amd._calls'] = None", "torch.__version__ = '1.0'"])
+def test_without_the_native_module_the_calls_go_through_ctypes(bf, spoil):
+    # missing, or built for another torch: a warning that says what to build, no error
+    code = f"""
+import sys, warnings, torch
+{spoil}
+import paper_2207_14696_amd as bf
+from paper_2207_14696_amd import binding
+q = bf.Quantizer(bf.Scheme(bf.UNIFORM, 8), 16)
+x = torch.zeros(4, 16, dtype=torch.uint8)
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    for call in (lambda: q.gather_dequant(x, x), lambda: q.gather_mean(x, x, x), lambda: q.gather_sum(x, x, x)):
+        try:
+            call()
+        except ValueError as e:
+            assert "CUDA tensor" in str(e)      # the check in front of the ctypes call
+        else:
+            raise AssertionError
+assert binding._calls is False
+assert [w.category for w in seen] == [RuntimeWarning] and "paper_2207_14696_amd.build" in str(seen[0].message)
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=120)
