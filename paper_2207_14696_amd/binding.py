@@ -185,6 +185,7 @@ class Quantizer:
 
     def __del__(self):
         h, self._h = getattr(self, "_h", None), None
+        self._native = (0,) + getattr(self, "_native", (0,))[1:]
         if h:
             self._lib.bifeat_params_destroy(h)
 

@@ -110,6 +110,14 @@ def test_product_does_not_import_the_oracle():
                 assert "oracle" not in text.lower() or f == "__init__.py" and "no CPU fallback" in text, f
 
 
+def test_a_destroyed_handle_is_refused(bf):
+    # what the native module is given goes with the handle: no address of a destroyed object is left
+    q = bf.Quantizer(bf.Scheme(bf.UNIFORM, 8), 16)
+    assert q._native[0] == q._h.value != 0
+    q.__del__()
+    assert q._h is None and q._native[0] == 0
+
+
 @pytest.mark.parametrize("spoil", ["sys.modules['paper_2207_14696_amd._calls'] = None", "torch.__version__ = '1.0'"])
 def test_without_the_native_module_the_calls_go_through_ctypes(bf, spoil):
     # missing, or built for another torch: a warning that says what to build, no error

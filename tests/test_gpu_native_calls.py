@@ -64,6 +64,18 @@ def test_what_is_refused_stays_refused(env):
         q.gather_dequant(shifted, indices)           # a base that is not aligned
 
 
+def test_a_destroyed_handle(env):
+    bf, torch, q, codes, indptr, indices = env
+    p = bf.Quantizer(bf.Scheme(bf.UNIFORM, 8), 24)
+    p.params_set_uniform(np.zeros(24, np.float32), np.ones(24, np.float32))
+    p.__del__()
+    for call in (lambda: p.gather_dequant(codes, indices), lambda: p.gather_mean(codes, indptr, indices),
+                 lambda: p.gather_sum(codes, indptr, indices.int())):
+        with pytest.raises(bf.BifeatError) as e:
+            call()
+        assert e.value.status == bf.EINVAL
+
+
 def test_a_broken_promise_is_reported_once(env):
     bf, torch, q, codes, indptr, indices = env
     p = bf.Quantizer(bf.Scheme(bf.UNIFORM, 8), 24)
