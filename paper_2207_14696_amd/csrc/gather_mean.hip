@@ -302,11 +302,11 @@ static void launch_2hop_float(bifeat_params *p, const HopCall &c, const float *p
     const int D = (int)p->D;
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const int gl_log2 = ilog2((D + 3) / 4 < 64 ? (D + 3) / 4 : 64);
-    // A workgroup a seed while the chip waits for chains of fetches rather than for rows: 8192 seeds, 480 000
-    // rows in all 95 -> 75 us (131 columns, 4-bit logarithmic); 7145 seeds, 790 000 rows would lose 7 %, 32 768
-    // seeds up to a fifth.
-    const double rows = (double)c.E2 * (double)c.E1 / (double)(c.V1 > 0 ? c.V1 : 1);
-    const bool wide = only_over == 0 && c.V2 <= 8192 && rows <= (1 << 19);
+    // A workgroup a seed while waves are few, unless a wave has as many groups as a seed has entries (4 logarithmic
+    // bits, seeds x rows a seed and list, a wave / a workgroup, us): 1024 of 160 columns x 10 x 10 25 / 12, 2048 38 / 27; more seeds
+    // lose where their lists are much alike, 4096 x 10 x 5 24 / 33, of 768 columns 62 / 85 (with skewed lists of 9
+    // they gain, 110 / 56, but what the lists are like is not known here); 4096 of 32 columns x 3 x 3 9 / 12.
+    const bool wide = only_over == 0 && c.V2 <= 2048 && c.E2 > c.V2 * (64 >> gl_log2);
     const int blocks = blocks_for(c.V2 * (wide ? kThreads : 64), 1 << 16);
 #define BF_HF1(B, VECV, WPS, GROUPS)                                                               \
     gather_mean_2hop_float_kernel<KIND, B, VECV, WPS, GROUPS><<<blocks, kThreads, 0, c.s>>>(               \
@@ -367,8 +367,8 @@ hipError_t launch_gather_mean_2hop(bifeat_params *p, const HopCall &c) {
         // codebooks in LDS where the sliced kernels' shapes allow (and the workspace can be had)
         const int w = p->scheme.vq_width;
         // (not for few seeds of narrow rows, where three launches and the staging of the codebooks are what
-        // counts: 256 seeds of 128 columns, 8 a part, 40 us against 11, 2048 44 against 20; 1024 of 256 columns
-        // 42 against 22, 2048 about equal)
+        // counts, and with longer lists the seeds fill the chip better from L2: 256 seeds of 128 columns, 8 a part, 10 x 5
+        // rows 16 us against 9, 2048 18 against 13, 60 x 70 rows 708 against 578; 1024 of 256 columns, 16 a part, 60 x 70 639 against 368)
         const bool few = p->opt_vq_sliced == 1 && w % 4 == 0 && D <= 256 && c.V2 * D <= (1 << 18);
         if (vec && p->opt_vq_sliced && !few && launch_gather_mean_2hop_vq_sliced(p, c)) return hipGetLastError();
         if (w % 4 == 0 && vec) launch_2hop_float<MK_VQ4>(p, c, p->d_cb, nullptr, vec, only_over);
