@@ -292,8 +292,8 @@ int bifeat_gather_sum_i32(bifeat_params *p, const uint8_t *codes, int64_t N, con
  * general kernel (any list length) the others.  Vector codes of power-of-two
  * width take a kernel with the codebooks in on-chip memory (any list length;
  * uses the handle's workspace like bifeat_gather_mean, sized by E1); the
- * remaining codes, and few seeds of narrow vector codes (V2 * D of up to 2^18),
- * take the general kernel throughout.
+ * remaining codes, and few seeds of narrow vector codes (V2 * D of up to 2^18,
+ * parts of 4 columns 2^16), take the general kernel throughout.
  * Option "validate" checks both blocks first.  V2 = 0 is a no-op. */
 int bifeat_gather_mean_2hop(bifeat_params *p, const uint8_t *codes, int64_t N,
                             const int64_t *indptr1, const int64_t *indices1, int64_t V1, int64_t E1,

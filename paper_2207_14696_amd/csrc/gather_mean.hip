@@ -368,8 +368,9 @@ hipError_t launch_gather_mean_2hop(bifeat_params *p, const HopCall &c) {
         const int w = p->scheme.vq_width;
         // (not for few seeds of narrow rows, where three launches and the staging of the codebooks are what
         // counts, and with longer lists the seeds fill the chip better from L2: 256 seeds of 128 columns, 8 a part, 10 x 5
-        // rows 16 us against 9, 2048 18 against 13, 60 x 70 rows 708 against 578; 1024 of 256 columns, 16 a part, 60 x 70 639 against 368)
-        const bool few = p->opt_vq_sliced == 1 && w % 4 == 0 && D <= 256 && c.V2 * D <= (1 << 18);
+        // rows 16 us against 9, 2048 18 against 13, 60 x 70 rows 708 against 578; 1024 of 256 columns, 16 a part, 60 x 70 639 against 368.
+        // 4 columns a part are twice as many look-ups: 1024 seeds of 256 columns, 25 x 10 rows 41 against 68, 512 of 128 46 against 87)
+        const bool few = p->opt_vq_sliced == 1 && w % 4 == 0 && D <= 256 && c.V2 * D <= (w == 4 ? 1 << 16 : 1 << 18);
         if (vec && p->opt_vq_sliced && !few && launch_gather_mean_2hop_vq_sliced(p, c)) return hipGetLastError();
         if (w % 4 == 0 && vec) launch_2hop_float<MK_VQ4>(p, c, p->d_cb, nullptr, vec, only_over);
         else launch_2hop_float<MK_VQ>(p, c, p->d_cb, nullptr, vec, only_over);
