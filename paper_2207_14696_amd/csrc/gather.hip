@@ -334,6 +334,19 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_vq_tile_kernel(
     }
 }
 
+// Whether rows that are not 16-byte aligned take the tile kernel.  Not few wide ones, which leave it with few waves
+// and long chains (50 rows of 7001 columns, 1 bit 6.2 us flat, 17.1 in tiles; 500 of 4001 7.2 and 11.7), nor where the
+// staged ranges leave a CU with few waves (5000 of 7001 52 and 70).  Of one-column granules not many of those that a
+// byte holds several of (us flat / in tiles: 100 000 rows, 1 bit 165 columns 27 / 26, 383 57 / 75, 575 81 / 107; 2 bits
+// logarithmic 733 121 / 147; 30 000 of 1001, 1 bit 46 / 66, 4 bits logarithmic 42 / 55; against that 30 000 of 301, 1
+// bit 19 / 12, 5000 of 1433 16 / 12, 262 144 of 131 53 / 29, of 575, 8 bits 339 / 160).
+static bool narrow_pays(int kind, int bits, int D, int64_t M, int gr) {
+    const bool uniform = kind == BIFEAT_SQ_UNIFORM;
+    if ((D > 1024 && M < 2048) || (D > 4096 && uniform)) return false;
+    if (gr == 2) return true;
+    return D <= 160 || (D < 700 && (M < 60000 || bits == 8)) || (D < 2048 && M <= 10000) || (uniform && bits >= 4);
+}
+
 hipError_t launch_gather_dequant(bifeat_params *p, const uint8_t *codes, const int64_t *idx,
                                  int64_t M, float *out, hipStream_t s, uint32_t *planes) {
     const int D = (int)p->D;
@@ -378,7 +391,7 @@ hipError_t launch_gather_dequant(bifeat_params *p, const uint8_t *codes, const i
     const size_t tile_lds = sizeof(uint32_t) * (size_t)(((kind == BIFEAT_SQ_UNIFORM ? 2 * D : (1 << bits)) + 3) & ~3) +
                             (size_t)(kThreads / 64) * 64 * 16;
     const int gr = vec ? 4 : D % 2 == 0 && (uintptr_t)out % 8 == 0 ? 2 : 1;
-    if (c16 <= 64 && !p->opt_dequant_flat && tile_lds <= 65536) {
+    if (c16 <= 64 && !p->opt_dequant_flat && tile_lds <= 65536 && (vec || narrow_pays(kind, bits, D, M, gr))) {
         // (narrow granules are many: few requests are spread over 4096 waves, 16 per CU)
         const int RT = gr == 4 ? 64 / c16 : (int)std::max<int64_t>(1, std::min<int64_t>(64 / c16, M / 4096));
         const int64_t tiles = (M + RT - 1) / RT;

@@ -81,3 +81,39 @@ def test_mean(kind, bits, D, V, offset, bound):
     want = orc.gather_sum(s, codes, sub, cat).astype(np.float64)
     n = np.maximum(np.diff(sub), 1)[:, None]
     assert (np.abs(total - want) <= REL_TOL * np.maximum(np.abs(want), column_magnitude(s)[None, :] * n)).all()
+
+
+# calls that such rows' own routes served worse than the ones they had before: few wide rows (the flat decode: 6.2 us
+# against 17.1), one-column granules (46, 66).  No slower than those by more than a third
+@pytest.mark.parametrize("call,D,n,option,value", [
+    ("decode", 7001, 50, "dequant_flat", 1), ("decode", 1001, 30_000, "dequant_flat", 1)])
+def test_no_slower_than_the_other_route(call, D, n, option, value):
+    torch, q, s, codes, table = _table("uniform", 1, D)
+    big = table.repeat(200, 1)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    rows = torch.randint(0, len(big), (n if call == "decode" else 30 * n,), generator=gen, device="cuda")
+    ptr = torch.arange(n + 1, device="cuda") * 30
+    out = torch.empty(n, D, device="cuda")
+
+    def run():
+        if call == "decode":
+            q.gather_dequant(big, rows, out)
+        else:
+            q.gather_mean(big, ptr, rows, out)
+
+    def us():
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            run()
+            a.record()
+            for _ in range(20):
+                run()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3 / 20)
+        return best
+    default = us()
+    q.set_option(option, value)
+    other = us()
+    assert default <= other * 4 / 3 + 0.5, (default, other)
