@@ -83,10 +83,29 @@ def test_mean(kind, bits, D, V, offset, bound):
     assert (np.abs(total - want) <= REL_TOL * np.maximum(np.abs(want), column_magnitude(s)[None, :] * n)).all()
 
 
+# the general mean's slots a list (1, 2, 4 and 8 here: a list of more than 32 rows a slot, or than the fields hold, is
+# the whole wave's), with lists on both sides of where that begins, and of two and three times what the fields hold
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+@pytest.mark.parametrize("D,V,avg", [(50, 8000, 10), (50, 16_000, 3), (18, 80_000, 3), (6, 70_000, 3), (131, 2000, 40), (602, 300, 5)])
+def test_mean_slots(bits, D, V, avg):
+    torch, q, s, codes, table = _table("uniform", bits, D)
+    rng = np.random.default_rng(V + bits)
+    edges = [k + d for k in (32, 64, 85, 128, 170, 255, 257, 510, 512) for d in (-1, 0, 1)]
+    indptr, indices = random_csr(V, len(codes), 2 * avg, rng, hubs=edges)
+    out = _out(torch, V, D, 0)
+    q.gather_mean(table, torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), out)
+    rows = np.r_[0:40, rng.integers(0, V, 500), V - 40:V]
+    lists = [indices[indptr[v]:indptr[v + 1]] for v in rows]
+    sub = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    got = out[torch.from_numpy(rows).cuda()].cpu().numpy()
+    assert_close(got, orc.gather_mean(s, codes, sub, np.concatenate(lists).astype(np.int64)), s)
+
+
 # calls that such rows' own routes served worse than the ones they had before: few wide rows (the flat decode: 6.2 us
-# against 17.1), one-column granules (46, 66).  No slower than those by more than a third
+# against 17.1), one-column granules (46, 66), many short chains for lists of 30 rows (2 slots: 9.8, 18.5).  No slower than those by more than a third
 @pytest.mark.parametrize("call,D,n,option,value", [
-    ("decode", 7001, 50, "dequant_flat", 1), ("decode", 1001, 30_000, "dequant_flat", 1)])
+    ("decode", 7001, 50, "dequant_flat", 1), ("decode", 1001, 30_000, "dequant_flat", 1),
+    ("mean", 3, 8000, "mean_slots", 2)])
 def test_no_slower_than_the_other_route(call, D, n, option, value):
     torch, q, s, codes, table = _table("uniform", 1, D)
     big = table.repeat(200, 1)
