@@ -381,9 +381,10 @@ hipError_t launch_gather_mean_2hop(bifeat_params *p, const HopCall &c) {
 // Output rows that are 8-byte aligned only: from 4 M values on the short-list kernel saves more than the second
 // launch costs that then looks for longer lists (46 546 destinations of 602 columns, 8 bits: 119 us against 62, 2
 // bits 59 and 45; 46 546 of 110, 4 bits: 21.6 and 15.9; 5603 of 110: 9.5 and 14.1).  Rows aligned to 4 bytes gain
-// nothing from it (46 546 of 131 columns, 4 bits: 24.9 and 25.4).
-static bool odd_rows_pay(const MeanCall &c, int D) {
-    return D % 2 == 0 && (uintptr_t)c.out % 8 == 0 && c.V * D >= (1 << 22);
+// nothing from it (46 546 of 131 columns, 4 bits: 24.9 and 25.4), nor do lists that need 1-bit codes' wide fields
+// (46 546 of 102, lists of 30: 37 and 55; of 10, 44 and 31).
+static bool odd_rows_pay(const MeanCall &c, int D, int bits) {
+    return D % 2 == 0 && !(bits == 1 && c.E > c.V * lean_capacity(1, false)) && (uintptr_t)c.out % 8 == 0 && c.V * D >= (1 << 22);
 }
 
 hipError_t launch_gather_mean(bifeat_params *p, const MeanCall &c) {
@@ -403,9 +404,6 @@ hipError_t launch_gather_mean(bifeat_params *p, const MeanCall &c) {
     // 1-bit logarithmic codes (Sec. 3.1: sign only) decode affinely, V[0] + q*(V[1]-V[0]),
     // so they take the integer-sum kernels of the uniform codes with that map per column
     const bool affine = kind == BIFEAT_SQ_UNIFORM || (kind == BIFEAT_SQ_LOG && p->scheme.bits == 1);
-    // Such launches take the short-list kernel, but never alone: a second kernel looks for longer
-    // lists, promised or not.
-    const bool lean_odd = !vec && odd_rows_pay(c, D);
     if (affine && !p->opt_mean_generic && D <= 2048) {
         // Short lists (sampled blocks) go to the lean kernel, anything longer to the
         // general one; each skips the other's destinations.  The caller's bound on
@@ -413,6 +411,9 @@ hipError_t launch_gather_mean(bifeat_params *p, const MeanCall &c) {
         // kernel's field width.
         const bool wide = need > lean_capacity(p->scheme.bits, false);
         const int thr = lean_capacity(p->scheme.bits, wide);
+        // (rows that are not 16-byte aligned take it never alone: a second kernel looks for longer lists,
+        // promised or not)
+        const bool lean_odd = !vec && odd_rows_pay(c, D, p->scheme.bits);
         const bool lean = p->opt_mean_lean && p->opt_mean_slots == 0 && (vec || lean_odd) && V > 0 && need <= thr && ids32 &&
                           launch_gather_mean_lean(p, c, thr, wide, -1, promised && vec);
         const bool all_short = lean && promised && vec;

@@ -102,10 +102,11 @@ def test_mean_slots(bits, D, V, avg):
 
 
 # calls that such rows' own routes served worse than the ones they had before: few wide rows (the flat decode: 6.2 us
-# against 17.1), one-column granules (46, 66), many short chains for lists of 30 rows (2 slots: 9.8, 18.5).  No slower than those by more than a third
+# against 17.1), one-column granules (46, 66), many short chains for lists of 30 rows (2 slots: 9.8, 18.5), wide fields of
+# 1-bit codes (the general mean: 37, 55).  No slower than those by more than a third
 @pytest.mark.parametrize("call,D,n,option,value", [
     ("decode", 7001, 50, "dequant_flat", 1), ("decode", 1001, 30_000, "dequant_flat", 1),
-    ("mean", 3, 8000, "mean_slots", 2)])
+    ("mean", 3, 8000, "mean_slots", 2), ("mean", 102, 46_546, "mean_lean", 0)])
 def test_no_slower_than_the_other_route(call, D, n, option, value):
     torch, q, s, codes, table = _table("uniform", 1, D)
     big = table.repeat(200, 1)
