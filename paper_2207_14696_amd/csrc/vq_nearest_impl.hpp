@@ -940,7 +940,7 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
     // (the kernel's few static words count too)
     const int64_t fit = kCuLds / ((int64_t)lds + 64);
     // (training at two a CU: as many sets, with one codebook for each)
-    if (fit >= 3 || (train && fit == 2 && G == 2)) return BF_VNL(256);
+    if (fit >= 3 || (train && fit == 2 && G >= 2)) return BF_VNL(256);
     if constexpr (G == 1) return fit == 2 ? BF_VNL(512) : BF_VNL(1024);
     else return BF_VNL(512);
 #undef BF_VNL

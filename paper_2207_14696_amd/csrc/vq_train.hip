@@ -309,7 +309,8 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
     while (w >= 8 && g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
     g.codes_bytes = (rows * p->P * p->cbytes + 255) / 256 * 256;
     g.sets = row_sets(p, rows);
-    deal_sets(g.sets, rows, cols, 256 * std::min<int64_t>(2 * kAccThreads / g.threads, 160 * 1024 / (lds + 64)), g.threads);
+    // (512 workgroups do: each also adds to the one distortion, 20 ns one after the other)
+    deal_sets(g.sets, rows, cols, 256 * std::min<int64_t>(2, 160 * 1024 / (lds + 64)), g.threads);
     if (g.sets.sub > 1 && sums_bytes(p, g.sets) > kMaxSumsBytes) g.sets = row_sets(p, rows);
     g.sums_bytes = sums_bytes(p, g.sets);
     return g;
