@@ -17,8 +17,9 @@
 // vq_cell_margin below); a row for which it is not - near ties, values outside the range the split
 // holds - is searched by the rule over the whole codebook, by the wave together, or lane by lane
 // when many rows of a wave need it; where most rows do, the scores are left out (search_costs below:
-// at no share of such rows is that dearer than the plain search by more than a tenth).  The codes
-// are therefore the same as the plain search gives, for any input.
+// at no share of such rows is that dearer than the plain search by more than a fifth, but parts of 4
+// columns, which count as 8 here: 96 x 256 x 4 464 us by the plain search, 130 with no such row, 570 at a fifth, 770 at worst).
+// The codes are therefore the same as the plain search gives, for any input.
 //
 // What bounds it: vector instructions and power.  Of ~470 per 64 rows and part 200 are the running
 // minima over 256 entries, 100 the scores inside the cell, 45 the split of x, 32 the products, at
@@ -843,21 +844,25 @@ bool entries_in_lds(const bifeat_params *p, bool train) {
 
 // Rows of a wave that the scores leave open are searched by the rule two at a time, the lanes sharing
 // the codebook, or, from `lane_rows` of 64 on, all in one pass over it; and from `plain_rows` on the
-// scores do not pay at all.  The costs in vector instructions, from times at shares of open rows
-// between 0 and 1 (65 536 rows; us with none open, per share of 1, all by the rule):
-//   96 x 256 x 8  193, 1930, 748      48 x 256 x 16  181, 2120, 846     24 x 64 x 32  112, 884, 262
-//   without the entries in LDS: 8 x 2048 x 16  214, 2280, 969   32 x 2048 x 8  424, 5040, 2127
-//   2 x 1000 x 32  134, 1960, 300     10 x 1000 x 13  204, 4430, 700
-// (with four piece products; with three, none open and all by the rule: 96 x 256 x 8 144 and 731 to 757, 48 x 256 x 16
-// 115 and 762, 8 x 2048 x 16 176 and 950, 32 x 2048 x 8 289 and 1980; 30 % open cost less than all do but at 96 x 256 x 8)
+// scores do not pay at all.  The costs in vector instructions, fitted to how many open rows of 64 make the
+// scores as dear as the rule for all (65 536 rows; us with none open, per share of 1 up to 0.2, all by the
+// rule; that number measured, and by the fit):
+//   96 x 256 x 8   142, 2300, 732: 18.0, 18.0    48 x 1000 x 8  213, 2860, 1570: 31.2, 31.4   16 x 1000 x 16  132, 1580, 933: 30.2, 32.1
+//   48 x 256 x 16  112, 1420, 765: 27.6, 23.2    24 x 512 x 16  108, 1560, 776: 28.6, 28.9    32 x 256 x 24  111, 1590, 723: 24.8, 24.1
+//   24 x 256 x 32  108, 1570, 755: 25.4, 24.6    24 x 64 x 32  68, 840, 218: 11.9, 14.6
+//   without the entries in LDS: 8 x 2048 x 16  175, 2450, 946: 22.5, 20.0   8 x 1500 x 24  203, 3130, 1060: 17.7, 19.5
+//   8 x 1000 x 32  250, 7600, 950: 6.1, 6.1 (entries of 128 bytes meet in the caches)   8 x 1500 x 21  413, 16 000, 1080: 3.4
+// By cosine the rule costs a multiplication and an addition instead of three instructions: 0.8 to 0.95 of these.
 template <typename T>
-void search_costs(VqNearestArgs<T> &a, int G, bool ent) {
+void search_costs(VqNearestArgs<T> &a, int G, bool ent, bool cosine) {
     const double entry = 3.0 * 8 * G + 3.0, all = a.len * entry;
-    const double apart = ent ? (G == 1 ? 1.1 : 1.7) : G <= 2 && a.bvec ? 2.2 : 6.0;  // each lane its own entry
+    // each lane its own entry
+    const double apart = ent ? (G == 1 ? 1.3 : G == 2 ? 1.45 : G == 3 ? 1.65 : 1.75) : !a.bvec ? 14.0 : a.w == 32 ? 7.4 : 2.5;
     const double one = (a.len + 63) / 64 * entry * apart + 170.0;
-    const double scores = 5.5 * a.len * G + 400.0;
+    const double scores = (ent ? 3.6 : G == 4 ? 6.5 : 4.7) * a.len * G + 400.0;
     a.lane_rows = (int)std::min(64.0, all / one);
-    a.plain_rows = (int)std::max(1.0, std::min(60.0, (all - scores) / one));
+    // (a wave that decides by itself keeps to it for 7 more strips: 5 rows, more than their number's spread, on top)
+    a.plain_rows = (int)std::max(1.0, std::min(60.0, (cosine ? 0.88 : 1.0) * (all - scores) / one + (ent ? 5.0 : 0.0)));
 }
 
 template <typename T, int G, int METRIC, bool ENT, bool TRAIN, int TH>
@@ -915,7 +920,7 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         ny = (a.rows + a.chunk - 1) / a.chunk;
     }
     a.ny = (int)ny;
-    search_costs(a, G, ENT);
+    search_costs(a, G, ENT, METRIC == BIFEAT_VQ_COSINE);
     const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
     kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
     if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.sets, a.one_set ? 1 : a.sub, s);
