@@ -154,10 +154,13 @@ def test_rows_without_a_nearest_entry(P, w, length, rows, metric, bad):
     np.testing.assert_array_equal(np.isnan(q.params_get_codebooks()), np.isnan(cb))
 
 
-# widths 1, 2 and 4 on both sides of 128 values, of 4096 rows and of 2^21 sample values; other widths
+# codes or the plain fused kernel: widths 1 and 2 on both sides of 64 entries and of 2^22 rows x parts, where one and
+# two columns of more entries take the latter; other widths
 @pytest.mark.parametrize("P,w,length,rows", [(3, 1, 64, 5000), (3, 1, 200, 5000), (3, 1, 64, 4096), (5, 4, 31, 4097),
                                              (5, 4, 32, 4097), (130, 4, 64, 4100), (8, 2, 64, 131_200),
-                                             (8, 2, 65, 131_200), (4, 5, 40, 700), (1, 64, 30, 900)])
+                                             (8, 2, 65, 131_200), (4, 5, 40, 700), (1, 64, 30, 900),
+                                             (64, 1, 65, 65_535), (64, 1, 65, 65_536), (64, 1, 64, 65_536),
+                                             (128, 2, 64, 32_768), (128, 2, 65, 32_768), (128, 2, 65, 32_767)])
 def test_small_codebooks(P, w, length, rows):
     import torch
     import paper_2207_14696_amd as bf
@@ -168,7 +171,7 @@ def test_small_codebooks(P, w, length, rows):
 
 
 @pytest.mark.parametrize("P,w,length,metric,reserve", [
-    (4, 16, 256, "l2", 0),         # no room: one set of sums
+    (4, 16, 256, "l2", 0), (4, 16, 256, "cosine", 0), (4, 8, 700, "l2", 0),  # search and sums, no room: one set of sums
     (4, 8, 32, "l2", 0), (4, 8, 32, "l2", 20_000), (2, 5, 40, "l2", 20_000),  # the plain fused kernel
     (2, 16, 700, "cosine", 20_000)])  # room for the codes only: one set of sums
 def test_training_under_capture(P, w, length, metric, reserve):
@@ -233,9 +236,10 @@ def _us(torch, f):
     return best
 
 
-@pytest.mark.parametrize("P,w,length,reserve", [(8, 16, 256, 0), (12, 8, 32, 65_536)])
+@pytest.mark.parametrize("P,w,length,reserve", [(8, 16, 256, 0), (12, 8, 32, 65_536), (8, 16, 1024, 65_536)])
 def test_training_under_capture_fills_the_chip(P, w, length, reserve):
-    # 0.9 and 1.7 times an eager call's time; with a workgroup per part it was 13 and 6 times
+    # search and sums in one kernel, twice, and the sums from codes, each with room for one set: 0.9 to 1.0 times an eager
+    # call's time; with a workgroup per part it was 6 to 13 times
     import torch
     import paper_2207_14696_amd as bf
     x = torch.randn(65_536, P * w, device="cuda")
