@@ -167,7 +167,7 @@ bool launch_gather_mean_lean_log2(bifeat_params *p, const MeanCall &c, int thr, 
                                   bool alone);
 bool launch_gather_mean_lean_odd(bifeat_params *p, const MeanCall &c, int thr, bool wide, int lo, bool alone);
 bool launch_gather_mean_lean(bifeat_params *p, const MeanCall &c, int thr, bool wide, int lo,
-                             bool alone);
+                             bool alone, bool vec);
 
 // Two rounds of the neighbourhood mean from the packed table: the outer block's lists hold
 // table rows (one list per first-round destination), the seed block's lists hold first-round

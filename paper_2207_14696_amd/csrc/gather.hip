@@ -55,16 +55,6 @@ __device__ inline uint32_t code_bits(const uint8_t *row, int g) {
     }
 }
 
-// the 4*BITS code bits of columns 4g..4g+3 of a packed row (always inside the
-// 16-byte padded row)
-template <int BITS>
-__device__ inline uint32_t code_bits4(const uint8_t *row, int g) {
-    if constexpr (BITS == 8) return *reinterpret_cast<const uint32_t *>(row + 4 * g);
-    else if constexpr (BITS == 4) return *reinterpret_cast<const uint16_t *>(row + 2 * g);
-    else if constexpr (BITS == 2) return row[g];
-    else return (uint32_t)(row[g >> 1] >> (4 * (g & 1))) & 0xFu;
-}
-
 template <bool VEC>
 __device__ inline void store4(float *out, int64_t row, int D, int col0, const float v[4]) {
     float *dst = out + row * D + col0;
@@ -108,7 +98,7 @@ __global__ __launch_bounds__(kThreads) void gather_dequant_sq_kernel(
     constexpr uint32_t mask = (1u << BITS) - 1u;
 #pragma unroll 4
     for (int64_t i = t / G; i < M; i += rows_per_pass) {
-        const uint32_t bits = code_bits4<BITS>(codes + idx[i] * rb, g);
+        const uint32_t bits = code_bits<BITS, 4>(codes + idx[i] * rb, g);
         float v[4];
 #pragma unroll
         for (int k = 0; k < 4; k++) {

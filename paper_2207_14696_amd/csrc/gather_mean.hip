@@ -415,7 +415,7 @@ hipError_t launch_gather_mean(bifeat_params *p, const MeanCall &c) {
         // promised or not)
         const bool lean_odd = !vec && odd_rows_pay(c, D, p->scheme.bits);
         const bool lean = p->opt_mean_lean && p->opt_mean_slots == 0 && (vec || lean_odd) && V > 0 && need <= thr && ids32 &&
-                          launch_gather_mean_lean(p, c, thr, wide, -1, promised && vec);
+                          launch_gather_mean_lean(p, c, thr, wide, -1, promised && vec, vec);
         const bool all_short = lean && promised && vec;
         if (!all_short) {
             // Without the caller's bound the narrow form was chosen on the average alone: the
@@ -424,7 +424,7 @@ hipError_t launch_gather_mean(bifeat_params *p, const MeanCall &c) {
             int covered = lean ? thr : -1;
             const int thr_wide = lean_capacity(p->scheme.bits, true);
             if (lean && !wide && thr_wide > thr &&
-                launch_gather_mean_lean(p, c, thr_wide, true, thr, false))
+                launch_gather_mean_lean(p, c, thr_wide, true, thr, false, vec))
                 covered = thr_wide;
             launch_gather_mean_swar(p, c, vec, covered);
         }

@@ -20,11 +20,10 @@ int lean_capacity(int bits, bool wide) {
 
 // Launches the short-list kernel (lists of more than `lo` and at most `thr` rows; wide =
 // the form with the larger field capacity); returns false (nothing launched) when the
-// table's shape is outside what it handles.
+// table's shape is outside what it handles.  vec: the output rows are 16-byte aligned, else 8-byte.
 bool launch_gather_mean_lean(bifeat_params *p, const MeanCall &c, int thr, bool wide, int lo,
-                             bool alone) {
-    const bool odd = p->D % 4 != 0 || (uintptr_t)c.out % 16 != 0;
-    return odd ? launch_gather_mean_lean_odd(p, c, thr, wide, lo, alone) : launch_lean<false>(p, c, thr, wide, lo, alone);
+                             bool alone, bool vec) {
+    return vec ? launch_lean<false>(p, c, thr, wide, lo, alone) : launch_gather_mean_lean_odd(p, c, thr, wide, lo, alone);
 }
 
 // 2-bit logarithmic codes (Sec. 3.1 Eq. (1)/(2) with k = 2): code q = 2*b1 + b0 decodes to

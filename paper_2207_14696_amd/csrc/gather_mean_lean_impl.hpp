@@ -226,97 +226,97 @@ __global__ __launch_bounds__(kLeanThreads, BF_LEAN_WPE) void gather_mean_lean_ke
                 }
             }
         } else {
-        // ---- the tile's output rows, one contiguous span of ndst*nf4 float4 granules
-        float4 *span = reinterpret_cast<float4 *>(out + v_tile * D);
-        const int ngran = ndst * nf4;
-        int d = lane_d, f = lane_f;
+            // ---- the tile's output rows, one contiguous span of ndst*nf4 float4 granules
+            float4 *span = reinterpret_cast<float4 *>(out + v_tile * D);
+            const int ngran = ndst * nf4;
+            int d = lane_d, f = lane_f;
 #pragma unroll 2
-        for (int m = lane; m < ngran; m += 64) {
-            const float md = meta[d];
-            const bool some = md > 0.0f;  // md == 0: empty list, zero row
-            float4 val;
-            if constexpr (PAIR) {
-                // 8 consecutive bit columns -> 4 output columns
-                const int j0 = 8 * f;
-                const int lc = j0 / CPL, jj = j0 % CPL;
-                const int k = jj / CPW, c = jj % CPW;  // c % 8 == 0
-                const uint32_t *sp = stage + (((d << lpr_log2) + lc) * CW + k) * W::kN;
-                uint32_t sum[8];
-                if constexpr (W::kN == 4) {  // codes c..c+3 in field c/4, c+4..c+7 in the next
-                    const uint4 q = *reinterpret_cast<const uint4 *>(sp);
-                    const int sh = W::kF * (c / 4);
-                    sum[0] = (q.x >> sh) & FMAX; sum[1] = (q.y >> sh) & FMAX;
-                    sum[2] = (q.z >> sh) & FMAX; sum[3] = (q.w >> sh) & FMAX;
-                    sum[4] = (q.x >> (sh + W::kF)) & FMAX; sum[5] = (q.y >> (sh + W::kF)) & FMAX;
-                    sum[6] = (q.z >> (sh + W::kF)) & FMAX; sum[7] = (q.w >> (sh + W::kF)) & FMAX;
-                } else {  // kN == 8: codes c..c+7 in registers 0..7, field c/8
-                    const uint4 qa = *reinterpret_cast<const uint4 *>(sp);
-                    const uint4 qb = *reinterpret_cast<const uint4 *>(sp + 4);
-                    const int sh = W::kF * (c / 8);
-                    sum[0] = (qa.x >> sh) & FMAX; sum[1] = (qa.y >> sh) & FMAX;
-                    sum[2] = (qa.z >> sh) & FMAX; sum[3] = (qa.w >> sh) & FMAX;
-                    sum[4] = (qb.x >> sh) & FMAX; sum[5] = (qb.y >> sh) & FMAX;
-                    sum[6] = (qb.z >> sh) & FMAX; sum[7] = (qb.w >> sh) & FMAX;
-                }
-                const float4 a0 = *reinterpret_cast<const float4 *>(s_sc + j0);
-                const float4 a1 = *reinterpret_cast<const float4 *>(s_sc + j0 + 4);
-                const float4 b0 = *reinterpret_cast<const float4 *>(s_mn + j0);
-                const float4 b1 = *reinterpret_cast<const float4 *>(s_mn + j0 + 4);
-                const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                float v[8];
+            for (int m = lane; m < ngran; m += 64) {
+                const float md = meta[d];
+                const bool some = md > 0.0f;  // md == 0: empty list, zero row
+                float4 val;
+                if constexpr (PAIR) {
+                    // 8 consecutive bit columns -> 4 output columns
+                    const int j0 = 8 * f;
+                    const int lc = j0 / CPL, jj = j0 % CPL;
+                    const int k = jj / CPW, c = jj % CPW;  // c % 8 == 0
+                    const uint32_t *sp = stage + (((d << lpr_log2) + lc) * CW + k) * W::kN;
+                    uint32_t sum[8];
+                    if constexpr (W::kN == 4) {  // codes c..c+3 in field c/4, c+4..c+7 in the next
+                        const uint4 q = *reinterpret_cast<const uint4 *>(sp);
+                        const int sh = W::kF * (c / 4);
+                        sum[0] = (q.x >> sh) & FMAX; sum[1] = (q.y >> sh) & FMAX;
+                        sum[2] = (q.z >> sh) & FMAX; sum[3] = (q.w >> sh) & FMAX;
+                        sum[4] = (q.x >> (sh + W::kF)) & FMAX; sum[5] = (q.y >> (sh + W::kF)) & FMAX;
+                        sum[6] = (q.z >> (sh + W::kF)) & FMAX; sum[7] = (q.w >> (sh + W::kF)) & FMAX;
+                    } else {  // kN == 8: codes c..c+7 in registers 0..7, field c/8
+                        const uint4 qa = *reinterpret_cast<const uint4 *>(sp);
+                        const uint4 qb = *reinterpret_cast<const uint4 *>(sp + 4);
+                        const int sh = W::kF * (c / 8);
+                        sum[0] = (qa.x >> sh) & FMAX; sum[1] = (qa.y >> sh) & FMAX;
+                        sum[2] = (qa.z >> sh) & FMAX; sum[3] = (qa.w >> sh) & FMAX;
+                        sum[4] = (qb.x >> sh) & FMAX; sum[5] = (qb.y >> sh) & FMAX;
+                        sum[6] = (qb.z >> sh) & FMAX; sum[7] = (qb.w >> sh) & FMAX;
+                    }
+                    const float4 a0 = *reinterpret_cast<const float4 *>(s_sc + j0);
+                    const float4 a1 = *reinterpret_cast<const float4 *>(s_sc + j0 + 4);
+                    const float4 b0 = *reinterpret_cast<const float4 *>(s_mn + j0);
+                    const float4 b1 = *reinterpret_cast<const float4 *>(s_mn + j0 + 4);
+                    const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                    const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+                    float v[8];
 #pragma unroll
-                for (int i = 0; i < 8; i++)
-                    v[i] = SUM ? fmaf(a[i], (float)sum[i], b[i] * md) : fmaf(a[i], (float)sum[i] * md, b[i]);
-                val.x = some ? v[0] + v[1] : 0.0f;
-                val.y = some ? v[2] + v[3] : 0.0f;
-                val.z = some ? v[4] + v[5] : 0.0f;
-                val.w = some ? v[6] + v[7] : 0.0f;
-            } else {
-            const int j0 = 4 * f;
-            const int lc = j0 / CPL, jj = j0 % CPL;
-            const int k = jj / CPW, c = jj % CPW;
-            const uint32_t *sp = stage + (((d << lpr_log2) + lc) * CW + k) * W::kN;
-            uint32_t sum[4];
-            if constexpr (W::kN >= 4) {
-                const uint4 q = *reinterpret_cast<const uint4 *>(sp + c % W::kN);
-                const int sh = W::kF * (c / W::kN);
-                sum[0] = (q.x >> sh) & FMAX;
-                sum[1] = (q.y >> sh) & FMAX;
-                sum[2] = (q.z >> sh) & FMAX;
-                sum[3] = (q.w >> sh) & FMAX;
-            } else {
-                const uint2 q = *reinterpret_cast<const uint2 *>(sp);
-                const int sh = W::kF * (c / 2);
-                sum[0] = (q.x >> sh) & FMAX;
-                sum[1] = (q.y >> sh) & FMAX;
-                sum[2] = (q.x >> (sh + W::kF)) & FMAX;
-                sum[3] = (q.y >> (sh + W::kF)) & FMAX;
-            }
-            const float4 a = *reinterpret_cast<const float4 *>(s_sc + j0);
-            const float4 b = *reinterpret_cast<const float4 *>(s_mn + j0);
-            if constexpr (SUM) {
-                val.x = some ? fmaf(a.x, (float)sum[0], b.x * md) : 0.0f;
-                val.y = some ? fmaf(a.y, (float)sum[1], b.y * md) : 0.0f;
-                val.z = some ? fmaf(a.z, (float)sum[2], b.z * md) : 0.0f;
-                val.w = some ? fmaf(a.w, (float)sum[3], b.w * md) : 0.0f;
-            } else {
-                val.x = some ? fmaf(a.x, (float)sum[0] * md, b.x) : 0.0f;
-                val.y = some ? fmaf(a.y, (float)sum[1] * md, b.y) : 0.0f;
-                val.z = some ? fmaf(a.z, (float)sum[2] * md, b.z) : 0.0f;
-                val.w = some ? fmaf(a.w, (float)sum[3] * md, b.w) : 0.0f;
-            }
-            }
-            if (md != md) val.x = val.y = val.z = val.w = md;  // list beyond the promised bound
-            if (!(md < 0.0f)) store_stream(&span[m], val);  // md < 0: not this kernel's destination
-            d += step_d;
-            f += step_f;
-            if (f >= nf4) {
-                f -= nf4;
-                d++;
+                    for (int i = 0; i < 8; i++)
+                        v[i] = SUM ? fmaf(a[i], (float)sum[i], b[i] * md) : fmaf(a[i], (float)sum[i] * md, b[i]);
+                    val.x = some ? v[0] + v[1] : 0.0f;
+                    val.y = some ? v[2] + v[3] : 0.0f;
+                    val.z = some ? v[4] + v[5] : 0.0f;
+                    val.w = some ? v[6] + v[7] : 0.0f;
+                } else {
+                    const int j0 = 4 * f;
+                    const int lc = j0 / CPL, jj = j0 % CPL;
+                    const int k = jj / CPW, c = jj % CPW;
+                    const uint32_t *sp = stage + (((d << lpr_log2) + lc) * CW + k) * W::kN;
+                    uint32_t sum[4];
+                    if constexpr (W::kN >= 4) {
+                        const uint4 q = *reinterpret_cast<const uint4 *>(sp + c % W::kN);
+                        const int sh = W::kF * (c / W::kN);
+                        sum[0] = (q.x >> sh) & FMAX;
+                        sum[1] = (q.y >> sh) & FMAX;
+                        sum[2] = (q.z >> sh) & FMAX;
+                        sum[3] = (q.w >> sh) & FMAX;
+                    } else {
+                        const uint2 q = *reinterpret_cast<const uint2 *>(sp);
+                        const int sh = W::kF * (c / 2);
+                        sum[0] = (q.x >> sh) & FMAX;
+                        sum[1] = (q.y >> sh) & FMAX;
+                        sum[2] = (q.x >> (sh + W::kF)) & FMAX;
+                        sum[3] = (q.y >> (sh + W::kF)) & FMAX;
+                    }
+                    const float4 a = *reinterpret_cast<const float4 *>(s_sc + j0);
+                    const float4 b = *reinterpret_cast<const float4 *>(s_mn + j0);
+                    if constexpr (SUM) {
+                        val.x = some ? fmaf(a.x, (float)sum[0], b.x * md) : 0.0f;
+                        val.y = some ? fmaf(a.y, (float)sum[1], b.y * md) : 0.0f;
+                        val.z = some ? fmaf(a.z, (float)sum[2], b.z * md) : 0.0f;
+                        val.w = some ? fmaf(a.w, (float)sum[3], b.w * md) : 0.0f;
+                    } else {
+                        val.x = some ? fmaf(a.x, (float)sum[0] * md, b.x) : 0.0f;
+                        val.y = some ? fmaf(a.y, (float)sum[1] * md, b.y) : 0.0f;
+                        val.z = some ? fmaf(a.z, (float)sum[2] * md, b.z) : 0.0f;
+                        val.w = some ? fmaf(a.w, (float)sum[3] * md, b.w) : 0.0f;
+                    }
+                }
+                if (md != md) val.x = val.y = val.z = val.w = md;  // list beyond the promised bound
+                if (!(md < 0.0f)) store_stream(&span[m], val);  // md < 0: not this kernel's destination
+                d += step_d;
+                f += step_f;
+                if (f >= nf4) {
+                    f -= nf4;
+                    d++;
+                }
             }
         }
-        }  // !ODD
         wave_sync();  // stage / meta are rewritten by the next tile
     }
 }
@@ -348,11 +348,9 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
     // average) is one step of BF_LEAN_U rows (the mean only: the sums keep one form), up to 2048 waves (8 per CU).  4-bit rows of 64 bytes,
     // lists of up to 25: 1 024 destinations 9.3 -> 4.8 us (512 waves); 6 200 destinations 8.9 us
     // unshared, 6.1 with 2048 waves, 7.1 with 4096.
-    const bool odd = p->D % 4 != 0 || (uintptr_t)c.out % 16 != 0;
-    if (odd != ODD || (odd && (PAIR || p->D % 2 != 0 || (uintptr_t)c.out % 8 != 0))) return false;
     const int64_t longest = c.max_degree > 0 ? c.max_degree : 2 * c.E / (V > 0 ? V : 1);
     int s_log2 = 0;
-    while (!c.agg_sum && !odd && (lpr << (s_log2 + 1)) <= 64 && ((int64_t)BF_LEAN_U << s_log2) < longest &&
+    while (!c.agg_sum && !ODD && (lpr << (s_log2 + 1)) <= 64 && ((int64_t)BF_LEAN_U << s_log2) < longest &&
            (V * (lpr << (s_log2 + 1)) + 63) / 64 <= kSplitWaves)
         s_log2++;
     const int dpw = 64 / (lpr << s_log2);
