@@ -133,12 +133,9 @@ hipError_t static_scratch_ptr(uint8_t **out);
 // 1/|entry| for every codebook entry, fp64 inside (cosine metric)
 void launch_vq_zero(float *a, int64_t n, hipStream_t s);
 void launch_vq_rnorm(bifeat_params *p, hipStream_t s);
-// nearest-entry search of `rows` rows: the index of row r's part p, p->cbytes bytes, goes to
-// codes + r * rb + p * pb.  Rows of a table: pb = cbytes, and the bytes from P * cbytes to rb are
-// zeroed; one part's indices after the other (training): rb = cbytes, pb = rows * cbytes.
+// the index of the nearest entry of every row's part, p->cbytes bytes, one part's after the other (training)
 template <typename T>
-void launch_vq_assign(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
-                      hipStream_t s);
+void launch_vq_assign_parts(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, hipStream_t s);
 // counts violations of 0 <= idx[i] < N (and, with indptr, of indptr[0] == 0, indptr
 // non-decreasing, indptr[V] == E, no list longer than max_len if that is positive) into
 // *d_bad (zeroed first)

@@ -13,7 +13,9 @@ bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows);
 // rows x parts from which on it takes some small codebooks
 constexpr int64_t kNearestManyParts = 1 << 18;
 
-// the index of every part's nearest entry, see launch_vq_assign
+// the index of every part's nearest entry: row r's part p, p->cbytes bytes, goes to codes + r * rb + p * pb.  Rows of
+// a table: pb = cbytes, and the bytes from P * cbytes to rb are zeroed; one part's indices after the other (training):
+// rb = cbytes, pb = rows * cbytes.
 template <typename T>
 bool launch_vq_nearest_codes(bifeat_params *p, const T *x, int64_t rows, uint8_t *codes, int64_t rb, int64_t pb,
                              hipStream_t s);

@@ -358,7 +358,7 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     uint32_t *counts = (uint32_t *)(sums + sets * sub * books * (sub > 1 ? 8 : 4));
     if (!all) launch_vq_zero(p->d_train, books + (int64_t)P * len, s);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
-    launch_vq_assign(p, x, rows, p->d_scratch, p->cbytes, rows * p->cbytes, s);
+    launch_vq_assign_parts(p, x, rows, p->d_scratch, s);
     // 4 columns at a time: whole fours everywhere, and where they lie
     const bool vec = g.DG % 4 == 0 && w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
     const bool ok = p->cbytes == 1
