@@ -145,9 +145,13 @@ int64_t bifeat_codes_per_row(const bifeat_params *p);
  *   `vq_length` rows (it must have at least that many); every update then runs
  *   Lloyd rounds over its chunk (10, option "vq_iters"): nearest entry by the
  *   encoder's rule for the scheme's metric, entry = mean of its members, an
- *   entry without members keeps its value.  Sums are accumulated with atomics,
- *   so the codebooks are reproducible in distortion, not bit for bit.
- *   Training uses library scratch: workgroups' partial sums of the codebooks, and for a
+ *   entry without members keeps its value.  An entry's mean comes from sums over
+ *   fixed sets of rows, each added up in 64 bits, rounded to 32 and taken in order:
+ *   the same sample gives the same codebook, but for a sum within 2^-53 of the
+ *   edge between two 32-bit values.  It is reproducible in distortion alone where
+ *   32-bit sums are added by atomics: some Euclidean codebooks of 1 or 2 columns and
+ *   65 to 256 entries, from 2^22 rows x parts on, and sums that find no scratch.
+ *   Training uses library scratch: the sets' partial sums of the codebooks, and for a
  *   codebook that does not fit a compute unit's on-chip memory next to its sums (w = 8: more than
  *   about 1100 entries, w = 16: 600, w = 32: 300), of w > 32 or too small or dense for the matrix
  *   cores mostly also a code per part and sample row (one byte up to 256 entries, else two), with

@@ -21,9 +21,9 @@
 // columns, which count as 8 here: 96 x 256 x 4 464 us by the plain search, 130 with no such row, 570 at a fifth, 770 at worst).
 // The codes are therefore the same as the plain search gives, for any input.
 //
-// What bounds it: vector instructions and power.  Of ~470 per 64 rows and part 200 are the running
+// What bounds it: vector instructions and power.  Of 479 per 64 rows and part 200 are the running
 // minima over 256 entries, 100 the scores inside the cell, 45 the split of x, 32 the products, at
-// 77 % of the issue rate; the clock falls to 1.8 GHz under it, so that every instruction and LDS
+// 78 % of the issue rate; the clock falls to 1.8 GHz under it, so that every instruction and LDS
 // read taken out counts, and a better overlap alone does not.  262 144 rows of 96 parts x 256 entries
 // x 8 columns: 535 us; with all four products of the pieces, |c|^2/2 read from LDS for every tile
 // and cells across two tiles (570 instructions, 77 LDS reads instead of 39) 650; the plain search
@@ -31,10 +31,11 @@
 //
 // Training adds each part to its entry's sum in LDS.  The sums are kept in 64 bits: an LDS
 // float add takes 196 cycles per wave here whatever the addresses, a double add 22 (integer: 8).
-// A workgroup writes its sums to the workspace and a second kernel adds them up in a fixed order
-// (global float adds onto the same few addresses ran at 22.6 G/s, a quarter of the round).  One
-// round over 65 536 rows of that shape: 165 us (with the search as it was, see above, 200; plain search
-// and fp32 adds 1030).
+// A workgroup writes the sums of its sets of rows (RowSets) to the workspace and a second kernel adds
+// them up in the sets' order (global float adds onto the same few addresses ran at 22.6 G/s, a quarter of
+// the round).  One round over 65 536 rows of that shape: 167 us (with the search as it was, see above,
+// 200; with the rows dealt evenly instead of in sets, and codebooks that depend on how many
+// workgroups there are, 164; plain search and fp32 adds 1030).
 #pragma once
 
 #include "vq_nearest.hpp"
@@ -888,7 +889,7 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         ny = r.groups;
         // the sets' sums; without room for them (a stream that is being captured) they add to
         // the handle's own block of one set (10 rounds on 65 536 rows, with workspace / so: 8 x 256 x 16
-        // 690 / 560 us, 96 x 256 x 8 1910 / 1930; one workgroup per part 8790 and 6370)
+        // 530 / 500 us, 96 x 256 x 8 1690 / 1650; one workgroup per part 8790 and 6370)
         const int64_t books = (int64_t)a.P * a.len * a.w, ents = (int64_t)a.P * a.len;
         if (ensure_scratch(p, (size_t)sums_bytes(p, r), s)) {
             a.sums = p->d_scratch;
@@ -940,7 +941,7 @@ bool launch_metric(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, hipStre
     // Workgroups of 256 threads while a CU holds three or more.  Larger codebooks would leave it with few
     // waves, so they are shared by as many as the registers allow: 65 536 rows of 96 x 1000 x 8 459 us (512
     // threads that read the entries from L2: 726), 48 x 512 x 16 207 (358), 24 x 270 x 32 124 (447); training
-    // 96 x 1000 x 8 4610 us (search and sums apart 7420).  9 to 16 columns: with three waves a SIMD in mind the
+    // 96 x 1000 x 8 4680 us (search and sums apart 5050).  9 to 16 columns: with three waves a SIMD in mind the
     // plain search spills, which workgroups of 512 do not have (48 x 512 x 16 244 in two of 256).
     // (the kernel's few static words count too)
     const int64_t fit = kCuLds / ((int64_t)lds + 64);

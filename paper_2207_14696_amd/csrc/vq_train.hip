@@ -13,7 +13,7 @@
 // Three forms:
 // - codebooks that the matrix-core search takes and that fit LDS next to their sums: search and
 //   sums in one kernel (vq_nearest.hip; 96 x 256 x 8 cosine, 10 rounds on 65 536 rows: 1760 us,
-//   apart 2340; 96 x 512 x 8 2470 and 3240);
+//   apart 2090; 96 x 512 x 8 2590 and 3070);
 // - everything else that the plain fused kernel cannot do (cosine metric, two-byte codes) or
 //   does badly (codes_pay below) runs the encoder's own kernel into a scratch code array and
 //   adds up from that, in LDS and per workgroup;
@@ -302,8 +302,8 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
         g.DG = (w + g.groups) / g.groups;
     }
     // smaller workgroups where a sample is too short to fill the chip with large ones, unless a
-    // workgroup's sums outnumber its rows then (3000 rows of 8 x 2048 x 16: 930 us against 980) or there
-    // are few columns to add (4096 rows of 96 x 64 x 1: 222 us against 259)
+    // workgroup's sums outnumber its rows then (3000 rows of 8 x 2048 x 16: 730 us against 930) or there
+    // are few columns to add (4096 rows of 24 x 64 x 4 cosine: 233 us against 262)
     const int64_t lds = (int64_t)8 * (g.DG + g.more) * acc_stride(len), cols = (int64_t)p->P * g.groups;
     g.threads = kAccThreads;
     while (w >= 8 && g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
@@ -319,9 +319,9 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
 // Whether a codebook that the plain fused kernel can train, and the matrix-core search does not take,
 // goes through codes.  The fused kernel reads the sample once a round and is bound by its LDS float
 // adds; the other way reads twice and adds in 64 bits at a ninth of the cost.  10 rounds, us, fused /
-// codes: 65 536 x 24 x 64 x 1 654 / 379, 16 384 x 96 x 250 x 2 1230 / 1030, 65 536 x 6 x 16 x 4 350 / 310.
+// codes: 65 536 x 24 x 64 x 1 657 / 422, 16 384 x 96 x 250 x 2 1250 / 1100, 65 536 x 6 x 16 x 4 274 / 277.
 // Of one or two columns there is little to add, and at millions of parts with more than 64 entries the
-// search is all that counts, which reads the sample as it lies in both (65 536 x 96 x 256 x 1 2390 / 2630).
+// search is all that counts, which reads the sample as it lies in both (65 536 x 96 x 256 x 1 2390 / 2670).
 bool codes_pay(const bifeat_params *p, int64_t rows) {
     return p->scheme.vq_width > 2 || p->scheme.vq_length <= 64 || rows * p->P < (1 << 22);
 }
@@ -351,7 +351,7 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     const GenericPlan g = generic_plan(p, rows);
     // without room for every workgroup's sums (a stream under capture) they add to the handle's own
     // block of one set (the codes' part of the workspace is there, see below): 8 x 2048 x 16 cosine,
-    // 10 rounds 2890 us so, with workspace 2980; one workgroup per part and group of columns 8690
+    // 10 rounds 1960 us so, with workspace 2020; one workgroup per part and group of columns 8690
     const bool all = (int64_t)p->scratch_bytes >= g.codes_bytes + g.sums_bytes;
     const int sets = all ? g.sets.sets : 1, sub = all ? g.sets.sub : 1;
     uint8_t *sums = all ? p->d_scratch + g.codes_bytes : (uint8_t *)p->d_train;
