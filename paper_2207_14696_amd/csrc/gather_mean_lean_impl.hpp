@@ -345,9 +345,9 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
     // A launch of few destinations leaves most of the chip idle and takes as long as its longest
     // chain of dependent row fetches: there the groups of a wave share the lists, until a group's
     // share of the longest list that is to be expected (the caller's bound, else twice the
-    // average) is one step of BF_LEAN_U rows (the mean only: the sums keep one form), up to 2048 waves (8 per CU).  4-bit rows of 64 bytes,
-    // lists of up to 25: 1 024 destinations 9.3 -> 4.8 us (512 waves); 6 200 destinations 8.9 us
-    // unshared, 6.1 with 2048 waves, 7.1 with 4096.
+    // average) is one step of BF_LEAN_U rows (the mean only: the sums keep one form), up to 2048
+    // waves (8 per CU).  4-bit rows of 64 bytes, lists of up to 25: 1 024 destinations 9.3 -> 4.8 us
+    // (512 waves); 6 200 destinations 8.9 us unshared, 6.1 with 2048 waves, 7.1 with 4096.
     const int64_t longest = c.max_degree > 0 ? c.max_degree : 2 * c.E / (V > 0 ? V : 1);
     int s_log2 = 0;
     while (!c.agg_sum && !ODD && (lpr << (s_log2 + 1)) <= 64 && ((int64_t)BF_LEAN_U << s_log2) < longest &&
@@ -369,7 +369,7 @@ bool launch_lean_bits(bifeat_params *p, const MeanCall &c, int thr, int lo, bool
         c.out, ilog2(lpr), s_log2, chunks, thr, lo, alone ? 1 : 0, c.status)
 #define BF_LK(CWV, SUMV, STG, IT)                                                                  \
     do {                                                                                           \
-        if constexpr (ODD) BF_LK1(CWV, SUMV, STG, false, true, IT);                                         \
+        if constexpr (ODD) BF_LK1(CWV, SUMV, STG, false, true, IT);                                \
         else if (!SUMV && s_log2 > 0) BF_LK1(CWV, SUMV, STG, !SUMV, false, IT);                    \
         else BF_LK1(CWV, SUMV, STG, false, false, IT);                                             \
     } while (0)

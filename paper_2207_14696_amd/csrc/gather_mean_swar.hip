@@ -420,8 +420,9 @@ static void launch_swar(bifeat_params *p, const MeanCall &c, int vec, int min_le
     // values a lane at a time, and a narrow row's single lane all of it.  More slots, up to one per entry
     // of the longest list to be expected, give such launches lanes and waves (1472 lists of up to 10 rows
     // of 110 columns, 1 bit 37 -> 8 us, 4 bits 9.2 -> 5.9; of 602, 1 bit 22 -> 11; 46 546 of 131, 1 bit 37 -> 31).
-    // Up to 4 within 4096 waves (46 546 lists of 3 rows, 1 bit: 50 columns 25 -> 17, but 3 columns 9.6 -> 13, of 30 rows 16 -> 13) and up to 8 within 1024: every doubling is one more exchange of all a lane's
-    // sums (1 bit, 50 columns, us with 1, 2, 4, 8, 16, 32 slots: 8000 lists of 10 rows 22.7, 12.8, 9.7, 8.6, 10.4, 16.7; 16 000 23.1,
+    // Up to 4 within 4096 waves (46 546 lists of 3 rows, 1 bit: 50 columns 25 -> 17, but 3 columns 9.6 -> 13, of
+    // 30 rows 16 -> 13) and up to 8 within 1024: every doubling is one more exchange of all a lane's sums (1 bit, 50
+    // columns, us with 1, 2, 4, 8, 16, 32 slots: 8000 lists of 10 rows 22.7, 12.8, 9.7, 8.6, 10.4, 16.7; 16 000 23.1,
     // 13.8, 9.9, 11.7, 16.6, 27.1; 8000 of 30 27.2, 15.1, 11.0, 9.4, 11.3, 18.9).
     // Lists that are long on average are the whole wave's one by one: there fewer to a wave are better (1472 of
     // 100 rows, 2 bits 51 -> 13).

@@ -354,442 +354,442 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
     [[maybe_unused]] int strip = 0;
     [[maybe_unused]] uint8_t *out = codes;
     do {
-    const int64_t begin = sub * a.chunk;
-    const int64_t end = min(TRAIN ? set_rows(set, a.sets, a.strip_log2, a.rows) : a.rows, begin + a.chunk);
-    if constexpr (!TRAIN) out += (begin + threadIdx.x) * a.rb + part * a.pb;
-    next = clamped(begin);
-    float xn[WP];
-    load_row(next, xn);
-    for (int64_t r0 = begin; r0 < end; r0 += ROWS) {
-        // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which the halves of
-        // the wave then hold for both sets of 32 rows
-        const bool valid = (int64_t)threadIdx.x < end - r0;
-        // (a wave without rows has nothing to do, but the workgroup decides together without a copy of
-        // the entries)
-        if (ENT && __builtin_amdgcn_readfirstlane(threadIdx.x) >= end - r0) break;
-        float xr[WP];
+        const int64_t begin = sub * a.chunk;
+        const int64_t end = min(TRAIN ? set_rows(set, a.sets, a.strip_log2, a.rows) : a.rows, begin + a.chunk);
+        if constexpr (!TRAIN) out += (begin + threadIdx.x) * a.rb + part * a.pb;
+        next = clamped(begin);
+        float xn[WP];
+        load_row(next, xn);
+        for (int64_t r0 = begin; r0 < end; r0 += ROWS) {
+            // ---- 64 rows per wave, one per lane: the sub-vector split into pieces, which the halves of
+            // the wave then hold for both sets of 32 rows
+            const bool valid = (int64_t)threadIdx.x < end - r0;
+            // (a wave without rows has nothing to do, but the workgroup decides together without a copy of
+            // the entries)
+            if (ENT && __builtin_amdgcn_readfirstlane(threadIdx.x) >= end - r0) break;
+            float xr[WP];
 #pragma unroll
-        for (int d = 0; d < WP; d++) xr[d] = xn[d];
-        int code = 0;
-        int all_code = 0;
-        float all_value = INFINITY;
-        auto search_all = [&]() {
-            // EP entries at a time, each read by all lanes from one address, the next ones while
-            // these are evaluated (those past the last one are in bounds and not used)
-            constexpr int EP = WP <= 16 ? 4 : 2;
-            float4 q[2][EP][WP / 4];
-            auto read = [&](float4 (&to)[EP][WP / 4], int e0) {
-                const float *src = plain_book(e0 & ~3) + (EP < 4 ? (e0 & 3) * WP : 0);
+            for (int d = 0; d < WP; d++) xr[d] = xn[d];
+            int code = 0;
+            int all_code = 0;
+            float all_value = INFINITY;
+            auto search_all = [&]() {
+                // EP entries at a time, each read by all lanes from one address, the next ones while
+                // these are evaluated (those past the last one are in bounds and not used)
+                constexpr int EP = WP <= 16 ? 4 : 2;
+                float4 q[2][EP][WP / 4];
+                auto read = [&](float4 (&to)[EP][WP / 4], int e0) {
+                    const float *src = plain_book(e0 & ~3) + (EP < 4 ? (e0 & 3) * WP : 0);
 #pragma unroll
-                for (int k = 0; k < EP; k++)
+                    for (int k = 0; k < EP; k++)
 #pragma unroll
-                    for (int i = 0; i < WP / 4; i++) to[k][i] = reinterpret_cast<const float4 *>(src + k * WP)[i];
-            };
-            // (the entries' sums side by side: with two waves a SIMD nothing else hides an addition)
-            auto take = [&](const float4 (&of)[EP][WP / 4], int e0, int n) {
-                float v[EP];
-                [[maybe_unused]] float rn[EP];
+                        for (int i = 0; i < WP / 4; i++) to[k][i] = reinterpret_cast<const float4 *>(src + k * WP)[i];
+                };
+                // (the entries' sums side by side: with two waves a SIMD nothing else hides an addition)
+                auto take = [&](const float4 (&of)[EP][WP / 4], int e0, int n) {
+                    float v[EP];
+                    [[maybe_unused]] float rn[EP];
 #pragma unroll
-                for (int k = 0; k < EP; k++) v[k] = 0.0f;
-                if constexpr (COS) {
-                    const float *src = ENT ? norm_at(e0) : part_rn + e0;
+                    for (int k = 0; k < EP; k++) v[k] = 0.0f;
+                    if constexpr (COS) {
+                        const float *src = ENT ? norm_at(e0) : part_rn + e0;
 #pragma unroll
-                    for (int k = 0; k < EP; k++) rn[k] = src[ENT || k < n ? k : 0];
-                }
+                        for (int k = 0; k < EP; k++) rn[k] = src[ENT || k < n ? k : 0];
+                    }
 #pragma unroll
-                for (int i = 0; i < WP / 4; i++)
+                    for (int i = 0; i < WP / 4; i++)
+#pragma unroll
+                        for (int k = 0; k < EP; k++) {
+                            v[k] = rule_step<METRIC>(v[k], xr[4 * i], of[k][i].x);
+                            v[k] = rule_step<METRIC>(v[k], xr[4 * i + 1], of[k][i].y);
+                            v[k] = rule_step<METRIC>(v[k], xr[4 * i + 2], of[k][i].z);
+                            v[k] = rule_step<METRIC>(v[k], xr[4 * i + 3], of[k][i].w);
+                        }
 #pragma unroll
                     for (int k = 0; k < EP; k++) {
-                        v[k] = rule_step<METRIC>(v[k], xr[4 * i], of[k][i].x);
-                        v[k] = rule_step<METRIC>(v[k], xr[4 * i + 1], of[k][i].y);
-                        v[k] = rule_step<METRIC>(v[k], xr[4 * i + 2], of[k][i].z);
-                        v[k] = rule_step<METRIC>(v[k], xr[4 * i + 3], of[k][i].w);
+                        if (k >= n) break;
+                        if constexpr (COS) v[k] = -__fmul_rn(v[k], rn[k]);
+                        if (v[k] < all_value) { all_value = v[k]; all_code = e0 + k; }
                     }
-#pragma unroll
-                for (int k = 0; k < EP; k++) {
-                    if (k >= n) break;
-                    if constexpr (COS) v[k] = -__fmul_rn(v[k], rn[k]);
-                    if (v[k] < all_value) { all_value = v[k]; all_code = e0 + k; }
+                };
+                const int last = a.NT * 32 - EP;
+                int e0 = 0;
+                read(q[0], 0);
+                for (; e0 + 2 * EP <= len; e0 += 2 * EP) {
+                    read(q[1], e0 + EP);
+                    take(q[0], e0, EP);
+                    read(q[0], min(e0 + 2 * EP, last));
+                    take(q[1], e0 + EP, EP);
+                }
+                if (e0 < len) take(q[0], e0, len - e0);
+                if (e0 + EP < len) {
+                    read(q[1], e0 + EP);
+                    take(q[1], e0 + EP, len - e0 - EP);
                 }
             };
-            const int last = a.NT * 32 - EP;
-            int e0 = 0;
-            read(q[0], 0);
-            for (; e0 + 2 * EP <= len; e0 += 2 * EP) {
-                read(q[1], e0 + EP);
-                take(q[0], e0, EP);
-                read(q[0], min(e0 + 2 * EP, last));
-                take(q[1], e0 + EP, EP);
+            if (plain || plain_left > 0) {
+                plain_left--;
+                load_next(r0, xn);
+                search_all();
+                code = all_code;
+            } else {
+            float f = scale;
+            bool bad = part_bad, zero = false;
+            if constexpr (COS) {  // the best entry does not depend on the row's length
+                float m = 0.0f;
+#pragma unroll
+                for (int d = 0; d < WP; d++) m = fmaxf(m, fabsf(xr[d]));
+                int e = 0;
+                frexpf(m, &e);
+                zero = m == 0.0f;
+                bad |= !zero && !(m >= 0x1p-50f && m <= 0x1p50f);
+                f = zero || bad ? 1.0f : ldexpf(1.0f, kScaleExp - e);
             }
-            if (e0 < len) take(q[0], e0, len - e0);
-            if (e0 + EP < len) {
-                read(q[1], e0 + EP);
-                take(q[1], e0 + EP, len - e0 - EP);
+            float s2 = 0.0f;
+            // products with the high pieces of the entries: the lower lanes multiply them with the row's high
+            // pieces, the upper ones with its low pieces; with their low pieces: two groups of columns side by
+            // side, of an odd last group beside |c|^2/2 (or the low pieces once more)
+            half8 xh[2][G], xl[2][LO];
+            {
+                uint32_t hi[4 * G], lo[4 * G];
+#pragma unroll
+                for (int j = 0; j < 4 * G; j++) {
+                    const float u = xr[2 * j] * f, v = xr[2 * j + 1] * f;
+                    const auto h = __builtin_amdgcn_cvt_pkrtz(u, v);
+                    hi[j] = __builtin_bit_cast(uint32_t, h);
+                    // |x|^2 from the high pieces, short of it by less than 2^-9 of itself (vq_margin)
+                    s2 = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, h), __builtin_bit_cast(half2v, h), s2, false);
+                    lo[j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(less_low(u, hi[j]), less_high(v, hi[j])));
+                }
+                // one exchange of halves of two registers: [rows 0..31 of both], [rows 32..63 of both]
+                auto both = [&](half8 (&x0), half8 (&x1), const uint32_t *p, const uint32_t *q) {
+                    uint32_t set[2][4];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        const auto e = __builtin_amdgcn_permlane32_swap(p[j], q[j], false, false);
+                        set[0][j] = e[0];
+                        set[1][j] = e[1];
+                    }
+                    __builtin_memcpy(&x0, set[0], 16);
+                    __builtin_memcpy(&x1, set[1], 16);
+                };
+#pragma unroll
+                for (int g = 0; g + 1 < G; g += 2) both(xl[0][g / 2], xl[1][g / 2], hi + 4 * g, hi + 4 * g + 4);
+#pragma unroll
+                for (int g = 0; g < G; g++) both(xh[0][g], xh[1][g], hi + 4 * g, lo + 4 * g);
+                if constexpr (G % 2 == 1) {
+#pragma unroll
+                    for (int s = 0; s < 2; s++) {
+                        xl[s][LO - 1] = xh[s][G - 1];
+                        if constexpr (NORM)
+                            if (half) xl[s][LO - 1] = norm_units;
+                    }
+                }
             }
-        };
-        if (plain || plain_left > 0) {
-            plain_left--;
+            bad |= !(s2 < kMaxNorm2);  // also NaN
+            const float big = COS ? sqrtf(s2) * 1024.5f : s2 + c2max;
+            const float margin = bad ? INFINITY : big * a.margin;
+            // (the cosine cell's scores are in units of |x|, unscaled)
+            const float cell_margin = COS ? sqrtf(s2) * a.cell_margin / f : big * unscale * a.cell_margin;
+            if constexpr (COS) zero = zero && s2 == 0.0f && !part_bad;  // not a NaN that fmaxf passed over
+            // the next strip's rows travel during this strip's search
             load_next(r0, xn);
-            search_all();
-            code = all_code;
-        } else {
-        float f = scale;
-        bool bad = part_bad, zero = false;
-        if constexpr (COS) {  // the best entry does not depend on the row's length
-            float m = 0.0f;
+            float best[2] = {3e38f, 3e38f}, second[2] = {3e38f, 3e38f};
+            {
+                const int nt = a.NT;
+                // A set's minima are taken while the matrix cores work on the other set: the next tile's
+                // product is started as soon as its accumulators are free, its operands having been
+                // read from LDS one half-step earlier.
+                half8 eh[G], el[LO];
+                float16v c;
+                auto fetch = [&](int t) {
+                    const half8 *tile = s_frag + t * UNITS;
+                    if constexpr (!NORM) {
 #pragma unroll
-            for (int d = 0; d < WP; d++) m = fmaxf(m, fabsf(xr[d]));
-            int e = 0;
-            frexpf(m, &e);
-            zero = m == 0.0f;
-            bad |= !zero && !(m >= 0x1p-50f && m <= 0x1p50f);
-            f = zero || bad ? 1.0f : ldexpf(1.0f, kScaleExp - e);
-        }
-        float s2 = 0.0f;
-        // products with the high pieces of the entries: the lower lanes multiply them with the row's high
-        // pieces, the upper ones with its low pieces; with their low pieces: two groups of columns side by
-        // side, of an odd last group beside |c|^2/2 (or the low pieces once more)
-        half8 xh[2][G], xl[2][LO];
-        {
-            uint32_t hi[4 * G], lo[4 * G];
-#pragma unroll
-            for (int j = 0; j < 4 * G; j++) {
-                const float u = xr[2 * j] * f, v = xr[2 * j + 1] * f;
-                const auto h = __builtin_amdgcn_cvt_pkrtz(u, v);
-                hi[j] = __builtin_bit_cast(uint32_t, h);
-                // |x|^2 from the high pieces, short of it by less than 2^-9 of itself (vq_margin)
-                s2 = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, h), __builtin_bit_cast(half2v, h), s2, false);
-                lo[j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(less_low(u, hi[j]), less_high(v, hi[j])));
-            }
-            // one exchange of halves of two registers: [rows 0..31 of both], [rows 32..63 of both]
-            auto both = [&](half8 (&x0), half8 (&x1), const uint32_t *p, const uint32_t *q) {
-                uint32_t set[2][4];
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const auto e = __builtin_amdgcn_permlane32_swap(p[j], q[j], false, false);
-                    set[0][j] = e[0];
-                    set[1][j] = e[1];
-                }
-                __builtin_memcpy(&x0, set[0], 16);
-                __builtin_memcpy(&x1, set[1], 16);
-            };
-#pragma unroll
-            for (int g = 0; g + 1 < G; g += 2) both(xl[0][g / 2], xl[1][g / 2], hi + 4 * g, hi + 4 * g + 4);
-#pragma unroll
-            for (int g = 0; g < G; g++) both(xh[0][g], xh[1][g], hi + 4 * g, lo + 4 * g);
-            if constexpr (G % 2 == 1) {
-#pragma unroll
-                for (int s = 0; s < 2; s++) {
-                    xl[s][LO - 1] = xh[s][G - 1];
-                    if constexpr (NORM)
-                        if (half) xl[s][LO - 1] = norm_units;
-                }
-            }
-        }
-        bad |= !(s2 < kMaxNorm2);  // also NaN
-        const float big = COS ? sqrtf(s2) * 1024.5f : s2 + c2max;
-        const float margin = bad ? INFINITY : big * a.margin;
-        // (the cosine cell's scores are in units of |x|, unscaled)
-        const float cell_margin = COS ? sqrtf(s2) * a.cell_margin / f : big * unscale * a.cell_margin;
-        if constexpr (COS) zero = zero && s2 == 0.0f && !part_bad;  // not a NaN that fmaxf passed over
-        // the next strip's rows travel during this strip's search
-        load_next(r0, xn);
-        float best[2] = {3e38f, 3e38f}, second[2] = {3e38f, 3e38f};
-        {
-            const int nt = a.NT;
-            // A set's minima are taken while the matrix cores work on the other set: the next tile's
-            // product is started as soon as its accumulators are free, its operands having been
-            // read from LDS one half-step earlier.
-            half8 eh[G], el[LO];
-            float16v c;
-            auto fetch = [&](int t) {
-                const half8 *tile = s_frag + t * UNITS;
-                if constexpr (!NORM) {
-#pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        const float4 n = *reinterpret_cast<const float4 *>(s_half + t * 32 + 8 * q + 4 * half);
-                        c[4 * q] = n.x; c[4 * q + 1] = n.y; c[4 * q + 2] = n.z; c[4 * q + 3] = n.w;
+                        for (int q = 0; q < 4; q++) {
+                            const float4 n = *reinterpret_cast<const float4 *>(s_half + t * 32 + 8 * q + 4 * half);
+                            c[4 * q] = n.x; c[4 * q + 1] = n.y; c[4 * q + 2] = n.z; c[4 * q + 3] = n.w;
+                        }
                     }
-                }
 #pragma unroll
-                for (int g = 0; g < G; g++) eh[g] = tile[32 * g + (lane & 31)];
+                    for (int g = 0; g < G; g++) eh[g] = tile[32 * g + (lane & 31)];
 #pragma unroll
-                for (int g = 0; g < G / 2; g++) el[g] = tile[32 * G + 64 * g + lane];
-                if constexpr (NORM) {
-                    // (the upper lanes: their entry's 8 bytes and the 8 after them, which meet zeros)
-                    const uint2 *p = reinterpret_cast<const uint2 *>(tile + 32 * (2 * G - 1)) + last_piece;
-                    const uint2 v0 = p[0], v1 = p[1];
-                    const uint4 v = make_uint4(v0.x, v0.y, v1.x, v1.y);
-                    __builtin_memcpy(&el[LO - 1], &v, 16);
-                } else if constexpr (G % 2 == 1) {
-                    el[LO - 1] = tile[32 * (2 * G - 1) + (lane & 31)];
-                }
-            };
-            float16v acc[2];
-            auto product = [&](int s) {
-                if constexpr (NORM) {
+                    for (int g = 0; g < G / 2; g++) el[g] = tile[32 * G + 64 * g + lane];
+                    if constexpr (NORM) {
+                        // (the upper lanes: their entry's 8 bytes and the 8 after them, which meet zeros)
+                        const uint2 *p = reinterpret_cast<const uint2 *>(tile + 32 * (2 * G - 1)) + last_piece;
+                        const uint2 v0 = p[0], v1 = p[1];
+                        const uint4 v = make_uint4(v0.x, v0.y, v1.x, v1.y);
+                        __builtin_memcpy(&el[LO - 1], &v, 16);
+                    } else if constexpr (G % 2 == 1) {
+                        el[LO - 1] = tile[32 * (2 * G - 1) + (lane & 31)];
+                    }
+                };
+                float16v acc[2];
+                auto product = [&](int s) {
+                    if constexpr (NORM) {
 #pragma unroll
-                    for (int i = 0; i < 16; i++) acc[s][i] = 0.0f;
-                } else {
-                    acc[s] = c;
-                }
+                        for (int i = 0; i < 16; i++) acc[s][i] = 0.0f;
+                    } else {
+                        acc[s] = c;
+                    }
 #pragma unroll
-                for (int g = 0; g < G; g++)
-                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(eh[g], xh[s][g], acc[s], 0, 0, 0);
+                    for (int g = 0; g < G; g++)
+                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(eh[g], xh[s][g], acc[s], 0, 0, 0);
 #pragma unroll
-                for (int g = 0; g < LO; g++)
-                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(el[g], xl[s][g], acc[s], 0, 0, 0);
-            };
-            // (the runner-up of a tile's two keys waits for the next tile's: one instruction for both; with
-            // more columns the registers are missed elsewhere)
-            constexpr bool PAIRED = G == 1;
-            float runner[2] = {3e38f, 3e38f};
-            auto minima = [&](int s, int t, auto odd) {
-                float key[2];
+                    for (int g = 0; g < LO; g++)
+                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_f16(el[g], xl[s][g], acc[s], 0, 0, 0);
+                };
+                // (the runner-up of a tile's two keys waits for the next tile's: one instruction for both; with
+                // more columns the registers are missed elsewhere)
+                constexpr bool PAIRED = G == 1;
+                float runner[2] = {3e38f, 3e38f};
+                auto minima = [&](int s, int t, auto odd) {
+                    float key[2];
 #pragma unroll
-                for (int q = 0; q < 2; q++) {
-                    uint32_t number = (uint32_t)(2 * t + q);
-                    asm volatile("" : "+s"(number));  // one scalar: the compiler would add it up per lane
-                    float m = acc[s][8 * q];
+                    for (int q = 0; q < 2; q++) {
+                        uint32_t number = (uint32_t)(2 * t + q);
+                        asm volatile("" : "+s"(number));  // one scalar: the compiler would add it up per lane
+                        float m = acc[s][8 * q];
 #pragma unroll
-                    for (int i = 1; i < 7; i += 2) m = minimum(minimum(m, acc[s][8 * q + i]), acc[s][8 * q + i + 1]);
-                    m = minimum(m, acc[s][8 * q + 7]);
-                    // the cell's number replaces the low bits of its score
-                    key[q] = __uint_as_float((__float_as_uint(m) & keep) | number);
-                }
-                const float r = __builtin_amdgcn_fmed3f(best[s], key[0], key[1]);
-                if constexpr (!PAIRED) second[s] = minimum(second[s], r);
-                else if constexpr (odd.value) second[s] = minimum(minimum(second[s], runner[s]), r);
-                else runner[s] = r;
-                best[s] = minimum(minimum(best[s], key[0]), key[1]);
-            };
-            fetch(0);
-            product(0);
-            product(1);
-            if constexpr (!NORM) asm volatile("" : : "v"(c));
-            fetch(min(1, nt - 1));
-            auto tile = [&](int t, auto odd) {
-                // (c outlives both products of a step: one of them would otherwise take over its
-                // registers, and 32 copies would put things back in place)
-                __builtin_amdgcn_sched_barrier(0);
-                minima(0, t, odd);
-                __builtin_amdgcn_sched_barrier(0);
+                        for (int i = 1; i < 7; i += 2) m = minimum(minimum(m, acc[s][8 * q + i]), acc[s][8 * q + i + 1]);
+                        m = minimum(m, acc[s][8 * q + 7]);
+                        // the cell's number replaces the low bits of its score
+                        key[q] = __uint_as_float((__float_as_uint(m) & keep) | number);
+                    }
+                    const float r = __builtin_amdgcn_fmed3f(best[s], key[0], key[1]);
+                    if constexpr (!PAIRED) second[s] = minimum(second[s], r);
+                    else if constexpr (odd.value) second[s] = minimum(minimum(second[s], runner[s]), r);
+                    else runner[s] = r;
+                    best[s] = minimum(minimum(best[s], key[0]), key[1]);
+                };
+                fetch(0);
                 product(0);
-                minima(1, t, odd);
-                __builtin_amdgcn_sched_barrier(0);
                 product(1);
                 if constexpr (!NORM) asm volatile("" : : "v"(c));
-                fetch(min(t + 2, nt - 1));
-            };
-            int t = 0;
-            if constexpr (!PAIRED)
-                for (; t + 1 < nt; t++) tile(t, std::false_type());
-            for (; PAIRED && t + 2 < nt; t += 2) {
-                tile(t, std::false_type());
-                tile(t + 1, std::true_type());
-            }
-            if (PAIRED && t + 1 < nt) {
-                tile(t, std::false_type());
-                t++;
-                __builtin_amdgcn_sched_barrier(0);
-                minima(0, t, std::true_type());
-                minima(1, t, std::true_type());
-            } else {
-                __builtin_amdgcn_sched_barrier(0);
-                minima(0, t, std::false_type());
-                minima(1, t, std::false_type());
+                fetch(min(1, nt - 1));
+                auto tile = [&](int t, auto odd) {
+                    // (c outlives both products of a step: one of them would otherwise take over its
+                    // registers, and 32 copies would put things back in place)
+                    __builtin_amdgcn_sched_barrier(0);
+                    minima(0, t, odd);
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(0);
+                    minima(1, t, odd);
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(1);
+                    if constexpr (!NORM) asm volatile("" : : "v"(c));
+                    fetch(min(t + 2, nt - 1));
+                };
+                int t = 0;
+                if constexpr (!PAIRED)
+                    for (; t + 1 < nt; t++) tile(t, std::false_type());
+                for (; PAIRED && t + 2 < nt; t += 2) {
+                    tile(t, std::false_type());
+                    tile(t + 1, std::true_type());
+                }
+                if (PAIRED && t + 1 < nt) {
+                    tile(t, std::false_type());
+                    t++;
+                    __builtin_amdgcn_sched_barrier(0);
+                    minima(0, t, std::true_type());
+                    minima(1, t, std::true_type());
+                } else {
+                    __builtin_amdgcn_sched_barrier(0);
+                    minima(0, t, std::false_type());
+                    minima(1, t, std::false_type());
 #pragma unroll
-                for (int s = 0; s < 2; s++) second[s] = PAIRED ? minimum(second[s], runner[s]) : second[s];
+                    for (int s = 0; s < 2; s++) second[s] = PAIRED ? minimum(second[s], runner[s]) : second[s];
+                }
             }
-        }
-        // ---- the two halves of the wave hold different cells of the same rows; one exchange gives lane
-        // half h both cells of the rows of set h, which it then decides
-        float b, gap;
-        int h_of;
-        {
-            const auto eb = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[0]), __float_as_uint(best[1]),
-                                                             false, false);
-            const auto es = __builtin_amdgcn_permlane32_swap(__float_as_uint(second[0]), __float_as_uint(second[1]),
-                                                             false, false);
-            const float b0 = __uint_as_float(eb[0]), b1 = __uint_as_float(eb[1]);
-            b = minimum(b0, b1);
-            gap = minimum(minimum(__builtin_elementwise_maximum(b0, b1), __uint_as_float(es[0])),
-                          __uint_as_float(es[1])) - b;
-            h_of = b0 <= b1 ? 0 : 1;
-        }
-        const uint32_t cell = __float_as_uint(b) & a.cell_mask;
-        bool open = !(gap > margin);  // the rule has to look at all entries
-        // ---- the cell's 8 entries in fp32, again with the second best; rows too close to call join
-        // the open ones
-        {
-            // the cell's entries are those from 16 * its number + 4h on, 4 of them and 4 from 8 further on
-            const uint32_t c0 = open ? 0u : cell, h4 = open ? 0u : 4u * (uint32_t)h_of, e0 = c0 * 16u + h4;
-            const float *near_ent = s_ent + __umul24(c0, GROUPS4) + __umul24(h4, GROUP / 4);
-            float4 near_norm[2];
-            if constexpr (ENT) {
-                near_norm[0] = *reinterpret_cast<const float4 *>(near_ent + 4 * WP);
-                near_norm[1] = *reinterpret_cast<const float4 *>(near_ent + 2 * GROUP + 4 * WP);
+            // ---- the two halves of the wave hold different cells of the same rows; one exchange gives lane
+            // half h both cells of the rows of set h, which it then decides
+            float b, gap;
+            int h_of;
+            {
+                const auto eb = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[0]), __float_as_uint(best[1]),
+                                                                 false, false);
+                const auto es = __builtin_amdgcn_permlane32_swap(__float_as_uint(second[0]), __float_as_uint(second[1]),
+                                                                 false, false);
+                const float b0 = __uint_as_float(eb[0]), b1 = __uint_as_float(eb[1]);
+                b = minimum(b0, b1);
+                gap = minimum(minimum(__builtin_elementwise_maximum(b0, b1), __uint_as_float(es[0])),
+                              __uint_as_float(es[1])) - b;
+                h_of = b0 <= b1 ? 0 : 1;
             }
-            float b1 = 3e38f, b2 = 3e38f, key[2];
-#pragma unroll
-            for (int k = 0; k < 8; k++) {
-                const int e = (int)e0 + (k & 3) + 8 * (k >> 2);
-                [[maybe_unused]] const float4 nn = near_norm[k >> 2];
-                [[maybe_unused]] const float norm = (k & 3) == 0 ? nn.x : (k & 3) == 1 ? nn.y : (k & 3) == 2 ? nn.z : nn.w;
-                float c[WP], rn, sc = 0.0f;
+            const uint32_t cell = __float_as_uint(b) & a.cell_mask;
+            bool open = !(gap > margin);  // the rule has to look at all entries
+            // ---- the cell's 8 entries in fp32, again with the second best; rows too close to call join
+            // the open ones
+            {
+                // the cell's entries are those from 16 * its number + 4h on, 4 of them and 4 from 8 further on
+                const uint32_t c0 = open ? 0u : cell, h4 = open ? 0u : 4u * (uint32_t)h_of, e0 = c0 * 16u + h4;
+                const float *near_ent = s_ent + __umul24(c0, GROUPS4) + __umul24(h4, GROUP / 4);
+                float4 near_norm[2];
                 if constexpr (ENT) {
-                    const float4 *src = reinterpret_cast<const float4 *>(near_ent + (k >> 2) * 2 * GROUP + (k & 3) * WP);
+                    near_norm[0] = *reinterpret_cast<const float4 *>(near_ent + 4 * WP);
+                    near_norm[1] = *reinterpret_cast<const float4 *>(near_ent + 2 * GROUP + 4 * WP);
+                }
+                float b1 = 3e38f, b2 = 3e38f, key[2];
 #pragma unroll
-                    for (int i = 0; i < WP / 4; i++) {
-                        const float4 v = src[i];
-                        c[4 * i] = v.x; c[4 * i + 1] = v.y; c[4 * i + 2] = v.z; c[4 * i + 3] = v.w;
+                for (int k = 0; k < 8; k++) {
+                    const int e = (int)e0 + (k & 3) + 8 * (k >> 2);
+                    [[maybe_unused]] const float4 nn = near_norm[k >> 2];
+                    [[maybe_unused]] const float norm = (k & 3) == 0 ? nn.x : (k & 3) == 1 ? nn.y : (k & 3) == 2 ? nn.z : nn.w;
+                    float c[WP], rn, sc = 0.0f;
+                    if constexpr (ENT) {
+                        const float4 *src = reinterpret_cast<const float4 *>(near_ent + (k >> 2) * 2 * GROUP + (k & 3) * WP);
+#pragma unroll
+                        for (int i = 0; i < WP / 4; i++) {
+                            const float4 v = src[i];
+                            c[4 * i] = v.x; c[4 * i + 1] = v.y; c[4 * i + 2] = v.z; c[4 * i + 3] = v.w;
+                        }
+                        rn = norm;
+                    } else {
+                        entry(min(e, len - 1), c, rn);
                     }
-                    rn = norm;
-                } else {
-                    entry(min(e, len - 1), c, rn);
+                    if constexpr (COS) {
+#pragma unroll
+                        for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
+                        sc *= rn;
+                    } else if constexpr (ENT) {
+                        sc = norm;
+#pragma unroll
+                        for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
+                    } else {
+#pragma unroll
+                        for (int d = 0; d < WP; d++) sc = fmaf(c[d], fmaf(0.5f, c[d], -xr[d]), sc);
+                    }
+                    if ((!ENT || COS) && e >= len) sc = 3e38f;
+                    key[k & 1] = __uint_as_float((__float_as_uint(sc) & ~7u) | (uint32_t)k);
+                    if (k & 1) {
+                        b2 = minimum(b2, __builtin_amdgcn_fmed3f(b1, key[0], key[1]));
+                        b1 = minimum(minimum(b1, key[0]), key[1]);
+                    }
                 }
-                if constexpr (COS) {
-#pragma unroll
-                    for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
-                    sc *= rn;
-                } else if constexpr (ENT) {
-                    sc = norm;
-#pragma unroll
-                    for (int d = 0; d < WP; d++) sc = fmaf(-xr[d], c[d], sc);
-                } else {
-#pragma unroll
-                    for (int d = 0; d < WP; d++) sc = fmaf(c[d], fmaf(0.5f, c[d], -xr[d]), sc);
-                }
-                if ((!ENT || COS) && e >= len) sc = 3e38f;
-                key[k & 1] = __uint_as_float((__float_as_uint(sc) & ~7u) | (uint32_t)k);
-                if (k & 1) {
-                    b2 = minimum(b2, __builtin_amdgcn_fmed3f(b1, key[0], key[1]));
-                    b1 = minimum(minimum(b1, key[0]), key[1]);
+                const int k = (int)(__float_as_uint(b1) & 7u);
+                open |= !(b2 - b1 > cell_margin);
+                code = (int)e0 + (k & 3) + 8 * (k >> 2);
+            }
+            if (COS && zero) {  // all scores are zero: the first entry
+                open = false;
+                code = 0;
+            }
+            uint64_t todo = __ballot(open && valid);
+            if constexpr (ENT) {
+                if (__popcll(todo) > a.plain_rows) plain_left = kPlainStrips;
+            } else {
+                // (strips 0, 1 and 3, then every eighth)
+                const bool look = strip < 4 ? strip != 2 : (strip & 7) == 7;
+                strip++;
+                if (look && __syncthreads_count(open && valid) > a.plain_rows * WAVES) {
+                    plain = true;  // (the barrier: no wave reads the pieces any more)
+                    float *dst = reinterpret_cast<float *>(s_frag);
+                    for (int i = threadIdx.x; i < len * WP; i += TH) {
+                        const int e = i / WP, d = i - e * WP;
+                        dst[i] = d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
+                    }
+                    __syncthreads();
                 }
             }
-            const int k = (int)(__float_as_uint(b1) & 7u);
-            open |= !(b2 - b1 > cell_margin);
-            code = (int)e0 + (k & 3) + 8 * (k >> 2);
-        }
-        if (COS && zero) {  // all scores are zero: the first entry
-            open = false;
-            code = 0;
-        }
-        uint64_t todo = __ballot(open && valid);
-        if constexpr (ENT) {
-            if (__popcll(todo) > a.plain_rows) plain_left = kPlainStrips;
-        } else {
-            // (strips 0, 1 and 3, then every eighth)
-            const bool look = strip < 4 ? strip != 2 : (strip & 7) == 7;
-            strip++;
-            if (look && __syncthreads_count(open && valid) > a.plain_rows * WAVES) {
-                plain = true;  // (the barrier: no wave reads the pieces any more)
-                float *dst = reinterpret_cast<float *>(s_frag);
-                for (int i = threadIdx.x; i < len * WP; i += TH) {
-                    const int e = i / WP, d = i - e * WP;
-                    dst[i] = d < w ? part_cb[(int64_t)e * w + d] : 0.0f;
+            if (todo) {
+                if ((ENT || plain) && __popcll(todo) >= a.lane_rows) {
+                    search_all();
+                    if (open) code = all_code;
+                } else {
+                    // two rows at a time, which halves the fetches of entries and has two reductions side by
+                    // side, where there are registers for it (8 columns, entries in LDS, 4 waves a SIMD: the
+                    // scores would lose 3 %)
+                    constexpr int NR = WP == 16 || (WP == 8 && !ENT) ? 2 : 1;
+                    while (todo) {
+                        int j[NR];
+                        float xj[NR][WP], bv[NR];
+                        int bc[NR];
+#pragma unroll
+                        for (int n = 0; n < NR; n++) {
+                            j[n] = todo ? __ffsll((unsigned long long)todo) - 1 : j[0];
+                            todo &= todo - 1;
+#pragma unroll
+                            for (int d = 0; d < WP; d++)
+                                xj[n][d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xr[d]), j[n]));
+                            bv[n] = INFINITY;
+                            bc[n] = 0x7FFFFFFF;
+                        }
+                        for (int e = lane; e < len; e += 64) {
+                            float c[WP], rn;
+                            entry(e, c, rn);
+#pragma unroll
+                            for (int n = 0; n < NR; n++) {
+                                const float v = rule_value<WP, METRIC>(xj[n], c, rn);
+                                if (v < bv[n]) { bv[n] = v; bc[n] = e; }
+                            }
+                        }
+#pragma unroll
+                        for (int n = 0; n < NR; n++) {
+#pragma unroll
+                            for (int o = 32; o > 0; o >>= 1) {
+                                const float ov = __shfl_xor(bv[n], o);
+                                const int oc = __shfl_xor(bc[n], o);
+                                if (ov < bv[n] || (ov == bv[n] && oc < bc[n])) { bv[n] = ov; bc[n] = oc; }
+                            }
+                            if (lane == j[n]) code = bc[n] == 0x7FFFFFFF ? 0 : bc[n];
+                        }
+                    }
                 }
+            }
+            }  // !plain
+            if constexpr (TRAIN) {
+                if (valid) {
+                    float c[WP], rn;
+                    entry(code, c, rn);
+                    dsum += rule_value<WP, BIFEAT_VQ_L2>(xr, c, rn);
+#pragma unroll
+                    for (int d = 0; d < WP; d++)
+                        if (d < w) unsafeAtomicAdd(&s_sum[d * len + code], (double)xr[d]);
+                    atomicAdd(&s_cnt[code], 1u);
+                }
+            } else {
+                // the next rows have arrived by now; waiting for them here keeps that wait from covering
+                // the stores below (loads and stores of a wave complete in one order)
+#pragma unroll
+                for (int d = 0; d < WP; d++) asm volatile("" : "+v"(xn[d]));
+                if (valid) {
+                    if (a.cbytes == 1) *out = (uint8_t)code;
+                    else *reinterpret_cast<uint16_t *>(out) = (uint16_t)code;
+                    if (part == 0)
+                        for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) out[k] = 0;  // padding
+                }
+                out += ROWS * a.rb;
+            }
+        }
+        if constexpr (TRAIN) {
+            const int this_set = set;
+            set += a.sub > 1 ? a.sets : a.ny;
+            if (a.one_set && set < a.sets) continue;  // (all sets' sums together)
+            __syncthreads();
+            const int64_t to = (a.one_set ? 0 : ((int64_t)this_set * a.sub + sub) * a.P) + part;
+            float *sums = static_cast<float *>(a.sums) + to * len * w;
+            uint32_t *counts = a.counts + to * len;
+            if (a.one_set) {
+                for (int i = threadIdx.x; i < len * w; i += TH)
+                    if (s_sum[i] != 0.0) unsafeAtomicAdd(&sums[i], (float)s_sum[i]);
+                for (int i = threadIdx.x; i < len; i += TH)
+                    if (s_cnt[i]) atomicAdd(&counts[i], s_cnt[i]);
+            } else {
+                if (a.sub > 1) {
+                    double *wide = static_cast<double *>(a.sums) + to * len * w;
+                    for (int i = threadIdx.x; i < len * w; i += TH) wide[i] = s_sum[i];
+                } else {
+                    for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
+                }
+                for (int i = threadIdx.x; i < len; i += TH) counts[i] = s_cnt[i];
+            }
+            if (set < a.sets) {  // (the same thread's as read above)
+                for (int i = threadIdx.x; i < len * w; i += TH) s_sum[i] = 0.0;
+                for (int i = threadIdx.x; i < len; i += TH) s_cnt[i] = 0u;
                 __syncthreads();
             }
         }
-        if (todo) {
-            if ((ENT || plain) && __popcll(todo) >= a.lane_rows) {
-                search_all();
-                if (open) code = all_code;
-            } else {
-                // two rows at a time, which halves the fetches of entries and has two reductions side by
-                // side, where there are registers for it (8 columns, entries in LDS, 4 waves a SIMD: the
-                // scores would lose 3 %)
-                constexpr int NR = WP == 16 || (WP == 8 && !ENT) ? 2 : 1;
-                while (todo) {
-                    int j[NR];
-                    float xj[NR][WP], bv[NR];
-                    int bc[NR];
-#pragma unroll
-                    for (int n = 0; n < NR; n++) {
-                        j[n] = todo ? __ffsll((unsigned long long)todo) - 1 : j[0];
-                        todo &= todo - 1;
-#pragma unroll
-                        for (int d = 0; d < WP; d++)
-                            xj[n][d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xr[d]), j[n]));
-                        bv[n] = INFINITY;
-                        bc[n] = 0x7FFFFFFF;
-                    }
-                    for (int e = lane; e < len; e += 64) {
-                        float c[WP], rn;
-                        entry(e, c, rn);
-#pragma unroll
-                        for (int n = 0; n < NR; n++) {
-                            const float v = rule_value<WP, METRIC>(xj[n], c, rn);
-                            if (v < bv[n]) { bv[n] = v; bc[n] = e; }
-                        }
-                    }
-#pragma unroll
-                    for (int n = 0; n < NR; n++) {
-#pragma unroll
-                        for (int o = 32; o > 0; o >>= 1) {
-                            const float ov = __shfl_xor(bv[n], o);
-                            const int oc = __shfl_xor(bc[n], o);
-                            if (ov < bv[n] || (ov == bv[n] && oc < bc[n])) { bv[n] = ov; bc[n] = oc; }
-                        }
-                        if (lane == j[n]) code = bc[n] == 0x7FFFFFFF ? 0 : bc[n];
-                    }
-                }
-            }
-        }
-        }  // !plain
-        if constexpr (TRAIN) {
-            if (valid) {
-                float c[WP], rn;
-                entry(code, c, rn);
-                dsum += rule_value<WP, BIFEAT_VQ_L2>(xr, c, rn);
-#pragma unroll
-                for (int d = 0; d < WP; d++)
-                    if (d < w) unsafeAtomicAdd(&s_sum[d * len + code], (double)xr[d]);
-                atomicAdd(&s_cnt[code], 1u);
-            }
-        } else {
-            // the next rows have arrived by now; waiting for them here keeps that wait from covering
-            // the stores below (loads and stores of a wave complete in one order)
-#pragma unroll
-            for (int d = 0; d < WP; d++) asm volatile("" : "+v"(xn[d]));
-            if (valid) {
-                if (a.cbytes == 1) *out = (uint8_t)code;
-                else *reinterpret_cast<uint16_t *>(out) = (uint16_t)code;
-                if (part == 0)
-                    for (int64_t k = (int64_t)a.P * a.cbytes; k < a.rb; k++) out[k] = 0;  // padding
-            }
-            out += ROWS * a.rb;
-        }
-    }
-    if constexpr (TRAIN) {
-        const int this_set = set;
-        set += a.sub > 1 ? a.sets : a.ny;
-        if (a.one_set && set < a.sets) continue;  // (all sets' sums together)
-        __syncthreads();
-        const int64_t to = (a.one_set ? 0 : ((int64_t)this_set * a.sub + sub) * a.P) + part;
-        float *sums = static_cast<float *>(a.sums) + to * len * w;
-        uint32_t *counts = a.counts + to * len;
-        if (a.one_set) {
-            for (int i = threadIdx.x; i < len * w; i += TH)
-                if (s_sum[i] != 0.0) unsafeAtomicAdd(&sums[i], (float)s_sum[i]);
-            for (int i = threadIdx.x; i < len; i += TH)
-                if (s_cnt[i]) atomicAdd(&counts[i], s_cnt[i]);
-        } else {
-            if (a.sub > 1) {
-                double *wide = static_cast<double *>(a.sums) + to * len * w;
-                for (int i = threadIdx.x; i < len * w; i += TH) wide[i] = s_sum[i];
-            } else {
-                for (int i = threadIdx.x; i < len * w; i += TH) sums[i] = (float)s_sum[i];
-            }
-            for (int i = threadIdx.x; i < len; i += TH) counts[i] = s_cnt[i];
-        }
-        if (set < a.sets) {  // (the same thread's as read above)
-            for (int i = threadIdx.x; i < len * w; i += TH) s_sum[i] = 0.0;
-            for (int i = threadIdx.x; i < len; i += TH) s_cnt[i] = 0u;
-            __syncthreads();
-        }
-    }
     } while (TRAIN && set < a.sets);
     if constexpr (TRAIN) {
         if (!COS && dsum != dsum) dsum = INFINITY;  // (a row that is near to no entry)

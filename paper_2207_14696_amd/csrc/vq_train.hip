@@ -175,7 +175,8 @@ __host__ __device__ constexpr int acc_stride(int len) { return len | 1; }
 template <typename T, typename CODE, bool VEC>
 __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     const T *__restrict__ x, int64_t rows, int D, int w, int len, int P, const CODE *__restrict__ codes,
-    const float *__restrict__ cb, int DG, int more, int groups, RowSets r, int lanes, int one_set, int l2, void *__restrict__ all_sums, uint32_t *__restrict__ counts, double *__restrict__ distortion) {
+    const float *__restrict__ cb, int DG, int more, int groups, RowSets r, int lanes, int one_set, int l2,
+    void *__restrict__ all_sums, uint32_t *__restrict__ counts, double *__restrict__ distortion) {
     extern __shared__ double s_acc[];  // [columns][acc_stride]
     const int ls = acc_stride(len);
     __shared__ double s_dist;
@@ -198,78 +199,78 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     };
     // (rows are counted within the set)
     for (int set = by / r.sub, next; set < r.sets; set = next) {
-    next = set + (r.sub > 1 ? r.sets : r.groups);
-    const int64_t begin = sub * r.share, end = min(set_rows(set, r.sets, r.strip_log2, rows), begin + r.share);
-    if constexpr (VEC) {
-        // `lanes` lanes (a power of two that divides the fours of columns) share a row: fewer lines an
-        // instruction; a lane has kAccRows rows in flight
-        const int lq = threadIdx.x & (lanes - 1), at = threadIdx.x / lanes, step = TH / lanes;
-        for (int64_t i = begin + at; i < end; i += (int64_t)step * kAccRows) {
-            int code[kAccRows];
-            int64_t row[kAccRows];
-#pragma unroll
-            for (int k = 0; k < kAccRows; k++) {
-                row[k] = set_row(set, r.sets, r.strip_log2, i + k * step);
-                code[k] = i + k * step < end ? part_codes[row[k]] : -1;
-            }
-            for (int j = 4 * lq; j < nd; j += 4 * lanes) {
-                float4 v[kAccRows], e[kAccRows];
+        next = set + (r.sub > 1 ? r.sets : r.groups);
+        const int64_t begin = sub * r.share, end = min(set_rows(set, r.sets, r.strip_log2, rows), begin + r.share);
+        if constexpr (VEC) {
+            // `lanes` lanes (a power of two that divides the fours of columns) share a row: fewer lines an
+            // instruction; a lane has kAccRows rows in flight
+            const int lq = threadIdx.x & (lanes - 1), at = threadIdx.x / lanes, step = TH / lanes;
+            for (int64_t i = begin + at; i < end; i += (int64_t)step * kAccRows) {
+                int code[kAccRows];
+                int64_t row[kAccRows];
 #pragma unroll
                 for (int k = 0; k < kAccRows; k++) {
-                    v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (code[k] < 0) continue;
-                    if (j < left) v[k] = load4(x + row[k] * D + (int64_t)p * w + c0 + j);
-                    e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
+                    row[k] = set_row(set, r.sets, r.strip_log2, i + k * step);
+                    code[k] = i + k * step < end ? part_codes[row[k]] : -1;
                 }
+                for (int j = 4 * lq; j < nd; j += 4 * lanes) {
+                    float4 v[kAccRows], e[kAccRows];
 #pragma unroll
-                for (int k = 0; k < kAccRows; k++) {
-                    if (code[k] < 0) continue;
-                    double *acc = s_acc + code[k];
-                    add(acc, j, v[k].x, e[k].x);
-                    add(acc, j + 1, v[k].y, e[k].y);
-                    add(acc, j + 2, v[k].z, e[k].z);
-                    add(acc, j + 3, v[k].w, e[k].w);
+                    for (int k = 0; k < kAccRows; k++) {
+                        v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        if (code[k] < 0) continue;
+                        if (j < left) v[k] = load4(x + row[k] * D + (int64_t)p * w + c0 + j);
+                        e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
+                    }
+#pragma unroll
+                    for (int k = 0; k < kAccRows; k++) {
+                        if (code[k] < 0) continue;
+                        double *acc = s_acc + code[k];
+                        add(acc, j, v[k].x, e[k].x);
+                        add(acc, j + 1, v[k].y, e[k].y);
+                        add(acc, j + 2, v[k].z, e[k].z);
+                        add(acc, j + 3, v[k].w, e[k].w);
+                    }
+                }
+                if (nc > nd && lq == 0) {
+#pragma unroll
+                    for (int k = 0; k < kAccRows; k++)
+                        if (code[k] >= 0) unsafeAtomicAdd(s_acc + code[k] + nd * ls, 1.0);
                 }
             }
-            if (nc > nd && lq == 0) {
-#pragma unroll
-                for (int k = 0; k < kAccRows; k++)
-                    if (code[k] >= 0) unsafeAtomicAdd(s_acc + code[k] + nd * ls, 1.0);
-            }
-        }
-    } else {
-        for (int64_t i = begin + threadIdx.x; i < end; i += TH) {
-            const int64_t row = set_row(set, r.sets, r.strip_log2, i);
-            const int code = part_codes[row];
-            const T *src = x + row * D + (int64_t)p * w + c0;
-            const float *ent = cb + ((int64_t)p * len + code) * w + c0;
-            double *acc = s_acc + code;
-#pragma unroll 4
-            for (int j = 0; j < nd; j++) add(acc, j, j < left ? load1(src + j) : 0.0f, ent[j]);
-            if (nc > nd) unsafeAtomicAdd(acc + nd * ls, 1.0);
-        }
-    }
-    if (one_set && next < r.sets) continue;  // (all sets' sums together)
-    __syncthreads();
-    for (int i = threadIdx.x; i < nc * len; i += TH) {
-        const int j = i / len, e = i - j * len, d = c0 + j;
-        const double sum = s_acc[j * ls + e];
-        s_acc[j * ls + e] = 0.0;
-        float *sums = static_cast<float *>(all_sums);
-        const int64_t slot = (int64_t)set * r.sub + sub;
-        if (one_set) {
-            if (sum == 0.0) continue;
-            if (d < w) unsafeAtomicAdd(&sums[((int64_t)p * w + d) * len + e], (float)sum);
-            else atomicAdd(&counts[(int64_t)p * len + e], (uint32_t)sum);
-        } else if (d < w) {
-            const int64_t to = ((slot * P + p) * w + d) * len + e;
-            if (r.sub > 1) static_cast<double *>(all_sums)[to] = sum;
-            else sums[to] = (float)sum;
         } else {
-            counts[(slot * P + p) * len + e] = (uint32_t)sum;
+            for (int64_t i = begin + threadIdx.x; i < end; i += TH) {
+                const int64_t row = set_row(set, r.sets, r.strip_log2, i);
+                const int code = part_codes[row];
+                const T *src = x + row * D + (int64_t)p * w + c0;
+                const float *ent = cb + ((int64_t)p * len + code) * w + c0;
+                double *acc = s_acc + code;
+#pragma unroll 4
+                for (int j = 0; j < nd; j++) add(acc, j, j < left ? load1(src + j) : 0.0f, ent[j]);
+                if (nc > nd) unsafeAtomicAdd(acc + nd * ls, 1.0);
+            }
         }
-    }
-    __syncthreads();
+        if (one_set && next < r.sets) continue;  // (all sets' sums together)
+        __syncthreads();
+        for (int i = threadIdx.x; i < nc * len; i += TH) {
+            const int j = i / len, e = i - j * len, d = c0 + j;
+            const double sum = s_acc[j * ls + e];
+            s_acc[j * ls + e] = 0.0;
+            float *sums = static_cast<float *>(all_sums);
+            const int64_t slot = (int64_t)set * r.sub + sub;
+            if (one_set) {
+                if (sum == 0.0) continue;
+                if (d < w) unsafeAtomicAdd(&sums[((int64_t)p * w + d) * len + e], (float)sum);
+                else atomicAdd(&counts[(int64_t)p * len + e], (uint32_t)sum);
+            } else if (d < w) {
+                const int64_t to = ((slot * P + p) * w + d) * len + e;
+                if (r.sub > 1) static_cast<double *>(all_sums)[to] = sum;
+                else sums[to] = (float)sum;
+            } else {
+                counts[(slot * P + p) * len + e] = (uint32_t)sum;
+            }
+        }
+        __syncthreads();
     }
     if (l2 && dsum != dsum) dsum = INFINITY;  // (a row that is near to no entry)
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
