@@ -246,6 +246,11 @@ __device__ inline void store_stream(uint4 *p, const uint4 v) {
     __builtin_nontemporal_store(v.z, &p->z);
     __builtin_nontemporal_store(v.w, &p->w);
 }
+__device__ inline void store_stream(uint2 *p, const uint2 v) {
+    __builtin_nontemporal_store(v.x, &p->x);
+    __builtin_nontemporal_store(v.y, &p->y);
+}
+__device__ inline void store_stream(uint32_t *p, const uint32_t v) { __builtin_nontemporal_store(v, p); }
 // index arrays are streamed once as well
 template <typename T>
 __device__ inline T load_stream(const T *p) { return __builtin_nontemporal_load(p); }

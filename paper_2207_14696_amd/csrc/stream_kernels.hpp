@@ -52,6 +52,12 @@ constexpr bool kHalfChunk = std::is_same<Src, ChunkSrc<__half>>::value;
 constexpr int kFitThreads = 1024;
 constexpr int kFitBlocks = 512;
 
+// A workgroup's rows come in pieces of so many of its iterations, the workgroups' pieces one after the
+// other: the chip then reads one window of the chunk at a time (805 MB of half precision 142 us, 146 with
+// one long piece each; 1 M x 100 floats fitted and encoded 271, 283).  Shorter pieces lose where
+// iterations are a power of two apart.
+constexpr int kFitPiece = 16;
+
 inline int fit_blocks(int64_t threads) {
     const int64_t b = (threads + kFitThreads - 1) / kFitThreads;
     return (int)(b < 1 ? 1 : b > kFitBlocks ? kFitBlocks : b);
@@ -96,9 +102,8 @@ __global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, i
         }
         __syncthreads();
     }
-    // A workgroup streams one contiguous piece of the chunk: TH/G whole rows per
-    // iteration when a row's G column groups fit a workgroup (a wave's lanes then read
-    // consecutive 16 bytes), else groups of G threads across the grid walk consecutive rows - also
+    // A workgroup takes TH/G whole rows per iteration when a row's G column groups fit it (a wave's
+    // lanes then read consecutive 16 bytes), else groups of G threads across the grid walk consecutive rows - also
     // where single columns would leave more than a quarter of the workgroup idle (601 half-precision
     // columns, 700 000 rows: 176 us so, 223 with one row per workgroup of 1024), and wider groups two
     // fifths (204 400 rows of 2052 floats 278 us, 300; but 4 194 of 3000 12.1, 10.1).
@@ -118,21 +123,8 @@ __global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, i
         }
         typename Src::Ctx ctx;
         src.prepare(ctx, g * VEC, D);
-        int64_t rbeg, rend, rstep;
-        if (by_block) {
-            const int64_t per_block = (rows + gridDim.x - 1) / gridDim.x;
-            rbeg = (int64_t)blockIdx.x * per_block + (int)threadIdx.x / G;
-            rend = min(rows, (int64_t)(blockIdx.x + 1) * per_block);
-            rstep = rpi;
-        } else {
-            const int64_t K = (rows + rows_per_pass - 1) / rows_per_pass;
-            rbeg = (int64_t)(t / G) * K;
-            rend = min(rows, rbeg + K);
-            rstep = 1;
-        }
         // fminf / fmaxf pass over a NaN like the comparisons they stand for
-#pragma unroll 4
-        for (int64_t r = rbeg; r < rend; r += rstep) {
+        auto take = [&](int64_t r) {
             float v[VEC];
             if constexpr (VEC == 8) {
                 src.load8(ctx, r, g * VEC, v);
@@ -147,6 +139,20 @@ __global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, i
                 mn[k] = fminf(mn[k], v[k]);
                 mx[k] = fmaxf(mx[k], v[k]);
             }
+        };
+        if (by_block) {
+            const uint32_t pass = gridDim.x * (uint32_t)rpi;
+            const int64_t steps = min((rows + pass - 1) / pass, (int64_t)kFitPiece), piece = steps * rpi;
+            for (int64_t r0 = blockIdx.x * piece; r0 < rows; r0 += gridDim.x * piece) {
+                const int64_t end = min(rows, r0 + piece);
+#pragma unroll 4
+                for (int64_t r = r0 + (int)threadIdx.x / G; r < end; r += rpi) take(r);
+            }
+        } else {
+            const int64_t K = (rows + rows_per_pass - 1) / rows_per_pass;
+            const int64_t rbeg = (int64_t)(t / G) * K, rend = min(rows, rbeg + K);
+#pragma unroll 4
+            for (int64_t r = rbeg; r < rend; r++) take(r);
         }
         // one or two column groups: the lanes of a wave that share one merge first (the same few
         // words of LDS for all of a workgroup's atomics: 3 M rows of 4 half-precision columns 17 us, 9 so)
@@ -312,8 +318,9 @@ struct LogCoder {
 // 16-byte load).  Where that is less than a 32-bit word, neighbouring lanes OR their pieces
 // together and one of them stores it.  Every word of the padded row is written (columns >= D
 // encode as 0).  Bound by memory (a plain copy moves 4.9 TB/s here): 524 288 x 768 half-precision
-// values to 4 bits 207 us, 4.86 TB/s (8-byte loads: 221), to 1 bit 177 (206).
-template <class Src, int BITS, typename Coder, bool VEC, int NC>
+// values to 4 bits 186 us, 5.4 TB/s (8-byte loads: 221), to 1 bit 177 (206).
+// STREAM: streaming stores, see launch_sq.
+template <class Src, int BITS, typename Coder, bool VEC, int NC, bool STREAM>
 __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t rows, int D, int64_t rb,
                                                               Coder coder,
                                                               uint8_t *__restrict__ codes) {
@@ -377,8 +384,14 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
             for (int o = 1; o < LG; o <<= 1) word[0] |= (uint32_t)__shfl_xor((int)word[0], o);
         }
         if (sub == 0) {
-            if constexpr (NW == 2) *reinterpret_cast<uint2 *>(dst_word + r * rw) = make_uint2(word[0], word[1]);
-            else dst_word[r * rw] = word[0];
+            uint32_t *dst = dst_word + r * rw;
+            if constexpr (NW == 2) {
+                if constexpr (STREAM) store_stream(reinterpret_cast<uint2 *>(dst), make_uint2(word[0], word[1]));
+                else *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
+            } else {
+                if constexpr (STREAM) store_stream(dst, word[0]);
+                else *dst = word[0];
+            }
         }
     }
 }
@@ -395,7 +408,16 @@ inline void launch_sq(const Src &src, int64_t rows, int D, int64_t rb, int bits,
     if (want < GW) want = GW;
     int blocks = blocks_for(want);
     if ((int64_t)blocks * kThreads < GW) blocks = (GW + kThreads - 1) / kThreads;
-#define BF_QK(B, VECV, NC) quantize_sq_kernel<Src, B, Coder, VECV, NC><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes)
+    // Codes that fill a tenth of the 256 MB cache or more are streamed past it: written back from there
+    // they slow down what comes next (tables fitted and encoded, ordinary stores / streamed: 2 x 201 MB of codes
+    // 769 / 742 us, of which the first range fit 190 / 163; 112 MB 296 / 282; 2 x 32 MB 546 / 540; 31 MB 146 / 140; but
+    // 2 x 24 MB 466 / 469).
+    const bool stream = rows * rb > ((int64_t)28 << 20);
+#define BF_QK(B, VECV, NC)                                                                                              \
+    do {                                                                                                               \
+        if (stream) quantize_sq_kernel<Src, B, Coder, VECV, NC, true><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes); \
+        else quantize_sq_kernel<Src, B, Coder, VECV, NC, false><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes); \
+    } while (0)
 #define BF_Q(B)                                                                                 \
     do {                                                                                        \
         if constexpr (kHalfChunk<Src>) {                                                        \
