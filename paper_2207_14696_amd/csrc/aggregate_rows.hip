@@ -2,15 +2,17 @@
 // neighbourhood mean runs over the previous layer's output instead of packed codes,
 // and the row-length reduction of the scale profile (Appendix A.1, A.5).
 //
-// Both are row gathers bound by HBM: a row of D floats is fetched whole, 16 bytes per
-// lane, several rows in flight per lane; nothing is staged.
+// Both are row gathers bound by memory: a row of D floats is fetched whole, 16 bytes per
+// lane, several rows in flight per lane.
 #include "common.hpp"
+
+#include <algorithm>
 
 namespace bf {
 namespace {
 
-constexpr int kAggInFlight = 4;  // rows in flight per lane
-constexpr int kItemsPerGroup = 4;  // (destination, tile) items a lane group works through
+constexpr int kAggInFlight = 4;  // rows that a lane adds up while as many travel
+constexpr int kMaxLists = 6;     // consecutive destinations of a lane group at most
 // A list longer than kLong is not walked by one lane group (a hub's thousands of rows,
 // one latency after the other, would outlast the rest of the launch): it is cut into
 // pieces of kSub list entries that many groups sum side by side.  A workgroup of that
@@ -58,17 +60,20 @@ struct Acc<4> {
     float4 v, c;
     __device__ void zero() { v = c = make_float4(0.f, 0.f, 0.f, 0.f); }
     __device__ static float4 load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+    __device__ static void hold(float4 &r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
     __device__ void add(const float4 r) {
         kahan_add(v.x, c.x, r.x);
         kahan_add(v.y, c.y, r.y);
         kahan_add(v.z, c.z, r.z);
         kahan_add(v.w, c.w, r.w);
     }
-    __device__ void store(float *p, int n, bool sum) const {
-        float4 o = v;
+    // a thread's sum of its group's k-th list, kept in LDS
+    __device__ void park(double *lds, int k) const { reinterpret_cast<float4 *>(lds)[k * kThreads + threadIdx.x] = v; }
+    __device__ static float4 parked(const double *lds, int k) { return reinterpret_cast<const float4 *>(lds)[k * kThreads + threadIdx.x]; }
+    __device__ static void store(float4 o, float *p, int n, bool sum) {
         if (!sum) {
             const float d = (float)n;
-            o = n > 0 ? make_float4(v.x / d, v.y / d, v.z / d, v.w / d) : make_float4(0.f, 0.f, 0.f, 0.f);
+            o = n > 0 ? make_float4(o.x / d, o.y / d, o.z / d, o.w / d) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
         store_stream(reinterpret_cast<float4 *>(p), o);
     }
@@ -85,14 +90,24 @@ struct Acc<1> {
     float v, c;
     __device__ void zero() { v = c = 0.f; }
     __device__ static float load(const float *p) { return *p; }
+    __device__ static void hold(float &r) { asm volatile("" : "+v"(r)); }
     __device__ void add(const float r) { kahan_add(v, c, r); }
-    __device__ void store(float *p, int n, bool sum) const {
-        __builtin_nontemporal_store(sum ? v : (n > 0 ? v / (float)n : 0.f), p);
+    __device__ void park(double *lds, int k) const { reinterpret_cast<float *>(lds)[k * kThreads + threadIdx.x] = v; }
+    __device__ static float parked(const double *lds, int k) { return reinterpret_cast<const float *>(lds)[k * kThreads + threadIdx.x]; }
+    __device__ static void store(float o, float *p, int n, bool sum) {
+        __builtin_nontemporal_store(sum ? o : (n > 0 ? o / (float)n : 0.f), p);
     }
     __device__ void add_to(double *p) const { unsafeAtomicAdd(p, kahan_sum(v, c)); }
 };
 
-// rows of `pieces` consecutive list entries [e, end) added into acc, U loads in flight
+// a 64-bit value of the wave's lane `at / 4`
+__device__ inline int64_t from_lane(int64_t v, int at) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)(v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// rows of the list entries [e, end) added into acc, U loads in flight
 template <int VEC, int U>
 __device__ inline void add_rows(Acc<VEC> &acc, const float *__restrict__ base, int64_t D,
                                 const int64_t *__restrict__ indices, int64_t e, int64_t end) {
@@ -107,30 +122,121 @@ __device__ inline void add_rows(Acc<VEC> &acc, const float *__restrict__ base, i
 }
 
 // The lists of up to kLong entries.  A group of `lpr` lanes (a power of two up to 64)
-// owns one (destination, column tile) item at a time: lane t of the group accumulates
-// columns VEC*(tile*lpr + t) .. +VEC-1 over the destination's list, in list order
-// (fp32, compensated).  Items are numbered tile-fastest so that neighbouring groups
-// write one contiguous row.  Long lists are left to long_lists().
+// owns a column tile of `lists` consecutive destinations at a time: lane t of the group accumulates
+// columns VEC*(tile*lpr + t) .. +VEC-1 over each destination's list, in list order
+// (fp32, compensated).  Items are numbered tile-fastest.  Long lists are left to long_lists().
+// What bounds it is how many rows are in flight: 2^20 rows of 100 columns, 17 M entries, ask for 6.9 GB
+// beyond the L2s, which move 7.4 TB/s of such lines at most.  The lists between two long ones are one
+// run of `indices`, whose rows travel 4 by 4 wherever a list begins and ends (most have 3 to 8 entries),
+// the next 4 while these are added.  The group fetches lpr entries with one load and hands the rows'
+// places round by lane exchange; a list's sum waits in LDS until the item's rows have been
+// read, as loads issued behind a store return behind it.  That launch: 1070 us with a list at a time, 4
+// rows in flight and every entry loaded by all lanes, 960 so; 500 000 rows of 37 columns 233 and 145.
 template <int VEC>
 __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
                                    const int64_t *__restrict__ indptr,
                                    const int64_t *__restrict__ indices, int64_t V, int lpr_log2,
-                                   int tiles, int sum, float *__restrict__ out, int64_t block,
+                                   int lists, int tiles, int sum, float *__restrict__ out, int64_t block,
                                    int64_t nblocks) {
+    constexpr int U = kAggInFlight;
+    using Row = decltype(Acc<VEC>::load(x));
+    extern __shared__ double s_sum[];
     const int lpr = 1 << lpr_log2;
-    const int t = threadIdx.x & (lpr - 1);
+    const int lane = threadIdx.x & 63, t = lane & (lpr - 1), first = lane & ~(lpr - 1);
     const int64_t groups = (nblocks * kThreads) >> lpr_log2;
-    const int64_t items = V * tiles;
+    const int64_t items = (V + lists - 1) / lists * tiles;
     for (int64_t item = (block * kThreads + threadIdx.x) >> lpr_log2; item < items; item += groups) {
-        const int64_t v = item / tiles;
-        const int tile = (int)(item - v * tiles);
+        const int64_t vg = item / tiles, v0 = vg * lists;
+        const int tile = (int)(item - vg * tiles);
         const int64_t col = (int64_t)VEC * (tile * lpr + t);
+        const bool in = col < D;  // (the other lanes read column 0 and write nothing)
+        const int nv = (int)min((int64_t)lists, V - v0);
+        // lane t: the t-th destination's bounds (lists < lpr)
+        const int64_t bound = indptr[v0 + min(t, nv)];
+        const int64_t after = from_lane(bound, 4 * (first + min(t + 1, lpr - 1)));
+        // (bit k: list k is a long one)
+        const uint32_t longs = (uint32_t)(__ballot(t < nv && after - bound > kLong) >> first);
+        const float *src = x + (in ? col : 0);
+        for (int i = 0; i < nv;) {
+            if ((longs >> i) & 1u) { i++; continue; }
+            const int j = i + __ffs((longs >> i) | (1u << (nv - i))) - 1;  // lists i .. j-1 are short
+            const int64_t base = from_lane(bound, 4 * (first + i));
+            const int rel = (int)(bound - base);  // (lanes i .. j)
+            const int n = __builtin_amdgcn_ds_bpermute(4 * (first + j), rel);
+            int end = __builtin_amdgcn_ds_bpermute(4 * (first + i + 1), rel);
+            Acc<VEC> acc;
+            acc.zero();
+            auto close = [&]() {  // list i is complete
+                acc.park(s_sum, i);
+                i++;
+                end = i < j ? __builtin_amdgcn_ds_bpermute(4 * (first + i + 1), rel) : 0x7FFFFFFF;
+                acc.zero();
+            };
+            while (end == 0) close();
+            if (n == 0) continue;
+            const int64_t *ind = indices + base;
+            // places of the rows of this chunk of lpr entries, of the next one (past the last entry: the last)
+            int64_t off = ind[min(t, n - 1)] * D, off1 = ind[min(lpr + t, n - 1)] * D;
+            Row r[2][U];
+            auto rows = [&](Row (&to)[U], int e) {  // entries e .. e + U - 1 travel
+                if (e > 0 && (e & (lpr - 1)) == 0) {
+                    off = off1;
+                    off1 = ind[min(e + lpr + t, n - 1)] * D;
+                }
+#pragma unroll
+                for (int u = 0; u < U; u++)
+                    to[u] = Acc<VEC>::load(src + from_lane(off, 4 * (first + ((e + u) & (lpr - 1)))));
+            };
+            auto take = [&](Row (&of)[U], int e) {
+                // (each in registers before the first is used: the compiler would otherwise move the loads into
+                // the branches, one after the other)
+#pragma unroll
+                for (int u = 0; u < U; u++) Acc<VEC>::hold(of[u]);
+                if (e + U < end) {
+#pragma unroll
+                    for (int u = 0; u < U; u++) acc.add(of[u]);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; u++) {
+                        if (e + u < n) {
+                            acc.add(of[u]);
+                            while (e + u + 1 == end) close();
+                        }
+                    }
+                }
+            };
+            rows(r[0], 0);
+            for (int e = 0; e < n; e += 2 * U) {
+                const bool second = e + U < n;
+                if (second) rows(r[1], e + U);
+                take(r[0], e);
+                if (e + 2 * U < n) rows(r[0], e + 2 * U);
+                if (second) take(r[1], e + U);
+            }
+        }
+        for (int k = 0; k < nv; k++) {
+            const int64_t len = from_lane(after, 4 * (first + k)) - from_lane(bound, 4 * (first + k));
+            if (in && len <= kLong) Acc<VEC>::store(Acc<VEC>::parked(s_sum, k), out + (v0 + k) * D + col, (int)len, sum != 0);
+        }
+    }
+}
+
+// The same for rows that four lanes take (up to 16 columns), a destination at a time: with 16 groups a wave
+// some list ends at every row, and short_lists() then walks its slow branch (10^6 rows of 3 columns 180 us,
+// 164 so; of 16 226, 217).
+template <int VEC>
+__device__ inline void short_lists_narrow(const float *__restrict__ x, int64_t D,
+                                          const int64_t *__restrict__ indptr,
+                                          const int64_t *__restrict__ indices, int64_t V, int sum,
+                                          float *__restrict__ out, int64_t block, int64_t nblocks) {
+    const int64_t col = (int64_t)VEC * (threadIdx.x & 3);
+    for (int64_t v = (block * kThreads + threadIdx.x) >> 2; v < V; v += (nblocks * kThreads) >> 2) {
         const int64_t beg = indptr[v], end = indptr[v + 1];
         if (col >= D || end - beg > kLong) continue;
         Acc<VEC> acc;
         acc.zero();
         add_rows<VEC, kAggInFlight>(acc, x + col, D, indices, beg, end);
-        acc.store(out + v * D + col, (int)(end - beg), sum != 0);
+        Acc<VEC>::store(acc.v, out + v * D + col, (int)(end - beg), sum != 0);
     }
 }
 
@@ -212,12 +318,12 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
                 const int tile = it % nt, piece = it / nt % kPieces, k = it / (nt * kPieces);
                 const int64_t b = s_beg[k] + (int64_t)piece * kSub;
                 const int64_t col = (int64_t)VEC * ((t0 + tile) * lpr + t);
-                if (b >= s_end[k] || col >= D) continue;
-                const int64_t end = b + kSub < s_end[k] ? b + kSub : s_end[k];
+                if (b >= s_end[k]) continue;
+                const bool in = col < D;
                 Acc<VEC> acc;
                 acc.zero();
-                add_rows<VEC, 2 * kAggInFlight>(acc, x + col, D, indices, b, end);
-                acc.add_to(s_sum + k * width + tile * tile_cols + VEC * t);
+                if (in) add_rows<VEC, 2 * kAggInFlight>(acc, x + col, D, indices, b, min(b + kSub, s_end[k]));
+                if (in) acc.add_to(s_sum + k * width + tile * tile_cols + VEC * t);
             }
             __syncthreads();
             for (int i = threadIdx.x; i < n_long * width; i += kThreads) {
@@ -235,27 +341,32 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
 // One launch for both: the first `long_blocks` workgroups (dispatched first; their
 // pieces are the longest single chains of the launch) take the long lists, the rest
 // the short ones.  The two write disjoint rows.
-template <int VEC>
+template <int VEC, bool NARROW>
 __device__ inline void aggregate(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
-                                 const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int tiles,
-                                 int sum, int long_blocks, float *__restrict__ out) {
-    if ((int)blockIdx.x < long_blocks)
-        long_lists<VEC>(x, D, indptr, indices, V, E, lpr_log2, tiles, sum, out, blockIdx.x,
-                        long_blocks);
+                                 const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int lists,
+                                 int tiles, int sum, int long_blocks, float *__restrict__ out) {
+    const int64_t block = (int64_t)blockIdx.x - long_blocks, nblocks = (int64_t)gridDim.x - long_blocks;
+    if (block < 0)
+        long_lists<VEC>(x, D, indptr, indices, V, E, lpr_log2, tiles, sum, out, blockIdx.x, long_blocks);
+    else if constexpr (NARROW)
+        short_lists_narrow<VEC>(x, D, indptr, indices, V, sum, out, block, nblocks);
     else
-        short_lists<VEC>(x, D, indptr, indices, V, lpr_log2, tiles, sum, out,
-                         (int64_t)blockIdx.x - long_blocks, (int64_t)gridDim.x - long_blocks);
+        short_lists<VEC>(x, D, indptr, indices, V, lpr_log2, lists, tiles, sum, out, block, nblocks);
 }
-#define BF_AGG(NAME, VEC)                                                                            \
-    void NAME(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,             \
-              const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int tiles,     \
-              int sum, int long_blocks, float *__restrict__ out) {                                    \
-        aggregate<VEC>(x, D, indptr, indices, V, E, lpr_log2, tiles, sum, long_blocks, out);          \
+#define BF_AGG(NAME, VEC, NARROW)                                                                           \
+    void NAME(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,                    \
+              const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int lists, int tiles, \
+              int sum, int long_blocks, float *__restrict__ out) {                                           \
+        aggregate<VEC, NARROW>(x, D, indptr, indices, V, E, lpr_log2, lists, tiles, sum, long_blocks, out);  \
     }
-__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_kernel4, 4)
+// (apart: with the registers of short_lists() a SIMD holds 5 waves instead of 8, and the narrow
+// lists, 10^6 rows of 8 columns, take 210 us instead of 197)
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_kernel4, 4, false)
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_narrow_kernel4, 4, true)
 // (with the 96 SGPRs it would take a SIMD holds 7 waves instead of 8, and launches without a long
 // list, 200 000 rows of 101 columns, take 289 us instead of 268)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_sgpr(80))) BF_AGG(aggregate_rows_kernel1, 1)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_sgpr(80))) BF_AGG(aggregate_rows_kernel1, 1, false)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_sgpr(80))) BF_AGG(aggregate_rows_narrow_kernel1, 1, true)
 #undef BF_AGG
 
 // Output rows of the long lists set to zero ahead of the launch above: a lane per
@@ -329,10 +440,18 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     int lpr_log2 = 2;  // at least four lanes per row
     while (lpr_log2 < 6 && ((int64_t)1 << lpr_log2) < granules) lpr_log2++;
     const int64_t tiles = (granules + ((int64_t)1 << lpr_log2) - 1) >> lpr_log2;
-    const int64_t threads = (V * tiles) << lpr_log2;
+    // Several lists a group only where the chip has enough of them at a time (us with 1, 2, 4, 6 of them: 10^6
+    // rows of 64 columns 538, 459, 452, 454; 500 000 of 37 271, 207, 176, 160; 100 000 of 64, 25 000 waves by one,
+    // 68, 68, 90; 20 000 of 100 58, 59, 72); of 8 lanes a row 3 (10^6 of 32 columns 2, 3, 6: 263, 261, 284), of
+    // wide rows 2 (300 000 of 768 2, 3, 6: 1607, 1632, 1652)
+    const int64_t waves = (V * tiles) >> (6 - lpr_log2);
+    int lists = waves < 16384 ? 1 : (int)std::min<int64_t>(kMaxLists, std::max<int64_t>(2, waves / 12288));
+    lists = lpr_log2 == 2 ? 0 : std::min(lists, lpr_log2 == 3 ? 3 : D >= 512 ? 2 : kMaxLists);
+    // (lists apart: 4 a group)
+    const int64_t items = lists ? (V + lists - 1) / lists * tiles : (V + 3) / 4;
     // many small workgroups rather than one resident set: the two kinds of work take turns
     // on the CUs as slots free up, and no workgroup's share is large enough to form a tail
-    const int short_blocks = blocks_for((threads + kItemsPerGroup - 1) / kItemsPerGroup, 1 << 20);
+    const int short_blocks = blocks_for(items << lpr_log2, 1 << 20);
     int long_blocks = 0;
     if (E > kLong) {  // otherwise no list is long
         const int64_t ranges = (E + kRange - 1) / kRange;
@@ -342,13 +461,11 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     const int blocks = short_blocks + long_blocks;
     const int64_t tile_cols = (int64_t)(vec ? 4 : 1) << lpr_log2;
     const int64_t most = vec ? kSums<4> : kSums<1>, all = kMaxLong * tiles * tile_cols;
-    const size_t shm = long_blocks > 0 ? sizeof(double) * (size_t)(all < most ? all : most) : 0;
-    if (vec)
-        aggregate_rows_kernel4<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
-                                                            (int)tiles, sum, long_blocks, out);
-    else
-        aggregate_rows_kernel1<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2,
-                                                            (int)tiles, sum, long_blocks, out);
+    size_t shm = long_blocks > 0 ? sizeof(double) * (size_t)(all < most ? all : most) : 0;
+    shm = std::max(shm, (size_t)lists * kThreads * (vec ? 16 : 4));  // the short lists' sums
+    auto *kern = lists ? (vec ? aggregate_rows_kernel4 : aggregate_rows_kernel1)
+                       : (vec ? aggregate_rows_narrow_kernel4 : aggregate_rows_narrow_kernel1);
+    kern<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2, lists, (int)tiles, sum, long_blocks, out);
     return hipGetLastError();
 }
 

@@ -1,0 +1,36 @@
+"""aggregate_rows over runs of short lists: a lane group takes 1, 2, 3 or 6 consecutive destinations (by how many waves
+they make), with empty and long lists at any place among them, for every number of lanes a row takes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# around the 4 rows that travel together, the 4 to 64 entries a group fetches at once, and the 256 of a long list
+EDGES = [0, 0, 1, 3, 4, 5, 0, 7, 8, 9, 12, 15, 16, 17, 31, 32, 33, 63, 64, 65, 257, 2, 256, 255, 0, 300, 300, 0, 1, 1025]
+
+
+@pytest.mark.parametrize("waves", [3, 16_383, 16_384, 36_864, 73_729])
+@pytest.mark.parametrize("D,per_wave,tiles", [(3, 16, 1), (16, 16, 1), (28, 8, 1), (64, 4, 1), (100, 2, 1), (300, 1, 2), (37, 1, 1)])
+def test_runs(D, per_wave, tiles, waves):
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(D + waves)
+    N, V = 5000, max(1, waves * per_wave // tiles + (waves % 2))
+    lens = rng.integers(0, 4, V)
+    for at in (0, V // 2, max(0, V - len(EDGES))):               # the last ones end the block
+        n = min(len(EDGES), V - at)
+        lens[at:at + n] = rng.permutation(EDGES)[:n] if at else EDGES[:n]
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)).cuda()
+    indices = torch.from_numpy(rng.integers(0, N, int(lens.sum()))).cuda()
+    x = torch.randn(N, D, device="cuda", generator=torch.Generator("cuda").manual_seed(D))
+    dst = torch.repeat_interleave(torch.arange(V, device="cuda"), indptr[1:] - indptr[:-1])
+    want = torch.zeros(V, D, dtype=torch.float64, device="cuda").index_add_(0, dst, x[indices].double())
+    scale = torch.zeros(V, D, dtype=torch.float64, device="cuda").index_add_(0, dst, x[indices].double().abs())
+    n = (indptr[1:] - indptr[:-1]).clamp(min=1)[:, None]
+    # compensated sums and one division: 3 units of 2^-24 of the terms' mean size; long lists: one more for each
+    # of at most 2 stretches
+    for as_sum in (False, True):
+        out = torch.full((V, D), float("nan"), device="cuda")
+        bf.aggregate_rows(x, indptr, indices, out=out, sum=as_sum)
+        per = 1 if as_sum else n
+        assert torch.all((out.double() - want / per).abs() <= 6 * 2.0 ** -24 * (scale / per))
