@@ -19,6 +19,7 @@
 // one 16-byte LDS read and one 16-byte store each; gather_mean: 8 columns where
 // the width allows); a wave covers 64/LPS rows (gather_dequant) or destinations
 // (gather_mean).
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
@@ -313,8 +314,11 @@ struct MeanLane {
     // lanes 0..31 in exchange for those lanes' second half (one cross-half swap per register),
     // so that the first instruction writes both halves of the destinations owned by lanes
     // 0..31 and the second both halves of the others: whole 128-byte lines per instruction.
-    // `write`: this lane's destination is to be written; v: its destination.
-    __device__ void store_tile(float *__restrict__ out, int64_t v, int D, const float (&res)[CPL],
+    // The tile's rows are a buffer of their own, whose bounds drop what is not to be written: with a branch
+    // round each store the compiler cannot count them, and has the wait for the next tile's codes
+    // cover this one's stores (837 000 entries of 96 x 256 x 8 into 96 839 rows: 134 us, 130 so).
+    // `write`: this lane's destination is to be written.
+    __device__ void store_tile(float *__restrict__ out, int64_t tile, int64_t V, int D, const float (&res)[CPL],
                                bool write) const {
         static_assert(CPL == 8, "two 16-byte halves per lane");
         const unsigned long long wmask = __ballot(write);
@@ -329,27 +333,22 @@ struct MeanLane {
             b[k] = r[1];
         }
         const bool upper = lane >= 32;
-        const int64_t half_dst = 32 >> (6 - rpw_log2);  // destinations owned by half a wave
-        // first instruction: destinations of lanes 0..31 (upper lanes write their partner's second half)
-        const int64_t v0 = upper ? v - half_dst : v;
-        const bool w0 = (wmask >> (lane & 31)) & 1ull;
-        // second instruction: destinations of lanes 32..63 (lower lanes write their partner's first half)
-        const int64_t v1 = upper ? v : v + half_dst;
-        const bool w1 = (wmask >> (32 + (lane & 31))) & 1ull;
+        const int half_dst = 32 >> (6 - rpw_log2);  // destinations owned by half a wave
+        // first instruction: destinations of lanes 0..31 (upper lanes write their partner's second half),
+        // second: destinations of lanes 32..63 (lower lanes write their partner's first half)
+        const int d0 = upper ? r_in - half_dst : r_in, d1 = upper ? r_in : r_in + half_dst;
+        const bool w0 = (wmask >> (lane & 31)) & 1ull, w1 = (wmask >> (32 + (lane & 31))) & 1ull;
         const int c0 = col + (upper ? 4 : 0);
-#ifdef BF_VQ_PLAIN
-        if (w0) *reinterpret_cast<uint4 *>(out + v0 * D + c0) = make_uint4(a[0], a[1], a[2], a[3]);
-        if (w1) *reinterpret_cast<uint4 *>(out + v1 * D + c0) = make_uint4(b[0], b[1], b[2], b[3]);
-        return;
-#endif
-        if (w0)
-            store_stream(reinterpret_cast<float4 *>(out + v0 * D + c0),
-                         make_float4(__uint_as_float(a[0]), __uint_as_float(a[1]), __uint_as_float(a[2]),
-                                     __uint_as_float(a[3])));
-        if (w1)
-            store_stream(reinterpret_cast<float4 *>(out + v1 * D + c0),
-                         make_float4(__uint_as_float(b[0]), __uint_as_float(b[1]), __uint_as_float(b[2]),
-                                     __uint_as_float(b[3])));
+        const int64_t v0 = tile << rpw_log2, rows = min((int64_t)1 << rpw_log2, V - v0);
+        const uint64_t base = reinterpret_cast<uint64_t>(out + v0 * D);
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<void *>(((uint64_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
+                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)base)),
+            0, __builtin_amdgcn_readfirstlane((int)(rows * D * 4)), 0x00027000);
+        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+        constexpr int nowhere = 0x7FFFFFF0, kNt = 2;  // (streaming)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{a[0], a[1], a[2], a[3]}, rsrc, w0 ? (d0 * D + c0) * 4 : nowhere, 0, kNt);
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{b[0], b[1], b[2], b[3]}, rsrc, w1 ? (d1 * D + c0) * 4 : nowhere, 0, kNt);
     }
 };
 
@@ -419,7 +418,7 @@ __global__ __launch_bounds__(kVqThreads) void gather_mean_vq_short_kernel(
         }
         if (over && L.g == 0 && L.slice == 0) raise_status(status, kStatusListTooLong);
         if constexpr (CPL == 8) {
-            L.store_tile(out, v, D, res, mine || over);
+            L.store_tile(out, tile, V, D, res, mine || over);
         } else {
             if (mine || over) L.store(out, v, D, res);
         }
@@ -686,7 +685,10 @@ bool launch_gather_mean_vq_sliced(bifeat_params *p, const MeanCall &c) {
     if (c.E > 0) launch_planes(p, c.codes, c.indices, c.idx32, c.E, (uint32_t *)p->d_scratch, c.s);
     const int lps = g.LPS * 4 / cpl, rpw = 64 / lps;
     const int64_t tiles = (c.V + rpw - 1) / rpw;
-    const int grid = sliced_grid(p, tiles * g.NS, 1024, g.NS);
+    // as many workgroups as run at a time: each stages its codebooks first (with 1024: 837 000 entries of 96 x
+    // 256 x 8 into 96 839 rows 130 us instead of 125, 76 000 of 16 x 1000 x 32 56 instead of 47)
+    const int64_t resident = 256 * std::max<int64_t>(1, std::min<int64_t>(2, 160 * 1024 / (int64_t)g.lds));
+    const int grid = sliced_grid(p, tiles * g.NS, resident, g.NS);
 #define BF_VQA                                                                                  \
     (const uint32_t *)p->d_scratch, MS, c.indptr, c.V, (int)p->D, p->P, w, len, g.SP, g.NS,     \
         ilog2(lps), p->cbytes, c.agg_sum, p->d_cb, c.out
