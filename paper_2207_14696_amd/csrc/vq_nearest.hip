@@ -15,13 +15,29 @@ namespace {
 template <int GROUPS>
 __global__ __launch_bounds__(kThreads) void vq_means_kernel(const void *__restrict__ sums,
                                                             const uint32_t *__restrict__ counts, int sets, int sub, int P,
-                                                            int w, int len, float *__restrict__ cb) {
+                                                            int w, int len, const double *__restrict__ dists, int n_dists,
+                                                            double *__restrict__ distortion, float *__restrict__ cb) {
     constexpr int OUT = kThreads / GROUPS;
+    const int first = dists ? 1 : 0, workers = (int)gridDim.x - first;
+    if ((int)blockIdx.x < first) {  // one more workgroup, beside those of the means
+        __shared__ double s_d[kThreads / 64];
+        double d = 0.0;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n_dists; i += kThreads) d += dists[i];
+        for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o);
+        if ((threadIdx.x & 63) == 0) s_d[threadIdx.x >> 6] = d;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < kThreads / 64; k++) d += s_d[k];
+            *distortion = d;
+        }
+        return;
+    }
     __shared__ double s_sum[GROUPS > 1 ? kThreads : 1];
     __shared__ uint64_t s_count[GROUPS > 1 ? kThreads : 1];
     const int64_t n = (int64_t)P * w * len;
     const int o = threadIdx.x % OUT, g = threadIdx.x / OUT;
-    for (int64_t i0 = (int64_t)blockIdx.x * OUT; i0 < n; i0 += (int64_t)gridDim.x * OUT) {
+    for (int64_t i0 = (int64_t)((int)blockIdx.x - first) * OUT; i0 < n; i0 += (int64_t)workers * OUT) {
         const int64_t i = i0 + o;
         const int e = (int)(i % len);
         const int64_t pd = i / len, p = pd / w;
@@ -88,11 +104,13 @@ bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows) {
     return !train || entries_in_lds(p, true);
 }
 
-void launch_vq_means(bifeat_params *p, const void *sums, const uint32_t *counts, int sets, int sub, hipStream_t s) {
+void launch_vq_means(bifeat_params *p, const void *sums, const uint32_t *counts, int sets, int sub, const double *dists,
+                     int n_dists, double *distortion, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const int64_t n = (int64_t)p->P * len * w;
 #define BF_VM(GROUPS) \
-    vq_means_kernel<GROUPS><<<blocks_for(GROUPS * n), kThreads, 0, s>>>(sums, counts, sets, sub, p->P, w, len, p->d_cb)
+    vq_means_kernel<GROUPS><<<blocks_for(GROUPS * n) + (dists ? 1 : 0), kThreads, 0, s>>>( \
+        sums, counts, sets, sub, p->P, w, len, dists, n_dists, distortion, p->d_cb)
     // (a thread each where that fills the chip: 10 sets of 96 x 256 x 8 take 6.5 us so, 13 by groups)
     if (sets * sub > 8 && n < (1 << 16)) BF_VM(8);
     else BF_VM(1);

@@ -71,7 +71,7 @@ struct VqNearestArgs {
     int one_set;            // (training) every workgroup adds to one set of sums, all zeros
     void *sums;             // [sets][sub][P][w][len], in 64 bits where sub > 1, else 32
     uint32_t *counts;       // [sets][sub][P][len]
-    double *distortion;
+    double *distortion;     // [workgroups], with one_set: the round's
 };
 
 // codebooks of fewer values (entries x columns; parts of 4 columns or more; with few rows x parts) and
@@ -796,7 +796,11 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
         for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
         if (lane == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
         __syncthreads();
-        if (threadIdx.x == 0) unsafeAtomicAdd(a.distortion, s_dist);
+        if (threadIdx.x == 0) {
+            // (id, from the registers that a workgroup starts with: one less to keep)
+            if (a.one_set) unsafeAtomicAdd(a.distortion, s_dist);
+            else a.distortion[(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)] = s_dist;
+        }
     }
 }
 
@@ -883,6 +887,7 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
     const int64_t resident =
         256 * std::min<int64_t>(ENT ? nearest_waves(G, true, TH) * 256 / TH : 1, kCuLds / (int64_t)lds);
     int64_t ny = 0;
+    [[maybe_unused]] double *const distortion = a.distortion;
     if constexpr (TRAIN) {
         RowSets r = row_sets(p, a.rows);
         deal_sets(r, a.rows, a.P, resident, TH);
@@ -891,9 +896,10 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         // the handle's own block of one set (10 rounds on 65 536 rows, with workspace / so: 8 x 256 x 16
         // 530 / 500 us, 96 x 256 x 8 1690 / 1650; one workgroup per part 8790 and 6370)
         const int64_t books = (int64_t)a.P * a.len * a.w, ents = (int64_t)a.P * a.len;
-        if (ensure_scratch(p, (size_t)sums_bytes(p, r), s)) {
+        if (ensure_scratch(p, (size_t)round_bytes(p, r, a.P), s)) {
             a.sums = p->d_scratch;
             a.counts = (uint32_t *)(p->d_scratch + r.sets * r.sub * books * (r.sub > 1 ? 8 : 4));
+            a.distortion = round_dists(p, r, p->d_scratch);
         } else {
             a.one_set = 1;
             a.sums = p->d_train;
@@ -924,7 +930,9 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
     search_costs(a, G, ENT, METRIC == BIFEAT_VQ_COSINE);
     const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
     kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
-    if constexpr (TRAIN) launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.sets, a.one_set ? 1 : a.sub, s);
+    if constexpr (TRAIN)
+        launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.sets, a.one_set ? 1 : a.sub,
+                        a.one_set ? nullptr : a.distortion, a.P * a.ny, distortion, s);
     return true;
 }
 

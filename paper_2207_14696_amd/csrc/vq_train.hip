@@ -276,7 +276,10 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
     if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&s_dist, (double)dsum);
     __syncthreads();
-    if (threadIdx.x == 0) unsafeAtomicAdd(distortion, s_dist);
+    if (threadIdx.x == 0) {
+        if (one_set) unsafeAtomicAdd(distortion, s_dist);
+        else distortion[(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)] = s_dist;  // [id]
+    }
 }
 
 // The generic round's workspace: the codes, then the workgroups' sums.
@@ -284,7 +287,7 @@ struct GenericPlan {
     int DG, more, groups;            // columns a group, 1: the last one counts on top of them
     int threads;
     RowSets sets;
-    int64_t codes_bytes, sums_bytes;  // codes (rounded up), sums and counts of every workgroup
+    int64_t codes_bytes, sums_bytes;  // codes (rounded up), sums, counts and distances of every workgroup
 };
 
 GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
@@ -310,10 +313,9 @@ GenericPlan generic_plan(const bifeat_params *p, int64_t rows) {
     while (w >= 8 && g.threads > 256 && g.threads / 2 >= len && cols * ((rows + g.threads - 1) / g.threads) < 512) g.threads /= 2;
     g.codes_bytes = (rows * p->P * p->cbytes + 255) / 256 * 256;
     g.sets = row_sets(p, rows);
-    // (512 workgroups do: each also adds to the one distortion, 20 ns one after the other)
     deal_sets(g.sets, rows, cols, 256 * std::min<int64_t>(2, 160 * 1024 / (lds + 64)), g.threads);
     if (g.sets.sub > 1 && sums_bytes(p, g.sets) > kMaxSumsBytes) g.sets = row_sets(p, rows);
-    g.sums_bytes = sums_bytes(p, g.sets);
+    g.sums_bytes = round_bytes(p, g.sets, cols);
     return g;
 }
 
@@ -329,7 +331,7 @@ bool codes_pay(const bifeat_params *p, int64_t rows) {
 
 template <typename T, typename CODE, bool VEC>
 bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericPlan &g, bool one_set, void *sums,
-                      uint32_t *counts, double *dist_slot, hipStream_t s) {
+                      uint32_t *counts, double *distortion, hipStream_t s) {
     const size_t shm = sizeof(double) * (size_t)(g.DG + g.more) * acc_stride(p->scheme.vq_length);
     auto kern = vq_accumulate_codes_kernel<T, CODE, VEC>;
     if (shm > 65536 - 64 &&
@@ -341,7 +343,7 @@ bool accumulate_codes(bifeat_params *p, const T *x, int64_t rows, const GenericP
     while (VEC && lanes < 16 && g.DG % (8 * lanes) == 0) lanes *= 2;
     kern<<<(unsigned)blocks, g.threads, shm, s>>>(
         x, rows, (int)p->D, p->scheme.vq_width, p->scheme.vq_length, p->P, (const CODE *)p->d_scratch, p->d_cb, g.DG,
-        g.more, g.groups, g.sets, lanes, one_set, p->scheme.vq_metric == BIFEAT_VQ_L2, sums, counts, dist_slot);
+        g.more, g.groups, g.sets, lanes, one_set, p->scheme.vq_metric == BIFEAT_VQ_L2, sums, counts, distortion);
     return true;
 }
 
@@ -357,18 +359,19 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     const int sets = all ? g.sets.sets : 1, sub = all ? g.sets.sub : 1;
     uint8_t *sums = all ? p->d_scratch + g.codes_bytes : (uint8_t *)p->d_train;
     uint32_t *counts = (uint32_t *)(sums + sets * sub * books * (sub > 1 ? 8 : 4));
+    double *dists = all ? round_dists(p, g.sets, sums) : nullptr, *distortion = all ? dists : dist_slot;
     if (!all) launch_vq_zero(p->d_train, books + (int64_t)P * len, s);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
     launch_vq_assign_parts(p, x, rows, p->d_scratch, s);
     // 4 columns at a time: whole fours everywhere, and where they lie
     const bool vec = g.DG % 4 == 0 && w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
     const bool ok = p->cbytes == 1
-                        ? (vec ? accumulate_codes<T, uint8_t, true>(p, x, rows, g, !all, sums, counts, dist_slot, s)
-                               : accumulate_codes<T, uint8_t, false>(p, x, rows, g, !all, sums, counts, dist_slot, s))
-                        : (vec ? accumulate_codes<T, uint16_t, true>(p, x, rows, g, !all, sums, counts, dist_slot, s)
-                               : accumulate_codes<T, uint16_t, false>(p, x, rows, g, !all, sums, counts, dist_slot, s));
+                        ? (vec ? accumulate_codes<T, uint8_t, true>(p, x, rows, g, !all, sums, counts, distortion, s)
+                               : accumulate_codes<T, uint8_t, false>(p, x, rows, g, !all, sums, counts, distortion, s))
+                        : (vec ? accumulate_codes<T, uint16_t, true>(p, x, rows, g, !all, sums, counts, distortion, s)
+                               : accumulate_codes<T, uint16_t, false>(p, x, rows, g, !all, sums, counts, distortion, s));
     if (!ok) return hipGetLastError();
-    launch_vq_means(p, sums, counts, sets, sub, s);
+    launch_vq_means(p, sums, counts, sets, sub, dists, g.groups * P * g.sets.groups, dist_slot, s);
     return hipSuccess;
 }
 
