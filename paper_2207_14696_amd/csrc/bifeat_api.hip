@@ -100,12 +100,20 @@ int ensure_device(bifeat_params *p) {
     if (p->scheme.kind == BIFEAT_SQ_LOG) p->d_hist = reinterpret_cast<unsigned long long *>(p->d_fit + 4);
     p->d_zero = reinterpret_cast<uint8_t *>(p->d_fit + nfit);
     // the status word: pinned host memory that the kernels write through its device mapping
+    // with room for what a fit leaves for the host
+    const size_t out = p->scheme.kind == BIFEAT_SQ_UNIFORM ? (D <= bf::kExportColumns ? 16 * D : 0)
+                       : p->scheme.kind == BIFEAT_SQ_LOG   ? sizeof(unsigned long long) * 2 * bf::kLogHistBins
+                                                           : sizeof(double) * 64;
     void *hs = nullptr, *ds = nullptr;
-    BF_HIP(hipHostMalloc(&hs, 64, hipHostMallocMapped));
-    memset(hs, 0, 64);
+    BF_HIP(hipHostMalloc(&hs, 64 + out, hipHostMallocMapped));
+    memset(hs, 0, 64 + out);
     BF_HIP(hipHostGetDevicePointer(&ds, hs, 0));
     p->h_status = (int32_t *)hs;
     p->d_status = (int32_t *)ds;
+    if (out) {
+        p->h_out = (uint8_t *)hs + 64;
+        p->d_out = (float *)((uint8_t *)ds + 64);
+    }
     return BIFEAT_OK;
 }
 
@@ -159,33 +167,13 @@ void build_log_tables(bifeat_params *p) {
     }
 }
 
-int upload_log(bifeat_params *p) {
+// (complete on return: the caller may gather on any stream)
+int upload_log(bifeat_params *p, hipStream_t s) {
     int rc = ensure_device(p);
     if (rc) return rc;
-    if (!p->h_T.empty())
-        BF_HIP(hipMemcpy(p->d_T, p->h_T.data(), sizeof(float) * p->h_T.size(), hipMemcpyHostToDevice));
-    BF_HIP(hipMemcpy(p->d_V, p->h_V.data(), sizeof(float) * p->h_V.size(), hipMemcpyHostToDevice));
-    if (p->scheme.bits == 1) {
-        // V[1] = -V[0]: the difference and V[0] + 1*(V[1]-V[0]) are exact
-        std::vector<float> col((size_t)2 * p->D);
-        for (int64_t j = 0; j < p->D; j++) {
-            col[j] = p->h_V[0];
-            col[p->D + j] = p->h_V[1] - p->h_V[0];
-        }
-        BF_HIP(hipMemcpy(p->d_min, col.data(), sizeof(float) * col.size(), hipMemcpyHostToDevice));
-    } else if (p->scheme.bits == 2) {
-        // decoded sum = (v1 - v0)*S0 - n*v1 + (v0 + v1)*S1 over the two bit planes of a column
-        // (V = [-v1, -v0, v0, v1]): bit column 2t maps S0, bit column 2t+1 maps S1
-        const double v0 = p->h_V[2], v1 = p->h_V[3];
-        std::vector<float> col((size_t)4 * p->D);
-        for (int64_t j = 0; j < p->D; j++) {
-            col[2 * j] = (float)-v1;
-            col[2 * j + 1] = 0.0f;
-            col[2 * p->D + 2 * j] = (float)(v1 - v0);
-            col[2 * p->D + 2 * j + 1] = (float)(v0 + v1);
-        }
-        BF_HIP(hipMemcpy(p->d_min, col.data(), sizeof(float) * col.size(), hipMemcpyHostToDevice));
-    }
+    bf::launch_log_tables(p, s);
+    BF_HIP(hipGetLastError());
+    BF_HIP(hipStreamSynchronize(s));
     return BIFEAT_OK;
 }
 
@@ -195,10 +183,15 @@ int sync_uniform_host(bifeat_params *p) {
     const size_t D = (size_t)p->D;
     p->h_min.resize(D); p->h_max.resize(D); p->h_scale.resize(D); p->h_inv.resize(D);
     BF_HIP(hipDeviceSynchronize());
-    BF_HIP(hipMemcpy(p->h_min.data(), p->d_min, 4 * D, hipMemcpyDeviceToHost));
-    BF_HIP(hipMemcpy(p->h_max.data(), p->d_max, 4 * D, hipMemcpyDeviceToHost));
-    BF_HIP(hipMemcpy(p->h_scale.data(), p->d_scale, 4 * D, hipMemcpyDeviceToHost));
-    BF_HIP(hipMemcpy(p->h_inv.data(), p->d_inv, 4 * D, hipMemcpyDeviceToHost));
+    if (p->h_out) {
+        float *const to[4] = {p->h_min.data(), p->h_scale.data(), p->h_inv.data(), p->h_max.data()};
+        for (int k = 0; k < 4; k++) memcpy(to[k], p->h_out + 4 * D * k, 4 * D);
+    } else {
+        BF_HIP(hipMemcpy(p->h_min.data(), p->d_min, 4 * D, hipMemcpyDeviceToHost));
+        BF_HIP(hipMemcpy(p->h_max.data(), p->d_max, 4 * D, hipMemcpyDeviceToHost));
+        BF_HIP(hipMemcpy(p->h_scale.data(), p->d_scale, 4 * D, hipMemcpyDeviceToHost));
+        BF_HIP(hipMemcpy(p->h_inv.data(), p->d_inv, 4 * D, hipMemcpyDeviceToHost));
+    }
     p->host_valid = true;
     return BIFEAT_OK;
 }
@@ -243,9 +236,9 @@ bool walk_histogram(const unsigned long long *h, int bins, unsigned long long ra
     return false;
 }
 
-int finish_log(bifeat_params *p) {
+int finish_log(bifeat_params *p, hipStream_t s) {
     build_log_tables(p);
-    int rc = upload_log(p);
+    int rc = upload_log(p, s);
     if (rc) return rc;
     p->host_valid = true;
     p->fit_open = false;
@@ -255,11 +248,10 @@ int finish_log(bifeat_params *p) {
 
 // one step of the three-pass radix selection (digits of 11, 11 and 9 bits)
 int finalize_log_clipped(bifeat_params *p, hipStream_t s) {
-    std::vector<unsigned long long> h((size_t)2 * bf::kLogHistBins);
-    BF_HIP(hipMemcpyAsync(h.data(), p->d_hist, sizeof(unsigned long long) * h.size(),
-                          hipMemcpyDeviceToHost, s));
+    bf::launch_export(p, p->d_hist, 4 * bf::kLogHistBins, s);
+    BF_HIP(hipGetLastError());
     BF_HIP(hipStreamSynchronize(s));
-    const unsigned long long *h0 = h.data(), *h1 = h.data() + bf::kLogHistBins;
+    const unsigned long long *h0 = (const unsigned long long *)p->h_out, *h1 = h0 + bf::kLogHistBins;
     unsigned long long before = 0;
     uint32_t bin = 0;
     if (p->fit_pass == 0) {
@@ -267,7 +259,7 @@ int finalize_log_clipped(bifeat_params *p, hipStream_t s) {
         for (int b = 0; b < bf::kLogHistBins; b++) n += h0[b];
         if (n == 0) {  // nothing but zeros / non-finite values
             p->e_min = p->e_max = 0.0;
-            return finish_log(p);
+            return finish_log(p, s);
         }
         const double f = p->clip_fraction;
         p->clip_rank[0] = (unsigned long long)floor(f * (double)(n - 1));
@@ -293,7 +285,7 @@ int finalize_log_clipped(bifeat_params *p, hipStream_t s) {
             memcpy(&hi, &p->clip_prefix[1], 4);
             p->e_min = log2((double)lo);
             p->e_max = log2((double)hi);
-            return finish_log(p);
+            return finish_log(p, s);
         }
     }
     p->fit_pass++;
@@ -437,8 +429,10 @@ int bifeat_fit_finalize(bifeat_params *p, void *stream) {
         return finalize_log_clipped(p, (hipStream_t)stream);
     } else {
         uint32_t st[2];
-        BF_HIP(hipMemcpyAsync(st, p->d_fit, sizeof(st), hipMemcpyDeviceToHost, (hipStream_t)stream));
+        bf::launch_export(p, p->d_fit, 2, (hipStream_t)stream);
+        BF_HIP(hipGetLastError());
         BF_HIP(hipStreamSynchronize((hipStream_t)stream));
+        memcpy(st, p->h_out, sizeof(st));
         float mmin, mmax;
         memcpy(&mmin, &st[0], 4);
         memcpy(&mmax, &st[1], 4);
@@ -448,10 +442,7 @@ int bifeat_fit_finalize(bifeat_params *p, void *stream) {
             p->e_min = log2((double)mmin);
             p->e_max = log2((double)mmax);
         }
-        build_log_tables(p);
-        int rc = upload_log(p);
-        if (rc) return rc;
-        p->host_valid = true;
+        return finish_log(p, (hipStream_t)stream);
     }
     p->fit_open = false;
     p->fitted = true;
@@ -506,13 +497,7 @@ int bifeat_params_set_log(bifeat_params *p, double e_min, double e_max) {
         return BIFEAT_EINVAL;
     p->e_min = e_min;
     p->e_max = e_max;
-    build_log_tables(p);
-    int rc = upload_log(p);
-    if (rc) return rc;
-    p->host_valid = true;
-    p->fitted = true;
-    p->fit_open = false;
-    return BIFEAT_OK;
+    return finish_log(p, nullptr);
 }
 
 int bifeat_params_get_log(bifeat_params *p, double *e_min, double *e_max, float *T, float *V) {
@@ -553,7 +538,7 @@ int bifeat_vq_distortion(bifeat_params *p, float *out, int32_t n) {
     if (!p->vq_seeded || p->vq_last_rows == 0) return BIFEAT_ENOTFIT;
     double tmp[64];
     BF_HIP(hipDeviceSynchronize());
-    BF_HIP(hipMemcpy(tmp, p->d_dist, sizeof(tmp), hipMemcpyDeviceToHost));
+    memcpy(tmp, p->h_out, sizeof(tmp));
     for (int k = 0; k < n; k++)
         out[k] = k < p->vq_last_rounds ? (float)(tmp[k] / (double)p->vq_last_rows) : 0.0f;
     return BIFEAT_OK;

@@ -60,6 +60,10 @@ struct bifeat_params {
     // mapped into the device's address space (h_status / d_status name the same word)
     int32_t *h_status = nullptr;
     int32_t *d_status = nullptr;
+    // after it, what a fit leaves on the device for the host to read (see launch_export): uniform [min | scale |
+    // inv | max] of up to kExportColumns columns, log the magnitudes' bits or the histograms, vq d_dist
+    uint8_t *h_out = nullptr;
+    float *d_out = nullptr;
 
     // launch tuning (0 = automatic)
     int opt_mean_slots = 0;
@@ -79,6 +83,7 @@ namespace bf {
 
 constexpr int kThreads = 256;
 constexpr int kLogHistBins = 2048;  // 11-bit digits of the clipped log fit
+constexpr int kExportColumns = 16384;
 // number of workgroups that fills the chip a few times over: 256 CUs x 8
 constexpr int kMaxBlocks = 2048;
 
@@ -86,6 +91,11 @@ hipError_t launch_fit_reset(bifeat_params *p, hipStream_t s);
 hipError_t launch_fit_update(bifeat_params *p, const void *chunk, int dtype, int64_t rows,
                              hipStream_t s);
 hipError_t launch_finalize_uniform(bifeat_params *p, hipStream_t s);
+// words of the device's memory into p->d_out: read there after a synchronisation, where each copy through
+// hipMemcpy takes 12 us of the host (small tables; a build of 25 677 x 768 floats 128 us, of them 55 for four)
+void launch_export(bifeat_params *p, const void *src, int words, hipStream_t s);
+// d_T, d_V and, for 1 and 2 bits, the table as per-column affine maps, from the host's tables
+void launch_log_tables(bifeat_params *p, hipStream_t s);
 void launch_log_hist_reset(bifeat_params *p, hipStream_t s);
 hipError_t launch_log_hist_update(bifeat_params *p, const void *chunk, int dtype, int64_t rows,
                                   hipStream_t s);

@@ -506,6 +506,7 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
                                                  : round((const __half *)chunk, p->d_dist + k);
         if (e != hipSuccess) return e;
     }
+    launch_export(p, p->d_dist, 128, s);  // (64 doubles)
     return hipGetLastError();
 }
 

@@ -1,0 +1,96 @@
+"""What a fit leaves for the host: parameters read through the handle's pinned block, by a copy beyond its columns,
+after a second fit, after one on another stream, and after a replayed graph of one."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from helpers import scheme_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(q, x, bits):
+    mn, mx = orc.fit_minmax(x)
+    scale, inv = orc.uniform_params(mn, mx, bits)
+    for got, want in zip(q.params_get_uniform(), (mn, mx, scale, inv)):
+        assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("D", [1, 255, 768, 16384, 16385])
+def test_uniform(D):
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(D)
+    q = bf.Quantizer(scheme_of("uniform", 4), D)
+    for k in range(3):
+        x = (rng.normal(size=(7, D)) * 10.0 ** k).astype(np.float32)
+        t = torch.from_numpy(x).cuda()
+        with torch.cuda.stream(torch.cuda.Stream() if k == 1 else torch.cuda.current_stream()):
+            torch.cuda.synchronize()
+            q.fit_reset()
+            q.fit_update(t)
+            q.fit_finalize()
+        _check(q, x, 4)
+        _check(q, x, 4)     # (from the host's copy)
+    q.params_set_uniform(x[0], x[0] + 1)
+    assert np.array_equal(q.params_get_uniform()[0], x[0])
+
+
+def test_uniform_replayed():
+    import torch
+    import paper_2207_14696_amd as bf
+    x = np.random.default_rng(1).normal(size=(100, 64)).astype(np.float32)
+    t = torch.from_numpy(x).cuda()
+    q = bf.Quantizer(scheme_of("uniform", 8), 64)
+    for _ in range(2):
+        q.fit_reset()
+        q.fit_update(t)
+        q.fit_finalize()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        q.fit_reset()
+        q.fit_update(t)
+        q.fit_finalize()
+    for k in range(3):
+        y = (x * (k + 2)).astype(np.float32)
+        t.copy_(torch.from_numpy(y))
+        g.replay()
+        q.fit_reset()       # (the host's copy is of the fit before)
+        q.fit_update(t)
+        q.fit_finalize()
+        _check(q, y, 8)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+@pytest.mark.parametrize("clip", [0.0, 0.02])
+def test_log(bits, clip):
+    import torch
+    import paper_2207_14696_amd as bf
+    D = 300     # (more columns than the tables have entries)
+    q = bf.Quantizer(scheme_of("log", bits), D)
+    if clip:
+        q.fit_set_log_clip(clip)
+    for k in range(2):
+        x = (np.random.default_rng(k).normal(size=(400, D)) * 3.0 ** k).astype(np.float32)
+        t = torch.from_numpy(x).cuda()
+        q.fit_reset()
+        q.fit_update(t)
+        while q.fit_finalize():
+            q.fit_update(t)
+        e_min, e_max, T, V = q.params_get_log()
+        mag = np.sort(np.abs(x[x != 0]))
+        lo, hi = mag[int(np.floor(clip * (mag.size - 1)))], mag[int(np.ceil((1 - clip) * (mag.size - 1)))]
+        assert (e_min, e_max) == (pytest.approx(np.log2(np.float64(lo)), abs=1e-12), pytest.approx(np.log2(np.float64(hi)), abs=1e-12))
+        codes = torch.zeros(400, q.row_bytes, dtype=torch.uint8, device="cuda")
+        q.quantize(t, codes, 0)
+        idx = torch.arange(400, device="cuda")
+        rows = q.gather_dequant(codes, idx).cpu().numpy()
+        level = np.searchsorted(T, np.abs(x), side="right")
+        half = 1 << (bits - 1)
+        want = V[np.where(x > 0, half + level, half - 1 - level)]
+        assert np.array_equal(rows, want)
+        # the same tables as per-column maps: means of 1- and 2-bit codes
+        ptr = torch.arange(0, 401, 4, device="cuda")
+        mean = q.gather_mean(codes, ptr, idx).cpu().numpy()
+        np.testing.assert_allclose(mean, want.reshape(100, 4, D).astype(np.float64).mean(1), rtol=0, atol=2e-6 * np.abs(V).max())
