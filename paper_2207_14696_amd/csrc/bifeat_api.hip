@@ -58,12 +58,12 @@ int ensure_device(bifeat_params *p) {
     BF_HIP(hipGetDevice(&p->device));
     const int64_t D = p->D;
     size_t nfloat = 0, nfit = 0;
-    if (p->scheme.kind == BIFEAT_SQ_UNIFORM) { nfloat = 4 * D; nfit = 2 * D; }
+    if (p->scheme.kind == BIFEAT_SQ_UNIFORM) { nfloat = 4 * D; nfit = bf::fit_copies(D) * 2 * D; }
     else if (p->scheme.kind == BIFEAT_SQ_LOG) {
         // bin edges, decode table and, for 1-bit codes, the table again as a per-column
         // affine map (decode = V[0] + q*(V[1]-V[0])) for the integer-sum mean kernels
         nfloat = 128 + 256 + (p->scheme.bits == 1 ? 2 * D : p->scheme.bits == 2 ? 4 * D : 0);
-        nfit = 4 + 2 * 2 * bf::kLogHistBins;
+        nfit = bf::kFitCopies * bf::kFitMagStride + 2 * 2 * bf::kLogHistBins;
     }
     else nfloat = (size_t)p->P * p->scheme.vq_length * (2 * p->scheme.vq_width + 2) + 128;
     nfloat = (nfloat + 3) / 4 * 4;
@@ -97,7 +97,7 @@ int ensure_device(bifeat_params *p) {
         p->d_dist = reinterpret_cast<double *>(p->d_train + ncb + nent);  // an even number of floats in
     }
     p->d_fit = reinterpret_cast<int32_t *>(p->d_block + nfloat);
-    if (p->scheme.kind == BIFEAT_SQ_LOG) p->d_hist = reinterpret_cast<unsigned long long *>(p->d_fit + 4);
+    if (p->scheme.kind == BIFEAT_SQ_LOG) p->d_hist = reinterpret_cast<unsigned long long *>(p->d_fit + bf::kFitCopies * bf::kFitMagStride);
     p->d_zero = reinterpret_cast<uint8_t *>(p->d_fit + nfit);
     // the status word: pinned host memory that the kernels write through its device mapping
     // with room for what a fit leaves for the host
@@ -428,14 +428,16 @@ int bifeat_fit_finalize(bifeat_params *p, void *stream) {
     } else if (p->clip_fraction > 0.0) {
         return finalize_log_clipped(p, (hipStream_t)stream);
     } else {
-        uint32_t st[2];
-        bf::launch_export(p, p->d_fit, 2, (hipStream_t)stream);
+        bf::launch_export(p, p->d_fit, bf::kFitCopies * bf::kFitMagStride, (hipStream_t)stream);
         BF_HIP(hipGetLastError());
         BF_HIP(hipStreamSynchronize((hipStream_t)stream));
-        memcpy(st, p->h_out, sizeof(st));
-        float mmin, mmax;
-        memcpy(&mmin, &st[0], 4);
-        memcpy(&mmax, &st[1], 4);
+        float mmin = INFINITY, mmax = 0.0f;
+        for (int c = 0; c < bf::kFitCopies; c++) {
+            float m[2];
+            memcpy(m, p->h_out + 4 * c * bf::kFitMagStride, sizeof(m));
+            mmin = fminf(mmin, m[0]);
+            mmax = fmaxf(mmax, m[1]);
+        }
         if (!(mmax > 0.0f)) {  // all-zero table
             p->e_min = p->e_max = 0.0;
         } else {

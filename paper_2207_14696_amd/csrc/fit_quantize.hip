@@ -13,8 +13,10 @@
 namespace bf {
 
 // ------------------------------------------------------------------ fit state
-__global__ void fit_reset_kernel(int32_t *state, int n_half, int32_t a, int32_t b) {
+// copy blockIdx.y of the state, `stride` words from one to the next
+__global__ void fit_reset_kernel(int32_t *state, int stride, int n_half, int32_t a, int32_t b) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
+    state += (int64_t)blockIdx.y * stride;
     if (i < n_half) {
         state[i] = a;
         state[n_half + i] = b;
@@ -24,10 +26,10 @@ __global__ void fit_reset_kernel(int32_t *state, int n_half, int32_t a, int32_t 
 hipError_t launch_fit_reset(bifeat_params *p, hipStream_t s) {
     if (p->scheme.kind == BIFEAT_SQ_UNIFORM) {
         int D = (int)p->D;
-        fit_reset_kernel<<<(D + 255) / 256, 256, 0, s>>>(p->d_fit, D, kKeyPosInf, kKeyNegInf);
+        fit_reset_kernel<<<dim3((D + 255) / 256, fit_copies(D)), 256, 0, s>>>(p->d_fit, 2 * D, D, kKeyPosInf, kKeyNegInf);
     } else {
         // log: [0] = smallest nonzero |x| (bits of +inf), [1] = largest finite |x| (0)
-        fit_reset_kernel<<<1, 64, 0, s>>>(p->d_fit, 1, 0x7F800000, 0);
+        fit_reset_kernel<<<dim3(1, kFitCopies), 64, 0, s>>>(p->d_fit, kFitMagStride, 1, 0x7F800000, 0);
     }
     return hipGetLastError();
 }
@@ -91,11 +93,17 @@ hipError_t launch_fit_update(bifeat_params *p, const void *chunk, int dtype, int
 
 // scale_j = (max_j - min_j)/L and inv_j = L/(max_j - min_j): fp64 subtraction
 // and division, one rounding to fp32; 0 for a constant column; zeros as +0.
-__global__ void finalize_uniform_kernel(const int32_t *state, int D, int bits, float *mn,
+__global__ void finalize_uniform_kernel(const int32_t *state, int copies, int D, int bits, float *mn,
                                         float *mx, float *scale, float *inv, float *host) {
     int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= D) return;
-    float lo = key_float(state[j]), hi = key_float(state[D + j]);
+    int32_t lo_k = state[j], hi_k = state[D + j];
+#pragma unroll 8
+    for (int c = 1; c < copies; c++) {
+        lo_k = min(lo_k, state[(int64_t)c * 2 * D + j]);
+        hi_k = max(hi_k, state[(int64_t)c * 2 * D + D + j]);
+    }
+    float lo = key_float(lo_k), hi = key_float(hi_k);
     if (lo == 0.0f) lo = 0.0f;
     if (hi == 0.0f) hi = 0.0f;
     double L = (double)((1u << bits) - 1u);
@@ -161,7 +169,7 @@ void launch_log_tables(bifeat_params *p, hipStream_t s) {
 
 hipError_t launch_finalize_uniform(bifeat_params *p, hipStream_t s) {
     int D = (int)p->D;
-    finalize_uniform_kernel<<<(D + 255) / 256, 256, 0, s>>>(p->d_fit, D, p->scheme.bits, p->d_min,
+    finalize_uniform_kernel<<<(D + 63) / 64, 64, 0, s>>>(p->d_fit, fit_copies(D), D, p->scheme.bits, p->d_min,
                                                             p->d_max, p->d_scale, p->d_inv, p->d_out);
     return hipGetLastError();
 }

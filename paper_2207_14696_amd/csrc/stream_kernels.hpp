@@ -43,10 +43,10 @@ struct ChunkSrc {
 template <class Src>
 constexpr bool kHalfChunk = std::is_same<Src, ChunkSrc<__half>>::value;
 
-// The fit kernels end with atomics on a few words (2*D of them, or two), and the workgroups of a
-// launch come to that end together: 2048 workgroups of 256 threads spent 80 of 210 us there (a
-// 524 288 x 768 half-precision chunk; the read alone takes 130).  So there are few workgroups, of
-// 1024 threads: two per CU.  That chunk's range with its reset: 245 -> 168 us; the extreme
+// The fit kernels end with atomics on a few words (2*D of them, or two, in kFitCopies copies), and the
+// workgroups of a launch come to that end together: 2048 workgroups of 256 threads spent 80 of 210 us there
+// (a 524 288 x 768 half-precision chunk and one copy; the read alone takes 130).  So there are few workgroups,
+// of 1024 threads: two per CU.  That chunk's range with its reset: 245 -> 168 us; the extreme
 // magnitudes of 1 M x 128 floats 234 -> 102 us, of half-precision values 210 -> 51 us (4 atomics a
 // workgroup on two words before, at most 2 now).
 constexpr int kFitThreads = 1024;
@@ -82,7 +82,7 @@ __device__ inline void merge_magnitudes(uint32_t mmin, uint32_t mmax, int32_t *s
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t *st = reinterpret_cast<uint32_t *>(state);
+        uint32_t *st = reinterpret_cast<uint32_t *>(state) + blockIdx.x % kFitCopies * kFitMagStride;
         if (s_mm[0] < __builtin_nontemporal_load(&st[0])) atomicMin(&st[0], s_mm[0]);
         if (s_mm[1] > __builtin_nontemporal_load(&st[1])) atomicMax(&st[1], s_mm[1]);
     }
@@ -95,6 +95,7 @@ template <class Src, int VEC, int TH>
 __global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, int D, int G, int32_t *state,
                                                         int use_lds) {
     extern __shared__ int32_t lds[];
+    if (use_lds) state += blockIdx.x % kFitCopies * 2 * D;
     if (use_lds) {
         for (int i = threadIdx.x; i < D; i += TH) {
             lds[i] = kKeyPosInf;
@@ -445,7 +446,7 @@ template <class Src>
 inline hipError_t launch_fit_minmax_src(bifeat_params *p, const Src &src, int64_t rows, bool vec,
                                         hipStream_t s) {
     const int D = (int)p->D;
-    const int use_lds = D <= 8192;
+    const int use_lds = D <= kFitCopiesColumns;
     // (columns merged without LDS, an atomic per thread and column: twice as many of them by 8 columns,
     // 5 242 rows of 20 000 half-precision columns 63 us, 185 by 8; few columns, merged in few words of
     // LDS: 524 288 rows of 24 6.4 us, 8.9 by 8)

@@ -94,3 +94,28 @@ def test_log(bits, clip):
         ptr = torch.arange(0, 401, 4, device="cuda")
         mean = q.gather_mean(codes, ptr, idx).cpu().numpy()
         np.testing.assert_allclose(mean, want.reshape(100, 4, D).astype(np.float64).mean(1), rtol=0, atol=2e-6 * np.abs(V).max())
+
+
+# running states in copies: fewer workgroups than copies, more, the last columns with copies and the first without,
+# extremes that only one workgroup sees
+@pytest.mark.parametrize("rows,D", [(3, 5), (900, 64), (200_000, 3), (5000, 601), (3000, 8192), (300, 8196), (3, 8193)])
+@pytest.mark.parametrize("half", [False, True])
+def test_copies(rows, D, half):
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(rows + D)
+    x = rng.normal(size=(rows, D)).astype(np.float16 if half else np.float32)
+    x[rng.integers(rows, size=D), np.arange(D)] = 9.0 + np.arange(D) % 50
+    x[rng.integers(rows, size=D), np.arange(D)] = -9.0 - np.arange(D) % 60
+    t = torch.from_numpy(x).cuda()
+    cut = rows // 3
+    q = bf.Quantizer(scheme_of("uniform", 8), D)
+    g = bf.Quantizer(scheme_of("log", 8), D)
+    for chunk in (t[:cut], t[cut:].contiguous()):
+        q.fit_update(chunk)
+        g.fit_update(chunk)
+    q.fit_finalize()
+    g.fit_finalize()
+    _check(q, x.astype(np.float32), 8)
+    mag = np.abs(x[x != 0].astype(np.float64))
+    assert g.params_get_log()[:2] == (pytest.approx(np.log2(mag.min()), abs=1e-12), pytest.approx(np.log2(mag.max()), abs=1e-12))
