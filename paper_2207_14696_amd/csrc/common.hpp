@@ -228,6 +228,18 @@ __device__ inline float4 load4(const __half *p) {
     float2 fa = __half22float2(a), fb = __half22float2(b);
     return make_float4(fa.x, fa.y, fb.x, fb.y);
 }
+// the same wherever the row begins: one load, of 4-byte (half precision: 2-byte) alignment
+struct __attribute__((packed, aligned(4))) FourFloats { float x, y, z, w; };
+struct __attribute__((packed, aligned(2))) FourHalves { uint32_t a, b; };
+__device__ inline float4 load4_any(const float *p) {
+    const FourFloats v = *reinterpret_cast<const FourFloats *>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ inline float4 load4_any(const __half *p) {
+    const FourHalves v = *reinterpret_cast<const FourHalves *>(p);
+    const float2 a = __half22float2(__builtin_bit_cast(__half2, v.a)), b = __half22float2(__builtin_bit_cast(__half2, v.b));
+    return make_float4(a.x, a.y, b.x, b.y);
+}
 // 8 consecutive elements (16 bytes of half precision)
 __device__ inline void load8(const __half *p, float (&v)[8]) {
     const uint4 u = *reinterpret_cast<const uint4 *>(p);

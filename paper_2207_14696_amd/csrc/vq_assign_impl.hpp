@@ -44,9 +44,17 @@ __global__ __launch_bounds__(kThreads) void vq_assign_kernel(
         const int64_t r = r0 + threadIdx.x;
         const bool valid = r < rows;
         float sub[WMAX];
+        if (W % 4 == 0 && W > 0 && p * W + W <= D) {  // (a row of 64 lanes is 64 lines, whatever is loaded of each)
 #pragma unroll
-        for (int d = 0; d < WMAX; d++)
-            sub[d] = (valid && d < w && p * w + d < D) ? load1(x + r * D + (int64_t)p * w + d) : 0.0f;
+            for (int d = 0; d < WMAX; d += 4) {
+                const float4 q = valid ? load4_any(x + r * D + (int64_t)p * W + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+                sub[d] = q.x; sub[(d + 1) % WMAX] = q.y; sub[(d + 2) % WMAX] = q.z; sub[(d + 3) % WMAX] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int d = 0; d < WMAX; d++)
+                sub[d] = (valid && d < w && p * w + d < D) ? load1(x + r * D + (int64_t)p * w + d) : 0.0f;
+        }
         int best = 0;
         float bestv = METRIC == BIFEAT_VQ_COSINE ? -INFINITY : INFINITY;
         for (int e0 = 0; e0 < len; e0 += EC) {

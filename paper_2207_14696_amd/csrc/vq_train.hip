@@ -202,6 +202,7 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
         next = set + (r.sub > 1 ? r.sets : r.groups);
         const int64_t begin = sub * r.share, end = min(set_rows(set, r.sets, r.strip_log2, rows), begin + r.share);
         if constexpr (VEC) {
+            // (rows that begin anywhere; `left` ends in the middle of a four in the last part only)
             // `lanes` lanes (a power of two that divides the fours of columns) share a row: fewer lines an
             // instruction; a lane has kAccRows rows in flight
             const int lq = threadIdx.x & (lanes - 1), at = threadIdx.x / lanes, step = TH / lanes;
@@ -219,7 +220,14 @@ __global__ __launch_bounds__(kAccThreads) void vq_accumulate_codes_kernel(
                     for (int k = 0; k < kAccRows; k++) {
                         v[k] = e[k] = make_float4(0.f, 0.f, 0.f, 0.f);
                         if (code[k] < 0) continue;
-                        if (j < left) v[k] = load4(x + row[k] * D + (int64_t)p * w + c0 + j);
+                        const T *src = x + row[k] * D + (int64_t)p * w + c0 + j;
+                        if (j + 4 <= left) {
+                            v[k] = load4_any(src);
+                        } else if (j < left) {
+                            v[k].x = load1(src);
+                            if (j + 1 < left) v[k].y = load1(src + 1);
+                            if (j + 2 < left) v[k].z = load1(src + 2);
+                        }
                         e[k] = load4(cb + ((int64_t)p * len + code[k]) * w + c0 + j);
                     }
 #pragma unroll
@@ -363,8 +371,8 @@ hipError_t lloyd_round_generic(bifeat_params *p, const T *x, int64_t rows, doubl
     if (!all) launch_vq_zero(p->d_train, books + (int64_t)P * len, s);
     if (p->scheme.vq_metric == BIFEAT_VQ_COSINE) launch_vq_rnorm(p, s);
     launch_vq_assign_parts(p, x, rows, p->d_scratch, s);
-    // 4 columns at a time: whole fours everywhere, and where they lie
-    const bool vec = g.DG % 4 == 0 && w % 4 == 0 && p->D % 4 == 0 && (uintptr_t)x % (4 * sizeof(T)) == 0;
+    // 4 columns at a time: whole fours of parts and of groups
+    const bool vec = g.DG % 4 == 0 && w % 4 == 0;
     const bool ok = p->cbytes == 1
                         ? (vec ? accumulate_codes<T, uint8_t, true>(p, x, rows, g, !all, sums, counts, distortion, s)
                                : accumulate_codes<T, uint8_t, false>(p, x, rows, g, !all, sums, counts, distortion, s))
