@@ -3,7 +3,9 @@
 // and the row-length reduction of the scale profile (Appendix A.1, A.5).
 //
 // Both are row gathers bound by memory: a row of D floats is fetched whole, 16 bytes per
-// lane, several rows in flight per lane.
+// lane, several rows in flight per lane.  Rows of a number of columns that is no multiple of four
+// begin anywhere; their last lane then takes the row's last four columns, some of them its neighbour's too,
+// with the same sums.  With 4 bytes per lane there, 147 743 rows of 101 columns took 197 us, 122 so.
 #include "common.hpp"
 
 #include <algorithm>
@@ -12,7 +14,7 @@ namespace bf {
 namespace {
 
 constexpr int kAggInFlight = 4;  // rows that a lane adds up while as many travel
-constexpr int kMaxLists = 6;     // consecutive destinations of a lane group at most
+constexpr int kMaxLists = 3;     // destinations of a lane group at most
 // A list longer than kLong is not walked by one lane group (a hub's thousands of rows,
 // one latency after the other, would outlast the rest of the launch): it is cut into
 // pieces of kSub list entries that many groups sum side by side.  A workgroup of that
@@ -26,15 +28,8 @@ constexpr int kLong = 256;
 constexpr int kRange = 2048;
 constexpr int kSub = 64;
 constexpr int kMaxLong = kRange / kLong + 2;
-// Columns that a workgroup adds up at a time, and the sums it has room for: a tile of 16-byte lanes
-// (20 KB); where rows allow 4-byte lanes only, four tiles, one for each of the workgroup's four lane
-// groups - one at a time takes barriers every 64 columns and the groups apart: 100 000 rows of 601
-// columns with hubs 843 us against 666 (every piece with atomics of its own, in 32 bits: 624) - or three where more than 7 lists
-// overlap a range (15 KB; with 20 a CU holds one workgroup less, 1.5 % on launches of short lists).
-template <int VEC>
-constexpr int kSums = kMaxLong * (VEC == 4 ? 256 : 192);
-template <int VEC>
-__device__ inline int pass_tiles(int n_long) { return VEC == 4 ? 1 : n_long <= 7 ? 4 : 3; }
+// The sums a workgroup has room for: a tile of 16-byte lanes (20 KB), which it adds up at a time.
+constexpr int kSums = kMaxLong * 256;
 
 // Compensated (Kahan) running sums: the rounding error of a sum stays at a couple of
 // ulps of the mean magnitude whatever the list length; the kernel waits on memory, so
@@ -59,7 +54,7 @@ template <>
 struct Acc<4> {
     float4 v, c;
     __device__ void zero() { v = c = make_float4(0.f, 0.f, 0.f, 0.f); }
-    __device__ static float4 load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+    __device__ static float4 load(const float *p) { return load4_any(p); }
     __device__ static void hold(float4 &r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
     __device__ void add(const float4 r) {
         kahan_add(v.x, c.x, r.x);
@@ -75,13 +70,13 @@ struct Acc<4> {
             const float d = (float)n;
             o = n > 0 ? make_float4(o.x / d, o.y / d, o.z / d, o.w / d) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        store_stream(reinterpret_cast<float4 *>(p), o);
+        store4_any(p, o);
     }
-    // this piece's sum
-    __device__ void add_to(double *p) const {
-        unsafeAtomicAdd(p + 0, kahan_sum(v.x, c.x));
-        unsafeAtomicAdd(p + 1, kahan_sum(v.y, c.y));
-        unsafeAtomicAdd(p + 2, kahan_sum(v.z, c.z));
+    // this piece's sum, without its first `skip` columns
+    __device__ void add_to(double *p, int skip) const {
+        if (skip < 1) unsafeAtomicAdd(p + 0, kahan_sum(v.x, c.x));
+        if (skip < 2) unsafeAtomicAdd(p + 1, kahan_sum(v.y, c.y));
+        if (skip < 3) unsafeAtomicAdd(p + 2, kahan_sum(v.z, c.z));
         unsafeAtomicAdd(p + 3, kahan_sum(v.w, c.w));
     }
 };
@@ -97,7 +92,7 @@ struct Acc<1> {
     __device__ static void store(float o, float *p, int n, bool sum) {
         __builtin_nontemporal_store(sum ? o : (n > 0 ? o / (float)n : 0.f), p);
     }
-    __device__ void add_to(double *p) const { unsafeAtomicAdd(p, kahan_sum(v, c)); }
+    __device__ void add_to(double *p, int) const { unsafeAtomicAdd(p, kahan_sum(v, c)); }
 };
 
 // a 64-bit value of the wave's lane `at / 4`
@@ -122,16 +117,19 @@ __device__ inline void add_rows(Acc<VEC> &acc, const float *__restrict__ base, i
 }
 
 // The lists of up to kLong entries.  A group of `lpr` lanes (a power of two up to 64)
-// owns a column tile of `lists` consecutive destinations at a time: lane t of the group accumulates
+// owns a column tile of `lists` destinations, V / lists apart: lane t of the group accumulates
 // columns VEC*(tile*lpr + t) .. +VEC-1 over each destination's list, in list order
 // (fp32, compensated).  Items are numbered tile-fastest.  Long lists are left to long_lists().
 // What bounds it is how many rows are in flight: 2^20 rows of 100 columns, 17 M entries, ask for 6.9 GB
-// beyond the L2s, which move 7.4 TB/s of such lines at most.  The lists between two long ones are one
-// run of `indices`, whose rows travel 4 by 4 wherever a list begins and ends (most have 3 to 8 entries),
+// beyond the L2s, which move 7.4 TB/s of such lines at most.  The group's lists are one run of entries,
+// whose rows travel 4 by 4 wherever a list begins and ends (most have 3 to 8 entries),
 // the next 4 while these are added.  The group fetches lpr entries with one load and hands the rows'
 // places round by lane exchange; a list's sum waits in LDS until the item's rows have been
 // read, as loads issued behind a store return behind it.  That launch: 1070 us with a list at a time, 4
-// rows in flight and every entry loaded by all lanes, 960 so; 500 000 rows of 37 columns 233 and 145.
+// rows in flight and every entry loaded by all lanes, 970 so; 310 237 rows of 128 columns 303 and 277.
+// Consecutive destinations instead share the loads of their bounds and entries (6 of them: 953 us a round), but lists of nearly
+// kLong entries tend to be neighbours, and one group's chain of them outlasts the launch (417 408 rows of 64
+// columns 318 us, 137 so; 55 456 of 100 sorted by degree 217, 77).
 template <int VEC>
 __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
                                    const int64_t *__restrict__ indptr,
@@ -144,44 +142,54 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
     const int lpr = 1 << lpr_log2;
     const int lane = threadIdx.x & 63, t = lane & (lpr - 1), first = lane & ~(lpr - 1);
     const int64_t groups = (nblocks * kThreads) >> lpr_log2;
-    const int64_t items = (V + lists - 1) / lists * tiles;
+    const int64_t step = (V + lists - 1) / lists, items = step * tiles;
     for (int64_t item = (block * kThreads + threadIdx.x) >> lpr_log2; item < items; item += groups) {
-        const int64_t vg = item / tiles, v0 = vg * lists;
-        const int tile = (int)(item - vg * tiles);
-        const int64_t col = (int64_t)VEC * (tile * lpr + t);
-        const bool in = col < D;  // (the other lanes read column 0 and write nothing)
-        const int nv = (int)min((int64_t)lists, V - v0);
-        // lane t: the t-th destination's bounds (lists < lpr)
-        const int64_t bound = indptr[v0 + min(t, nv)];
-        const int64_t after = from_lane(bound, 4 * (first + min(t + 1, lpr - 1)));
-        // (bit k: list k is a long one)
-        const uint32_t longs = (uint32_t)(__ballot(t < nv && after - bound > kLong) >> first);
-        const float *src = x + (in ? col : 0);
-        for (int i = 0; i < nv;) {
-            if ((longs >> i) & 1u) { i++; continue; }
-            const int j = i + __ffs((longs >> i) | (1u << (nv - i))) - 1;  // lists i .. j-1 are short
-            const int64_t base = from_lane(bound, 4 * (first + i));
-            const int rel = (int)(bound - base);  // (lanes i .. j)
-            const int n = __builtin_amdgcn_ds_bpermute(4 * (first + j), rel);
-            int end = __builtin_amdgcn_ds_bpermute(4 * (first + i + 1), rel);
-            Acc<VEC> acc;
+        const int64_t v0 = item / tiles;
+        const int tile = (int)(item - v0 * tiles);
+        const int64_t col0 = (int64_t)VEC * (tile * lpr + t), col = min(col0, D - VEC);
+        const bool in = col0 < D;  // (the other lanes read a row's end and write nothing)
+        // lane t: the t-th destination's list (lists < lpr), none for a long one
+        const int64_t v = v0 + t * step;
+        const bool mine = t < lists && v < V;
+        const int64_t beg = mine ? indptr[v] : 0;
+        const int all = mine ? (int)min(indptr[v + 1] - beg, (int64_t)kLong + 1) : kLong + 1;
+        const int len = all <= kLong ? all : 0;
+        // where it begins in the run of all of them (from lane `lists` on: the run's end)
+        int rel = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxLists; k++) {
+            const int len_k = __builtin_amdgcn_ds_bpermute(4 * (first + k), len);
+            rel += t > k ? len_k : 0;
+        }
+        const int64_t shift = beg - rel;
+        const int n = __builtin_amdgcn_ds_bpermute(4 * (first + lists), rel);
+        const float *src = x + col;
+        int i = 0, end = __builtin_amdgcn_ds_bpermute(4 * (first + 1), rel);
+        Acc<VEC> acc;
+        acc.zero();
+        auto close = [&]() {  // list i is complete
+            acc.park(s_sum, i);
+            i++;
+            end = i < lists ? __builtin_amdgcn_ds_bpermute(4 * (first + i + 1), rel) : 0x7FFFFFFF;
             acc.zero();
-            auto close = [&]() {  // list i is complete
-                acc.park(s_sum, i);
-                i++;
-                end = i < j ? __builtin_amdgcn_ds_bpermute(4 * (first + i + 1), rel) : 0x7FFFFFFF;
-                acc.zero();
+        };
+        while (end == 0) close();
+        if (n > 0) {
+            // place of the row of the run's e-th entry (past the last one: the last)
+            auto place = [&](int e) {
+                e = min(e, n - 1);
+                int k = 0;
+#pragma unroll
+                for (int j = 1; j < kMaxLists; j++) k += e >= __builtin_amdgcn_ds_bpermute(4 * (first + j), rel);
+                return indices[from_lane(shift, 4 * (first + k)) + e] * D;
             };
-            while (end == 0) close();
-            if (n == 0) continue;
-            const int64_t *ind = indices + base;
-            // places of the rows of this chunk of lpr entries, of the next one (past the last entry: the last)
-            int64_t off = ind[min(t, n - 1)] * D, off1 = ind[min(lpr + t, n - 1)] * D;
+            // of this chunk of lpr entries, and of the next one
+            int64_t off = place(t), off1 = place(lpr + t);
             Row r[2][U];
             auto rows = [&](Row (&to)[U], int e) {  // entries e .. e + U - 1 travel
                 if (e > 0 && (e & (lpr - 1)) == 0) {
                     off = off1;
-                    off1 = ind[min(e + lpr + t, n - 1)] * D;
+                    off1 = place(e + lpr + t);
                 }
 #pragma unroll
                 for (int u = 0; u < U; u++)
@@ -214,9 +222,9 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
                 if (second) take(r[1], e + U);
             }
         }
-        for (int k = 0; k < nv; k++) {
-            const int64_t len = from_lane(after, 4 * (first + k)) - from_lane(bound, 4 * (first + k));
-            if (in && len <= kLong) Acc<VEC>::store(Acc<VEC>::parked(s_sum, k), out + (v0 + k) * D + col, (int)len, sum != 0);
+        for (int k = 0; k < lists; k++) {
+            const int n_k = __builtin_amdgcn_ds_bpermute(4 * (first + k), all);  // (more than kLong: none, or a long one)
+            if (in && n_k <= kLong) Acc<VEC>::store(Acc<VEC>::parked(s_sum, k), out + (v0 + k * step) * D + col, n_k, sum != 0);
         }
     }
 }
@@ -229,10 +237,10 @@ __device__ inline void short_lists_narrow(const float *__restrict__ x, int64_t D
                                           const int64_t *__restrict__ indptr,
                                           const int64_t *__restrict__ indices, int64_t V, int sum,
                                           float *__restrict__ out, int64_t block, int64_t nblocks) {
-    const int64_t col = (int64_t)VEC * (threadIdx.x & 3);
+    const int64_t col0 = (int64_t)VEC * (threadIdx.x & 3), col = min(col0, D - VEC);
     for (int64_t v = (block * kThreads + threadIdx.x) >> 2; v < V; v += (nblocks * kThreads) >> 2) {
         const int64_t beg = indptr[v], end = indptr[v + 1];
-        if (col >= D || end - beg > kLong) continue;
+        if (col0 >= D || end - beg > kLong) continue;
         Acc<VEC> acc;
         acc.zero();
         add_rows<VEC, kAggInFlight>(acc, x + col, D, indices, beg, end);
@@ -307,28 +315,25 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
         }
         const int n_long = s_n < kMaxLong ? s_n : kMaxLong;
         const int tile_cols = lpr * VEC;
-        // neighbouring groups work on neighbouring tiles of a pass
-        const int pass = pass_tiles<VEC>(n_long);
-        for (int t0 = 0; t0 < tiles && n_long > 0; t0 += pass) {
-            const int nt = min(tiles - t0, pass);
-            const int width = nt * tile_cols;
-            for (int i = threadIdx.x; i < n_long * width; i += kThreads) s_sum[i] = 0.0;
+        for (int tile = 0; tile < tiles && n_long > 0; tile++) {
+            for (int i = threadIdx.x; i < n_long * tile_cols; i += kThreads) s_sum[i] = 0.0;
             __syncthreads();
-            for (int it = group; it < n_long * kPieces * nt; it += groups) {
-                const int tile = it % nt, piece = it / nt % kPieces, k = it / (nt * kPieces);
+            for (int it = group; it < n_long * kPieces; it += groups) {
+                const int piece = it % kPieces, k = it / kPieces;
                 const int64_t b = s_beg[k] + (int64_t)piece * kSub;
-                const int64_t col = (int64_t)VEC * ((t0 + tile) * lpr + t);
+                const int64_t col0 = (int64_t)VEC * (tile * lpr + t), col = min(col0, D - VEC);
                 if (b >= s_end[k]) continue;
-                const bool in = col < D;
+                const bool in = col0 < D;
                 Acc<VEC> acc;
                 acc.zero();
                 if (in) add_rows<VEC, 2 * kAggInFlight>(acc, x + col, D, indices, b, min(b + kSub, s_end[k]));
-                if (in) acc.add_to(s_sum + k * width + tile * tile_cols + VEC * t);
+                const int skip = (int)(col0 - col);
+                if (in) acc.add_to(s_sum + k * tile_cols + VEC * t - skip, skip);
             }
             __syncthreads();
-            for (int i = threadIdx.x; i < n_long * width; i += kThreads) {
-                const int k = i / width;
-                const int64_t col = (int64_t)t0 * tile_cols + (i - k * width);
+            for (int i = threadIdx.x; i < n_long * tile_cols; i += kThreads) {
+                const int k = i / tile_cols;
+                const int64_t col = (int64_t)tile * tile_cols + (i - k * tile_cols);
                 if (col < D)
                     unsafeAtomicAdd(out + s_v[k] * D + col, (float)(sum ? s_sum[i] : s_sum[i] / (double)s_deg[k]));
             }
@@ -363,10 +368,8 @@ __device__ inline void aggregate(const float *__restrict__ x, int64_t D, const i
 // lists, 10^6 rows of 8 columns, take 210 us instead of 197)
 __global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_kernel4, 4, false)
 __global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_narrow_kernel4, 4, true)
-// (with the 96 SGPRs it would take a SIMD holds 7 waves instead of 8, and launches without a long
-// list, 200 000 rows of 101 columns, take 289 us instead of 268)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_sgpr(80))) BF_AGG(aggregate_rows_kernel1, 1, false)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_sgpr(80))) BF_AGG(aggregate_rows_narrow_kernel1, 1, true)
+// (up to 3 columns)
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_narrow_kernel1, 1, true)
 #undef BF_AGG
 
 // Output rows of the long lists set to zero ahead of the launch above: a lane per
@@ -435,18 +438,17 @@ bool vec_ok(const void *a, const void *b, int64_t D) {
 hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indptr,
                                  const int64_t *indices, int64_t V, int64_t E, int sum, float *out,
                                  hipStream_t s) {
-    const bool vec = vec_ok(x, out, D);
-    const int64_t granules = vec ? D / 4 : D;
+    const bool vec = D >= 4;
+    const int64_t granules = vec ? (D + 3) / 4 : D;
     int lpr_log2 = 2;  // at least four lanes per row
     while (lpr_log2 < 6 && ((int64_t)1 << lpr_log2) < granules) lpr_log2++;
     const int64_t tiles = (granules + ((int64_t)1 << lpr_log2) - 1) >> lpr_log2;
-    // Several lists a group only where the chip has enough of them at a time (us with 1, 2, 4, 6 of them: 10^6
-    // rows of 64 columns 538, 459, 452, 454; 500 000 of 37 271, 207, 176, 160; 100 000 of 64, 25 000 waves by one,
-    // 68, 68, 90; 20 000 of 100 58, 59, 72); of 8 lanes a row 3 (10^6 of 32 columns 2, 3, 6: 263, 261, 284), of
-    // wide rows 2 (300 000 of 768 2, 3, 6: 1607, 1632, 1652)
+    // Several lists a group only where the chip has enough of them at a time (us with 1, 2, 3, 4, 6 of them: 2^20
+    // rows of 64 columns 776, 680, 595, 566, 575, of 100 1174, 1017, 973, 993, 992; 417 408 of 100 354, 336, 334, 336, 339;
+    // 114 390 of 64, 29 000 waves by one, 85, 74, 72, 71, 69; 29 113 of 101, 15 000 waves, 58, 52, 89, 48, 59; 20 000
+    // of 100 57 in all)
     const int64_t waves = (V * tiles) >> (6 - lpr_log2);
-    int lists = waves < 16384 ? 1 : (int)std::min<int64_t>(kMaxLists, std::max<int64_t>(2, waves / 12288));
-    lists = lpr_log2 == 2 ? 0 : std::min(lists, lpr_log2 == 3 ? 3 : D >= 512 ? 2 : kMaxLists);
+    const int lists = lpr_log2 == 2 ? 0 : waves < 12288 ? 1 : waves < 32768 ? 2 : kMaxLists;
     // (lists apart: 4 a group)
     const int64_t items = lists ? (V + lists - 1) / lists * tiles : (V + 3) / 4;
     // many small workgroups rather than one resident set: the two kinds of work take turns
@@ -460,11 +462,9 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     }
     const int blocks = short_blocks + long_blocks;
     const int64_t tile_cols = (int64_t)(vec ? 4 : 1) << lpr_log2;
-    const int64_t most = vec ? kSums<4> : kSums<1>, all = kMaxLong * tiles * tile_cols;
-    size_t shm = long_blocks > 0 ? sizeof(double) * (size_t)(all < most ? all : most) : 0;
-    shm = std::max(shm, (size_t)lists * kThreads * (vec ? 16 : 4));  // the short lists' sums
-    auto *kern = lists ? (vec ? aggregate_rows_kernel4 : aggregate_rows_kernel1)
-                       : (vec ? aggregate_rows_narrow_kernel4 : aggregate_rows_narrow_kernel1);
+    size_t shm = long_blocks > 0 ? sizeof(double) * (size_t)std::min<int64_t>(kSums, kMaxLong * tile_cols) : 0;
+    shm = std::max(shm, (size_t)lists * kThreads * 16);  // the short lists' sums
+    auto *kern = lists ? aggregate_rows_kernel4 : vec ? aggregate_rows_narrow_kernel4 : aggregate_rows_narrow_kernel1;
     kern<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2, lists, (int)tiles, sum, long_blocks, out);
     return hipGetLastError();
 }

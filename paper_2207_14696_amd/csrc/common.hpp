@@ -240,6 +240,11 @@ __device__ inline float4 load4_any(const __half *p) {
     const float2 a = __half22float2(__builtin_bit_cast(__half2, v.a)), b = __half22float2(__builtin_bit_cast(__half2, v.b));
     return make_float4(a.x, a.y, b.x, b.y);
 }
+// a store of 4-byte alignment, streaming
+__device__ inline void store4_any(float *p, float4 v) {
+    typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p));
+}
 // 8 consecutive elements (16 bytes of half precision)
 __device__ inline void load8(const __half *p, float (&v)[8]) {
     const uint4 u = *reinterpret_cast<const uint4 *>(p);

@@ -1,4 +1,4 @@
-"""aggregate_rows over runs of short lists: a lane group takes 1, 2, 3 or 6 consecutive destinations (by how many waves
+"""aggregate_rows over runs of short lists: a lane group takes 1, 2 or 3 destinations apart from each other (by how many waves
 they make), with empty and long lists at any place among them, for every number of lanes a row takes."""
 import numpy as np
 import pytest
@@ -12,10 +12,23 @@ EDGES = [0, 0, 1, 3, 4, 5, 0, 7, 8, 9, 12, 15, 16, 17, 31, 32, 33, 63, 64, 65, 2
 @pytest.mark.parametrize("waves", [3, 16_383, 16_384, 36_864, 73_729])
 @pytest.mark.parametrize("D,per_wave,tiles", [(3, 16, 1), (16, 16, 1), (28, 8, 1), (64, 4, 1), (100, 2, 1), (300, 1, 2), (37, 1, 1)])
 def test_runs(D, per_wave, tiles, waves):
+    _check(D, max(1, waves * per_wave // tiles + (waves % 2)), D + waves)
+
+
+# rows that begin anywhere (their last lane shares columns with its neighbour), on both sides of one, two and three
+# lists a group, and one destination more or less than a whole number of lists apart
+@pytest.mark.parametrize("waves", [3, 12_287, 12_288, 32_767, 32_768])
+@pytest.mark.parametrize("D,per_wave,tiles", [(4, 16, 1), (5, 16, 1), (15, 16, 1), (30, 8, 1), (101, 2, 1), (257, 1, 2)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_row_starts(D, per_wave, tiles, waves, more):
+    _check(D, -(-waves * per_wave // tiles) + more, D + waves)
+
+
+def _check(D, V, seed):
     import torch
     import paper_2207_14696_amd as bf
-    rng = np.random.default_rng(D + waves)
-    N, V = 5000, max(1, waves * per_wave // tiles + (waves % 2))
+    rng = np.random.default_rng(seed)
+    N = 5000
     lens = rng.integers(0, 4, V)
     for at in (0, V // 2, max(0, V - len(EDGES))):               # the last ones end the block
         n = min(len(EDGES), V - at)
