@@ -4,6 +4,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <new>
@@ -167,13 +168,37 @@ void build_log_tables(bifeat_params *p) {
     }
 }
 
-// (complete on return: the caller may gather on any stream)
-int upload_log(bifeat_params *p, hipStream_t s) {
+// d_T, d_V and, for 1 and 2 bits, the table as per-column affine maps lie in one piece: a blocking copy on the
+// null stream, so that gathers queued there before still find the old tables, complete on return, whatever
+// device is current.  (One copy instead of two or three, 12 us each.)
+int upload_log(bifeat_params *p) {
     int rc = ensure_device(p);
     if (rc) return rc;
-    bf::launch_log_tables(p, s);
-    BF_HIP(hipGetLastError());
-    BF_HIP(hipStreamSynchronize(s));
+    const int64_t D = p->D;
+    const int bits = p->scheme.bits;
+    const size_t maps = 128 + 256;
+    std::vector<float> t(maps + (bits == 1 ? 2 * D : bits == 2 ? 4 * D : 0));
+    std::copy(p->h_T.begin(), p->h_T.end(), t.begin());
+    std::copy(p->h_V.begin(), p->h_V.end(), t.begin() + 128);
+    float *col = t.data() + maps;
+    if (bits == 1) {
+        // V[1] = -V[0]: the difference and V[0] + 1*(V[1]-V[0]) are exact
+        for (int64_t j = 0; j < D; j++) {
+            col[j] = p->h_V[0];
+            col[D + j] = p->h_V[1] - p->h_V[0];
+        }
+    } else if (bits == 2) {
+        // decoded sum = (v1 - v0)*S0 - n*v1 + (v0 + v1)*S1 over the two bit planes of a column
+        // (V = [-v1, -v0, v0, v1]): bit column 2t maps S0, bit column 2t+1 maps S1
+        const double v0 = p->h_V[2], v1 = p->h_V[3];
+        for (int64_t j = 0; j < D; j++) {
+            col[2 * j] = (float)-v1;
+            col[2 * j + 1] = 0.0f;
+            col[2 * D + 2 * j] = (float)(v1 - v0);
+            col[2 * D + 2 * j + 1] = (float)(v0 + v1);
+        }
+    }
+    BF_HIP(hipMemcpy(p->d_T, t.data(), sizeof(float) * t.size(), hipMemcpyHostToDevice));
     return BIFEAT_OK;
 }
 
@@ -236,9 +261,9 @@ bool walk_histogram(const unsigned long long *h, int bins, unsigned long long ra
     return false;
 }
 
-int finish_log(bifeat_params *p, hipStream_t s) {
+int finish_log(bifeat_params *p) {
     build_log_tables(p);
-    int rc = upload_log(p, s);
+    int rc = upload_log(p);
     if (rc) return rc;
     p->host_valid = true;
     p->fit_open = false;
@@ -259,7 +284,7 @@ int finalize_log_clipped(bifeat_params *p, hipStream_t s) {
         for (int b = 0; b < bf::kLogHistBins; b++) n += h0[b];
         if (n == 0) {  // nothing but zeros / non-finite values
             p->e_min = p->e_max = 0.0;
-            return finish_log(p, s);
+            return finish_log(p);
         }
         const double f = p->clip_fraction;
         p->clip_rank[0] = (unsigned long long)floor(f * (double)(n - 1));
@@ -285,7 +310,7 @@ int finalize_log_clipped(bifeat_params *p, hipStream_t s) {
             memcpy(&hi, &p->clip_prefix[1], 4);
             p->e_min = log2((double)lo);
             p->e_max = log2((double)hi);
-            return finish_log(p, s);
+            return finish_log(p);
         }
     }
     p->fit_pass++;
@@ -444,7 +469,7 @@ int bifeat_fit_finalize(bifeat_params *p, void *stream) {
             p->e_min = log2((double)mmin);
             p->e_max = log2((double)mmax);
         }
-        return finish_log(p, (hipStream_t)stream);
+        return finish_log(p);
     }
     p->fit_open = false;
     p->fitted = true;
@@ -499,7 +524,7 @@ int bifeat_params_set_log(bifeat_params *p, double e_min, double e_max) {
         return BIFEAT_EINVAL;
     p->e_min = e_min;
     p->e_max = e_max;
-    return finish_log(p, nullptr);
+    return finish_log(p);
 }
 
 int bifeat_params_get_log(bifeat_params *p, double *e_min, double *e_max, float *T, float *V) {

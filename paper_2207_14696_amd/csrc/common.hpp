@@ -101,8 +101,6 @@ hipError_t launch_finalize_uniform(bifeat_params *p, hipStream_t s);
 // words of the device's memory into p->d_out: read there after a synchronisation, where each copy through
 // hipMemcpy takes 12 us of the host (small tables; a build of 25 677 x 768 floats 128 us, of them 55 for four)
 void launch_export(bifeat_params *p, const void *src, int words, hipStream_t s);
-// d_T, d_V and, for 1 and 2 bits, the table as per-column affine maps, from the host's tables
-void launch_log_tables(bifeat_params *p, hipStream_t s);
 void launch_log_hist_reset(bifeat_params *p, hipStream_t s);
 hipError_t launch_log_hist_update(bifeat_params *p, const void *chunk, int dtype, int64_t rows,
                                   hipStream_t s);

@@ -129,44 +129,6 @@ void launch_export(bifeat_params *p, const void *src, int words, hipStream_t s) 
     export_kernel<<<(words + 255) / 256, 256, 0, s>>>((const uint32_t *)src, (uint32_t *)p->d_out, words);
 }
 
-// The tables come as kernel arguments (1.5 KB).
-struct LogTables {
-    float T[128], V[256];
-};
-
-__global__ void log_tables_kernel(LogTables t, int bits, int64_t D, float *T, float *V, float *maps) {
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-    if (i0 < 128) T[i0] = t.T[i0];
-    if (i0 < 256) V[i0] = t.V[i0];
-    if (bits == 1) {
-        // V[1] = -V[0]: the difference and V[0] + 1*(V[1]-V[0]) are exact
-        const float v0 = t.V[0], d = t.V[1] - t.V[0];
-        for (int64_t j = i0; j < D; j += step) {
-            maps[j] = v0;
-            maps[D + j] = d;
-        }
-    } else if (bits == 2) {
-        // decoded sum = (v1 - v0)*S0 - n*v1 + (v0 + v1)*S1 over the two bit planes of a column
-        // (V = [-v1, -v0, v0, v1]): bit column 2t maps S0, bit column 2t+1 maps S1
-        const double v0 = t.V[2], v1 = t.V[3];
-        const float m0 = (float)-v1, d = (float)(v1 - v0), u = (float)(v0 + v1);
-        for (int64_t j = i0; j < D; j += step) {
-            maps[2 * j] = m0;
-            maps[2 * j + 1] = 0.0f;
-            maps[2 * D + 2 * j] = d;
-            maps[2 * D + 2 * j + 1] = u;
-        }
-    }
-}
-
-void launch_log_tables(bifeat_params *p, hipStream_t s) {
-    LogTables t{};
-    std::copy(p->h_T.begin(), p->h_T.end(), t.T);
-    std::copy(p->h_V.begin(), p->h_V.end(), t.V);
-    const int64_t cols = p->scheme.bits <= 2 ? std::max<int64_t>(p->D, 256) : 256;
-    log_tables_kernel<<<blocks_for(cols, 1024), 256, 0, s>>>(t, p->scheme.bits, p->D, p->d_T, p->d_V, p->d_min);
-}
-
 hipError_t launch_finalize_uniform(bifeat_params *p, hipStream_t s) {
     int D = (int)p->D;
     finalize_uniform_kernel<<<(D + 63) / 64, 64, 0, s>>>(p->d_fit, fit_copies(D), D, p->scheme.bits, p->d_min,

@@ -119,3 +119,33 @@ def test_copies(rows, D, half):
     _check(q, x.astype(np.float32), 8)
     mag = np.abs(x[x != 0].astype(np.float64))
     assert g.params_get_log()[:2] == (pytest.approx(np.log2(mag.min()), abs=1e-12), pytest.approx(np.log2(mag.max()), abs=1e-12))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 8])
+def test_log_refit_beside_queued_gathers(bits):
+    """A refit on a stream of its own leaves the tables alone that gathers queued on the default stream are to decode with."""
+    import torch
+    import paper_2207_14696_amd as bf
+    D = 64
+    x = torch.randn(500, D, device="cuda")
+    q = bf.Quantizer(scheme_of("log", bits), D)
+    q.params_set_log(-6.0, 1.75)
+    codes = torch.zeros(500, q.row_bytes, dtype=torch.uint8, device="cuda")
+    q.quantize(x, codes, 0)
+    idx, ptr = torch.arange(500, device="cuda"), torch.arange(0, 501, 4, device="cuda")
+    want = q.gather_dequant(codes, idx).clone(), q.gather_mean(codes, ptr, idx).clone()
+    a = torch.randn(8192, 8192, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(8):      # (some ms each)
+        b = a @ a
+    got = q.gather_dequant(codes, idx), q.gather_mean(codes, ptr, idx)
+    with torch.cuda.stream(side):
+        y = x * 5
+        q.fit_reset()
+        q.fit_update(y)
+        q.fit_finalize()
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert torch.equal(g, w)
+    assert not torch.equal(q.gather_dequant(codes, idx), want[0])
