@@ -499,6 +499,10 @@ int bifeat_params_set_uniform(bifeat_params *p, const float *mn, const float *mx
     BF_HIP(hipMemcpy(p->d_max, p->h_max.data(), 4 * D, hipMemcpyHostToDevice));
     BF_HIP(hipMemcpy(p->d_scale, p->h_scale.data(), 4 * D, hipMemcpyHostToDevice));
     BF_HIP(hipMemcpy(p->d_inv, p->h_inv.data(), 4 * D, hipMemcpyHostToDevice));
+    if (p->h_out) {  // (a finalize that is captured but not replayed leaves these to be read)
+        const float *const from[4] = {p->h_min.data(), p->h_scale.data(), p->h_inv.data(), p->h_max.data()};
+        for (int k = 0; k < 4; k++) memcpy(p->h_out + 4 * D * k, from[k], 4 * D);
+    }
     p->host_valid = true;
     p->fitted = true;
     p->fit_open = false;

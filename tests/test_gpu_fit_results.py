@@ -62,6 +62,29 @@ def test_uniform_replayed():
         _check(q, y, 8)
 
 
+@pytest.mark.parametrize("D", [64, 16385])
+def test_uniform_set_then_captured(D):
+    """A fit that is captured, but not replayed, leaves the parameters that were set before it."""
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(D)
+    t = torch.from_numpy(rng.normal(size=(100, D)).astype(np.float32)).cuda()
+    q = bf.Quantizer(scheme_of("uniform", 8), D)
+    mn = rng.normal(size=D).astype(np.float32)
+    mx = mn + rng.uniform(0, 2, D).astype(np.float32)
+    q.fit_update(t)
+    q.fit_finalize()
+    q.params_set_uniform(mn, mx)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        q.fit_reset()
+        q.fit_update(t)
+        q.fit_finalize()
+    for got, want in zip(q.params_get_uniform(), (mn, mx, *orc.uniform_params(mn, mx, 8))):
+        assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("bits", [1, 2, 4, 8])
 @pytest.mark.parametrize("clip", [0.0, 0.02])
 def test_log(bits, clip):
