@@ -152,7 +152,8 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
         const int64_t v = v0 + t * step;
         const bool mine = t < lists && v < V;
         const int64_t beg = mine ? indptr[v] : 0;
-        const int all = mine ? (int)min(indptr[v + 1] - beg, (int64_t)kLong + 1) : kLong + 1;
+        // (bounds that decrease, against the contract, leave an empty list: the others' places must not move)
+        const int all = mine ? (int)min(max(indptr[v + 1] - beg, (int64_t)0), (int64_t)kLong + 1) : kLong + 1;
         const int len = all <= kLong ? all : 0;
         // where it begins in the run of all of them (from lane `lists` on: the run's end)
         int rel = 0;

@@ -24,6 +24,30 @@ def test_row_starts(D, per_wave, tiles, waves, more):
     _check(D, -(-waves * per_wave // tiles) + more, D + waves)
 
 
+# (the index contract excludes it, the call does not look: every place read lies within the entries)
+@pytest.mark.parametrize("D,V", [(100, 20), (100, 30_000), (64, 200_000), (8, 1000)])
+def test_bounds_that_decrease(D, V):
+    import torch
+    import paper_2207_14696_amd as bf
+    rng = np.random.default_rng(V)
+    lens = rng.integers(0, 4, V)
+    lens[:16] = 3                       # (what lies before any of them, 40 entries or more)
+    at = rng.choice(np.arange(16, V - 1, 2), max(1, V // 50), replace=False)
+    lens[at] = -2
+    lens[at + 1] = 3
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    indices = rng.integers(0, 500, int(ptr.max())).astype(np.int64)
+    x = torch.randn(500, D, device="cuda", generator=torch.Generator("cuda").manual_seed(D))
+    out = torch.full((V, D), float("nan"), device="cuda")
+    bf.aggregate_rows(x, torch.from_numpy(ptr).cuda(), torch.from_numpy(indices).cuda(), out=out, sum=True)
+    want = np.zeros((V, D))
+    host = x.double().cpu().numpy()
+    n = np.maximum(lens, 0)
+    entry = np.repeat(ptr[:-1], n) + np.concatenate([np.arange(k) for k in n])
+    np.add.at(want, np.repeat(np.arange(V), n), host[indices[entry.astype(np.int64)]])
+    np.testing.assert_allclose(out.cpu().numpy(), want, rtol=0, atol=6 * 2.0 ** -24 * 3 * 6)     # (|x| < 6, 3 rows)
+
+
 def _check(D, V, seed):
     import torch
     import paper_2207_14696_amd as bf
