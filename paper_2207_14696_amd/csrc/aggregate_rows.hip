@@ -14,7 +14,7 @@ namespace bf {
 namespace {
 
 constexpr int kAggInFlight = 4;  // rows that a lane adds up while as many travel
-constexpr int kMaxLists = 3;     // destinations of a lane group at most
+constexpr int kMaxLists = 3;     // destinations of a lane group of short_lists() at most
 // A list longer than kLong is not walked by one lane group (a hub's thousands of rows,
 // one latency after the other, would outlast the rest of the launch): it is cut into
 // pieces of kSub list entries that many groups sum side by side.  A workgroup of that
@@ -85,10 +85,7 @@ struct Acc<1> {
     float v, c;
     __device__ void zero() { v = c = 0.f; }
     __device__ static float load(const float *p) { return *p; }
-    __device__ static void hold(float &r) { asm volatile("" : "+v"(r)); }
     __device__ void add(const float r) { kahan_add(v, c, r); }
-    __device__ void park(double *lds, int k) const { reinterpret_cast<float *>(lds)[k * kThreads + threadIdx.x] = v; }
-    __device__ static float parked(const double *lds, int k) { return reinterpret_cast<const float *>(lds)[k * kThreads + threadIdx.x]; }
     __device__ static void store(float o, float *p, int n, bool sum) {
         __builtin_nontemporal_store(sum ? o : (n > 0 ? o / (float)n : 0.f), p);
     }
@@ -116,9 +113,13 @@ __device__ inline void add_rows(Acc<VEC> &acc, const float *__restrict__ base, i
     for (; e < end; e++) acc.add(Acc<VEC>::load(base + indices[e] * D));
 }
 
-// The lists of up to kLong entries.  A group of `lpr` lanes (a power of two up to 64)
+// Of a group's lists the k-th one, with `before` entries in those ahead of it, is left to left_lists() where it would make
+// the group's chain longer than one list's can be.
+__device__ inline bool is_left(int k, int before, int len) { return k > 0 && len > 0 && before + len > kLong; }
+
+// The lists of up to kLong entries.  A group of `lpr` lanes (a power of two from 8 to 64)
 // owns a column tile of `lists` destinations, V / lists apart: lane t of the group accumulates
-// columns VEC*(tile*lpr + t) .. +VEC-1 over each destination's list, in list order
+// columns 4*(tile*lpr + t) .. +3 over each destination's list, in list order
 // (fp32, compensated).  Items are numbered tile-fastest.  Long lists are left to long_lists().
 // What bounds it is how many rows are in flight: 2^20 rows of 100 columns, 17 M entries, ask for 6.9 GB
 // beyond the L2s, which move 7.4 TB/s of such lines at most.  The group's lists are one run of entries,
@@ -126,18 +127,21 @@ __device__ inline void add_rows(Acc<VEC> &acc, const float *__restrict__ base, i
 // the next 4 while these are added.  The group fetches lpr entries with one load and hands the rows'
 // places round by lane exchange; a list's sum waits in LDS until the item's rows have been
 // read, as loads issued behind a store return behind it.  That launch: 1070 us with a list at a time, 4
-// rows in flight and every entry loaded by all lanes, 970 so; 310 237 rows of 128 columns 303 and 277.
+// rows in flight and every entry loaded by all lanes, 960 so; 300 000 rows of 100 columns 271 and 234.
 // Consecutive destinations instead share the loads of their bounds and entries (6 of them: 953 us a round), but lists of nearly
 // kLong entries tend to be neighbours, and one group's chain of them outlasts the launch (417 408 rows of 64
-// columns 318 us, 137 so; 55 456 of 100 sorted by degree 217, 77).
-template <int VEC>
+// columns 318 us, 137 apart; 55 456 of 100 sorted by degree 217, 77).  Apart they meet where the numbering has a stride
+// of about V / lists (rank r at (1 000 003 r + 12 345) mod V: 68 182 rows of 100 columns 126 us, 230 249 of 64 175);
+// with such groups' further lists left to others 77 and 115.  Blocks of destinations paired as hashed instead: 92 there, but
+// some heavy list ends every launch (200 047 rows of 64 columns 131, 115 so); left to the workgroup's
+// other groups, which have as heavy ones: 126.
 __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
                                    const int64_t *__restrict__ indptr,
                                    const int64_t *__restrict__ indices, int64_t V, int lpr_log2,
                                    int lists, int tiles, int sum, float *__restrict__ out, int64_t block,
                                    int64_t nblocks) {
     constexpr int U = kAggInFlight;
-    using Row = decltype(Acc<VEC>::load(x));
+    using Sum = Acc<4>;
     extern __shared__ double s_sum[];
     const int lpr = 1 << lpr_log2;
     const int lane = threadIdx.x & 63, t = lane & (lpr - 1), first = lane & ~(lpr - 1);
@@ -146,27 +150,36 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
     for (int64_t item = (block * kThreads + threadIdx.x) >> lpr_log2; item < items; item += groups) {
         const int64_t v0 = item / tiles;
         const int tile = (int)(item - v0 * tiles);
-        const int64_t col0 = (int64_t)VEC * (tile * lpr + t), col = min(col0, D - VEC);
+        const int64_t col0 = (int64_t)4 * (tile * lpr + t), col = min(col0, D - 4);
         const bool in = col0 < D;  // (the other lanes read a row's end and write nothing)
         // lane t: the t-th destination's list (lists < lpr), none for a long one
         const int64_t v = v0 + t * step;
         const bool mine = t < lists && v < V;
         const int64_t beg = mine ? indptr[v] : 0;
         // (bounds that decrease, against the contract, leave an empty list: the others' places must not move)
-        const int all = mine ? (int)min(max(indptr[v + 1] - beg, (int64_t)0), (int64_t)kLong + 1) : kLong + 1;
-        const int len = all <= kLong ? all : 0;
+        int all = mine ? (int)min(max(indptr[v + 1] - beg, (int64_t)0), (int64_t)kLong + 1) : kLong + 1;
+        int len = all <= kLong ? all : 0;
         // where it begins in the run of all of them (from lane `lists` on: the run's end)
-        int rel = 0;
+        auto begins = [&]() {
+            int at = 0;
 #pragma unroll
-        for (int k = 0; k < kMaxLists; k++) {
-            const int len_k = __builtin_amdgcn_ds_bpermute(4 * (first + k), len);
-            rel += t > k ? len_k : 0;
+            for (int k = 0; k < kMaxLists; k++) {
+                const int len_k = __builtin_amdgcn_ds_bpermute(4 * (first + k), len);
+                at += t > k ? len_k : 0;
+            }
+            return at;
+        };
+        int rel = begins();
+        const bool left = t < lists && is_left(t, rel, len);
+        if (__any(left)) {
+            if (left) { all = kLong + 1; len = 0; }
+            rel = begins();
         }
         const int64_t shift = beg - rel;
         const int n = __builtin_amdgcn_ds_bpermute(4 * (first + lists), rel);
         const float *src = x + col;
         int i = 0, end = __builtin_amdgcn_ds_bpermute(4 * (first + 1), rel);
-        Acc<VEC> acc;
+        Sum acc;
         acc.zero();
         auto close = [&]() {  // list i is complete
             acc.park(s_sum, i);
@@ -186,21 +199,21 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
             };
             // of this chunk of lpr entries, and of the next one
             int64_t off = place(t), off1 = place(lpr + t);
-            Row r[2][U];
-            auto rows = [&](Row (&to)[U], int e) {  // entries e .. e + U - 1 travel
+            float4 r[2][U];
+            auto rows = [&](float4 (&to)[U], int e) {  // entries e .. e + U - 1 travel
                 if (e > 0 && (e & (lpr - 1)) == 0) {
                     off = off1;
                     off1 = place(e + lpr + t);
                 }
 #pragma unroll
                 for (int u = 0; u < U; u++)
-                    to[u] = Acc<VEC>::load(src + from_lane(off, 4 * (first + ((e + u) & (lpr - 1)))));
+                    to[u] = Sum::load(src + from_lane(off, 4 * (first + ((e + u) & (lpr - 1)))));
             };
-            auto take = [&](Row (&of)[U], int e) {
+            auto take = [&](float4 (&of)[U], int e) {
                 // (each in registers before the first is used: the compiler would otherwise move the loads into
                 // the branches, one after the other)
 #pragma unroll
-                for (int u = 0; u < U; u++) Acc<VEC>::hold(of[u]);
+                for (int u = 0; u < U; u++) Sum::hold(of[u]);
                 if (e + U < end) {
 #pragma unroll
                     for (int u = 0; u < U; u++) acc.add(of[u]);
@@ -225,7 +238,46 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
         }
         for (int k = 0; k < lists; k++) {
             const int n_k = __builtin_amdgcn_ds_bpermute(4 * (first + k), all);  // (more than kLong: none, or a long one)
-            if (in && n_k <= kLong) Acc<VEC>::store(Acc<VEC>::parked(s_sum, k), out + (v0 + k * step) * D + col, n_k, sum != 0);
+            if (in && n_k <= kLong) Sum::store(Sum::parked(s_sum, k), out + (v0 + k * step) * D + col, n_k, sum != 0);
+        }
+    }
+}
+
+// The lists that short_lists() leaves, a lane group each.  A lane looks one item's lists over; lanes of a wave are far apart,
+// as such items tend to be neighbours.  (Another look at the bounds: 2^20 rows of 100 columns 955 us without, 960.)
+__device__ inline void left_lists(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
+                                  const int64_t *__restrict__ indices, int64_t V, int lpr_log2, int lists, int tiles, int sum,
+                                  float *__restrict__ out, int64_t block, int64_t nblocks) {
+    const int64_t step = (V + lists - 1) / lists, items = step * tiles;
+    const int lane = threadIdx.x & 63, lpr = 1 << lpr_log2, t = lane & (lpr - 1);
+    block = (block & 7) * (nblocks >> 3) + (block >> 3);  // (a multiple of 8: consecutive ones on one XCD)
+    const int64_t wave = block * (kThreads / 64) + (threadIdx.x >> 6), waves = nblocks * (kThreads / 64);
+    for (int64_t first = 0; first < items; first += 64 * waves) {
+        const int64_t item = first + wave + waves * lane;
+        const int64_t tile = item / step, v0 = item - tile * step;
+        int before = 0;
+        for (int k = 0; k < lists; k++) {
+            const int64_t v = v0 + k * step;
+            const bool mine = item < items && v < V;
+            const int64_t beg = mine ? indptr[v] : 0, all = mine ? indptr[v + 1] - beg : 0;
+            const int len = all > 0 && all <= kLong ? (int)all : 0;
+            const uint64_t left = __ballot(is_left(k, before, len));
+            before += len;
+            const int n = __popcll(left);
+            for (int it0 = 0; it0 < n; it0 += 64 >> lpr_log2) {
+                const int it = it0 + (lane >> lpr_log2);
+                uint64_t m = left;
+                for (int i = 0; i < it; i++) m &= m - 1;
+                const int at = 4 * (m ? __ffsll((unsigned long long)m) - 1 : 0);
+                const int64_t of = from_lane(v, at), b = from_lane(beg, at);
+                const int len_of = __builtin_amdgcn_ds_bpermute(at, len);
+                const int64_t col0 = 4 * (__builtin_amdgcn_ds_bpermute(at, (int)tile) * lpr + t), col = min(col0, D - 4);
+                const bool in = it < n && col0 < D;
+                Acc<4> acc;
+                acc.zero();
+                if (in) add_rows<4, 2 * kAggInFlight>(acc, x + col, D, indices, b, b + len_of);
+                if (in) Acc<4>::store(acc.v, out + of * D + col, len_of, sum != 0);
+            }
         }
     }
 }
@@ -234,12 +286,16 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
 // some list ends at every row, and short_lists() then walks its slow branch (10^6 rows of 3 columns 180 us,
 // 164 so; of 16 226, 217).
 template <int VEC>
-__device__ inline void short_lists_narrow(const float *__restrict__ x, int64_t D,
+__device__ inline void short_lists_single(const float *__restrict__ x, int64_t D,
                                           const int64_t *__restrict__ indptr,
-                                          const int64_t *__restrict__ indices, int64_t V, int sum,
+                                          const int64_t *__restrict__ indices, int64_t V, int lpr_log2, int tiles, int sum,
                                           float *__restrict__ out, int64_t block, int64_t nblocks) {
-    const int64_t col0 = (int64_t)VEC * (threadIdx.x & 3), col = min(col0, D - VEC);
-    for (int64_t v = (block * kThreads + threadIdx.x) >> 2; v < V; v += (nblocks * kThreads) >> 2) {
+    const int lpr = 1 << lpr_log2, t = threadIdx.x & (lpr - 1);
+    const int64_t items = V * tiles, groups = (nblocks * kThreads) >> lpr_log2;
+    for (int64_t item = (block * kThreads + threadIdx.x) >> lpr_log2; item < items; item += groups) {
+        const int64_t v = item / tiles;
+        const int tile = (int)(item - v * tiles);
+        const int64_t col0 = (int64_t)VEC * (tile * lpr + t), col = min(col0, D - VEC);
         const int64_t beg = indptr[v], end = indptr[v + 1];
         if (col0 >= D || end - beg > kLong) continue;
         Acc<VEC> acc;
@@ -263,7 +319,7 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
                                   int64_t block, int64_t nblocks) {
     __shared__ int64_t s_v[kMaxLong], s_beg[kMaxLong], s_end[kMaxLong], s_first;
     __shared__ int s_deg[kMaxLong], s_n;
-    extern __shared__ double s_sum[];  // [long lists][columns of a pass]
+    extern __shared__ double s_sum[];  // [long lists][columns of a tile]
     const int lpr = 1 << lpr_log2;
     const int t = threadIdx.x & (lpr - 1);
     const int group = threadIdx.x >> lpr_log2, groups = kThreads >> lpr_log2;
@@ -344,33 +400,34 @@ __device__ inline void long_lists(const float *__restrict__ x, int64_t D,
     }
 }
 
-// One launch for both: the first `long_blocks` workgroups (dispatched first; their
+// One launch for all: the first `long_blocks` workgroups (dispatched first; their
 // pieces are the longest single chains of the launch) take the long lists, the rest
-// the short ones.  The two write disjoint rows.
-template <int VEC, bool NARROW>
+// the short ones, one or, where `lists` is not 0, several at a time, those that these leave first.  All write disjoint rows.
+template <int VEC, bool SINGLE>
 __device__ inline void aggregate(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
                                  const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int lists,
-                                 int tiles, int sum, int long_blocks, float *__restrict__ out) {
+                                 int left_blocks, int tiles, int sum, int long_blocks, float *__restrict__ out) {
     const int64_t block = (int64_t)blockIdx.x - long_blocks, nblocks = (int64_t)gridDim.x - long_blocks;
     if (block < 0)
         long_lists<VEC>(x, D, indptr, indices, V, E, lpr_log2, tiles, sum, out, blockIdx.x, long_blocks);
-    else if constexpr (NARROW)
-        short_lists_narrow<VEC>(x, D, indptr, indices, V, sum, out, block, nblocks);
+    else if constexpr (SINGLE)
+        short_lists_single<VEC>(x, D, indptr, indices, V, lpr_log2, tiles, sum, out, block, nblocks);
+    else if (block < left_blocks)
+        left_lists(x, D, indptr, indices, V, lpr_log2, lists, tiles, sum, out, block, left_blocks);
     else
-        short_lists<VEC>(x, D, indptr, indices, V, lpr_log2, lists, tiles, sum, out, block, nblocks);
+        short_lists(x, D, indptr, indices, V, lpr_log2, lists, tiles, sum, out, block - left_blocks, nblocks - left_blocks);
 }
-#define BF_AGG(NAME, VEC, NARROW)                                                                           \
-    void NAME(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,                    \
-              const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int lists, int tiles, \
-              int sum, int long_blocks, float *__restrict__ out) {                                           \
-        aggregate<VEC, NARROW>(x, D, indptr, indices, V, E, lpr_log2, lists, tiles, sum, long_blocks, out);  \
+#define BF_AGG(NAME, VEC, SINGLE)                                                                            \
+    void NAME(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,                     \
+              const int64_t *__restrict__ indices, int64_t V, int64_t E, int lpr_log2, int lists, int left_blocks, \
+              int tiles, int sum, int long_blocks, float *__restrict__ out) {                                 \
+        aggregate<VEC, SINGLE>(x, D, indptr, indices, V, E, lpr_log2, lists, left_blocks, tiles, sum, long_blocks, out); \
     }
 // (apart: with the registers of short_lists() a SIMD holds 5 waves instead of 8, and the narrow
 // lists, 10^6 rows of 8 columns, take 210 us instead of 197)
-__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_kernel4, 4, false)
-__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_narrow_kernel4, 4, true)
-// (up to 3 columns)
-__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_narrow_kernel1, 1, true)
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_kernel, 4, false)
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_single_kernel4, 4, true)
+__global__ __launch_bounds__(kThreads) BF_AGG(aggregate_rows_single_kernel1, 1, true)
 #undef BF_AGG
 
 // Output rows of the long lists set to zero ahead of the launch above: a lane per
@@ -444,29 +501,32 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     int lpr_log2 = 2;  // at least four lanes per row
     while (lpr_log2 < 6 && ((int64_t)1 << lpr_log2) < granules) lpr_log2++;
     const int64_t tiles = (granules + ((int64_t)1 << lpr_log2) - 1) >> lpr_log2;
-    // Several lists a group only where the chip has enough of them at a time (us with 1, 2, 3, 4, 6 of them: 2^20
-    // rows of 64 columns 776, 680, 595, 566, 575, of 100 1174, 1017, 973, 993, 992; 417 408 of 100 354, 336, 334, 336, 339;
-    // 114 390 of 64, 29 000 waves by one, 85, 74, 72, 71, 69; 29 113 of 101, 15 000 waves, 58, 52, 89, 48, 59; 20 000
-    // of 100 57 in all)
+    // Several lists a group only where the chip has enough of them at a time (us with 1, 2, 3 of them: 2^20
+    // rows of 64 columns 776, 680, 595, of 100 1174, 1017, 973; 417 408 of 100 354, 336, 334; 114 390 of 64, 29 000
+    // waves by one, 85, 74, 72).  0: short_lists_single().
     const int64_t waves = (V * tiles) >> (6 - lpr_log2);
-    const int lists = lpr_log2 == 2 ? 0 : waves < 12288 ? 1 : waves < 32768 ? 2 : kMaxLists;
+    int lists = lpr_log2 == 2 ? 0 : waves < 12288 ? 1 : waves < 32768 ? 2 : kMaxLists;
+    // (no more than make one list of kLong on average: what is left is dearer; 100 000 rows of 100 columns and 120 entries
+    // each 766 us by two, 1180 by three)
+    if (lists * E > kLong * V) lists = lists == 1 || 2 * E > kLong * V ? 1 : 2;
     // (lists apart: 4 a group)
     const int64_t items = lists ? (V + lists - 1) / lists * tiles : (V + 3) / 4;
     // many small workgroups rather than one resident set: the two kinds of work take turns
     // on the CUs as slots free up, and no workgroup's share is large enough to form a tail
     const int short_blocks = blocks_for(items << lpr_log2, 1 << 20);
+    const int left_blocks = lists > 1 ? (blocks_for(items, 1 << 20) + 7) / 8 * 8 : 0;
     int long_blocks = 0;
     if (E > kLong) {  // otherwise no list is long
         const int64_t ranges = (E + kRange - 1) / kRange;
         long_blocks = (int)(ranges < (1 << 20) ? ranges : (1 << 20));
         aggregate_zero_long_kernel<<<blocks_for(V, 8 * 256), kThreads, 0, s>>>(indptr, V, D, out);
     }
-    const int blocks = short_blocks + long_blocks;
+    const int blocks = short_blocks + left_blocks + long_blocks;
     const int64_t tile_cols = (int64_t)(vec ? 4 : 1) << lpr_log2;
     size_t shm = long_blocks > 0 ? sizeof(double) * (size_t)std::min<int64_t>(kSums, kMaxLong * tile_cols) : 0;
     shm = std::max(shm, (size_t)lists * kThreads * 16);  // the short lists' sums
-    auto *kern = lists ? aggregate_rows_kernel4 : vec ? aggregate_rows_narrow_kernel4 : aggregate_rows_narrow_kernel1;
-    kern<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2, lists, (int)tiles, sum, long_blocks, out);
+    auto *kern = lists ? aggregate_rows_kernel : vec ? aggregate_rows_single_kernel4 : aggregate_rows_single_kernel1;
+    kern<<<blocks, kThreads, shm, s>>>(x, D, indptr, indices, V, E, lpr_log2, lists, left_blocks, (int)tiles, sum, long_blocks, out);
     return hipGetLastError();
 }
 

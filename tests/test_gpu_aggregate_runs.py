@@ -24,6 +24,53 @@ def test_row_starts(D, per_wave, tiles, waves, more):
     _check(D, -(-waves * per_wave // tiles) + more, D + waves)
 
 
+# Lists that together make a longer run than one list can: at the same place in every half or third of the destinations, so
+# that they share a lane group, which leaves all but the first of them to others.
+@pytest.mark.parametrize("waves", [12_288, 32_768])
+@pytest.mark.parametrize("D,per_wave,tiles", [(20, 8, 1), (64, 4, 1), (101, 2, 1), (200, 1, 1), (300, 1, 2)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_long_runs(D, per_wave, tiles, waves, more):
+    V = -(-waves * per_wave // tiles) + more
+    lens = np.random.default_rng(D + V).integers(0, 3, V)
+    together = [(256, 256, 256), (256, 1, 0), (1, 255, 1), (1, 256, 0), (0, 256, 256), (128, 128, 1), (257, 10, 250), (100, 157, 99),
+                (0, 0, 256), (256, 257, 256)] + [(250, 249, 248)] * 70
+    for lists in (2, 3):
+        step = -(-V // lists)
+        for i, three in enumerate(together):
+            for k in range(lists):
+                if k * step + i < V:
+                    lens[k * step + i + (100 if lists == 3 else 0)] = three[k]
+    _check(D, V, D, lens)
+
+
+def test_long_runs_are_shared():
+    """Where heavy lists lie makes no difference: 200 of 250 entries at the same place in every third of the destinations, or not."""
+    import torch
+    import paper_2207_14696_amd as bf
+    V, D = 73_728, 100
+    step = V // 3
+    x = torch.randn(2000, D, device="cuda")
+    took = []
+    for apart in (0, 1000):
+        lens = torch.ones(V, dtype=torch.int64)
+        for k in range(3):
+            at = k * step + 1000 + k * apart
+            lens[at:at + 600:3] = 250
+        ptr = torch.cat([torch.zeros(1, dtype=torch.int64), lens.cumsum(0)]).cuda()
+        idx = torch.randint(0, 2000, (int(lens.sum()),), device="cuda")
+        out = torch.empty(V, D, device="cuda")
+        best = 1e9
+        for _ in range(30):
+            e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e[0].record()
+            bf.aggregate_rows(x, ptr, idx, out=out)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        took.append(best)
+    assert took[0] < 1.5 * took[1], took
+
+
 # (the index contract excludes it, the call does not look: every place read lies within the entries)
 @pytest.mark.parametrize("D,V", [(100, 20), (100, 30_000), (64, 200_000), (8, 1000)])
 def test_bounds_that_decrease(D, V):
@@ -48,15 +95,16 @@ def test_bounds_that_decrease(D, V):
     np.testing.assert_allclose(out.cpu().numpy(), want, rtol=0, atol=6 * 2.0 ** -24 * 3 * 6)     # (|x| < 6, 3 rows)
 
 
-def _check(D, V, seed):
+def _check(D, V, seed, lens=None):
     import torch
     import paper_2207_14696_amd as bf
     rng = np.random.default_rng(seed)
     N = 5000
-    lens = rng.integers(0, 4, V)
-    for at in (0, V // 2, max(0, V - len(EDGES))):               # the last ones end the block
-        n = min(len(EDGES), V - at)
-        lens[at:at + n] = rng.permutation(EDGES)[:n] if at else EDGES[:n]
+    if lens is None:
+        lens = rng.integers(0, 4, V)
+        for at in (0, V // 2, max(0, V - len(EDGES))):               # the last ones end the block
+            n = min(len(EDGES), V - at)
+            lens[at:at + n] = rng.permutation(EDGES)[:n] if at else EDGES[:n]
     indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)).cuda()
     indices = torch.from_numpy(rng.integers(0, N, int(lens.sum()))).cuda()
     x = torch.randn(N, D, device="cuda", generator=torch.Generator("cuda").manual_seed(D))
