@@ -282,9 +282,11 @@ __device__ inline void left_lists(const float *__restrict__ x, int64_t D, const 
     }
 }
 
-// The same for rows that four lanes take (up to 16 columns), a destination at a time: with 16 groups a wave
-// some list ends at every row, and short_lists() then walks its slow branch (10^6 rows of 3 columns 180 us,
-// 164 so; of 16 226, 217).
+// The lists of up to kLong entries again, a destination at a time.  For launches that do not fill the chip several times over:
+// a group each of as many lists as there are hides more than runs of them do (25 323 rows of 64 columns 42 us by
+// runs, 32 so; 8500 of 32 37, 25).  And for rows that four lanes take (up to 16 columns): with 16 groups a wave some list
+// ends at every row, and short_lists() then walks its slow branch (10^6 rows of 16 226, 217).  One list a group: four, far
+// apart, were 3 to 15 % slower (500 000 rows of 16 columns 118 us, 105 so; 3000 of 64 33, 25).
 template <int VEC>
 __device__ inline void short_lists_single(const float *__restrict__ x, int64_t D,
                                           const int64_t *__restrict__ indptr,
@@ -505,16 +507,15 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     // rows of 64 columns 776, 680, 595, of 100 1174, 1017, 973; 417 408 of 100 354, 336, 334; 114 390 of 64, 29 000
     // waves by one, 85, 74, 72).  0: short_lists_single().
     const int64_t waves = (V * tiles) >> (6 - lpr_log2);
-    int lists = lpr_log2 == 2 ? 0 : waves < 12288 ? 1 : waves < 32768 ? 2 : kMaxLists;
+    int lists = lpr_log2 == 2 || waves < 12288 ? 0 : waves < 32768 ? 2 : kMaxLists;
     // (no more than make one list of kLong on average: what is left is dearer; 100 000 rows of 100 columns and 120 entries
     // each 766 us by two, 1180 by three)
-    if (lists * E > kLong * V) lists = lists == 1 || 2 * E > kLong * V ? 1 : 2;
-    // (lists apart: 4 a group)
-    const int64_t items = lists ? (V + lists - 1) / lists * tiles : (V + 3) / 4;
+    if (lists * E > kLong * V) lists = 2 * E > kLong * V ? 0 : 2;
+    const int64_t step = lists ? (V + lists - 1) / lists : V, items = step * tiles;
     // many small workgroups rather than one resident set: the two kinds of work take turns
     // on the CUs as slots free up, and no workgroup's share is large enough to form a tail
     const int short_blocks = blocks_for(items << lpr_log2, 1 << 20);
-    const int left_blocks = lists > 1 ? (blocks_for(items, 1 << 20) + 7) / 8 * 8 : 0;
+    const int left_blocks = lists ? (blocks_for(items, 1 << 20) + 7) / 8 * 8 : 0;
     int long_blocks = 0;
     if (E > kLong) {  // otherwise no list is long
         const int64_t ranges = (E + kRange - 1) / kRange;
