@@ -498,7 +498,10 @@ bool vec_ok(const void *a, const void *b, int64_t D) {
 hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indptr,
                                  const int64_t *indices, int64_t V, int64_t E, int sum, float *out,
                                  hipStream_t s) {
-    const bool vec = D >= 4;
+    // 16 bytes a lane.  Rows of few columns that begin anywhere: 4 bytes where there are not many, more lanes
+    // then share a hub's (us by 16 bytes / 4: 20 000 rows of 30 columns 48 / 31, of 15 32 / 29; 200 000 of 15 71 / 65, of 23
+    // 92 / 92, 500 000 of 15 136 / 153, of 30 181 / 246; 20 000 of 33 44 / 46)
+    const bool vec = D >= 4 && (D % 4 == 0 || D > 32 || V >= (D > 16 ? 1 << 17 : 1 << 18));
     const int64_t granules = vec ? (D + 3) / 4 : D;
     int lpr_log2 = 2;  // at least four lanes per row
     while (lpr_log2 < 6 && ((int64_t)1 << lpr_log2) < granules) lpr_log2++;
@@ -507,7 +510,7 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     // rows of 64 columns 776, 680, 595, of 100 1174, 1017, 973; 417 408 of 100 354, 336, 334; 114 390 of 64, 29 000
     // waves by one, 85, 74, 72).  0: short_lists_single().
     const int64_t waves = (V * tiles) >> (6 - lpr_log2);
-    int lists = lpr_log2 == 2 || waves < 12288 ? 0 : waves < 32768 ? 2 : kMaxLists;
+    int lists = !vec || lpr_log2 == 2 || waves < 12288 ? 0 : waves < 32768 ? 2 : kMaxLists;
     // (no more than make one list of kLong on average: what is left is dearer; 100 000 rows of 100 columns and 120 entries
     // each 766 us by two, 1180 by three)
     if (lists * E > kLong * V) lists = 2 * E > kLong * V ? 0 : 2;

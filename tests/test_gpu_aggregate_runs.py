@@ -24,6 +24,36 @@ def test_row_starts(D, per_wave, tiles, waves, more):
     _check(D, -(-waves * per_wave // tiles) + more, D + waves)
 
 
+# 4 or 16 bytes a lane
+@pytest.mark.parametrize("D,V", [(15, (1 << 18) - 1), (15, 1 << 18), (17, (1 << 17) - 1), (31, 1 << 17), (31, 70), (33, 70)])
+def test_odd_widths(D, V):
+    _check(D, V, D + V)
+
+
+def test_narrow_odd_widths_are_no_slower():
+    """Few rows of 31 columns (8 lanes of 16 bytes would share a hub's) take no longer than of 35."""
+    import torch
+    import paper_2207_14696_amd as bf
+    V = 20_000
+    rank = np.random.default_rng(0).permutation(V)
+    lens = np.minimum(10_000, (3 * ((rank + 0.5) / V) ** (-1 / 1.1)).astype(np.int64) + 1)
+    ptr = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)])).cuda()
+    idx = torch.randint(0, V, (int(lens.sum()),), device="cuda")
+    took = []
+    for D in (31, 35):
+        x, out = torch.randn(V, D, device="cuda"), torch.empty(V, D, device="cuda")
+        best = 1e9
+        for _ in range(30):
+            e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e[0].record()
+            bf.aggregate_rows(x, ptr, idx, out=out)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        took.append(best)
+    assert took[0] < took[1], took
+
+
 # Lists that together make a longer run than one list can: at the same place in every half or third of the destinations, so
 # that they share a lane group, which leaves all but the first of them to others.
 @pytest.mark.parametrize("waves", [12_288, 32_768])
