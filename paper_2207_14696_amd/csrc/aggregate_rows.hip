@@ -244,7 +244,8 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
 }
 
 // The lists that short_lists() leaves, a lane group each.  A lane looks one item's lists over; lanes of a wave are far apart,
-// as such items tend to be neighbours.  (Another look at the bounds: 2^20 rows of 100 columns 955 us without, 960.)
+// as such items tend to be neighbours.  (Another look at the bounds: 2^20 rows of 100 columns 955 us without,
+// 960; 300 000 of 64 128, 131; one list's after the other 133.)
 __device__ inline void left_lists(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
                                   const int64_t *__restrict__ indices, int64_t V, int lpr_log2, int lists, int tiles, int sum,
                                   float *__restrict__ out, int64_t block, int64_t nblocks) {
@@ -254,8 +255,18 @@ __device__ inline void left_lists(const float *__restrict__ x, int64_t D, const 
     const int64_t wave = block * (kThreads / 64) + (threadIdx.x >> 6), waves = nblocks * (kThreads / 64);
     for (int64_t first = 0; first < items; first += 64 * waves) {
         const int64_t item = first + wave + waves * lane;
-        const int64_t tile = item / step, v0 = item - tile * step;
+        const int64_t tile = tiles == 1 && item < items ? 0 : item / step, v0 = item - tile * step;
         int before = 0;
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < kMaxLists; k++) {  // (all bounds at once; hardly a wave finds anything)
+            const int64_t v = min(v0 + k * step, V - 1), all = indptr[v + 1] - indptr[v];
+            const int len = item < items && k < lists && v0 + k * step < V && all > 0 && all <= kLong ? (int)all : 0;
+            any |= is_left(k, before, len);
+            before += len;
+        }
+        if (!__any(any)) continue;
+        before = 0;
         for (int k = 0; k < lists; k++) {
             const int64_t v = v0 + k * step;
             const bool mine = item < items && v < V;
