@@ -245,7 +245,7 @@ __device__ inline void short_lists(const float *__restrict__ x, int64_t D,
 
 // The lists that short_lists() leaves, a lane group each.  A lane looks one item's lists over; lanes of a wave are far apart,
 // as such items tend to be neighbours.  (Another look at the bounds: 2^20 rows of 100 columns 955 us without,
-// 960; 300 000 of 64 128, 131; one list's after the other 133.)
+// 960; 300 000 of 64 128, 131; one list after the other 133.)
 __device__ inline void left_lists(const float *__restrict__ x, int64_t D, const int64_t *__restrict__ indptr,
                                   const int64_t *__restrict__ indices, int64_t V, int lpr_log2, int lists, int tiles, int sum,
                                   float *__restrict__ out, int64_t block, int64_t nblocks) {
@@ -519,9 +519,12 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     const int64_t tiles = (granules + ((int64_t)1 << lpr_log2) - 1) >> lpr_log2;
     // Several lists a group only where the chip has enough of them at a time (us with 1, 2, 3 of them: 2^20
     // rows of 64 columns 776, 680, 595, of 100 1174, 1017, 973; 417 408 of 100 354, 336, 334; 114 390 of 64, 29 000
-    // waves by one, 85, 74, 72).  0: short_lists_single().
+    // waves by one, 85, 74, 72).  Rows of 64 lanes: 100 000 of 256 columns 154, 160, 167, 196 516 304, 271, 273; 100 000 of 768
+    // 512, 548, 570, 500 000 of 300 two 1322, three 1239.  0: short_lists_single().
     const int64_t waves = (V * tiles) >> (6 - lpr_log2);
-    int lists = !vec || lpr_log2 == 2 || waves < 12288 ? 0 : waves < 32768 ? 2 : kMaxLists;
+    int lists = !vec || lpr_log2 == 2 || waves < 12288                   ? 0
+                : waves < 32768 || (lpr_log2 == 6 && V < (int64_t)1 << 17) ? 2
+                                                                           : kMaxLists;
     // (no more than make one list of kLong on average: what is left is dearer; 100 000 rows of 100 columns and 120 entries
     // each 766 us by two, 1180 by three)
     if (lists * E > kLong * V) lists = 2 * E > kLong * V ? 0 : 2;
