@@ -429,11 +429,12 @@ inline void launch_sq(const Src &src, int64_t rows, int D, int64_t rb, int bits,
     if (want < GW) want = GW;
     int blocks = blocks_for(want);
     if ((int64_t)blocks * kThreads < GW) blocks = (GW + kThreads - 1) / kThreads;
-    // Codes that fill a tenth of the 256 MB cache or more are streamed past it: written back from there
-    // they slow down what comes next (tables fitted and encoded, ordinary stores / streamed: 2 x 201 MB of codes
-    // 769 / 742 us, of which the first range fit 190 / 163; 112 MB 296 / 282; 2 x 32 MB 546 / 540; 31 MB 146 / 140; but
-    // 2 x 24 MB 466 / 469).
-    const bool stream = rows * rb > ((int64_t)28 << 20);
+    // Codes that fill much of the 256 MB cache are streamed past it: written back from there they slow down what comes
+    // next, unless that is the first gather from them, which then finds them there.  Ordinary stores / streamed, us, for
+    // 768 columns of half precision to 4 bits: the next range fit, of as many rows, and a first gather of 65 536 and of
+    // 300 000 rows: 32 MB of codes 33 / 31, 38 / 54, 147 / 191; 48 MB 50 / 43, 38 / 54, 153 / 213; 64 MB 68 / 55, 46 / 53, 185 / 232;
+    // 80 MB 82 / 64, 49 / 53, 214 / 234; 100 MB 96 / 77, 52 / 54, 225 / 237; 128 MB 112 / 95, 53 / 53, 235 / 239.
+    const bool stream = rows * rb > ((int64_t)80 << 20);
 #define BF_QK(B, VECV, NC)                                                                                              \
     do {                                                                                                               \
         if (stream) quantize_sq_kernel<Src, B, Coder, VECV, NC, true><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes); \

@@ -1,5 +1,5 @@
 """Large chunks: the range fit's pieces of rows (extremes planted at their edges) and codes on both sides of the
-28 MB from which on they are streamed past the caches, bit for bit against the oracle."""
+80 MB from which on they are streamed past the caches, bit for bit against the oracle."""
 import numpy as np
 import pytest
 
@@ -35,7 +35,7 @@ def test_range_fit(half, D, piece, over):
 
 @pytest.mark.parametrize("kind,bits,half", [("uniform", 1, True), ("uniform", 4, False), ("uniform", 8, True), ("log", 8, True),
                                             ("log", 4, False)])
-@pytest.mark.parametrize("rows", [(28 << 20) // 16, (28 << 20) // 16 + 1])
+@pytest.mark.parametrize("rows", [(80 << 20) // 16, (80 << 20) // 16 + 1])
 def test_codes(kind, bits, half, rows):
     import torch
     import paper_2207_14696_amd as bf
