@@ -36,30 +36,38 @@ def test_uniform(D):
     assert np.array_equal(q.params_get_uniform()[0], x[0])
 
 
-def test_uniform_replayed():
+@pytest.mark.parametrize("D", [64, 16385])
+def test_uniform_replayed(D):
+    """The first read after the capture is of what a replay left; what later replays leave shows in the codes."""
     import torch
     import paper_2207_14696_amd as bf
-    x = np.random.default_rng(1).normal(size=(100, 64)).astype(np.float32)
+    x = np.random.default_rng(1).normal(size=(100, D)).astype(np.float32)
     t = torch.from_numpy(x).cuda()
-    q = bf.Quantizer(scheme_of("uniform", 8), 64)
-    for _ in range(2):
-        q.fit_reset()
-        q.fit_update(t)
-        q.fit_finalize()
-        torch.cuda.synchronize()
-        g = torch.cuda.CUDAGraph()
+    q = bf.Quantizer(scheme_of("uniform", 8), D)
+    q.fit_reset()
+    q.fit_update(t)
+    q.fit_finalize()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         q.fit_reset()
         q.fit_update(t)
         q.fit_finalize()
     for k in range(3):
-        y = (x * (k + 2)).astype(np.float32)
+        y = (x * (k + 2) + k).astype(np.float32)
         t.copy_(torch.from_numpy(y))
         g.replay()
-        q.fit_reset()       # (the host's copy is of the fit before)
-        q.fit_update(t)
-        q.fit_finalize()
-        _check(q, y, 8)
+        if k == 0:
+            _check(q, y, 8)
+        codes = torch.zeros((100, q.row_bytes), dtype=torch.uint8, device="cuda")
+        q.quantize(t, codes, 0)
+        mn, mx = orc.fit_minmax(y)
+        want = orc.pack(orc.uniform_encode(y, 8, mn, orc.uniform_params(mn, mx, 8)[1]), 8)
+        assert np.array_equal(codes.cpu().numpy(), want)
+    q.fit_reset()       # (an eager fit after them)
+    q.fit_update(t)
+    q.fit_finalize()
+    _check(q, y, 8)
 
 
 @pytest.mark.parametrize("D", [64, 16385])
