@@ -229,12 +229,39 @@ __device__ inline float4 load4(const __half *p) {
 // the same wherever the row begins: one load, of 4-byte (half precision: 2-byte) alignment
 struct __attribute__((packed, aligned(4))) FourFloats { float x, y, z, w; };
 struct __attribute__((packed, aligned(2))) FourHalves { uint32_t a, b; };
+struct __attribute__((packed, aligned(2))) TwoHalves { uint32_t a; };
 __device__ inline float4 load4_any(const float *p) {
     const FourFloats v = *reinterpret_cast<const FourFloats *>(p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ inline float4 load4_any(const __half *p) {
     const FourHalves v = *reinterpret_cast<const FourHalves *>(p);
+    const float2 a = __half22float2(__builtin_bit_cast(__half2, v.a)), b = __half22float2(__builtin_bit_cast(__half2, v.b));
+    return make_float4(a.x, a.y, b.x, b.y);
+}
+// the first n of four columns (uniform; none below 1), zeros for the rest.  Half precision is converted behind the branches: in them it
+// would wait for each load
+__device__ inline float4 load4_first(const float *p, int n) {
+    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n >= 4) {
+        q = load4_any(p);
+    } else if (n > 0) {
+        q.x = p[0];
+        if (n > 1) q.y = p[1];
+        if (n > 2) q.z = p[2];
+    }
+    return q;
+}
+__device__ inline float4 load4_first(const __half *p, int n) {
+    FourHalves v{0, 0};
+    const uint16_t *h = reinterpret_cast<const uint16_t *>(p);
+    if (n >= 4) {
+        v = *reinterpret_cast<const FourHalves *>(p);
+    } else if (n > 0) {
+        if (n > 1) v.a = reinterpret_cast<const TwoHalves *>(p)->a;
+        else v.a = h[0];
+        if (n > 2) v.b = h[2];
+    }
     const float2 a = __half22float2(__builtin_bit_cast(__half2, v.a)), b = __half22float2(__builtin_bit_cast(__half2, v.b));
     return make_float4(a.x, a.y, b.x, b.y);
 }

@@ -328,16 +328,11 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
         // (rows that begin anywhere too: with a load a column, each of 64 lines, 141 483 half-precision rows of 11 x 64 x
         // 16 by cosine, 174 columns, took 120 us, 49 so; 83 639 of 10 x 256 x 32, 301 columns, 157 and 75)
         if (a.bvec) {
+            int left = have;  // (compared anew for every row: kept, the outcomes take more scalar registers than there are)
+            asm volatile("" : "+s"(left));
 #pragma unroll
             for (int k = 0; k < WP / 4; k++) {
-                float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (4 * k + 4 <= have) {
-                    q = load4_any(src + 4 * k);
-                } else if (4 * k < have) {  // the last part of a row
-                    q.x = load1(src + 4 * k);
-                    if (4 * k + 1 < have) q.y = load1(src + 4 * k + 1);
-                    if (4 * k + 2 < have) q.z = load1(src + 4 * k + 2);
-                }
+                const float4 q = load4_first(src + 4 * k, left - 4 * k);
                 v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
             }
         } else {
