@@ -99,8 +99,7 @@ bool vq_nearest_takes(const bifeat_params *p, bool train, int64_t rows) {
         return false;
     if (few && len < 48 && w * len < kNearestMinBook) return false;
     if (nearest_lds(p, G, tiles, false, false) > kCuLds - 4096) return false;
-    const double gap = pow((double)len, -2.0 / w) * std::min(1.0, 2.0 / w);
-    if (vq_margin(w, len) > 0.01 * gap) return false;
+    if (too_dense(w, len, w)) return false;
     return !train || entries_in_lds(p, true);
 }
 

@@ -62,7 +62,9 @@ struct VqNearestArgs {
     int lane_rows, plain_rows;  // see search_costs
     int NT;                 // tiles of 32 entries
     int ny;                 // workgroups per part
+    int more;               // (the encoder) of the last part on top of these
     int64_t chunk;          // rows of each, a whole number of waves
+    int64_t last_chunk;     // (the encoder) the last part's
     int strip_log2, sets, sub;  // (training) see RowSets
     const float *rnorm;     // [P][len], cosine metric
     float margin, cell_margin;  // see vq_margin
@@ -164,8 +166,11 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
     // of rows, which share memory lines of x and of the codes) belong on one XCD
     const unsigned per_xcd = gridDim.x >> 3;
     const unsigned id = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
-    if (id >= (unsigned)(a.P * a.ny)) return;
-    const int part = (int)(id % (unsigned)a.P), by = (int)(id / (unsigned)a.P);
+    const unsigned even = (unsigned)(a.P * a.ny);
+    if (id >= even + (TRAIN ? 0u : (unsigned)a.more)) return;
+    const bool extra = !TRAIN && id >= even;
+    const int part = extra ? a.P - 1 : (int)(id % (unsigned)a.P), by = extra ? (int)(id - even) + a.ny : (int)(id / (unsigned)a.P);
+    const int64_t chunk = !TRAIN && part == a.P - 1 ? a.last_chunk : a.chunk;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5;
     const int w = a.w, len = a.len;
@@ -358,8 +363,8 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
     [[maybe_unused]] int strip = 0;
     [[maybe_unused]] uint8_t *out = codes;
     do {
-        const int64_t begin = sub * a.chunk;
-        const int64_t end = min(TRAIN ? set_rows(set, a.sets, a.strip_log2, a.rows) : a.rows, begin + a.chunk);
+        const int64_t begin = sub * chunk;
+        const int64_t end = min(TRAIN ? set_rows(set, a.sets, a.strip_log2, a.rows) : a.rows, begin + chunk);
         if constexpr (!TRAIN) out += (begin + threadIdx.x) * a.rb + part * a.pb;
         next = clamped(begin);
         float xn[WP];
@@ -829,6 +834,12 @@ float vq_margin(int w, int len) {
     return (float)(1.25 * 2.0 * score);
 }
 
+// whether the entries lie so densely in `cols` columns of a part that most rows are open, see vq_nearest_takes
+bool too_dense(int w, int len, int cols) {
+    const double gap = pow((double)len, -2.0 / cols) * std::min(1.0, 2.0 / cols);
+    return vq_margin(w, len) > 0.01 * gap;
+}
+
 // The same for the scores inside a cell: fp32 throughout, (w + 4) u M, and three low bits.
 float vq_cell_margin(int w) {
     const double u = ldexp(1.0, -24);
@@ -862,13 +873,15 @@ bool entries_in_lds(const bifeat_params *p, bool train) {
 //   without the entries in LDS: 8 x 2048 x 16  175, 2450, 946: 22.5, 20.0   8 x 1500 x 24  203, 3130, 1060: 17.7, 19.5
 //   8 x 1000 x 32  250, 7600, 950: 6.1, 6.1 (entries of 128 bytes meet in the caches)   8 x 1500 x 21  413, 16 000, 1080: 3.4
 // By cosine the rule costs a multiplication and an addition instead of three instructions: 0.8 to 0.95 of these.
+inline double rule_cost(int len, int G) { return len * (3.0 * 8 * G + 3.0); }
+inline double scores_cost(int len, int G, bool ent) { return (ent ? 3.6 : G == 4 ? 6.5 : 4.7) * len * G + 400.0; }
 template <typename T>
 void search_costs(VqNearestArgs<T> &a, int G, bool ent, bool cosine) {
-    const double entry = 3.0 * 8 * G + 3.0, all = a.len * entry;
+    const double entry = 3.0 * 8 * G + 3.0, all = rule_cost(a.len, G);
     // each lane its own entry
     const double apart = ent ? (G == 1 ? 1.3 : G == 2 ? 1.45 : G == 3 ? 1.65 : 1.75) : !a.bvec ? 14.0 : a.w == 32 ? 7.4 : 2.5;
     const double one = (a.len + 63) / 64 * entry * apart + 170.0;
-    const double scores = (ent ? 3.6 : G == 4 ? 6.5 : 4.7) * a.len * G + 400.0;
+    const double scores = scores_cost(a.len, G, ent);
     a.lane_rows = (int)std::min(64.0, all / one);
     // (a wave that decides by itself keeps to it for 7 more strips: 5 rows, more than their number's spread, on top)
     a.plain_rows = (int)std::max(1.0, std::min(60.0, (cosine ? 0.88 : 1.0) * (all - scores) / one + (ent ? 5.0 : 0.0)));
@@ -915,24 +928,35 @@ bool launch_one(bifeat_params *p, VqNearestArgs<T> a, uint8_t *codes, size_t lds
         a.sub = r.sub;
         a.chunk = r.share;
     } else {
+        // A last part of so few columns that most of its rows go by the rule (see too_dense) costs as many times the
+        // others and gets as many times their workgroups: dealt evenly, 100 000 half-precision rows of 601 columns by 8,
+        // 256 entries, took 588 us, 202 so (608 columns: 160); 65 536 of 129 by 16 136, 62; of 769 by 16, 2048 entries, 5990, 1490.
+        const int rest = (int)(p->D % a.w);
+        const double last = !rest || !too_dense(a.w, a.len, rest) ? 1.0
+                            : (METRIC == BIFEAT_VQ_COSINE ? 0.88 : 1.0) * rule_cost(a.len, G) / scores_cost(a.len, G, ENT);
         const int64_t strips = (a.rows + TH - 1) / TH;
-        ny = resident / a.P;
+        int64_t ny_last = 0;
         double least = 0.0;
         for (int m = 1; m <= 4; m++) {
-            const int64_t n = m * resident / a.P;
+            const int64_t n = (int64_t)(m * resident / (a.P - 1 + last));
             if (n < 1) continue;
-            const double rows_long = m * ((double)a.rows / (double)n + 0.8 * TH);
-            if (least == 0.0 || rows_long < least) { least = rows_long; ny = n; }
+            const int64_t n_last = last > 1.0 ? std::max(n, m * resident - n * (a.P - 1)) : n;
+            const double rows_long = m * (std::max(1.0 / n, last / n_last) * a.rows + 0.8 * TH);
+            if (least == 0.0 || rows_long < least) { least = rows_long; ny = n; ny_last = n_last; }
         }
-        if (ny < 1) ny = 1;
-        if (ny > strips) ny = strips;
         // (whole strips instead would leave the chip waiting for the workgroups with one more)
-        a.chunk = ((a.rows + ny - 1) / ny + 63) / 64 * 64;
-        ny = (a.rows + a.chunk - 1) / a.chunk;
+        auto deal = [&](int64_t &n, int64_t &chunk) {
+            n = std::min(std::max<int64_t>(n, 1), strips);
+            chunk = ((a.rows + n - 1) / n + 63) / 64 * 64;
+            n = (a.rows + chunk - 1) / chunk;
+        };
+        deal(ny, a.chunk);
+        deal(ny_last, a.last_chunk);
+        a.more = (int)std::max<int64_t>(0, ny_last - ny);
     }
     a.ny = (int)ny;
     search_costs(a, G, ENT, METRIC == BIFEAT_VQ_COSINE);
-    const int64_t blocks = ((int64_t)a.P * ny + 7) / 8 * 8;
+    const int64_t blocks = ((int64_t)a.P * ny + a.more + 7) / 8 * 8;
     kern<<<(unsigned)blocks, TH, lds, s>>>(a, p->d_cb, codes);
     if constexpr (TRAIN)
         launch_vq_means(p, a.sums, a.counts, a.one_set ? 1 : a.sets, a.one_set ? 1 : a.sub,
