@@ -16,11 +16,14 @@ template <int GROUPS>
 __global__ __launch_bounds__(kThreads) void vq_means_kernel(const void *__restrict__ sums,
                                                             const uint32_t *__restrict__ counts, int sets, int sub, int P,
                                                             int w, int len, const double *__restrict__ dists, int n_dists,
-                                                            double *__restrict__ distortion, float *__restrict__ cb) {
+                                                            double *__restrict__ distortion, int round, double *host,
+                                                            float *__restrict__ cb) {
     constexpr int OUT = kThreads / GROUPS;
-    const int first = dists ? 1 : 0, workers = (int)gridDim.x - first;
+    const int first = dists || host ? 1 : 0, workers = (int)gridDim.x - first;
     if ((int)blockIdx.x < first) {  // one more workgroup, beside those of the means
         __shared__ double s_d[kThreads / 64];
+        if (host && (int)threadIdx.x < round + (dists ? 0 : 1)) host[threadIdx.x] = distortion[threadIdx.x];
+        if (!dists) return;
         double d = 0.0;
 #pragma unroll 4
         for (int i = threadIdx.x; i < n_dists; i += kThreads) d += dists[i];
@@ -29,7 +32,8 @@ __global__ __launch_bounds__(kThreads) void vq_means_kernel(const void *__restri
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int k = 1; k < kThreads / 64; k++) d += s_d[k];
-            *distortion = d;
+            distortion[round] = d;
+            if (host) host[round] = d;
         }
         return;
     }
@@ -107,9 +111,11 @@ void launch_vq_means(bifeat_params *p, const void *sums, const uint32_t *counts,
                      int n_dists, double *distortion, hipStream_t s) {
     const int w = p->scheme.vq_width, len = p->scheme.vq_length;
     const int64_t n = (int64_t)p->P * len * w;
+    const int round = (int)(distortion - p->d_dist);
+    double *const host = last_round(p, round);
 #define BF_VM(GROUPS) \
-    vq_means_kernel<GROUPS><<<blocks_for(GROUPS * n) + (dists ? 1 : 0), kThreads, 0, s>>>( \
-        sums, counts, sets, sub, p->P, w, len, dists, n_dists, distortion, p->d_cb)
+    vq_means_kernel<GROUPS><<<blocks_for(GROUPS * n) + (dists || host ? 1 : 0), kThreads, 0, s>>>( \
+        sums, counts, sets, sub, p->P, w, len, dists, n_dists, p->d_dist, round, host, p->d_cb)
     // (a thread each where that fills the chip: 10 sets of 96 x 256 x 8 take 6.5 us so, 13 by groups)
     if (sets * sub > 8 && n < (1 << 16)) BF_VM(8);
     else BF_VM(1);

@@ -60,8 +60,14 @@ __device__ inline int64_t set_row(int set, int sets, int strip_log2, int64_t i) 
     return ((set + (i >> strip_log2) * sets) << strip_log2) + (i & ((1 << strip_log2) - 1));
 }
 
+// where the last round's last kernel leaves all rounds' squared distances for the host, else nullptr.  (A kernel of its own for that
+// took 3 us of each training: 1000 rows of 1 x 256 x 16 205 us, 201 so.)
+inline double *last_round(const bifeat_params *p, int round) {
+    return round + 1 == p->opt_vq_iters ? reinterpret_cast<double *>(p->d_out) : nullptr;
+}
+
 // every entry with members becomes their mean, from the sums [sets][sub][P][w][len] (64 bits where sub > 1, else
-// 32) and counts [sets][sub][P][len]; *distortion = the sum of the n_dists workgroups' dists (nullptr: it is there)
+// 32) and counts [sets][sub][P][len]; *distortion, one of p->d_dist = the sum of the n_dists workgroups' dists (nullptr: it is there)
 void launch_vq_means(bifeat_params *p, const void *sums, const uint32_t *counts, int sets, int sub, const double *dists,
                      int n_dists, double *distortion, hipStream_t s);
 

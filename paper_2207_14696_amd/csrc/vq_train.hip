@@ -110,7 +110,9 @@ __global__ __launch_bounds__(kThreads) void vq_lloyd_accumulate_kernel(
 }
 
 __global__ void vq_lloyd_update_kernel(float *__restrict__ cb, const float *__restrict__ sums,
-                                       const float *__restrict__ counts, int w, int64_t n) {
+                                       const float *__restrict__ counts, int w, int64_t n,
+                                       const double *__restrict__ distortion, int rounds, double *host) {
+    if (host && blockIdx.x == 0 && (int)threadIdx.x < rounds) host[threadIdx.x] = distortion[threadIdx.x];
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const float cnt = counts[i / w];
@@ -141,7 +143,8 @@ void lloyd_round(bifeat_params *p, const T *x, int64_t rows, double *dist_slot, 
         default: BF_LL(0); break;
     }
 #undef BF_LL
-    vq_lloyd_update_kernel<<<256, 256, 0, s>>>(p->d_cb, sums, counts, w, n);
+    const int k = (int)(dist_slot - p->d_dist);
+    vq_lloyd_update_kernel<<<256, 256, 0, s>>>(p->d_cb, sums, counts, w, n, p->d_dist, k + 1, last_round(p, k));
 }
 
 // rnorm[i] = fp32(1 / sqrt(sum_d C_id^2)), 0 for an all-zero entry; sum and root in fp64
@@ -514,7 +517,6 @@ hipError_t launch_vq_train(bifeat_params *p, const void *chunk, int dtype, int64
                                                  : round((const __half *)chunk, p->d_dist + k);
         if (e != hipSuccess) return e;
     }
-    launch_export(p, p->d_dist, 128, s);  // (64 doubles)
     return hipGetLastError();
 }
 
