@@ -230,41 +230,39 @@ __device__ inline float4 load4(const __half *p) {
 struct __attribute__((packed, aligned(4))) FourFloats { float x, y, z, w; };
 struct __attribute__((packed, aligned(2))) FourHalves { uint32_t a, b; };
 struct __attribute__((packed, aligned(2))) TwoHalves { uint32_t a; };
-__device__ inline float4 load4_any(const float *p) {
-    const FourFloats v = *reinterpret_cast<const FourFloats *>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ inline float4 load4_any(const __half *p) {
-    const FourHalves v = *reinterpret_cast<const FourHalves *>(p);
-    const float2 a = __half22float2(__builtin_bit_cast(__half2, v.a)), b = __half22float2(__builtin_bit_cast(__half2, v.b));
-    return make_float4(a.x, a.y, b.x, b.y);
-}
-// the first n of four columns (uniform; none below 1), zeros for the rest.  Half precision is converted behind the branches: in them it
-// would wait for each load
-__device__ inline float4 load4_first(const float *p, int n) {
-    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+__device__ inline FourFloats four_any(const float *p) { return *reinterpret_cast<const FourFloats *>(p); }
+__device__ inline FourHalves four_any(const __half *p) { return *reinterpret_cast<const FourHalves *>(p); }
+// the first n of four columns (uniform; none below 1), zeros for the rest
+__device__ inline FourFloats four_first(const float *p, int n) {
+    FourFloats v{0.f, 0.f, 0.f, 0.f};
     if (n >= 4) {
-        q = load4_any(p);
+        v = four_any(p);
     } else if (n > 0) {
-        q.x = p[0];
-        if (n > 1) q.y = p[1];
-        if (n > 2) q.z = p[2];
+        v.x = p[0];
+        if (n > 1) v.y = p[1];
+        if (n > 2) v.z = p[2];
     }
-    return q;
+    return v;
 }
-__device__ inline float4 load4_first(const __half *p, int n) {
+__device__ inline FourHalves four_first(const __half *p, int n) {
     FourHalves v{0, 0};
     const uint16_t *h = reinterpret_cast<const uint16_t *>(p);
     if (n >= 4) {
-        v = *reinterpret_cast<const FourHalves *>(p);
+        v = four_any(p);
     } else if (n > 0) {
         if (n > 1) v.a = reinterpret_cast<const TwoHalves *>(p)->a;
         else v.a = h[0];
         if (n > 2) v.b = h[2];
     }
+    return v;
+}
+__device__ inline float4 to_float4(FourFloats v) { return make_float4(v.x, v.y, v.z, v.w); }
+__device__ inline float4 to_float4(FourHalves v) {
     const float2 a = __half22float2(__builtin_bit_cast(__half2, v.a)), b = __half22float2(__builtin_bit_cast(__half2, v.b));
     return make_float4(a.x, a.y, b.x, b.y);
 }
+template <typename T>
+__device__ inline float4 load4_any(const T *p) { return to_float4(four_any(p)); }
 // a store of 4-byte alignment, streaming
 __device__ inline void store4_any(float *p, float4 v) {
     typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));

@@ -333,12 +333,24 @@ __global__ __launch_bounds__(TH, nearest_waves(G, ENT, TH)) void vq_nearest_kern
         // (rows that begin anywhere too: with a load a column, each of 64 lines, 141 483 half-precision rows of 11 x 64 x
         // 16 by cosine, 174 columns, took 120 us, 49 so; 83 639 of 10 x 256 x 32, 301 columns, 157 and 75)
         if (a.bvec) {
-            int left = have;  // (compared anew for every row: kept, the outcomes take more scalar registers than there are)
+            // (compared anew for every row: kept, the outcomes take more scalar registers than there are; half precision is
+            // converted behind the branches, which would otherwise wait for their loads)
+            int left = have;
             asm volatile("" : "+s"(left));
+            decltype(four_any(src)) q[WP / 4];
+            // (whole parts without a branch a load: training 65 536 rows of 8 x 256 x 16 505 -> 495 us, 48 x 256 x 16 1655 -> 1646, encoding
+            // 100 000 of 76 x 64 x 8 100 -> 88; but training 1000 rows of 4 x 64 x 8 143 -> 146.5)
+            if ((!TRAIN || WP > 8) && left >= WP) {
+#pragma unroll
+                for (int k = 0; k < WP / 4; k++) q[k] = four_any(src + 4 * k);
+            } else {
+#pragma unroll
+                for (int k = 0; k < WP / 4; k++) q[k] = four_first(src + 4 * k, left - 4 * k);
+            }
 #pragma unroll
             for (int k = 0; k < WP / 4; k++) {
-                const float4 q = load4_first(src + 4 * k, left - 4 * k);
-                v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
+                const float4 f = to_float4(q[k]);
+                v[4 * k] = f.x; v[4 * k + 1] = f.y; v[4 * k + 2] = f.z; v[4 * k + 3] = f.w;
             }
         } else {
 #pragma unroll
