@@ -24,6 +24,17 @@ def test_row_starts(D, per_wave, tiles, waves, more):
     _check(D, -(-waves * per_wave // tiles) + more, D + waves)
 
 
+# with fewer than 4 entries a list on average, two lists a group only where three are taken
+@pytest.mark.parametrize("less", [0, 1])
+@pytest.mark.parametrize("D,V", [(64, 12_288 * 4), (64, 32_767 * 4), (64, 32_768 * 4), (300, 6144), (300, 16_384)])
+def test_few_entries(D, V, less):
+    lens = np.full(V, 4)
+    lens[:V // 2:2] += 3
+    lens[1:V // 2:2] -= 3
+    lens[7] -= less
+    _check(D, V, D + V, lens)
+
+
 # 4 or 16 bytes a lane
 @pytest.mark.parametrize("D,V", [(15, (1 << 18) - 1), (15, 1 << 18), (17, (1 << 17) - 1), (31, 1 << 17), (31, 70), (33, 70)])
 def test_odd_widths(D, V):
@@ -61,7 +72,7 @@ def test_narrow_odd_widths_are_no_slower():
 @pytest.mark.parametrize("more", [0, 1])
 def test_long_runs(D, per_wave, tiles, waves, more):
     V = -(-waves * per_wave // tiles) + more
-    lens = np.random.default_rng(D + V).integers(0, 3, V)
+    lens = np.random.default_rng(D + V).integers(2, 8, V)
     together = [(256, 256, 256), (256, 1, 0), (1, 255, 1), (1, 256, 0), (0, 256, 256), (128, 128, 1), (257, 10, 250), (100, 157, 99),
                 (0, 0, 256), (256, 257, 256)] + [(250, 249, 248)] * 70
     for lists in (2, 3):
@@ -131,7 +142,7 @@ def _check(D, V, seed, lens=None):
     rng = np.random.default_rng(seed)
     N = 5000
     if lens is None:
-        lens = rng.integers(0, 4, V)
+        lens = rng.integers(0, 10, V)                                # (4 on average, or more: as many lists a group as there can be)
         for at in (0, V // 2, max(0, V - len(EDGES))):               # the last ones end the block
             n = min(len(EDGES), V - at)
             lens[at:at + n] = rng.permutation(EDGES)[:n] if at else EDGES[:n]
