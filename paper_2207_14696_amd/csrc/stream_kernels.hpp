@@ -57,13 +57,13 @@ constexpr bool kHalfChunk = std::is_same<Src, ChunkSrc<__half>>::value;
 constexpr int kFitThreads = 1024;
 constexpr int kFitBlocks = 512;
 
-// A workgroup's rows come in pieces of so many of its iterations, the workgroups' pieces one after the
-// other: the chip then reads one window of the chunk at a time (805 MB of half precision 133 us, 136 with
-// one long piece each; 1 M x 100 floats fitted and encoded 271, 283).  The last round's rows are dealt evenly: by pieces
-// of as many iterations a tenth of the workgroups could have them all (90 000 x 768 half precision 32 us, 27 so).
-// Pieces a power of two apart cost: 600 000 x 128 floats 53, one piece each 50 (15 or 17 iterations 52.6, but 1 M x 100
-// floats fitted and encoded 242 and 237 instead of 235).
-constexpr int kFitPiece = 16;
+// A workgroup's rows of a chunk come in pieces of so many of its iterations, the workgroups' pieces one after the
+// other: the chip then reads one window of the chunk at a time (2^20 x 1024 half precision 360 us with one long piece each,
+// 336 so).  The last round's rows are dealt evenly (90 000 x 768 half precision: by pieces of this length too a tenth of the
+// workgroups could have them all, 32 us, 27 so).  Whole pieces have a number of iterations that the compiler knows: worked out for
+// each, with a 64-bit division, pieces of 16 cost more than they gave (2^20 x 128 floats 88 us with one long piece, 93, and 84 so).
+// Not a power of two, which the iterations' 16 KB often are (2^20 x 256 floats by 16 of them 176, by 20 167; by 12, 28 or 40 as by 20).
+constexpr int kFitPiece = 20;
 
 inline int fit_blocks(int64_t threads) {
     const int64_t b = (threads + kFitThreads - 1) / kFitThreads;
@@ -149,13 +149,20 @@ __global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, i
             }
         };
         if (by_block) {
-            const int64_t pass = (int64_t)gridDim.x * rpi;
-            for (int64_t base = 0; base < rows; base += pass * kFitPiece) {
-                const int64_t left = rows - base, steps = left >= pass * kFitPiece ? kFitPiece : (left + pass - 1) / pass;
-                const int64_t r0 = base + blockIdx.x * steps * rpi, end = min(rows, r0 + steps * rpi);
+            const int row = (int)threadIdx.x / G;
+            const int64_t round = (int64_t)gridDim.x * rpi * kFitPiece;
+            int64_t base = 0;
+            if constexpr (kChunk<Src>) {
+                for (; base + round <= rows; base += round) {
+                    const int64_t r0 = base + (int64_t)blockIdx.x * (rpi * kFitPiece) + row;
 #pragma unroll 4
-                for (int64_t r = r0 + (int)threadIdx.x / G; r < end; r += rpi) take(r);
+                    for (int k = 0; k < kFitPiece; k++) take(r0 + k * rpi);
+                }
             }
+            const int64_t pass = (int64_t)gridDim.x * rpi, piece = (rows - base + pass - 1) / pass * rpi;
+            const int64_t r0 = base + blockIdx.x * piece, end = min(rows, r0 + piece);
+#pragma unroll 4
+            for (int64_t r = r0 + row; r < end; r += rpi) take(r);
         } else {
             const int64_t K = (rows + rows_per_pass - 1) / rows_per_pass;
             const int64_t rbeg = (int64_t)(t / G) * K, rend = min(rows, rbeg + K);
