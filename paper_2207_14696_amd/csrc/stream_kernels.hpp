@@ -334,10 +334,10 @@ struct LogCoder {
 // together and one of them stores it.  Every word of the padded row is written (columns >= D
 // encode as 0).  Bound by memory (a plain copy moves 4.9 TB/s here): 524 288 x 768 half-precision
 // values to 4 bits 186 us, 5.4 TB/s (8-byte loads: 221), to 1 bit 177 (206).
-// STREAM: streaming stores, see launch_sq.
-template <class Src, int BITS, typename Coder, bool VEC, int NC, bool STREAM>
+// stream: streaming stores, see launch_sq.
+template <class Src, int BITS, typename Coder, bool VEC, int NC>
 __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t rows, int D, int64_t rb,
-                                                              Coder coder,
+                                                              Coder coder, int stream,
                                                               uint8_t *__restrict__ codes) {
     __shared__ float s_edges[130];
     typename Coder::template Ctx<NC> ctx;
@@ -412,12 +412,17 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
             for (int o = 1; o < LG; o <<= 1) word[0] |= (uint32_t)__shfl_xor((int)word[0], o);
         }
         if (sub == 0) {
-            uint32_t *dst = dst_word + r * rw;
-            if constexpr (NW == 2) {
-                if constexpr (STREAM) store_stream(reinterpret_cast<uint2 *>(dst), make_uint2(word[0], word[1]));
-                else *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
+            if (NC * BITS >= 16 && stream) {  // (whole lines of a wave's codes)
+                // (a place that is another one to the compiler, which would make one ordinary store of this one and the one below)
+                int64_t at = r * rw;
+                asm volatile("" : "+v"(at));
+                uint32_t *dst = dst_word + at;
+                if constexpr (NW == 2) store_stream(reinterpret_cast<uint2 *>(dst), make_uint2(word[0], word[1]));
+                else store_stream(dst, word[0]);
+                asm volatile("");
             } else {
-                if constexpr (STREAM) store_stream(dst, word[0]);
+                uint32_t *dst = dst_word + r * rw;
+                if constexpr (NW == 2) *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
                 else *dst = word[0];
             }
         }
@@ -442,11 +447,10 @@ inline void launch_sq(const Src &src, int64_t rows, int D, int64_t rb, int bits,
     // 300 000 rows: 32 MB of codes 33 / 31, 38 / 54, 147 / 191; 48 MB 50 / 43, 38 / 54, 153 / 213; 64 MB 68 / 55, 46 / 53, 185 / 232;
     // 80 MB 82 / 64, 49 / 53, 214 / 234; 100 MB 96 / 77, 52 / 54, 225 / 237; 128 MB 112 / 95, 53 / 53, 235 / 239.
     const bool stream = rows * rb > ((int64_t)80 << 20);
-#define BF_QK(B, VECV, NC)                                                                                              \
-    do {                                                                                                               \
-        if (stream) quantize_sq_kernel<Src, B, Coder, VECV, NC, true><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes); \
-        else quantize_sq_kernel<Src, B, Coder, VECV, NC, false><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, codes); \
-    } while (0)
+    // The kernel does so where a wave's codes make whole lines (streamed by 32 or 64 bytes, 2^20 x 768 floats to 1 bit took 680 us,
+    // 648 not so, half precision 349 and 340).
+#define BF_QK(B, VECV, NC) \
+    quantize_sq_kernel<Src, B, Coder, VECV, NC><<<blocks, kThreads, 0, s>>>(src, rows, D, rb, coder, stream, codes)
 #define BF_Q(B)                                                                                 \
     do {                                                                                        \
         if constexpr (kHalfChunk<Src>) {                                                        \
