@@ -522,11 +522,13 @@ hipError_t launch_aggregate_rows(const float *x, int64_t D, const int64_t *indpt
     // waves by one, 85, 74, 72).  Rows of 64 lanes: 100 000 of 256 columns 154, 160, 167, 196 516 304, 271, 273; 100 000 of 768
     // 512, 548, 570, 500 000 of 300 two 1322, three 1239.  0: short_lists_single().  Fewer than 4 entries a list on
     // average end too often for two (none / 2: 50 021 rows of 64 columns, 2.3 entries, 28 / 40, 50 000 of 100, 2 each, 15.5 / 17.0, 114 390 of 64,
-    // 3.6, 54 / 59; but by three 200 047 of 64, 3.6, 72 / 66).
+    // 3.6, 54 / 59; but by three 200 047 of 64, 3.6, 72 / 66), fewer than 2 for three up to 256 MB of sums (400 000 of 100, one each, 69 / 79;
+    // but 2^20 of 100, 1.5 each, 298 / 248).
     const int64_t waves = (V * tiles) >> (6 - lpr_log2);
-    int lists = !vec || lpr_log2 == 2 || waves < (E < 4 * V ? 32768 : 12288) ? 0
+    int lists = !vec || lpr_log2 == 2 || waves < (E < 4 * V ? 32768 : 12288) ||
+                        (E < 2 * V && V * D <= (int64_t)1 << 26)         ? 0
                 : waves < 32768 || (lpr_log2 == 6 && V < (int64_t)1 << 17) ? 2
-                                                                           : kMaxLists;
+                                                                         : kMaxLists;
     // (no more than make one list of kLong on average: what is left is dearer; 100 000 rows of 100 columns and 120 entries
     // each 766 us by two, 1180 by three)
     if (lists * E > kLong * V) lists = 2 * E > kLong * V ? 0 : 2;

@@ -35,6 +35,16 @@ def test_few_entries(D, V, less):
     _check(D, V, D + V, lens)
 
 
+# with fewer than two, neither (2^26 sums at most)
+@pytest.mark.parametrize("D,V,less", [(64, 32_768 * 4, 0), (64, 32_768 * 4, 1), (128, 1 << 19, 1), (128, (1 << 19) + 1, 2), (300, 1 << 17, 1)])
+def test_hardly_any_entries(D, V, less):
+    lens = np.full(V, 2)
+    lens[:V // 2:2] += 2
+    lens[1:V // 2:2] -= 2
+    lens[8] -= less
+    _check(D, V, D + V, lens)
+
+
 # 4 or 16 bytes a lane
 @pytest.mark.parametrize("D,V", [(15, (1 << 18) - 1), (15, 1 << 18), (17, (1 << 17) - 1), (31, 1 << 17), (31, 70), (33, 70)])
 def test_odd_widths(D, V):
