@@ -344,6 +344,10 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
     constexpr int LG = NC * BITS >= 32 ? 1 : 32 / (NC * BITS);  // lanes per 32-bit word
     constexpr int NW = NC * BITS > 32 ? NC * BITS / 32 : 1;     // words per lane
     constexpr int CPW = NC / NW;                                // columns of a lane per word
+    // Columns of a row from which on rows that begin anywhere are loaded by fours, below which the lanes without columns of
+    // a padded row wait for as much work (us by single columns / so: 1 M x 21 floats to 1 bit 49 / 55, to 1 logarithmic one 41 / 54,
+    // 1 M x 5 to 4 15.7 / 17.3, but 1 M x 9 to 2 bits 41 / 30; half precision to 1 bit 1 M x 5 71 / 56).
+    [[maybe_unused]] constexpr int kFours = kHalfChunk<Src> ? 4 : BITS == 1 || (Coder::kEdges && BITS >= 4) ? 40 : 7;
     const int GW = (int)(8 * rb / (NC * BITS));  // NC-column groups per padded row; a multiple of LG
     if constexpr (Coder::kEdges) {
         for (int i = threadIdx.x; i <= coder.H; i += kThreads)
@@ -377,7 +381,7 @@ __global__ __launch_bounds__(kThreads) void quantize_sq_kernel(Src src, int64_t 
                 float4 q = src.load4(sctx, r, col0);
                 v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
             }
-        } else if (kChunk<Src> && D >= 4) {
+        } else if (kChunk<Src> && D >= kFours) {
             // rows that begin anywhere; the last lane takes the row's last four columns (200 000 x 602
             // floats to 4 logarithmic bits 148 us by single columns, 119 so; 66 901 x 602 half precision to 1 bit 34, 25)
             if constexpr (kChunk<Src>) {

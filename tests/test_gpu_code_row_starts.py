@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bits", [1, 2, 4, 8])
-@pytest.mark.parametrize("D", [1, 2, 3, 4, 5, 6, 7, 9, 63, 130, 131, 602])
+@pytest.mark.parametrize("D", [1, 2, 3, 4, 5, 6, 7, 9, 39, 41, 63, 130, 131, 602])
 @pytest.mark.parametrize("half,shift", [(False, 0), (False, 1), (True, 1), (True, 2)])
 def test_codes(bits, D, half, shift):
     import torch
