@@ -63,7 +63,9 @@ constexpr int kFitBlocks = 512;
 // workgroups could have them all, 32 us, 27 so).  Whole pieces have a number of iterations that the compiler knows: worked out for
 // each, with a 64-bit division, pieces of 16 cost more than they gave (2^20 x 128 floats 88 us with one long piece, 93, and 84 so).
 // Not a power of two, which the iterations' 16 KB often are (2^20 x 256 floats by 16 of them 176, by 20 167; by 12, 28 or 40 as by 20).
-constexpr int kFitPiece = 20;
+// Half precision by 16 bytes whose iterations are no whole number of 4 KB: 8 loads at a time (524 288 x 768 135 us by 4, 133 so, 2^20 x 896
+// 304 and 298; but 2^20 x 512 170 and 178, floats by 8 a tenth slower).
+constexpr int kFitPiece = 20, kFitPieceBy8 = 32;
 
 inline int fit_blocks(int64_t threads) {
     const int64_t b = (threads + kFitThreads - 1) / kFitThreads;
@@ -150,13 +152,20 @@ __global__ __launch_bounds__(TH) void fit_minmax_kernel(Src src, int64_t rows, i
         };
         if (by_block) {
             const int row = (int)threadIdx.x / G;
-            const int64_t round = (int64_t)gridDim.x * rpi * kFitPiece;
+            const bool by8 = VEC == 8 && rpi * D * 2 % 4096 != 0;
+            const int steps = by8 ? kFitPieceBy8 : kFitPiece;
+            const int64_t round = (int64_t)gridDim.x * rpi * steps;
             int64_t base = 0;
             if constexpr (kChunk<Src>) {
                 for (; base + round <= rows; base += round) {
-                    const int64_t r0 = base + (int64_t)blockIdx.x * (rpi * kFitPiece) + row;
+                    const int64_t r0 = base + (int64_t)blockIdx.x * (rpi * steps) + row;
+                    if (by8) {
+#pragma unroll 8
+                        for (int k = 0; k < kFitPieceBy8; k++) take(r0 + k * rpi);
+                    } else {
 #pragma unroll 4
-                    for (int k = 0; k < kFitPiece; k++) take(r0 + k * rpi);
+                        for (int k = 0; k < kFitPiece; k++) take(r0 + k * rpi);
+                    }
                 }
             }
             const int64_t pass = (int64_t)gridDim.x * rpi, piece = (rows - base + pass - 1) / pass * rpi;

@@ -9,8 +9,8 @@ from helpers import scheme_of
 pytestmark = pytest.mark.gpu
 
 
-# rows of a piece: 20 iterations of 1024 // (D / 8 or D / 4) rows (512 workgroups of 1024 threads)
-@pytest.mark.parametrize("half,D,piece", [(True, 768, 200), (False, 256, 320), (False, 100, 800)])
+# rows of a piece: 20 iterations (half precision of 768 columns: 32) of 1024 // (D / 8 or D / 4) rows (512 workgroups of 1024 threads)
+@pytest.mark.parametrize("half,D,piece", [(True, 768, 320), (True, 512, 320), (False, 256, 320), (False, 100, 800)])
 # (20 487: a last round of several iterations)
 @pytest.mark.parametrize("over", [0, 1, 161, 20_487])
 def test_range_fit(half, D, piece, over):
